@@ -7,6 +7,26 @@
 
 namespace cg {
 
+// LDS written by the lanes of a wave is seen by all of its lanes after this:
+// a wave's LDS accesses are carried out in order, so this only keeps the
+// compiler from moving accesses across it
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// the first position in the sorted a[0, q) holding a value >= x
+__device__ __forceinline__ int32_t lds_lower_bound(const int32_t *a, int q, int32_t x) {
+  int lo = 0, hi = q;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (a[mid] < x) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
 // ---------------------------------------------------------------------------
 // BranchRemoval: flags of a vertex whose row starts at b and has `deg`
 // entries: bit0 branch (deg >= 3); bit1 / bit2 entry 0 / 1 kept (neither end
@@ -826,16 +846,15 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
 constexpr int kIndBlock = 256;
 constexpr int kIndLocalCap = 1024;
 
-// lidx (the local number of each read) is written for every component when
-// lidx_always, else only for components above CAP reads (the ones whose
-// neighbours are then numbered through it instead of the sorted block).
+// lidx (the local number of each read) is written for components above CAP
+// reads only (the ones whose neighbours are then numbered through it instead
+// of the sorted block).
 // Member i's id is members[MS * i].
 template <int BLOCK, int CAP, int MS = 1>
 __device__ __forceinline__ void sort_component_block(int q, int st,
                                                      const int32_t *__restrict__ members,
                                                      int32_t *__restrict__ perm,
-                                                     int32_t *__restrict__ lidx, int32_t *a,
-                                                     bool lidx_always = true) {
+                                                     int32_t *__restrict__ lidx, int32_t *a) {
   if (q <= CAP) {
     int N2 = 1;
     while (N2 < q) N2 <<= 1;
@@ -844,19 +863,66 @@ __device__ __forceinline__ void sort_component_block(int q, int st,
     // non-negative ids padded with the largest int32: the same order as uint32
     bitonic_sort(reinterpret_cast<uint32_t *>(a), N2);
     for (int i = threadIdx.x; i < q; i += BLOCK) {
-      const int32_t v = a[i];
-      perm[st + i] = v;
-      if (lidx_always) lidx[v] = st + i;
+      perm[st + i] = a[i];
     }
   } else {
-    // large component: the rank of a read is the number of smaller ids in
-    // its block (ids are distinct)
+    // large component: its ids in a bitmap of CAP / 2 words of LDS, one window
+    // of ids after another, and the set bits before each word: a read's rank
+    // is the bits below its own (every member is loaded twice per window;
+    // counting the smaller ids took q loads per read, 1.5 ms for the 3,000
+    // reads of one component)
+    constexpr int kWords = CAP / 2;
+    __shared__ int32_t sh_lo, sh_hi;
+    __shared__ int32_t sh_cnt[BLOCK / kWave + 1];
+    if (threadIdx.x == 0) {
+      sh_lo = 0x7FFFFFFF;
+      sh_hi = 0;
+    }
+    __syncthreads();
+    int32_t mn = 0x7FFFFFFF, mx = 0;
     for (int i = threadIdx.x; i < q; i += BLOCK) {
-      const int32_t x = members[MS * i];
-      int r = 0;
-      for (int t = 0; t < q; ++t) r += members[MS * t] < x;
-      perm[st + r] = x;
-      lidx[x] = st + r;
+      const int32_t x = members[MS * (int64_t)i];
+      mn = x < mn ? x : mn;
+      mx = x > mx ? x : mx;
+    }
+    atomicMin(&sh_lo, mn);
+    atomicMax(&sh_hi, mx);
+    __syncthreads();
+    uint32_t *bits = reinterpret_cast<uint32_t *>(a);
+    int32_t *pre = a + kWords;
+    int32_t done = 0;  // members below the window
+    for (int64_t w0 = sh_lo & ~31; w0 <= sh_hi; w0 += 32 * kWords) {
+      for (int i = threadIdx.x; i < kWords; i += BLOCK) bits[i] = 0;
+      __syncthreads();
+      for (int i = threadIdx.x; i < q; i += BLOCK) {
+        const int64_t x = members[MS * (int64_t)i] - w0;
+        if (x >= 0 && x < 32 * kWords) atomicOr(bits + (x >> 5), 1u << (x & 31));
+      }
+      __syncthreads();
+      constexpr int E = kWords / BLOCK;  // consecutive words per thread
+      static_assert(E * BLOCK == kWords, "whole words per thread");
+      int32_t sum = 0;
+#pragma unroll
+      for (int k = 0; k < E; ++k) sum += __popc(bits[threadIdx.x * E + k]);
+      int32_t tot;
+      int32_t ex = done + block_excl_scan<int32_t, BLOCK>(sum, sh_cnt, &tot);
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        pre[threadIdx.x * E + k] = ex;
+        ex += __popc(bits[threadIdx.x * E + k]);
+      }
+      done += tot;
+      __syncthreads();
+      for (int i = threadIdx.x; i < q; i += BLOCK) {
+        const int32_t v = members[MS * (int64_t)i];
+        const int64_t x = v - w0;
+        if (x >= 0 && x < 32 * kWords) {
+          const int32_t r = pre[x >> 5] + __popc(bits[x >> 5] & ((1u << (x & 31)) - 1u));
+          perm[st + r] = v;
+          lidx[v] = st + r;
+        }
+      }
+      __syncthreads();
     }
   }
   __syncthreads();
@@ -876,7 +942,7 @@ __device__ __forceinline__ void induce_component(
     int32_t *__restrict__ perm, int32_t *__restrict__ lidx, int32_t *__restrict__ loc_row_ptr,
     int32_t *__restrict__ loc_col, int32_t *__restrict__ loc_eid, int32_t *a,
     int32_t *sh_scan) {
-  sort_component_block<BLOCK, CAP, MS>(q, st, members, perm, lidx, a, false);  // ends with a barrier
+  sort_component_block<BLOCK, CAP, MS>(q, st, members, perm, lidx, a);  // ends with a barrier
   const bool in_lds = q <= CAP;
   int carry = 0;
   for (int base = 0; base < q; base += BLOCK) {

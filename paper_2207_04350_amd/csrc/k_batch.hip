@@ -1356,16 +1356,6 @@ __device__ __forceinline__ void induce_listed(const BatchDev &B, int4 d, int32_t
 // the ids; every field goes into the walk's LDS arrays at its local number
 // while perm and the local CSR rows are written out, so the walk reads
 // nothing back.
-__device__ __forceinline__ int32_t lds_lower_bound(const int32_t *a, int q, int32_t x) {
-  int lo = 0, hi = q;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < x) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
 template <int BLOCK, int CAP>
 __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkArrays w,
                                              uint32_t *sh_scan) {

@@ -1,216 +1,310 @@
 // InducedSubgraph (Section 4.3): V_i = reads owned by bin i, E_i = entries of
 // L with both ends in V_i, renumbered locally with the global ids kept.  All
 // bins share one local numbering ordered by (bin, label, id): a component's
-// reads form the block [comp_start, comp_start + q).
+// reads form the block [comp_start, comp_start + q), and its local CSR rows
+// the entries from comp_estart on, so one component's part of every output is
+// independent of the others':
 //
-//  k_ind_zero   bucket cursors; bin_vptr (scan of the reads of each bin); n_e
-//  k_ind_fill   each eligible read claims a slot in its component's block
-//  k_ind_local  one workgroup per component: sort the block by read id
-//               (LDS bitonic up to 1024 reads, rank counting above)
-//  k_ind_rows   local CSR rows (look-back scan of kept degrees), columns
-//               renumbered through the local numbers, entry index kept;
-//               k_ind_rows_wide does the same four rows per thread
+//  k_ind_init   bucket cursors, components by rank, the cycle marks cleared
+//  k_ind_fill   each read with kept entries claims a slot in its component's
+//               block; bin_vptr and n_e from the components in rank order;
+//               cycles marked by rank
+//  k_ind_comp   sorts each component's reads by id and writes perm and the
+//               local CSR rows: lanes for one-read components, a wave up to
+//               128 reads, a workgroup above
+//
+// The entries before a component need no scan of the rows: a path of q reads
+// has 2q - 2 of them and a cycle 2q, so they are 2 (comp_start - comp_rank),
+// plus two for every cycle of lower rank.
 #include "cg_device.h"
 
 namespace cg {
 
+// Cycles by component rank: a bitmap, the cycles of every kCycSuper ranks,
+// and whether there is any (most graphs have none, and then nothing else is
+// read).  Kept in the scratch's estart array.
+constexpr int kCycSuper = 2048;
+struct CycMarks {
+  uint32_t *bits, *super, *any;
+};
+__host__ __device__ __forceinline__ CycMarks cyc_marks(int32_t *area, int32_t n) {
+  uint32_t *b = reinterpret_cast<uint32_t *>(area);
+  const int64_t w = ((int64_t)n + 31) / 32, sp = ((int64_t)n + kCycSuper - 1) / kCycSuper;
+  return CycMarks{b, b + w, b + w + sp};
+}
 
-constexpr int kIndBinLds = 2048;  // bins whose reads k_ind_zero sums in LDS
-__global__ __launch_bounds__(kScanBlock) void k_ind_zero(int32_t P, const int32_t *__restrict__ d_n_comp,
-                                                         const int32_t *__restrict__ comp_bin,
-                                                         const int32_t *__restrict__ comp_size,
-                                                         uint64_t *bin_reads,
-                                                         uint32_t *__restrict__ fill,
-                                                         int32_t *__restrict__ bin_vptr,
-                                                         int32_t *__restrict__ d_sizes) {
-  const int nc = *d_n_comp;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nc;
-       c += (int64_t)gridDim.x * blockDim.x)
+// cycles of rank below r; called by a whole wave with uniform r
+__device__ __forceinline__ int32_t cycles_before(const CycMarks &m, int32_t r) {
+  if (*m.any == 0) return 0;
+  const int32_t sp = r / kCycSuper, w = r >> 5;
+  int32_t k = 0;
+  for (int32_t i = lane_id(); i < sp; i += kWave) k += (int32_t)m.super[i];
+  for (int32_t i = sp * (kCycSuper / 32) + lane_id(); i < w; i += kWave) k += __popc(m.bits[i]);
+  if (lane_id() == 0) k += __popc(m.bits[w] & ((1u << (r & 31)) - 1u));
+  return wave_sum(k);
+}
+
+constexpr int kIndInitBlock = 256;
+__global__ __launch_bounds__(kIndInitBlock) void k_ind_init(
+    int32_t n, int32_t P, const int32_t *__restrict__ d_n_comp,
+    const int32_t *__restrict__ comp_rank, uint32_t *__restrict__ fill,
+    int32_t *__restrict__ by_rank, CycMarks cyc, int32_t *__restrict__ bin_vptr,
+    int32_t *__restrict__ loc_row_ptr, int32_t *__restrict__ d_sizes) {
+  const int32_t nc = *d_n_comp;
+  const int64_t t0 = (int64_t)blockIdx.x * kIndInitBlock + threadIdx.x;
+  const int64_t nt = (int64_t)gridDim.x * kIndInitBlock;
+  for (int64_t c = t0; c < nc; c += nt) {
     fill[c] = 0;
-  if (blockIdx.x == 0) {
-    // the reads of each bin (in LDS up to kIndBinLds bins, four components'
-    // loads per thread issued together), then their prefix: bin_vptr
-    __shared__ int64_t sh[kScanBlock / kWave + 1];
-    __shared__ unsigned long long s_br[kIndBinLds];
-    const bool lds = P <= kIndBinLds;
-    if (lds) {
-      for (int b = threadIdx.x; b < P; b += kScanBlock) s_br[b] = 0;
-      __syncthreads();
-      for (int c0 = threadIdx.x; c0 < nc; c0 += 4 * kScanBlock) {
-        int32_t bb[4], sz[4];
+    by_rank[comp_rank[c]] = (int32_t)c;
+  }
+  for (int64_t w = t0; w < (nc + 31) / 32; w += nt) cyc.bits[w] = 0;
+  for (int64_t w = t0; w < (nc + kCycSuper - 1) / kCycSuper; w += nt) cyc.super[w] = 0;
+  if (t0 == 0 && n > 0) *cyc.any = 0;
+  if (nc == 0) {
+    for (int64_t b = t0; b <= P; b += nt) bin_vptr[b] = 0;
+    if (t0 == 0) {
+      loc_row_ptr[0] = 0;
+      d_sizes[0] = d_sizes[1] = 0;
+    }
+  }
+}
+
+// The slots of a workgroup's reads are counted per component in an LDS hash
+// table first, so that the workgroup takes one slot range per component: one
+// atomic per read on the component's cursor queues on its address (about
+// 4.5 ns each: 69 us for the 15,000 reads of 13 components, 10 us now; 13 to
+// 11 us where 556 components share them).
+constexpr int kFillBlock = 1024;
+constexpr int kFillPer = 2;                           // reads per thread
+constexpr int kFillSlots = 2 * kFillBlock * kFillPer;  // at most half full
+__global__ __launch_bounds__(kFillBlock) void k_ind_fill(
+    int32_t n, int32_t P, const uint8_t *__restrict__ flags, const int32_t *__restrict__ label,
+    cg_parts parts, uint32_t *fill, const int32_t *__restrict__ by_rank, CycMarks cyc,
+    int32_t *__restrict__ tmp, int32_t *__restrict__ bin_vptr, int32_t *__restrict__ d_sizes) {
+  __shared__ int32_t s_key[kFillSlots];
+  __shared__ uint32_t s_cnt[kFillSlots];
+  const int32_t nc = *parts.d_n_comp;
+  const int64_t t0 = (int64_t)blockIdx.x * kFillBlock + threadIdx.x;
+  const int64_t nt = (int64_t)gridDim.x * kFillBlock;
+  // the reads' flags and labels, and their components (-1: none, or a read
+  // of a one-read component, which needs no slot)
+  int32_t v[kFillPer], c[kFillPer], lab[kFillPer];
+  bool in[kFillPer];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int c = c0 + r * kScanBlock;
-          bb[r] = c < nc ? comp_bin[c] : -1;
-          sz[r] = c < nc ? comp_size[c] : 0;
-        }
+  for (int k = 0; k < kFillPer; ++k) {
+    const int64_t x = ((int64_t)blockIdx.x * kFillPer + k) * kFillBlock + threadIdx.x;
+    v[k] = (int32_t)x;
+    in[k] = x < n && (flags[x] & 6u);
+    lab[k] = in[k] ? label[x] : 0;
+  }
+  for (int i = threadIdx.x; i < kFillSlots; i += kFillBlock) {
+    s_key[i] = -1;
+    s_cnt[i] = 0;
+  }
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (bb[r] >= 0) atomicAdd(s_br + bb[r], (unsigned long long)sz[r]);
+  for (int k = 0; k < kFillPer; ++k) c[k] = in[k] ? parts.label_comp[lab[k]] : -1;
+  // components in rank order: where the bins start
+  for (int64_t r = t0; r < nc; r += nt) {
+    const int32_t x = by_rank[r], prev = r > 0 ? parts.comp_bin[by_rank[r - 1]] : -1;
+    const int32_t st = parts.comp_start[x];
+    for (int32_t b = prev + 1; b <= parts.comp_bin[x]; ++b) bin_vptr[b] = st;
+    if (parts.comp_kind[x] == CG_KIND_CYCLE) {
+      atomicOr(cyc.bits + (r >> 5), 1u << (r & 31));
+      atomicAdd(cyc.super + r / kCycSuper, 1u);
+      *cyc.any = 1;
+    }
+  }
+  if (nc > 0) {
+    const int32_t x = by_rank[nc - 1];
+    const int32_t n_e = parts.comp_start[x] + parts.comp_size[x];
+    for (int64_t b = (int64_t)parts.comp_bin[x] + 1 + t0; b <= P; b += nt) bin_vptr[b] = n_e;
+    if (t0 == 0) d_sizes[0] = n_e;
+  }
+  __syncthreads();
+  int slot[kFillPer];
+  uint32_t at[kFillPer];
+#pragma unroll
+  for (int k = 0; k < kFillPer; ++k) {
+    slot[k] = -1;
+    if (c[k] < 0) continue;
+    uint32_t h = ((uint32_t)c[k] * 2654435761u) >> 16 & (kFillSlots - 1);
+    while (true) {  // ends: the table is at most half full
+      const int32_t old = atomicCAS(s_key + h, -1, c[k]);
+      if (old == -1 || old == c[k]) break;
+      h = (h + 1) & (kFillSlots - 1);
+    }
+    slot[k] = (int)h;
+    at[k] = atomicAdd(s_cnt + h, 1u);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kFillSlots; i += kFillBlock) {
+    const int32_t x = s_key[i];
+    if (x >= 0) s_cnt[i] = (uint32_t)parts.comp_start[x] + atomicAdd(fill + x, s_cnt[i]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kFillPer; ++k)
+    if (slot[k] >= 0) tmp[s_cnt[slot[k]] + at[k]] = v[k];
+}
+
+// One component of 2 .. kIndWaveCap reads by one wave.  The ranks of the ids
+// are counted over the lanes; every member's kept columns go to LDS at its
+// rank, then lane i writes local read i.  s points at 4 * kIndWaveCap ints of
+// the wave's own.
+constexpr int kIndWaveCap = 128;
+__device__ __forceinline__ void ind_wave(int q, int st, int estart, const int32_t *members,
+                                         const uint8_t *__restrict__ flags,
+                                         const int32_t *__restrict__ row_ptr,
+                                         const int32_t *__restrict__ col, int32_t *s,
+                                         const cg_local &out) {
+  constexpr int R = kIndWaveCap / kWave;
+  const int l = lane_id();
+  int32_t *s_id = s, *s_b = s + kIndWaveCap, *s_c0 = s + 2 * kIndWaveCap,
+          *s_c1 = s + 3 * kIndWaveCap;
+  int32_t v[R], b[R], c0[R], c1[R], rk[R];
+  uint32_t f[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const int i = l + u * kWave;
+    v[u] = i < q ? members[i] : 0x7FFFFFFF;
+  }
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const bool live = l + u * kWave < q;
+    f[u] = live ? flags[v[u]] : 0u;
+    b[u] = live ? row_ptr[v[u]] : 0;
+    rk[u] = 0;
+  }
+#pragma unroll
+  for (int u2 = 0; u2 < R; ++u2) {
+    const int cnt = q - u2 * kWave < kWave ? q - u2 * kWave : kWave;
+    for (int l2 = 0; l2 < cnt; ++l2) {
+      const int32_t x = __builtin_amdgcn_readlane(v[u2], l2);
+#pragma unroll
+      for (int u = 0; u < R; ++u) rk[u] += x < v[u] ? 1 : 0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    c0[u] = (f[u] & 2u) ? col[b[u]] : -1;
+    c1[u] = (f[u] & 4u) ? col[b[u] + 1] : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+    if (l + u * kWave < q) {
+      s_id[rk[u]] = v[u];
+      s_b[rk[u]] = b[u];
+      s_c0[rk[u]] = c0[u];
+      s_c1[rk[u]] = c1[u];
+    }
+  wave_lds_sync();
+  int32_t r0 = estart;
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const int i = l + u * kWave;
+    const bool live = i < q;
+    const int32_t x0 = live ? s_c0[i] : -1, x1 = live ? s_c1[i] : -1;
+    const int32_t deg = (x0 >= 0 ? 1 : 0) + (x1 >= 0 ? 1 : 0);
+    const int32_t inc = wave_incl_scan(deg);
+    int32_t t = r0 + inc - deg;
+    if (live) {
+      out.perm[st + i] = s_id[i];
+      out.loc_row_ptr[st + i] = t;
+      const int32_t e = s_b[i];
+      if (x0 >= 0) {
+        out.loc_col[t] = st + lds_lower_bound(s_id, q, x0);
+        out.loc_eid[t] = e;
+        ++t;
       }
-    } else {
-      for (int b = threadIdx.x; b < P; b += kScanBlock) bin_reads[b] = 0;
+      if (x1 >= 0) {
+        out.loc_col[t] = st + lds_lower_bound(s_id, q, x1);
+        out.loc_eid[t] = e + 1;
+      }
+    }
+    r0 += __shfl(inc, kWave - 1);
+  }
+  wave_lds_sync();
+}
+
+// Workgroups 0 .. n_big - 1 take the components above kIndWaveCap reads (the
+// longest ones start first); the waves of the others take runs of consecutive
+// components, one-read components a lane each.  1024 threads and at most
+// 64 registers: two workgroups, all 32 waves of a compute unit, and LDS for
+// the sort of 16,384 reads.
+constexpr int kIndCompBlock = 1024;
+constexpr int kIndCompCap = 16384;
+constexpr int kIndCompWaves = kIndCompBlock / kWave;
+static_assert(kIndCompWaves * 4 * kIndWaveCap <= kIndCompCap, "the waves' LDS fits the sort's");
+__global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const uint8_t *__restrict__ flags, cg_parts parts, const int32_t *__restrict__ tmp,
+    int32_t *__restrict__ lidx, CycMarks cyc, cg_local out, int n_big) {
+  __shared__ int32_t a[kIndCompCap];
+  __shared__ int32_t sh_scan[kIndCompBlock / kWave + 1];
+  __shared__ int s_n;
+  __shared__ int32_t s_list[kIndCompBlock];
+  const int32_t nc = *parts.d_n_comp;
+  if ((int)blockIdx.x < n_big) {
+    // this workgroup's components: blockIdx.x, + n_big, + 2 n_big, ...
+    for (int64_t base = blockIdx.x; base < nc; base += (int64_t)n_big * kIndCompBlock) {
+      if (threadIdx.x == 0) s_n = 0;
       __syncthreads();
-      for (int c = threadIdx.x; c < nc; c += kScanBlock)
-        atomicAdd((unsigned long long *)bin_reads + comp_bin[c], (unsigned long long)comp_size[c]);
+      const int64_t c = base + (int64_t)n_big * threadIdx.x;
+      if (c < nc && parts.comp_size[c] > kIndWaveCap) s_list[atomicAdd(&s_n, 1)] = (int32_t)c;
+      __syncthreads();
+      const int k = s_n;
+      for (int i = 0; i < k; ++i) {
+        const int32_t x = s_list[i];
+        const int32_t q = parts.comp_size[x], st = parts.comp_start[x], r = parts.comp_rank[x];
+        const int32_t es = 2 * (st - r + cycles_before(cyc, r));
+        induce_component<kIndCompBlock, kIndCompCap>(q, st, es, tmp + st, flags, row_ptr, col,
+                                                     out.perm, lidx, out.loc_row_ptr, out.loc_col,
+                                                     out.loc_eid, a, sh_scan);
+        if (threadIdx.x == 0 && r == nc - 1) {
+          const int32_t m_e = es + 2 * q - (parts.comp_kind[x] == CG_KIND_CYCLE ? 0 : 2);
+          out.loc_row_ptr[st + q] = m_e;
+          out.d_sizes[1] = m_e;
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
-    int64_t carry = 0;
-    for (int base = 0; base < P; base += kScanBlock) {
-      const int b = base + threadIdx.x;
-      int64_t x = 0;
-      if (b < P)
-        x = lds ? (int64_t)s_br[b]
-                : (int64_t)__hip_atomic_load(bin_reads + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      int64_t tot;
-      const int64_t ex = block_excl_scan<int64_t, kScanBlock>(x, sh, &tot);
-      if (b < P) bin_vptr[b] = (int32_t)(carry + ex);
-      carry += tot;
-    }
-    if (threadIdx.x == 0) {
-      bin_vptr[P] = (int32_t)carry;
-      d_sizes[0] = (int32_t)carry;
-    }
-  }
-}
-
-__global__ __launch_bounds__(kIndBlock) void k_ind_fill(int32_t n, const int32_t *__restrict__ label,
-                                                        const int32_t *__restrict__ label_comp,
-                                                        const int32_t *__restrict__ comp_start,
-                                                        uint32_t *fill, int32_t *__restrict__ tmp) {
-  const int64_t v = (int64_t)blockIdx.x * kIndBlock + threadIdx.x;
-  if (v >= n) return;
-  const int32_t c = label_comp[label[v]];
-  if (c < 0) return;
-  const uint32_t slot = atomicAdd(fill + c, 1u);
-  tmp[comp_start[c] + slot] = (int32_t)v;
-}
-
-__global__ __launch_bounds__(kIndBlock) void k_ind_local(const int32_t *__restrict__ d_n_comp,
-                                                         const int32_t *__restrict__ comp_size,
-                                                         const int32_t *__restrict__ comp_start,
-                                                         const int32_t *__restrict__ tmp,
-                                                         int32_t *__restrict__ perm,
-                                                         int32_t *__restrict__ lidx) {
-  __shared__ int32_t a[kIndLocalCap];
-  const int nc = *d_n_comp;
-  for (int c = blockIdx.x; c < nc; c += gridDim.x)
-    sort_component_block<kIndBlock, kIndLocalCap>(comp_size[c], comp_start[c], tmp + comp_start[c], perm, lidx, a);
-}
-
-__global__ __launch_bounds__(kScanBlock) void k_ind_rows(
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const uint8_t *__restrict__ flags, const int32_t *__restrict__ bin_vptr, int32_t P,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ lidx,
-    int32_t *__restrict__ loc_row_ptr, int32_t *__restrict__ loc_col,
-    int32_t *__restrict__ loc_eid, int32_t *__restrict__ d_sizes, ScanCtx sc, int nblocks) {
-  const int blk = lookback_ticket(sc);
-  const int64_t i = (int64_t)blk * kScanBlock + threadIdx.x;
-  const int32_t n_e = bin_vptr[P];
-  // the grid covers every read and only the n_e reads of the contigs have
-  // local numbers: blocks past them take no part in the scan (a block looks
-  // back at lower tickets only, and the last block out clears every status)
-  if ((int64_t)blk * kScanBlock > n_e) {
-    lookback_finish(sc, nblocks);
     return;
   }
-  int32_t v = -1;
-  uint32_t f = 0;
-  if (i < n_e) {
-    v = perm[i];
-    f = flags[v];
-  }
-  const uint32_t deg = ((f >> 1) & 1) + ((f >> 2) & 1);
-  unsigned long long incl_end;
-  const unsigned long long ex = lookback_block_scan(sc, blk, deg, &incl_end);
-  if (i <= n_e) loc_row_ptr[i] = (int32_t)ex;
-  if (i == n_e) d_sizes[1] = (int32_t)ex;
-  if (i < n_e && deg) {
-    const int32_t b = row_ptr[v];
-    int32_t t = (int32_t)ex;
-    if (f & 2) {
-      loc_col[t] = lidx[col[b]];
-      loc_eid[t] = b;
-      ++t;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int64_t w = (int64_t)(blockIdx.x - n_big) * kIndCompWaves + wv;
+  const int64_t nw = (int64_t)(gridDim.x - n_big) * kIndCompWaves;
+  // components per wave: at most one each where the waves suffice
+  int64_t run = (nc + nw - 1) / nw;
+  if (run > kWave) run = kWave;
+  for (int64_t c0 = w * run; c0 < nc; c0 += nw * run) {
+    const int64_t c = c0 + lane_id();
+    const bool live = lane_id() < run && c < nc;
+    const int32_t q = live ? parts.comp_size[c] : 0;
+    const int32_t st = live ? parts.comp_start[c] : 0, r = live ? parts.comp_rank[c] : 0;
+    const int32_t lab = live ? parts.comp_label[c] : 0;
+    const bool cycles = *cyc.any != 0;
+    int32_t es = 2 * (st - r);
+    if (cycles)
+      for (int t = 0; t < (int)run; ++t) {
+        const int32_t k = cycles_before(cyc, __builtin_amdgcn_readlane(r, t));
+        if (lane_id() == t) es += 2 * k;
+      }
+    if (live && q == 1) {
+      out.perm[st] = lab;
+      out.loc_row_ptr[st] = es;
     }
-    if (f & 4) {
-      loc_col[t] = lidx[col[b + 1]];
-      loc_eid[t] = b + 1;
+    if (live && r == nc - 1 && q <= kIndWaveCap) {
+      const int32_t m_e = es + 2 * q - (parts.comp_kind[c] == CG_KIND_CYCLE ? 0 : 2);
+      out.loc_row_ptr[st + q] = m_e;
+      out.d_sizes[1] = m_e;
+    }
+    for (uint64_t todo = __ballot(q > 1 && q <= kIndWaveCap); todo; todo &= todo - 1) {
+      const int t = (int)__builtin_ctzll(todo);
+      const int tq = __builtin_amdgcn_readlane(q, t), tst = __builtin_amdgcn_readlane(st, t);
+      ind_wave(tq, tst, __builtin_amdgcn_readlane(es, t), tmp + tst, flags, row_ptr, col,
+               a + wv * 4 * kIndWaveCap, out);
     }
   }
-  lookback_finish(sc, nblocks);
-}
-
-// k_ind_rows with kRowsWide consecutive local numbers per thread.  On a
-// large graph it keeps four rows' loads in flight per thread and puts a
-// quarter of the blocks in the look-back; on a small one, whose few thousand
-// contig reads fill only a few dozen blocks, one row per thread spreads them
-// over four times as many compute units and is the faster form.
-constexpr int32_t kRowsWideReads = 1 << 19;  // reads from which the wide form runs
-constexpr int kRowsWide = 4;
-__global__ __launch_bounds__(kScanBlock) void k_ind_rows_wide(
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const uint8_t *__restrict__ flags, const int32_t *__restrict__ bin_vptr, int32_t P,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ lidx,
-    int32_t *__restrict__ loc_row_ptr, int32_t *__restrict__ loc_col,
-    int32_t *__restrict__ loc_eid, int32_t *__restrict__ d_sizes, ScanCtx sc, int nblocks) {
-  const int blk = lookback_ticket(sc);
-  const int32_t n_e = bin_vptr[P];
-  // the grid covers every read and only the n_e reads of the contigs have
-  // local numbers: blocks past them take no part in the scan (a block looks
-  // back at lower tickets only, and the last block out clears every status)
-  if ((int64_t)blk * kScanBlock * kRowsWide > n_e) {
-    lookback_finish(sc, nblocks);
-    return;
-  }
-  const int64_t i0 = ((int64_t)blk * kScanBlock + threadIdx.x) * kRowsWide;
-  // every load of the thread's rows is issued before the scan, level by
-  // level (read, flags, row start, columns, their local numbers), and the
-  // stores come after it: gfx9 counts loads and stores in one counter, so a
-  // load behind a store would wait for it
-  int32_t v[kRowsWide], b[kRowsWide], c0[kRowsWide], c1[kRowsWide];
-  uint32_t f[kRowsWide];
-  uint32_t sum = 0;
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) v[k] = i0 + k < n_e ? perm[i0 + k] : -1;
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) {
-    f[k] = v[k] >= 0 ? flags[v[k]] : 0u;
-    sum += ((f[k] >> 1) & 1) + ((f[k] >> 2) & 1);
-  }
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) b[k] = (f[k] & 6u) ? row_ptr[v[k]] : 0;
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) {
-    c0[k] = (f[k] & 2u) ? col[b[k]] : -1;
-    c1[k] = (f[k] & 4u) ? col[b[k] + 1] : -1;
-  }
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) {
-    c0[k] = c0[k] >= 0 ? lidx[c0[k]] : -1;
-    c1[k] = c1[k] >= 0 ? lidx[c1[k]] : -1;
-  }
-  unsigned long long incl_end;
-  unsigned long long ex = lookback_block_scan(sc, blk, (unsigned long long)sum, &incl_end);
-#pragma unroll
-  for (int k = 0; k < kRowsWide; ++k) {
-    const int64_t i = i0 + k;
-    if (i <= n_e) loc_row_ptr[i] = (int32_t)ex;
-    if (i == n_e) d_sizes[1] = (int32_t)ex;
-    int32_t t = (int32_t)ex;
-    if (f[k] & 2u) {
-      loc_col[t] = c0[k];
-      loc_eid[t] = b[k];
-      ++t;
-    }
-    if (f[k] & 4u) {
-      loc_col[t] = c1[k];
-      loc_eid[t] = b[k] + 1;
-      ++t;
-    }
-    ex = (unsigned long long)t;
-  }
-  lookback_finish(sc, nblocks);
 }
 
 int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
@@ -218,28 +312,23 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
                   hipStream_t st) {
   const PhaseRange range("cg: InducedSubgraph");
   const int32_t n = g.n;
-  const int zgrid = n > 0 ? (int)((n + kScanBlock - 1) / kScanBlock) : 1;
-  CG_LAUNCH(ctx, k_ind_zero, dim3(zgrid < 256 ? zgrid : 256), dim3(kScanBlock), st, P,
-                     parts.d_n_comp, parts.comp_bin, parts.comp_size, s.bin_reads, s.fill,
-                     out.bin_vptr, out.d_sizes);
+  const CycMarks cyc = cyc_marks(s.estart, n);
+  const int64_t zg = ((int64_t)n + kIndInitBlock - 1) / kIndInitBlock;
+  CG_LAUNCH(ctx, k_ind_init, dim3((unsigned)(zg < 1 ? 1 : (zg > 256 ? 256 : zg))),
+            dim3(kIndInitBlock), st, n, P, parts.d_n_comp, parts.comp_rank, s.fill, s.aux, cyc,
+            out.bin_vptr, out.loc_row_ptr, out.d_sizes);
   if (n > 0) {
-    const int grid = (int)((n + kIndBlock - 1) / kIndBlock);
-    CG_LAUNCH(ctx, k_ind_fill, dim3(grid), dim3(kIndBlock), st, n, label, parts.label_comp,
-                       parts.comp_start, s.fill, s.tmp);
-    const int lgrid = n < 4096 ? n : 4096;
-    CG_LAUNCH(ctx, k_ind_local, dim3(lgrid), dim3(kIndBlock), st, parts.d_n_comp,
-                       parts.comp_size, parts.comp_start, s.tmp, out.perm, s.lidx);
-  }
-  if (n >= kRowsWideReads) {
-    const int nb = scan_blocks(((int64_t)n + kRowsWide) / kRowsWide);
-    CG_LAUNCH(ctx, k_ind_rows_wide, dim3(nb), dim3(kScanBlock), st, g.row_ptr, g.col, flags,
-              out.bin_vptr, P, out.perm, s.lidx, out.loc_row_ptr, out.loc_col, out.loc_eid,
-              out.d_sizes, scan_ctx(ctx, s), nb);
-  } else {
-    const int nb = scan_blocks((int64_t)n + 1);
-    CG_LAUNCH(ctx, k_ind_rows, dim3(nb), dim3(kScanBlock), st, g.row_ptr, g.col, flags,
-              out.bin_vptr, P, out.perm, s.lidx, out.loc_row_ptr, out.loc_col, out.loc_eid,
-              out.d_sizes, scan_ctx(ctx, s), nb);
+    const int64_t per = (int64_t)kFillBlock * kFillPer;
+    CG_LAUNCH(ctx, k_ind_fill, dim3((unsigned)((n + per - 1) / per)), dim3(kFillBlock), st, n, P,
+              flags, label, parts, s.fill, s.aux, cyc, s.tmp, out.bin_vptr, out.d_sizes);
+    // workgroups: as many as can hold a component above kIndWaveCap reads,
+    // up to one per compute unit; waves for components of two reads, up to
+    // what is resident at once
+    const int n_big = n / (kIndWaveCap + 1) < 256 ? n / (kIndWaveCap + 1) : 256;
+    const int64_t nw = ((int64_t)n / 2 + kIndCompWaves) / kIndCompWaves;
+    CG_LAUNCH(ctx, k_ind_comp, dim3((unsigned)(n_big + (nw < 512 ? nw : 512))),
+              dim3(kIndCompBlock), st, g.row_ptr, g.col, flags, parts, s.tmp, s.lidx, cyc, out,
+              n_big);
   }
   return hip_check(hipGetLastError(), "k_ind");
 }

@@ -40,15 +40,6 @@ __device__ __forceinline__ int32_t red_row(int32_t n) {
   return u < n ? u : -1;
 }
 
-// LDS written by the lanes of a wave is seen by all of its lanes after this:
-// a wave's LDS accesses are carried out in order, so this only keeps the
-// compiler from moving accesses across it
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __global__ __launch_bounds__(kRedRowBlock) void k_red_contained(cg_graph g, uint8_t *contained) {
   const int32_t v = red_row(g.n);
   if (v < 0) return;
