@@ -3,6 +3,8 @@
 // base access.  Each part names the step of Algorithm 2 it serves.
 #pragma once
 
+#include <type_traits>
+
 #include "cg_internal.h"
 
 namespace cg {
@@ -989,7 +991,7 @@ __device__ __forceinline__ void induce_component(
 // LocalAssembly: chain walk of one component, packed base access
 // ---------------------------------------------------------------------------
 constexpr int kWalkBlock = 256;
-constexpr int kWalkCap = 1024;               // reads per component handled in LDS
+constexpr int kWalkRaysCap = 4096;           // reads per component with rays in LDS
 // small components: one wave each, so many more are walked at once
 constexpr int kWalkSmallBlock = 64;
 constexpr int kWalkSmallCap = 128;
@@ -1008,10 +1010,10 @@ __device__ __forceinline__ uint64_t piece_anchor(uint64_t roff, uint32_t rlen, u
 
 struct WalkArrays {
   int32_t *nb;     // [2q] local neighbour of slot k of read i (-1: none / cut)
-  int32_t *eid;    // [2q] entry index in S of that slot
-  int32_t *nxt;    // [2q] ray successor
-  int32_t *dist;   // [2q] ray length
-  int32_t *endv;   // [2q] ray end
+  int32_t *eid;    // [2q] entry index in S of that slot (LDS form: the piece lengths
+                   // in walk order take its place once the rows are written)
+  uint32_t *ray;   // [2q] rays in LDS (see walk_chain)
+  uint64_t *gray;  // [2q] rays in global memory, of a component too large for LDS rays
   // the LDS form also keeps what the pieces need, loaded before the doubling:
   int32_t *vid;    // [q] read id of local read i
   uint32_t *rlen;  // [q] its length
@@ -1021,12 +1023,21 @@ struct WalkArrays {
   uint32_t *ep;    // [2q] its post (explicit coordinates)
 };
 
-template <int BLOCK, int CAP, bool kLds>
-__device__ __forceinline__ void walk_component(
-    int c, int q, int st, WalkArrays w, const cg_graph &g, const cg_parts &parts,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ loc_row_ptr,
-    const int32_t *__restrict__ loc_col, const int32_t *__restrict__ loc_eid,
-    const cg_contigs &out, const Scratch &s, int32_t *sh_small, uint32_t *sh_scan);
+// What a walk keeps where: everything in LDS; only the rays in LDS; nothing.
+enum WalkMode { kWalkLds, kWalkRaysLds, kWalkGlobal };
+
+// The arrays in global scratch (16 n ints) of the component whose block
+// starts at st: the blocks of different components are disjoint, so slices
+// never overlap.
+__device__ __forceinline__ WalkArrays walk_scratch(int32_t *buf, int64_t n, int64_t st,
+                                                   uint32_t *ray) {
+  WalkArrays w{};
+  w.nb = buf + 2 * st;
+  w.eid = buf + 2 * n + 2 * st;
+  w.gray = reinterpret_cast<uint64_t *>(buf + 4 * n) + 2 * st;
+  w.ray = ray;
+  return w;
+}
 
 // What a component's contig record takes from the component table: its
 // record index (the component's (bin, label) rank), label and bin.  Loaded
@@ -1043,23 +1054,28 @@ __device__ __forceinline__ CompRec comp_rec(const cg_parts &parts, int c) {
 }
 
 // Steps 2-5 of the walk, from the component's rows in w (nb, eid; and in the
-// LDS form vid, rlen, roff, es, eo, ep).
-template <int BLOCK, int CAP, bool kLds>
-__device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, WalkArrays w,
+// LDS form vid, rlen, roff, es, eo, ep); first: the smallest of the thread's
+// reads that has one neighbour (0x7FFFFFFF: none).
+template <int BLOCK, int CAP, WalkMode kMode>
+__device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int first, WalkArrays w,
                                            const cg_graph &g, const int32_t *__restrict__ perm,
                                            const cg_contigs &out, const Scratch &s,
-                                           uint32_t *sh_scan);
+                                           uint64_t *sh_scan);
 
-template <int BLOCK, int CAP, bool kLds>
+// A component of one workgroup of BLOCK threads, or of one wave of a larger
+// workgroup (BLOCK = kWave: no workgroup barrier, the arrays are the wave's
+// own).
+template <int BLOCK, int CAP, WalkMode kMode>
 __device__ __forceinline__ void walk_component(
     int c, int q, int st, WalkArrays w, const cg_graph &g, const cg_parts &parts,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ loc_row_ptr,
     const int32_t *__restrict__ loc_col, const int32_t *__restrict__ loc_eid,
-    const cg_contigs &out, const Scratch &s, int32_t *sh_small, uint32_t *sh_scan) {
-  const int tid = threadIdx.x;
+    const cg_contigs &out, const Scratch &s, uint64_t *sh_scan) {
+  const int tid = BLOCK == kWave ? lane_id() : (int)threadIdx.x;
   const CompRec cr = comp_rec(parts, c);
+  int first = 0x7FFFFFFF;
   // 1. local rows of the component's block
-  if constexpr (kLds) {
+  if constexpr (kMode == kWalkLds) {
     // and, in three rounds of loads issued together, the read ids and
     // lengths and the entries' strand bits and overlaps (or coordinates)
     constexpr int R = CAP / BLOCK;
@@ -1128,8 +1144,7 @@ __device__ __forceinline__ void walk_component(
       if (i >= q) continue;
       w.nb[2 * i] = c0[u] >= 0 ? c0[u] - st : -1;
       w.nb[2 * i + 1] = c1[u] >= 0 ? c1[u] - st : -1;
-      w.eid[2 * i] = e0[u];
-      w.eid[2 * i + 1] = e1[u];
+      if (c0[u] >= 0 && c1[u] < 0 && i < first) first = i;
       w.vid[i] = rv[u];
       w.rlen[i] = rl[u];
       w.roff[i] = ro[u];
@@ -1141,249 +1156,347 @@ __device__ __forceinline__ void walk_component(
       w.ep[2 * i + 1] = p1[u];
     }
   } else {
-    for (int i = tid; i < q; i += BLOCK) {
-      const int a = loc_row_ptr[st + i], b = loc_row_ptr[st + i + 1];
-      const int deg = b - a;
-      w.nb[2 * i] = deg >= 1 ? loc_col[a] - st : -1;
-      w.nb[2 * i + 1] = deg >= 2 ? loc_col[a + 1] - st : -1;
-      w.eid[2 * i] = deg >= 1 ? loc_eid[a] : -1;
-      w.eid[2 * i + 1] = deg >= 2 ? loc_eid[a + 1] : -1;
+    constexpr int U = 4;
+    for (int b0 = tid; b0 < q; b0 += U * BLOCK) {
+      int a[U], deg[U], c0[U], c1[U], e0[U], e1[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = b0 + u * BLOCK < q ? b0 + u * BLOCK : q - 1;
+        a[u] = loc_row_ptr[st + i];
+        deg[u] = loc_row_ptr[st + i + 1] - a[u];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c0[u] = deg[u] >= 1 ? loc_col[a[u]] - st : -1;
+        c1[u] = deg[u] >= 2 ? loc_col[a[u] + 1] - st : -1;
+        e0[u] = deg[u] >= 1 ? loc_eid[a[u]] : -1;
+        e1[u] = deg[u] >= 2 ? loc_eid[a[u] + 1] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = b0 + u * BLOCK;
+        if (i >= q) continue;
+        w.nb[2 * i] = c0[u];
+        w.nb[2 * i + 1] = c1[u];
+        if (deg[u] == 1 && i < first) first = i;
+        w.eid[2 * i] = e0[u];
+        w.eid[2 * i + 1] = e1[u];
+      }
     }
   }
-  __syncthreads();
-  walk_chain<BLOCK, CAP, kLds>(cr, q, st, w, g, perm, out, s, sh_scan);
-  (void)sh_small;
+  walk_chain<BLOCK, CAP, kMode>(cr, q, st, first, w, g, perm, out, s, sh_scan);
 }
 
-template <int BLOCK, int CAP, bool kLds>
-__device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, WalkArrays w,
+// Ray (i, k) leaves read i through slot k.  It holds how many steps it has
+// gone and the ray it goes on with, or how it ended: at the walk's start or
+// at the chain's other end.  Both are in one word, so that a jump
+// (ray += the ray it goes on with) replaces them together: a ray's word is
+// true whenever it is read, and no barrier is needed between jumps.
+struct Ray32 {  // LDS: steps << 16 | next (rays and steps below 0xFFFE)
+  typedef uint32_t T;
+  static constexpr T kAtStart = 0xFFFEu, kAtEnd = 0xFFFFu;
+  static __device__ __forceinline__ T make(uint32_t steps, T next) { return steps << 16 | next; }
+  static __device__ __forceinline__ T next(T x) { return x & 0xFFFFu; }
+  static __device__ __forceinline__ int steps(T x) { return (int)(x >> 16); }
+  static __device__ __forceinline__ T jump(T x, T y) { return (x & 0xFFFF0000u) + y; }
+};
+struct Ray64 {  // global memory: steps << 32 | next
+  typedef uint64_t T;
+  static constexpr T kAtStart = 0xFFFFFFFEull, kAtEnd = 0xFFFFFFFFull;
+  static __device__ __forceinline__ T make(uint32_t steps, T next) {
+    return (uint64_t)steps << 32 | next;
+  }
+  static __device__ __forceinline__ T next(T x) { return x & 0xFFFFFFFFull; }
+  static __device__ __forceinline__ int steps(T x) { return (int)(x >> 32); }
+  static __device__ __forceinline__ T jump(T x, T y) { return (x & ~0xFFFFFFFFull) + y; }
+};
+template <typename T>
+__device__ __forceinline__ T ray_ld(const T *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void ray_st(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Jumps the rays to their ends (pointer doubling; U rays of a thread at a
+// time, their loads issued together).  Every pass of the loop moves a ray
+// that has not ended at least one ray on, so it ends within q passes
+// whatever the other waves do, and within about log2 q when they keep up.
+template <typename RAY, int BLOCK, int U>
+__device__ __forceinline__ void walk_rays(typename RAY::T *ray, int n_rays, int tid) {
+  typedef typename RAY::T T;
+  for (int r0 = tid; r0 < n_rays; r0 += U * BLOCK) {
+    T x[U];
+    bool more = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + u * BLOCK;
+      x[u] = r < n_rays ? ray_ld(ray + r) : RAY::kAtEnd;
+      more = more || RAY::next(x[u]) < RAY::kAtStart;
+    }
+    // (no more passes than reads, so that no input can keep it here)
+    for (int pass = 0; more && pass < n_rays / 2; ++pass) {
+      T y[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const T nx = RAY::next(x[u]);
+        y[u] = ray_ld(ray + (nx < RAY::kAtStart ? (int)nx : 0));
+      }
+      more = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (RAY::next(x[u]) >= RAY::kAtStart) continue;
+        x[u] = RAY::jump(x[u], y[u]);
+        ray_st(ray + r0 + u * BLOCK, x[u]);
+        more = more || RAY::next(x[u]) < RAY::kAtStart;
+      }
+    }
+  }
+}
+
+template <int BLOCK, int CAP, WalkMode kMode>
+__device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int first, WalkArrays w,
                                            const cg_graph &g, const int32_t *__restrict__ perm,
                                            const cg_contigs &out, const Scratch &s,
-                                           uint32_t *sh_scan) {
-  const int tid = threadIdx.x;
+                                           uint64_t *sh_scan) {
+  constexpr bool kLds = kMode == kWalkLds;
+  constexpr bool kOneWave = BLOCK == kWave;
+  const int tid = kOneWave ? lane_id() : (int)threadIdx.x;
   // the LDS form orders LDS only at its barriers (its global stores stay in
   // flight; nothing it reads back from global memory was written here); the
-  // global form's arrays are global memory
+  // other forms' arrays are global memory
   auto wbar = [] {
-    if constexpr (kLds) lds_barrier();
+    if constexpr (kOneWave) wave_lds_sync();
+    else if constexpr (kLds) lds_barrier();
     else __syncthreads();
   };
-  __shared__ int s_start, s_cyc, s_sej;
-  __shared__ uint64_t s_carry;
-  if (tid == 0) {
-    s_start = 0x7FFFFFFF;
-    s_cyc = 0;
-    s_sej = 0;
-    s_carry = 0;
-  }
-  wbar();
   // 2. start: the first read of local degree 1 (the smaller-id root, since
   // the block is in id order); a cycle starts at its first read and loses
   // the edge to the larger-numbered neighbour of it
-  for (int i = tid; i < q; i += BLOCK)
-    if ((w.nb[2 * i] >= 0) != (w.nb[2 * i + 1] >= 0)) atomicMin(&s_start, i);
+  __shared__ int s_start, s_sej;  // (a one-wave walk keeps these in registers)
+  if constexpr (!kOneWave) {
+    if (tid == 0) {
+      s_start = 0x7FFFFFFF;
+      s_sej = 0;
+    }
+  }
   wbar();
-  if (tid == 0) {
-    if (s_start == 0x7FFFFFFF) {
-      s_start = 0;
-      if (q > 1) {
-        s_cyc = 1;
-        const int x = w.nb[0], y = w.nb[1];
-        const int t = x > y ? x : y;  // closing neighbour
-        if (x > y) w.nb[0] = -1; else w.nb[1] = -1;
-        if (w.nb[2 * t] == 0) w.nb[2 * t] = -1; else w.nb[2 * t + 1] = -1;
+  if constexpr (kOneWave) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      const int o = __shfl_xor(first, off);
+      first = o < first ? o : first;
+    }
+  } else {
+    if (first != 0x7FFFFFFF) atomicMin(&s_start, first);
+    wbar();
+    first = s_start;
+  }
+  const bool cyc = first == 0x7FFFFFFF && q > 1;
+  const int s0 = first == 0x7FFFFFFF ? 0 : first;
+  if (cyc) {  // uniform
+    if (tid == 0) {
+      const int x = w.nb[0], y = w.nb[1];
+      const int t = x > y ? x : y;  // closing neighbour
+      if (x > y) w.nb[0] = -1; else w.nb[1] = -1;
+      if (w.nb[2 * t] == 0) w.nb[2 * t] = -1; else w.nb[2 * t + 1] = -1;
+    }
+    wbar();
+  }
+  // 3. rays, jumped along the chain to its ends
+  typedef typename std::conditional<kMode == kWalkGlobal, Ray64, Ray32>::type RAY;
+  typename RAY::T *ray;
+  if constexpr (kMode == kWalkGlobal) ray = w.gray;
+  else ray = w.ray;
+  constexpr int V = kLds ? (CAP > BLOCK ? CAP / BLOCK : 1) : 2;  // reads of a thread at a time
+  for (int b0 = tid; b0 < q; b0 += V * BLOCK) {
+    int y[V][2], z[V][2][2];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const int i = b0 + u * BLOCK;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) y[u][k] = i < q ? w.nb[2 * i + k] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int x = y[u][k] >= 0 ? y[u][k] : 0;
+        z[u][k][0] = w.nb[2 * x];
+        z[u][k][1] = w.nb[2 * x + 1];
+      }
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const int i = b0 + u * BLOCK;
+      if (i >= q) continue;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        typename RAY::T x = RAY::kAtEnd;
+        if (y[u][k] >= 0) {
+          const int k2 = z[u][k][0] == i ? 1 : 0;  // the neighbour's slot that does not lead back
+          x = RAY::make(1, (k2 ? z[u][k][1] : z[u][k][0]) >= 0
+                               ? (typename RAY::T)(2 * y[u][k] + k2)
+                               : (y[u][k] == s0 ? RAY::kAtStart : RAY::kAtEnd));
+        }
+        ray_st(ray + 2 * i + k, x);
       }
     }
   }
   wbar();
-  const int s0 = s_start;
-  // 3. rays (i, k): leave read i through slot k.  A ray jumps along the
-  // chain; after ceil(log2 q) doublings it knows the chain end it reaches and
-  // how many steps away that end is.
-  for (int r = tid; r < 2 * q; r += BLOCK) {
-    const int y = w.nb[r];
-    if (y < 0) {
-      w.nxt[r] = -1;
-      w.dist[r] = 0;
-      w.endv[r] = -1;
-    } else {
-      const int i = r >> 1;
-      const int k2 = w.nb[2 * y] == i ? 1 : 0;  // y's slot that does not lead back
-      const int z = w.nb[2 * y + k2];
-      w.nxt[r] = z >= 0 ? 2 * y + k2 : -1;
-      w.dist[r] = 1;
-      w.endv[r] = y;
-    }
-  }
+  walk_rays<RAY, BLOCK, kLds ? 2 * CAP / BLOCK : 4>(ray, 2 * q, tid);
   wbar();
-  for (int span = 1; span < q; span <<= 1) {
-    if (kLds && BLOCK == kWave) {
-      // one wave: the rays' successors, then the successors' fields, each
-      // round of a lane's LDS loads issued together (indices in bounds,
-      // results selected after), so a doubling step waits for two rounds of
-      // loads (in a 256-thread workgroup this measured no better)
-      constexpr int U = 2 * CAP / BLOCK;
-      int xr[U], rn[U], rd[U], re[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = tid + u * BLOCK;
-        xr[u] = r < 2 * q ? w.nxt[r] : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = tid + u * BLOCK;
-        const int x = xr[u] >= 0 ? xr[u] : 0;
-        rn[u] = w.nxt[x];
-        rd[u] = w.dist[r] + w.dist[x];
-        re[u] = w.endv[x];
-      }
-      wbar();
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int r = tid + u * BLOCK;
-        if (xr[u] >= 0) {
-          w.nxt[r] = rn[u];
-          w.dist[r] = rd[u];
-          w.endv[r] = re[u];
-        }
-      }
-      wbar();
-    } else if (kLds) {
-      int rn[(2 * CAP / BLOCK)], rd[(2 * CAP / BLOCK)], re[(2 * CAP / BLOCK)];
-#pragma unroll
-      for (int u = 0; u < (2 * CAP / BLOCK); ++u) {
-        const int r = tid + u * BLOCK;
-        rn[u] = -2;
-        if (r < 2 * q) {
-          const int x = w.nxt[r];
-          if (x >= 0) {
-            rn[u] = w.nxt[x];
-            rd[u] = w.dist[r] + w.dist[x];
-            re[u] = w.endv[x];
-          }
-        }
-      }
-      wbar();
-#pragma unroll
-      for (int u = 0; u < (2 * CAP / BLOCK); ++u) {
-        const int r = tid + u * BLOCK;
-        if (rn[u] != -2) {
-          w.nxt[r] = rn[u];
-          w.dist[r] = rd[u];
-          w.endv[r] = re[u];
-        }
-      }
-      wbar();
-    } else {
-      // large component (global arrays): ray r's successor x is only
-      // rewritten by its own owner, so read all then write all in two passes
-      // with the new values parked in the endv/dist of the high half
-      for (int r = tid; r < 2 * q; r += BLOCK) {
-        const int x = w.nxt[r];
-        if (x >= 0) {
-          // encode the update next to the ray: (new nxt, new dist, new end)
-          w.nxt[2 * q + r] = w.nxt[x];
-          w.dist[2 * q + r] = w.dist[r] + w.dist[x];
-          w.endv[2 * q + r] = w.endv[x];
-        } else {
-          w.nxt[2 * q + r] = -2;
-        }
-      }
-      wbar();
-      for (int r = tid; r < 2 * q; r += BLOCK) {
-        const int x = w.nxt[2 * q + r];
-        if (x != -2) {
-          w.nxt[r] = x;
-          w.dist[r] = w.dist[2 * q + r];
-          w.endv[r] = w.endv[2 * q + r];
-        }
-      }
-      wbar();
-    }
-  }
-  // 4. rank, predecessor, successor, orientation and piece of every read
+  // 4. rank, predecessor, successor, orientation and piece of every read, U
+  // reads of a thread at a time: what a read needs comes in three rounds of
+  // loads (its slots and rays; its predecessor's slots, its entries and the
+  // read itself; the two entries' fields), each round's issued together.  In
+  // LDS the compiler keeps more in flight with one read at a time.
   int32_t *R_vid = out.layout_vid + st;
   uint8_t *R_rev = out.layout_rev + st;
   uint32_t *R_len = s.piece_len + st;
   uint64_t *R_src = s.piece_src + st;
   const int rank_c = cr.rank;
-  for (int i = tid; i < q; i += BLOCK) {
-    int rank = 0, pred = -1, succ = -1, succ_e = -1;
-    int ss = -1;  // slot of i leading to its successor
-    if (i == s0) {
-      if (w.nb[2 * i] >= 0) ss = 2 * i;
-      else if (w.nb[2 * i + 1] >= 0) ss = 2 * i + 1;
-    } else {
-      for (int k = 0; k < 2; ++k) {
-        if (w.nb[2 * i + k] >= 0 && w.endv[2 * i + k] == s0) {
-          rank = w.dist[2 * i + k];
-          pred = w.nb[2 * i + k];
-          const int o = 1 - k;
-          if (w.nb[2 * i + o] >= 0) ss = 2 * i + o;
+  const bool coords = g.pre != nullptr;
+  bool sej = false;
+  constexpr int U = kLds ? 1 : 2;
+  for (int b0 = tid; b0 < q; b0 += U * BLOCK) {
+    int rank[U], pred[U], ss[U], ps[U], pe[U], se[U];
+    int32_t v[U];
+    uint32_t L[U], ses[U], pes[U], so[U], pp[U];
+    uint64_t roff[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = b0 + u * BLOCK;
+      rank[u] = 0;
+      pred[u] = ss[u] = -1;
+      v[u] = 0;
+      if (i >= q) continue;
+      const int n0 = w.nb[2 * i], n1 = w.nb[2 * i + 1];
+      const typename RAY::T y0 = ray[2 * i], y1 = ray[2 * i + 1];
+      v[u] = kLds ? w.vid[i] : perm[st + i];
+      if (i == s0) {
+        ss[u] = n0 >= 0 ? 2 * i : (n1 >= 0 ? 2 * i + 1 : -1);
+      } else if (n0 >= 0 && RAY::next(y0) == RAY::kAtStart) {
+        rank[u] = RAY::steps(y0);
+        pred[u] = n0;
+        if (n1 >= 0) ss[u] = 2 * i + 1;
+      } else if (n1 >= 0 && RAY::next(y1) == RAY::kAtStart) {
+        rank[u] = RAY::steps(y1);
+        pred[u] = n1;
+        if (n0 >= 0) ss[u] = 2 * i;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = b0 + u * BLOCK;
+      ps[u] = pe[u] = se[u] = -1;  // ps: slot of pred leading to i (its entry pred -> i)
+      L[u] = 0;
+      roff[u] = 0;
+      if (i >= q) continue;
+      L[u] = kLds ? w.rlen[i] : g.read_len[v[u]];
+      roff[u] = kLds ? w.roff[i] : g.read_off[v[u]];
+      if (!kLds && ss[u] >= 0) se[u] = w.eid[ss[u]];
+      if (pred[u] >= 0) {
+        const bool back0 = w.nb[2 * pred[u]] == i;
+        ps[u] = back0 ? 2 * pred[u] : 2 * pred[u] + 1;
+        if constexpr (!kLds) {
+          const int e0 = w.eid[2 * pred[u]], e1 = w.eid[2 * pred[u] + 1];
+          pe[u] = back0 ? e0 : e1;
         }
       }
     }
-    if (ss >= 0) {
-      succ = w.nb[ss];
-      succ_e = w.eid[ss];
+    // strand bits, overlap or coordinates of the two entries
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      ses[u] = pes[u] = so[u] = pp[u] = 0;
+      if (ss[u] >= 0) {
+        ses[u] = kLds ? w.es[ss[u]] : (uint32_t)g.strand[se[u]];
+        so[u] = kLds ? w.eo[ss[u]] : (coords ? g.pre[se[u]] : g.ovl[se[u]]);
+      }
+      if (ps[u] >= 0) {
+        pes[u] = kLds ? w.es[ps[u]] : (uint32_t)g.strand[pe[u]];
+        if (coords) pp[u] = kLds ? w.ep[ps[u]] : g.post[pe[u]];
+      }
     }
-    int ps = -1;  // slot of pred leading to i (its entry pred -> i)
-    if (i != s0 && pred >= 0) ps = w.nb[2 * pred] == i ? 2 * pred : 2 * pred + 1;
-    // strand bits, overlap or coordinates of the two entries, and the read
-    const int32_t v = kLds ? w.vid[i] : perm[st + i];
-    const uint32_t L = kLds ? w.rlen[i] : g.read_len[v];
-    const uint64_t roff = kLds ? w.roff[i] : g.read_off[v];
-    const uint32_t ses = ss < 0 ? 0u : (kLds ? w.es[ss] : (uint32_t)g.strand[succ_e]);
-    const uint32_t pes = ps < 0 ? 0u : (kLds ? w.es[ps] : (uint32_t)g.strand[w.eid[ps]]);
-    int orient;
-    if (i == s0) orient = ss >= 0 ? (int)(ses & 1) : 0;
-    else if (ps >= 0) orient = (int)((pes >> 1) & 1);
-    else orient = 0;  // unreachable for a chain: every read but the start has a predecessor
-    // the piece: walking offsets [skip, end] of the read (Section 4.4: from
-    // post of the entering entry to pre of the leaving one, in stored
-    // coordinates; from overlap lengths: the read minus its overlap with the
-    // successor)
-    uint32_t skip = 0, plen = L;
-    if (g.pre) {
-      const uint32_t post_in = ps < 0 ? 0u : (kLds ? w.ep[ps] : g.post[w.eid[ps]]);
-      const uint32_t pre_out = ss < 0 ? 0u : (kLds ? w.eo[ss] : g.pre[succ_e]);
-      const int64_t first = ps >= 0 ? (orient ? (int64_t)L - 1 - post_in : post_in) : 0;
-      const int64_t last =
-          ss >= 0 ? (orient ? (int64_t)L - 1 - pre_out : pre_out) : (int64_t)L - 1;
-      skip = (uint32_t)first;
-      plen = last >= first ? (uint32_t)(last - first + 1) : 0u;
-    } else if (ss >= 0) {
-      plen -= kLds ? w.eo[ss] : g.ovl[succ_e];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = b0 + u * BLOCK;
+      if (i >= q) continue;
+      int orient;
+      if (i == s0) orient = ss[u] >= 0 ? (int)(ses[u] & 1) : 0;
+      else if (ps[u] >= 0) orient = (int)((pes[u] >> 1) & 1);
+      else orient = 0;  // unreachable for a chain: every read but the start has a predecessor
+      // the piece: walking offsets [skip, end] of the read (Section 4.4: from
+      // post of the entering entry to pre of the leaving one, in stored
+      // coordinates; from overlap lengths: the read minus its overlap with the
+      // successor)
+      uint32_t skip = 0, plen = L[u];
+      if (coords) {
+        const int64_t first_b =
+            ps[u] >= 0 ? (orient ? (int64_t)L[u] - 1 - pp[u] : (int64_t)pp[u]) : 0;
+        const int64_t last_b =
+            ss[u] >= 0 ? (orient ? (int64_t)L[u] - 1 - so[u] : (int64_t)so[u]) : (int64_t)L[u] - 1;
+        skip = (uint32_t)first_b;
+        plen = last_b >= first_b ? (uint32_t)(last_b - first_b + 1) : 0u;
+      } else if (ss[u] >= 0) {
+        plen -= so[u];
+      }
+      if (ss[u] >= 0 && (int)(ses[u] & 1) != orient) sej = true;
+      R_vid[rank[u]] = v[u];
+      R_rev[rank[u]] = (uint8_t)orient;
+      R_len[rank[u]] = plen;
+      if constexpr (kLds) w.eid[rank[u]] = (int32_t)plen;
+      R_src[rank[u]] = piece_anchor(roff[u], L[u], skip, orient != 0);
+      s.lay_contig[st + rank[u]] = rank_c;
     }
-    if (ss >= 0 && (int)(ses & 1) != orient) s_sej = 1;
-    R_vid[rank] = v;
-    R_rev[rank] = (uint8_t)orient;
-    R_len[rank] = plen;
-    if constexpr (kLds) w.nxt[rank] = (int32_t)plen;  // nxt is free after the rays
-    R_src[rank] = piece_anchor(roff, L, skip, orient != 0);
-    s.lay_contig[st + rank] = rank_c;
-    (void)succ;
+  }
+  uint64_t carry = 0;
+  if constexpr (kOneWave) {
+    sej = __ballot(sej) != 0ull;
+  } else {
+    if (sej) s_sej = 1;
   }
   wbar();
   // 5. piece offsets in walk order
-  for (int base = 0; base < q; base += BLOCK) {
-    const int i = base + tid;
-    const uint32_t x = i < q ? (kLds ? (uint32_t)w.nxt[i] : R_len[i]) : 0u;
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan<uint32_t, BLOCK, kLds>(x, sh_scan, &tot);
-    if (i < q) s.piece_off[st + i] = s_carry + ex;
-    wbar();
-    if (tid == 0) s_carry += tot;
-    wbar();
+  if constexpr (kOneWave) {
+    for (int base = 0; base < q; base += BLOCK) {
+      const int i = base + tid;
+      const uint32_t x = i < q ? (kLds ? (uint32_t)w.eid[i] : R_len[i]) : 0u;
+      const uint32_t inc = wave_incl_scan(x);
+      if (i < q) s.piece_off[st + i] = carry + (inc - x);
+      carry += __shfl(inc, kWave - 1);
+    }
+  } else {
+    // (above the LDS form's sizes, a run of E pieces per thread)
+    constexpr int E = kLds ? 1 : 4;
+    for (int base = 0; base < q; base += E * BLOCK) {
+      const int i = base + tid * E;
+      uint32_t x[E];
+      uint64_t sum = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        x[e] = i + e < q ? (kLds ? (uint32_t)w.eid[i + e] : R_len[i + e]) : 0u;
+        sum += x[e];
+      }
+      uint64_t tot;
+      uint64_t ex = carry + block_excl_scan<uint64_t, BLOCK, kLds>(sum, sh_scan, &tot);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        if (i + e < q) s.piece_off[st + i + e] = ex;
+        ex += x[e];
+      }
+      carry += tot;
+    }
   }
   if (tid == 0) {
+    if constexpr (!kOneWave) sej = s_sej != 0;
     out.label[rank_c] = cr.label;
     out.bin[rank_c] = cr.bin;
     out.start[rank_c] = kLds ? w.vid[s0] : perm[st + s0];
     out.n_reads[rank_c] = q;
-    out.len[rank_c] = s_carry;
-    out.cflags[rank_c] = (q == 1 ? CG_CONTIG_SINGLE : 0u) | (s_cyc ? CG_CONTIG_CIRCULAR : 0u) |
-                         (s_sej ? CG_CONTIG_SAME_END_JOIN : 0u);
+    out.len[rank_c] = carry;
+    out.cflags[rank_c] = (q == 1 ? CG_CONTIG_SINGLE : 0u) | (cyc ? CG_CONTIG_CIRCULAR : 0u) |
+                         (sej ? CG_CONTIG_SAME_END_JOIN : 0u);
     out.layout_off[rank_c] = st;
   }
   wbar();

@@ -4,12 +4,10 @@
 // contributes the part of its walking orientation that precedes its overlap
 // with the next read (len - ovl bases), the last read all its bases.
 //
-//  k_asm_walk_small  one wave per component of at most kWalkSmallCap reads
-//                 (small LDS arrays, so many are walked at once per CU)
-//  k_asm_walk     one workgroup per larger component: start read, walk order
-//                 by pointer jumping over the chain's arcs (Wyllie list
-//                 ranking), orientation from the strand bits, piece lengths
-//                 and offsets, layout and contig record
+//  k_asm_walk     every component by its size (a lane, a wave, a workgroup):
+//                 start read, walk order by pointer jumping over the chain's
+//                 arcs (Wyllie list ranking), orientation from the strand
+//                 bits, piece lengths and offsets, layout and contig record
 //  k_asm_offsets  contig base offsets (16-base aligned) in (bin, label) order
 //  k_asm_copy     chunks of consecutive pieces, one wave each: every output
 //                 word is written by the piece holding its first base, 2-bit
@@ -19,111 +17,159 @@
 
 namespace cg {
 
-constexpr int32_t kWalkSplitReads = 1 << 19;  // reads from which the walk takes two passes
-
-__global__ __launch_bounds__(kWalkSmallBlock) void k_asm_walk_small(cg_graph g, cg_parts parts,
-                                                                   cg_local local, cg_contigs out,
-                                                                   Scratch s) {
-  __shared__ int32_t s_nb[2 * kWalkSmallCap], s_eid[2 * kWalkSmallCap], s_nxt[2 * kWalkSmallCap],
-      s_dist[2 * kWalkSmallCap], s_endv[2 * kWalkSmallCap], s_vid[kWalkSmallCap];
-  __shared__ uint32_t s_rlen[kWalkSmallCap], s_eo[2 * kWalkSmallCap], s_ep[2 * kWalkSmallCap];
-  __shared__ uint64_t s_roff[kWalkSmallCap];
-  __shared__ uint8_t s_es[2 * kWalkSmallCap];
-  __shared__ uint32_t sh_scan[kWalkSmallBlock / kWave + 1];
-  const int nc = *parts.d_n_comp;
-  for (int c = blockIdx.x; c < nc; c += gridDim.x) {
-    const int q = parts.comp_size[c];
-    if (q > kWalkSmallCap) continue;  // k_asm_walk's
-    const int st = parts.comp_start[c];
-    WalkArrays w{s_nb, s_eid, s_nxt, s_dist, s_endv, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
-    walk_component<kWalkSmallBlock, kWalkSmallCap, true>(c, q, st, w, g, parts, local.perm,
-                                                         local.loc_row_ptr, local.loc_col,
-                                                         local.loc_eid, out, s, nullptr, sh_scan);
-  }
+// One-read components: a lane each.
+__device__ __forceinline__ void walk_single(const cg_graph &g, const cg_parts &parts, int c, int st,
+                                            const cg_contigs &out, const Scratch &s) {
+  const CompRec cr = comp_rec(parts, c);
+  const int32_t v = cr.label;
+  const uint32_t L = g.read_len[v];
+  const uint64_t off = g.read_off[v];
+  out.layout_vid[st] = v;
+  out.layout_rev[st] = 0;
+  s.piece_len[st] = L;
+  s.piece_src[st] = piece_anchor(off, L, 0, false);
+  s.piece_off[st] = 0;
+  s.lay_contig[st] = cr.rank;
+  out.label[cr.rank] = v;
+  out.bin[cr.rank] = cr.bin;
+  out.start[cr.rank] = v;
+  out.n_reads[cr.rank] = 1;
+  out.len[cr.rank] = L;
+  out.cflags[cr.rank] = CG_CONTIG_SINGLE;
+  out.layout_off[cr.rank] = st;
 }
 
-// skip_to: components of at most this many reads are k_asm_walk_small's (0:
-// every component is this kernel's).  Components of up to kAsmWalkCap reads
-// are walked in LDS, larger ones in global scratch: LDS arrays for 512 reads
-// let four workgroups share a compute unit (two with arrays for 1024), and
-// a component's walk is mostly latency, so more of them at once pays.
+// Components by size: a lane for one read, a wave up to kWalkSmallCap reads,
+// a workgroup up to kAsmWalkCap reads with everything in LDS, up to
+// kAsmRaysCap reads with the rays in LDS, and above with them in global
+// memory.  A component's walk is mostly latency (dependent gathers), so as
+// many as possible run at once: the LDS of four waves' components is that of
+// a workgroup's, 27 KB, five workgroups to a compute unit.
+// Workgroups 0 .. n_big - 1 take the components above kWalkSmallCap reads, so
+// that the longest ones start first; the waves of the others take runs of
+// consecutive components.
+constexpr int kAsmWalkBlock = 256;
 constexpr int kAsmWalkCap = 512;
-static_assert(kAsmWalkCap % kWalkBlock == 0, "whole members per thread");
-__global__ __launch_bounds__(kWalkBlock) void k_asm_walk(cg_graph g, cg_parts parts, cg_local local,
-                                                         cg_contigs out, Scratch s,
-                                                         int32_t *gbuf, int32_t skip_to) {
-  __shared__ int32_t s_nb[2 * kAsmWalkCap], s_eid[2 * kAsmWalkCap], s_nxt[2 * kAsmWalkCap],
-      s_dist[2 * kAsmWalkCap], s_endv[2 * kAsmWalkCap], s_vid[kAsmWalkCap];
-  __shared__ uint32_t s_rlen[kAsmWalkCap], s_eo[2 * kAsmWalkCap], s_ep[2 * kAsmWalkCap];
-  __shared__ uint64_t s_roff[kAsmWalkCap];
-  __shared__ uint8_t s_es[2 * kAsmWalkCap];
-  __shared__ uint32_t sh_scan[kWalkBlock / kWave + 1];
+constexpr int kAsmWalkWaves = kAsmWalkBlock / kWave;
+static_assert(kAsmWalkCap % kAsmWalkBlock == 0, "whole members per thread");
+static_assert(kAsmWalkCap == kAsmWalkWaves * kWalkSmallCap, "the waves share the workgroup's LDS");
+constexpr int kAsmWalkWords = 13 * kAsmWalkCap + kAsmWalkCap / 2;  // 54 bytes per read
+constexpr int kAsmRaysCap = kAsmWalkWords / 2;
+__global__ __launch_bounds__(kAsmWalkBlock, 5) void k_asm_walk(
+    cg_graph g, cg_parts parts, cg_local local, cg_contigs out, Scratch s, int n_big) {
+  __shared__ alignas(16) uint32_t buf[kAsmWalkWords];
+  __shared__ uint64_t sh_scan[kAsmWalkBlock / kWave + 1];
+  __shared__ int s_n;
+  __shared__ int32_t s_list[kAsmWalkBlock];
   const int nc = *parts.d_n_comp;
-  const int n = g.n;
-  for (int c = blockIdx.x; c < nc; c += gridDim.x) {
-    const int q = parts.comp_size[c];
-    if (q <= skip_to) continue;  // k_asm_walk_small's
-    const int st = parts.comp_start[c];
-    if (q <= kAsmWalkCap) {
-      WalkArrays w{s_nb, s_eid, s_nxt, s_dist, s_endv, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
-      walk_component<kWalkBlock, kAsmWalkCap, true>(c, q, st, w, g, parts, local.perm, local.loc_row_ptr, local.loc_col,
-                           local.loc_eid, out, s, nullptr, sh_scan);
-    } else {
-      // per-component slices of global scratch: the blocks of different
-      // components are disjoint, so slices never overlap
-      WalkArrays w{gbuf + 2 * (int64_t)st, gbuf + 2 * (int64_t)n + 2 * (int64_t)st,
-                   gbuf + 4 * (int64_t)n + 4 * (int64_t)st,
-                   gbuf + 8 * (int64_t)n + 4 * (int64_t)st,
-                   gbuf + 12 * (int64_t)n + 4 * (int64_t)st};
-      walk_component<kWalkBlock, kWalkCap, false>(c, q, st, w, g, parts, local.perm, local.loc_row_ptr, local.loc_col,
-                            local.loc_eid, out, s, nullptr, sh_scan);
+  // the arrays of cap reads from read slot r0 of kAsmWalkCap on
+  auto arrays = [&](int r0) {
+    constexpr int C = kAsmWalkCap;
+    WalkArrays w{};
+    w.roff = reinterpret_cast<uint64_t *>(buf) + r0;
+    w.nb = reinterpret_cast<int32_t *>(buf + 2 * C) + 2 * r0;
+    w.ray = buf + 4 * C + 2 * r0;
+    w.eo = buf + 6 * C + 2 * r0;
+    w.ep = buf + 8 * C + 2 * r0;
+    w.vid = reinterpret_cast<int32_t *>(buf + 10 * C) + r0;
+    w.rlen = buf + 11 * C + r0;
+    w.eid = reinterpret_cast<int32_t *>(buf + 12 * C) + r0;  // the piece lengths only
+    w.es = reinterpret_cast<uint8_t *>(buf + 13 * C) + 2 * r0;
+    return w;
+  };
+  if ((int)blockIdx.x < n_big) {
+    for (int64_t base = blockIdx.x; base < nc; base += (int64_t)n_big * kAsmWalkBlock) {
+      if (threadIdx.x == 0) s_n = 0;
+      __syncthreads();
+      const int64_t x = base + (int64_t)n_big * threadIdx.x;
+      if (x < nc && parts.comp_size[x] > kWalkSmallCap) s_list[atomicAdd(&s_n, 1)] = (int32_t)x;
+      __syncthreads();
+      const int k = s_n;
+      for (int i = 0; i < k; ++i) {
+        const int c = __builtin_amdgcn_readfirstlane(s_list[i]);
+        const int q = parts.comp_size[c], st = parts.comp_start[c];
+        if (q <= kAsmWalkCap) {
+          walk_component<kAsmWalkBlock, kAsmWalkCap, kWalkLds>(
+              c, q, st, arrays(0), g, parts, local.perm, local.loc_row_ptr, local.loc_col,
+              local.loc_eid, out, s, sh_scan);
+        } else if (q <= kAsmRaysCap) {
+          walk_component<kAsmWalkBlock, kAsmRaysCap, kWalkRaysLds>(
+              c, q, st, walk_scratch(s.walk, g.n, st, buf), g, parts, local.perm,
+              local.loc_row_ptr, local.loc_col, local.loc_eid, out, s, sh_scan);
+        } else {
+          walk_component<kAsmWalkBlock, kAsmRaysCap, kWalkGlobal>(
+              c, q, st, walk_scratch(s.walk, g.n, st, buf), g, parts, local.perm,
+              local.loc_row_ptr, local.loc_col, local.loc_eid, out, s, sh_scan);
+        }
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int64_t w = (int64_t)(blockIdx.x - n_big) * kAsmWalkWaves + wv;
+  const int64_t nw = (int64_t)(gridDim.x - n_big) * kAsmWalkWaves;
+  int64_t run = (nc + nw - 1) / nw;
+  if (run > kWave) run = kWave;
+  for (int64_t c0 = w * run; c0 < nc; c0 += nw * run) {
+    const int64_t c = c0 + lane_id();
+    const bool live = lane_id() < run && c < nc;
+    const int32_t q = live ? parts.comp_size[c] : 0;
+    const int32_t st = live ? parts.comp_start[c] : 0;
+    if (q == 1) walk_single(g, parts, (int)c, st, out, s);
+    for (uint64_t todo = __ballot(q > 1 && q <= kWalkSmallCap); todo; todo &= todo - 1) {
+      const int t = (int)__builtin_ctzll(todo);
+      const int tq = __builtin_amdgcn_readlane(q, t), tst = __builtin_amdgcn_readlane(st, t);
+      walk_component<kWave, kWalkSmallCap, kWalkLds>(
+          (int)c0 + t, tq, tst, arrays(wv * kWalkSmallCap), g, parts, local.perm,
+          local.loc_row_ptr, local.loc_col, local.loc_eid, out, s, sh_scan);
     }
   }
 }
 
-// contig word offsets: one workgroup, scan of ceil(len/16) in record order
-constexpr int kOffRun = 8;  // contigs per thread k_asm_offsets holds in registers
+// contig word offsets: scan of ceil(len/16) in record order.  One workgroup
+// up to kOffItems contigs, what its threads hold in registers (5 us); above,
+// the workgroups of a look-back scan over kOffItems contigs each, the others
+// leave at once (110,000 contigs: 15 us, 146 us in one workgroup's rounds).
+constexpr int kOffRun = 8;  // contigs per thread, in registers
+constexpr int kOffItems = kOffRun * kScanBlock;
 __global__ __launch_bounds__(kScanBlock) void k_asm_offsets(const int32_t *__restrict__ d_n_comp,
                                                             const uint64_t *__restrict__ len,
                                                             uint64_t *__restrict__ base_off,
                                                             uint64_t cap_words,
                                                             uint64_t *__restrict__ d_total_words,
-                                                            Fixed *fx) {
+                                                            Fixed *fx, ScanCtx sc) {
   __shared__ unsigned long long sh[kScanBlock / kWave + 1];
   const int nc = *d_n_comp;
-  unsigned long long carry = 0;
-  if (nc <= kOffRun * kScanBlock) {
-    // thread t takes contigs t*E .. t*E + E-1: their lengths loaded at once,
-    // one block scan of the thread sums (a loop over blocks of contigs
-    // waited for a load and a scan per block)
-    const int E = (nc + kScanBlock - 1) / kScanBlock;
-    const int k0 = (int)threadIdx.x * E;
-    unsigned long long w[kOffRun], x = 0;
+  const int nblocks = nc > kOffItems ? (int)(((int64_t)nc + kOffItems - 1) / kOffItems) : 1;
+  if ((int)blockIdx.x >= nblocks) return;
+  const int blk = nblocks > 1 ? lookback_ticket(sc) : 0;
+  // thread t takes E consecutive contigs, their lengths loaded at once: one
+  // block scan of the thread sums (a loop over blocks of contigs waited for a
+  // load and a scan per block)
+  const int cnt = nc - blk * kOffItems < kOffItems ? nc - blk * kOffItems : kOffItems;
+  const int E = (cnt + kScanBlock - 1) / kScanBlock;
+  const int k0 = blk * kOffItems + (int)threadIdx.x * E;
+  const int k1 = blk * kOffItems + cnt;
+  unsigned long long w[kOffRun], x = 0;
 #pragma unroll
-    for (int r = 0; r < kOffRun; ++r) {
-      w[r] = r < E && k0 + r < nc ? (len[k0 + r] + 15) / 16 : 0;
-      x += w[r];
-    }
-    unsigned long long ex = block_excl_scan<unsigned long long, kScanBlock>(x, sh, &carry);
+  for (int r = 0; r < kOffRun; ++r) {
+    w[r] = r < E && k0 + r < k1 ? (len[k0 + r] + 15) / 16 : 0;
+    x += w[r];
+  }
+  unsigned long long ex, total;
+  if (nblocks > 1) ex = lookback_block_scan(sc, blk, x, &total);
+  else ex = block_excl_scan<unsigned long long, kScanBlock>(x, sh, &total);
 #pragma unroll
-    for (int r = 0; r < kOffRun; ++r) {
-      if (r < E && k0 + r < nc) base_off[k0 + r] = 16 * ex;
-      ex += w[r];
-    }
-  } else {
-    for (int base = 0; base < nc; base += kScanBlock) {
-      const int k = base + threadIdx.x;
-      const unsigned long long wds = k < nc ? (len[k] + 15) / 16 : 0;
-      unsigned long long tot;
-      const unsigned long long ex = block_excl_scan<unsigned long long, kScanBlock>(wds, sh, &tot);
-      if (k < nc) base_off[k] = 16 * (carry + ex);
-      carry += tot;
-    }
+  for (int r = 0; r < kOffRun; ++r) {
+    if (r < E && k0 + r < k1) base_off[k0 + r] = 16 * ex;
+    ex += w[r];
   }
-  if (threadIdx.x == 0) {
-    *d_total_words = carry;
-    if (carry > cap_words) atomicOr(&fx->status, CG_STATUS_BASES_OVERFLOW);
+  if (threadIdx.x == 0 && blk == nblocks - 1) {
+    *d_total_words = total;
+    if (total > cap_words) atomicOr(&fx->status, CG_STATUS_BASES_OVERFLOW);
   }
+  if (nblocks > 1) lookback_finish(sc, nblocks);
 }
 
 constexpr int kCopyBlock = 256;
@@ -171,22 +217,20 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
   const int32_t n = g.n;
   if (n == 0) {
     CG_LAUNCH(ctx, k_asm_offsets, dim3(1), dim3(kScanBlock), st, parts.d_n_comp, out.len,
-                       out.base_off, out.cap_words, out.d_total_words, ctx->fixed);
+                       out.base_off, out.cap_words, out.d_total_words, ctx->fixed,
+                       scan_ctx(ctx, s));
     return hip_check(hipGetLastError(), "k_asm");
   }
-  const int wgrid = n < 4096 ? n : 4096;
-  // A large graph has thousands of components, most of them small: those of
-  // at most kWalkSmallCap reads go one wave each to a pass of their own with
-  // small LDS arrays (many per CU).  On a smaller graph the second launch
-  // costs more than it saves (on 125,000 reads: 26 us against 17).
-  const bool split = n >= kWalkSplitReads;
-  if (split)
-    CG_LAUNCH(ctx, k_asm_walk_small, dim3(n < 8192 ? n : 8192), dim3(kWalkSmallBlock), st, g,
-              parts, local, out, s);
-  CG_LAUNCH(ctx, k_asm_walk, dim3(wgrid), dim3(kWalkBlock), st, g, parts, local, out, s,
-                     s.walk, split ? kWalkSmallCap : 0);
-  CG_LAUNCH(ctx, k_asm_offsets, dim3(1), dim3(kScanBlock), st, parts.d_n_comp, out.len,
-                     out.base_off, out.cap_words, out.d_total_words, ctx->fixed);
+  // workgroups for as many components above kWalkSmallCap reads as there can
+  // be, and waves for components of two reads, up to a few rounds of what is
+  // resident at once
+  const int n_big = n / (kWalkSmallCap + 1) < 2048 ? n / (kWalkSmallCap + 1) : 2048;
+  const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
+  CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
+            dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
+  CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
+            dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
+            out.d_total_words, ctx->fixed, scan_ctx(ctx, s));
   // about eight pieces per wave, so a small graph still spreads over the chip
   const int cgrid = (n + 31) / 32 < 8192 ? (n + 31) / 32 : 8192;
   // chunks: kCopyRounds per resident wave slot (kCopyWavesPerCU per compute

@@ -1358,7 +1358,7 @@ __device__ __forceinline__ void induce_listed(const BatchDev &B, int4 d, int32_t
 // nothing back.
 template <int BLOCK, int CAP>
 __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkArrays w,
-                                             uint32_t *sh_scan) {
+                                             uint64_t *sh_scan) {
   constexpr int R = CAP >= BLOCK ? CAP / BLOCK : 1;  // members per thread
   const int tid = threadIdx.x;
   const int q = e.q, st = e.st;
@@ -1433,9 +1433,9 @@ __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkAr
       if (coords) Cq[u].y = (int32_t)gpost[b + 1];
     }
   }
-  // 2. local numbers: the ids in order in a (the walk's nxt array, unused
+  // 2. local numbers: the ids in order in a (the walk's ray array, unused
   // until its rays), each member's rank among them
-  int32_t *a = w.nxt;
+  int32_t *a = reinterpret_cast<int32_t *>(w.ray);
   int32_t rk[R];
   if constexpr (BLOCK == kWave) {
     // one wave: a rank is the number of smaller ids, counted over the lanes
@@ -1508,12 +1508,14 @@ __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkAr
   CG_GLOBAL int32_t *leid = (CG_GLOBAL int32_t *)J.local.loc_eid;
   const int32_t estart = e.estart;
   int32_t carry = 0;
+  int first = 0x7FFFFFFF;  // the thread's first read with one neighbour
   for (int base = 0; base < q; base += BLOCK) {
     const int i = base + tid;
     int32_t n0 = -1, n1 = -1;
     if (i < q) {
       n0 = w.nb[2 * i];
       n1 = w.nb[2 * i + 1];
+      if (n0 >= 0 && n1 < 0 && i < first) first = i;
     }
     const int32_t deg = (n0 >= 0 ? 1 : 0) + (n1 >= 0 ? 1 : 0);
     int32_t tot;
@@ -1533,19 +1535,18 @@ __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkAr
     }
     carry += tot;
   }
-  walk_chain<BLOCK, CAP, true>(cr, q, st, w, J.g, J.local.perm, J.out, J.s, sh_scan);
+  walk_chain<BLOCK, CAP, kWalkLds>(cr, q, st, first, w, J.g, J.local.perm, J.out, J.s, sh_scan);
 }
 
 // 6a. components of at most kWalkTinyCap reads (the queue's tail): one wave
 // each, both steps in one pass, with small LDS arrays so that many waves run
 // at once
 __global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_tiny(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kWalkTinyCap], s_eid[2 * kWalkTinyCap], s_nxt[2 * kWalkTinyCap],
-      s_dist[2 * kWalkTinyCap], s_endv[2 * kWalkTinyCap], s_vid[kWalkTinyCap];
-  __shared__ uint32_t s_rlen[kWalkTinyCap], s_eo[2 * kWalkTinyCap], s_ep[2 * kWalkTinyCap];
+  __shared__ int32_t s_nb[2 * kWalkTinyCap], s_eid[2 * kWalkTinyCap], s_vid[kWalkTinyCap];
+  __shared__ uint32_t s_ray[2 * kWalkTinyCap], s_rlen[kWalkTinyCap], s_eo[2 * kWalkTinyCap], s_ep[2 * kWalkTinyCap];
   __shared__ uint64_t s_roff[kWalkTinyCap];
   __shared__ uint8_t s_es[2 * kWalkTinyCap];
-  __shared__ uint32_t sh_scan[kWalkSmallBlock / kWave + 1];
+  __shared__ uint64_t sh_scan[kWalkSmallBlock / kWave + 1];
   const int32_t lo = ld_const(B.wq_meta, 3), hi = ld_const(B.wq_meta, 0);
   // each round's entry is fetched while the previous round's component runs
   int32_t x = wq_entry(lo, hi, 0);
@@ -1556,19 +1557,18 @@ __global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_tiny(BatchDev 
     x = wq_entry(lo, hi, r);
     if (x >= 0) nx = wq_get(B, x);
     const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_nxt, s_dist, s_endv, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
+    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
     iw_component<kWalkSmallBlock, kWalkTinyCap>(J, e, w, sh_scan);
   }
 }
 
 // 6b. components of kWalkTinyCap + 1 .. kWalkSmallCap reads: one wave each
 __global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_small(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kWalkSmallCap], s_eid[2 * kWalkSmallCap], s_nxt[2 * kWalkSmallCap],
-      s_dist[2 * kWalkSmallCap], s_endv[2 * kWalkSmallCap], s_vid[kWalkSmallCap];
-  __shared__ uint32_t s_rlen[kWalkSmallCap], s_eo[2 * kWalkSmallCap], s_ep[2 * kWalkSmallCap];
+  __shared__ int32_t s_nb[2 * kWalkSmallCap], s_eid[2 * kWalkSmallCap], s_vid[kWalkSmallCap];
+  __shared__ uint32_t s_ray[2 * kWalkSmallCap], s_rlen[kWalkSmallCap], s_eo[2 * kWalkSmallCap], s_ep[2 * kWalkSmallCap];
   __shared__ uint64_t s_roff[kWalkSmallCap];
   __shared__ uint8_t s_es[2 * kWalkSmallCap];
-  __shared__ uint32_t sh_scan[kWalkSmallBlock / kWave + 1];
+  __shared__ uint64_t sh_scan[kWalkSmallBlock / kWave + 1];
   const int32_t lo = ld_const(B.wq_meta, 1), hi = ld_const(B.wq_meta, 3);
   // each round's entry is fetched while the previous round's component runs
   int32_t x = wq_entry(lo, hi, 0);
@@ -1579,7 +1579,7 @@ __global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_small(BatchDev
     x = wq_entry(lo, hi, r);
     if (x >= 0) nx = wq_get(B, x);
     const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_nxt, s_dist, s_endv, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
+    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
     // one member per lane up to kWave reads (a uniform branch), two above
     if (e.q <= kWave) iw_component<kWalkSmallBlock, kWave>(J, e, w, sh_scan);
     else iw_component<kWalkSmallBlock, kWalkSmallCap>(J, e, w, sh_scan);
@@ -1592,15 +1592,14 @@ __global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_small(BatchDev
 // sort in LDS up to kIndLocalCap reads, else in scratch (its walk, whose
 // arrays reuse the tile lists' memory, waits for the next launch)
 static_assert(kIndBlock == kWalkBlock, "one workgroup shape for both components' steps");
-static_assert(kIndLocalCap <= 2 * kIwCap, "the induce step's sort buffer is the walk's nxt array");
-static_assert(kIwCap <= kWalkCap && kIwCap % kWalkBlock == 0, "whole members per thread");
+static_assert(kIndLocalCap <= 2 * kIwCap, "the induce step's sort buffer is the walk's ray array");
+static_assert(kIwCap % kWalkBlock == 0, "whole members per thread");
 __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kIwCap], s_eid[2 * kIwCap], s_nxt[2 * kIwCap],
-      s_dist[2 * kIwCap], s_endv[2 * kIwCap], s_vid[kIwCap];
-  __shared__ uint32_t s_rlen[kIwCap], s_eo[2 * kIwCap], s_ep[2 * kIwCap];
+  __shared__ int32_t s_nb[2 * kIwCap], s_eid[2 * kIwCap], s_vid[kIwCap];
+  __shared__ uint32_t s_ray[2 * kIwCap], s_rlen[kIwCap], s_eo[2 * kIwCap], s_ep[2 * kIwCap];
   __shared__ uint64_t s_roff[kIwCap];
   __shared__ uint8_t s_es[2 * kIwCap];
-  __shared__ uint32_t sh_scan[kWalkBlock / kWave + 1];
+  __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
   const int32_t hi = ld_const(B.wq_meta, 1);
   // each round's entry is fetched while the previous round's component runs
   int32_t x = wq_entry(0, hi, 0);
@@ -1612,33 +1611,36 @@ __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
     if (x >= 0) nx = wq_get(B, x);
     if (e.q > kIwCap) {
       __syncthreads();  // the previous round's LDS is free
-      induce_listed<kIndBlock, kIndLocalCap>(B, make_int4(e.job, e.c, e.q, e.st), s_nxt,
+      induce_listed<kIndBlock, kIndLocalCap>(B, make_int4(e.job, e.c, e.q, e.st), (int32_t *)s_ray,
                                              (int32_t *)sh_scan);
       __syncthreads();
       continue;
     }
     const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_nxt, s_dist, s_endv, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
+    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
     iw_component<kWalkBlock, kIwCap>(J, e, w, sh_scan);
   }
 }
 
-// 7. their walks, with the walk's arrays in scratch
+// 7. their walks, with the walk's arrays in scratch (the rays in LDS up to
+// kWalkRaysCap reads)
 __global__ __launch_bounds__(kWalkBlock) void kb_walk(BatchDev B) {
-  __shared__ uint32_t sh_scan[kWalkBlock / kWave + 1];
+  __shared__ uint32_t s_ray[2 * kWalkRaysCap];
+  __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
   const int32_t hi = ld_const(B.wq_meta, 2);
   for (int32_t r = 0, x; (x = wq_entry(0, hi, r)) >= 0; ++r) {
     const int4 d = wq_at(B, x);
     const int c = d.y, q = d.z, st = d.w;
     const BJob J = job_at(B.jobs, d.x);
-    const int64_t n = J.g.n;
-    int32_t *gb = J.s.walk;
-    WalkArrays w{gb + 2 * (int64_t)st, gb + 2 * n + 2 * (int64_t)st,
-                 gb + 4 * n + 4 * (int64_t)st, gb + 8 * n + 4 * (int64_t)st,
-                 gb + 12 * n + 4 * (int64_t)st};
-    walk_component<kWalkBlock, kWalkCap, false>(c, q, st, w, J.g, J.parts, J.local.perm,
-                                                J.local.loc_row_ptr, J.local.loc_col,
-                                                J.local.loc_eid, J.out, J.s, nullptr, sh_scan);
+    const WalkArrays w = walk_scratch(J.s.walk, J.g.n, st, s_ray);
+    if (q <= kWalkRaysCap)
+      walk_component<kWalkBlock, kWalkRaysCap, kWalkRaysLds>(
+          c, q, st, w, J.g, J.parts, J.local.perm, J.local.loc_row_ptr, J.local.loc_col,
+          J.local.loc_eid, J.out, J.s, sh_scan);
+    else
+      walk_component<kWalkBlock, kWalkRaysCap, kWalkGlobal>(
+          c, q, st, w, J.g, J.parts, J.local.perm, J.local.loc_row_ptr, J.local.loc_col,
+          J.local.loc_eid, J.out, J.s, sh_scan);
   }
 }
 

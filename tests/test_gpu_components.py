@@ -1,5 +1,7 @@
-"""The induce step at the edges of its kernels: components at the sizes where
-a wave, the sort in LDS and the bitmap windows take over from one another,
+"""The induce and assemble steps at the edges of their kernels: components at
+the sizes where a lane, a wave, a workgroup, the sort in LDS and the bitmap
+windows, the walk in LDS, with rays in LDS and with rays in global memory take
+over from one another,
 cycles among them (a cycle moves every later row by two), read ids spread
 wider than one bitmap window, and many cycles by rank.  Outputs are integers:
 equal to the oracle's, element by element."""
@@ -41,8 +43,9 @@ def _graph(rng, chains, cycles=(), isolated=0):
 
 CASES = {
     "wave edges": ([2, 3, 63, 64, 65, 127, 128, 129, 130], [3, 64, 65, 128, 129], 40),
-    "workgroup edges": ([1024, 1025, 2047, 4097], [1023, 3000], 100),
+    "workgroup edges": ([512, 513, 1024, 1025, 3456, 3457], [511, 3000], 100),
     "sort and bitmap": ([16383, 16384, 16385], [16390, 5], 7),
+    "rays apart": ([1025, 3455, 3456, 3457], [7000, 514], 30_000),
     "two windows": ([17000, 40, 2], [16500], 300_000),
     "cycles by rank": ([2] * 3000, [3] * 5000 + [4] * 300, 11),
 }
@@ -50,9 +53,9 @@ CASES = {
 
 @pytest.mark.parametrize("name", sorted(CASES))
 @pytest.mark.parametrize("min_reads", [1, 2])
-def test_induce_edges(name, min_reads):
+def test_component_edges(name, min_reads):
     from paper_2207_04350_amd import cg
-    print("induce case", name, min_reads, flush=True)
+    print("component case", name, min_reads, flush=True)
     g = _graph(np.random.default_rng(3), *CASES[name])
     P = 5
     ctx = cg.Context.for_graph(g.n, g.m, P)
@@ -65,11 +68,11 @@ def test_induce_edges(name, min_reads):
     assert mismatches(got, oracle.run(g, P=P, min_reads=min_reads)) == []
 
 
-def test_induce_batched_windows():
-    """A component above the batched sort's LDS with ids wider than its
-    bitmap windows."""
+def test_batched_windows_and_rays():
+    """Components above the batched sort's LDS, with ids wider than its bitmap
+    windows and with more rays than LDS holds."""
     from paper_2207_04350_amd import cg
-    g = _graph(np.random.default_rng(4), [3000, 1100, 9], [2000], 60_000)
+    g = _graph(np.random.default_rng(4), [4097, 1100, 513, 9], [700], 60_000)
     ctx = cg.Context(0, 0)
     dg = cg.DeviceGraph(g, "cuda")
     out = cg.Outputs(g.n, 3, g.seq_words, "cuda")
