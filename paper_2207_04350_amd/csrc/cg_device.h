@@ -393,6 +393,108 @@ __device__ __forceinline__ uint32_t *radix_sort_hi16(uint32_t *a, uint32_t *tmp,
   return src;
 }
 
+// The same sort for more keys than registers and LDS hold: n 64-bit keys
+// already in the order of their low words, sorted by the bytes of their high
+// words.  Each wave reads its run twice a pass, for the counts and for the
+// places; a round of 64 keys that all hold one digit (most of a graph's
+// components are one read long) needs no ballots.  For 110,000 keys of one
+// byte a pass takes about 20 us of one workgroup where the bitonic sort,
+// which this replaces, took 3 ms.
+template <int BLOCK>
+__device__ __forceinline__ uint64_t *radix_sort_hi32(uint64_t *a, uint64_t *tmp, int n, int passes,
+                                                     uint32_t *cnt, uint32_t *sh) {
+  constexpr int NW = BLOCK / kWave;
+  constexpr int E = 256 * NW / BLOCK;
+  constexpr int U = 8;  // rounds whose loads are issued together
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), l = lane_id();
+  const int per_w = ((n + NW - 1) / NW + kWave - 1) & ~(kWave - 1);
+  const int64_t i0 = (int64_t)w * per_w;
+  const int64_t i1 = i0 + per_w < n ? i0 + per_w : n;
+  const uint64_t below = (1ull << l) - 1ull;
+  uint32_t *my = cnt + w * 256;
+  uint64_t *src = a, *dst = tmp;
+  for (int p = 0; p < passes; ++p) {
+    const int s = 32 + 8 * p;
+    for (int d = l; d < 256; d += kWave) my[d] = 0;
+    wave_lds_sync();
+    for (int64_t i = i0; i < i1; i += U * kWave) {
+      uint32_t d[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = i + u * kWave + l;
+        d[u] = k < i1 ? (uint32_t)(src[k] >> s) & 255u : 256u;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint64_t live = __ballot(d[u] < 256u);
+        const uint32_t d0 = __builtin_amdgcn_readfirstlane((int)d[u]);
+        if (__ballot(d[u] == d0) == live) {
+          if (l == 0 && live) my[d0] += (uint32_t)__popcll(live);
+        } else if (d[u] < 256u) {
+          atomicAdd(my + d[u], 1u);
+        }
+        wave_lds_sync();
+      }
+    }
+    __syncthreads();
+    uint32_t c[E], sum = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int e = (int)threadIdx.x * E + k;
+      c[k] = cnt[(e % NW) * 256 + e / NW];
+      sum += c[k];
+    }
+    uint32_t tot;
+    uint32_t ex = block_excl_scan<uint32_t, BLOCK>(sum, sh, &tot);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int e = (int)threadIdx.x * E + k;
+      cnt[(e % NW) * 256 + e / NW] = ex;
+      ex += c[k];
+    }
+    __syncthreads();
+    for (int64_t i = i0; i < i1; i += U * kWave) {
+      uint64_t x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = i + u * kWave + l;
+        x[u] = k < i1 ? src[k] : 0ull;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool v = i + u * kWave + l < i1;
+        const uint64_t live = __ballot(v);
+        const uint32_t d = (uint32_t)(x[u] >> s) & 255u;
+        const uint32_t d0 = __builtin_amdgcn_readfirstlane((int)d);
+        uint64_t peers = live;
+        if (__ballot(v && d == d0) != live) {
+#pragma unroll
+          for (int b = 0; b < 8; ++b) {
+            const bool bit = (d >> b) & 1u;
+            const uint64_t m = __ballot(v && bit);
+            peers &= bit ? m : ~m;
+          }
+        }
+        const uint32_t at = my[d];
+        wave_lds_sync();
+        if (v) {
+          dst[at + (uint32_t)__popcll(peers & below)] = x[u];
+          if ((peers & below) == 0) my[d] = at + (uint32_t)__popcll(peers);
+        }
+        wave_lds_sync();
+      }
+    }
+    __syncthreads();
+    uint64_t *t = src;
+    src = dst;
+    dst = t;
+  }
+  return src;
+}
+
+// bytes of x that are not all zero from the top
+__device__ __forceinline__ int value_bytes(uint32_t x) { return (39 - __clz(x)) >> 3; }
+
 // number of elements of the sorted array a[0..len) that are < x
 __device__ __forceinline__ int lower_bound_u64(const uint64_t *a, int len, uint64_t x) {
   int lo = 0, hi = len;
@@ -435,16 +537,56 @@ __device__ __forceinline__ uint32_t lpt_item_weight(const uint32_t *srt, const u
 constexpr int kBinBits = 16;
 constexpr int kLptRoundMin = 6;   // equal items taken as one round from this many
 constexpr int kLptPrefixMin = 8;  // prefix rounds (any weights) from this many items
+constexpr int kLptBulkMin = 256;  // whole rounds of equal items taken at once from this many
+
+// One past the last item of item a's weight wt, by the whole wave: 64 probes
+// a step.  a holds wt; the items' weights do not increase.
+__device__ __forceinline__ int lpt_run_end(const uint32_t *srt, const uint64_t *keys, bool k32,
+                                           int a, int nc, uint32_t wt) {
+  int lo = a, hi = nc;  // lo holds wt, hi does not (or is the end)
+  while (hi - lo > 1) {
+    const int step = (hi - lo + kWave - 1) / kWave;
+    const int64_t i = (int64_t)lo + (int64_t)(lane_id() + 1) * step;
+    const int k = __popcll(__ballot(i < hi && lpt_item_weight(srt, keys, k32, (int)i) == wt));
+    lo += k * step;
+    hi = hi < lo + step ? hi : lo + step;
+  }
+  return hi;
+}
+
+// The values of lanes 0..c-1 and those of lanes c..63, each sorted across its
+// lanes, merged by rank: lanes 0..c-1 search lanes c..63, the others lanes
+// 0..c-1 (every lane runs every step; equal values, which only padding lanes
+// hold, keep their order).
+__device__ __forceinline__ uint32_t lpt_merge_lanes(uint32_t x, int l, int c) {
+  int lo = l < c ? c : 0, hi = l < c ? kWave : c;
+  for (int it = 0; it < 7; ++it) {
+    const int mid = (lo + hi) >> 1;
+    const uint32_t v = (uint32_t)__shfl((int)x, mid & (kWave - 1));
+    if (lo < hi) {
+      if (v < x) lo = mid + 1;
+      else hi = mid;
+    }
+  }
+  const int pos = l < c ? l + (lo - c) : (l - c) + lo;
+  return (uint32_t)__builtin_amdgcn_ds_permute(pos * 4, (int)x);
+}
 
 // With comp_kind and comp_estart given, it also writes each component's
 // first local CSR entry (2(q-1) entries for a path, 2q for a cycle, none for
-// a single read, in (bin, label) order) and returns their total.  bin_reads
-// (global memory, read back with atomic loads) gets the reads of each bin.
-template <int BLOCK>
+// a single read, in (bin, label) order) and returns their total.  bin_reads,
+// if given (global memory, read back with atomic loads), gets the reads of
+// each bin.  kBig: keys and bin_of are global memory (2 nc keys), else LDS
+// (nc up to 8 BLOCK).
+// s_cnt: LDS for the radix sorts, 256 words per wave.
+// comp_rank null: the (bin, label) order is left to a later pass, and bin_of
+// is comp_bin itself.
+template <int BLOCK, bool kBig>
 __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict__ comp_size,
                                         const uint64_t *__restrict__ weight,
-                                        uint64_t *keys, int32_t *bin_of, uint64_t *binA,
-                                        uint64_t *binB, int32_t *__restrict__ comp_bin,
+                                        uint64_t *keys, int32_t *bin_of, uint32_t *s_cnt,
+                                        uint64_t *binA,
+                                        uint64_t *binB, int32_t *comp_bin,
                                         int32_t *__restrict__ comp_rank,
                                         int32_t *__restrict__ comp_start,
                                         uint64_t *__restrict__ bin_load,
@@ -454,17 +596,15 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
                                         int32_t *__restrict__ comp_estart = nullptr) {
   static_assert(BLOCK > 2 * kWave, "the pipelined windows' merge needs threads beyond two waves");
   __shared__ uint64_t win[2][kWave];  // a window's raised keys, alternating buffers
-  __shared__ uint32_t s_cnt[BLOCK >= 1024 ? BLOCK / kWave * 256 : 1];  // the radix sorts' counters
+  __shared__ int32_t s_opbin[kWave];                 // rounds taken at once: their bins in order,
+  __shared__ int32_t s_op_at, s_op_items, s_op_bins;  // first item, items (0: none), bins
   __shared__ int32_t sh_scan[BLOCK / kWave + 1];
   __shared__ int64_t sh_scan64[BLOCK / kWave + 1];
-  __shared__ unsigned long long s_wsum;
   __shared__ unsigned int s_wmax;
+  constexpr bool kBulk = kBig || BLOCK < 1024;
   const int tid = threadIdx.x;
   const int N2 = next_pow2(nc > 0 ? nc : 1);
-  if (tid == 0) {
-    s_wsum = 0;
-    s_wmax = 0;
-  }
+  if (tid == 0) s_wmax = 0;
   __syncthreads();
 
   // 1. sort by (weight desc, label asc); components are indexed in label
@@ -472,49 +612,76 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   // Keys are ((2^32-1 - w) << 32) | i, or, when every weight and index fits
   // 16 bits, ((2^16-1 - w) << 16) | i in 32 bits (k32: the first half of
   // keys holds them); ~0 pads to N2.
-  unsigned long long wsum = 0;
-  uint32_t wmax = 0;
-  for (int i = tid; i < nc; i += blockDim.x) {
-    uint64_t w = weight ? weight[i] : (uint64_t)comp_size[i];
-    if (w > 0xFFFFFFFFull) {
-      atomicOr(status, CG_STATUS_WEIGHT_RANGE);
-      w = 0xFFFFFFFFull;
+  // Eight components per thread and round, their weights loaded together;
+  // the LDS form's are all held in one round.
+  constexpr int kPer = 8;
+  uint32_t *keys32 = reinterpret_cast<uint32_t *>(keys);
+  uint32_t wt8[kPer], wmax = 0;
+  for (int base = 0; base < nc; base += kPer * BLOCK) {
+    if (weight) {
+      uint64_t w[kPer];
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int i = base + k * BLOCK + tid;
+        w[k] = base + k * BLOCK < nc && i < nc ? weight[i] : 0;
+      }
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        if (w[k] > 0xFFFFFFFFull) {
+          atomicOr(status, CG_STATUS_WEIGHT_RANGE);
+          w[k] = 0xFFFFFFFFull;
+        }
+        wt8[k] = (uint32_t)w[k];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int i = base + k * BLOCK + tid;
+        wt8[k] = base + k * BLOCK < nc && i < nc ? (uint32_t)comp_size[i] : 0u;
+      }
     }
-    wsum += w;
-    wmax = w > wmax ? (uint32_t)w : wmax;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) wmax = wt8[k] > wmax ? wt8[k] : wmax;
+    if constexpr (kBig) {
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) {
+        const int i = base + k * BLOCK + tid;
+        if (i < nc) keys[i] = ((uint64_t)(0xFFFFFFFFu - wt8[k]) << 32) | (uint32_t)i;
+      }
+    }
   }
   for (int off = kWave / 2; off > 0; off >>= 1) {
-    wsum += __shfl_xor(wsum, off);
     const uint32_t o = (uint32_t)__shfl_xor((int)wmax, off);
     wmax = o > wmax ? o : wmax;
   }
-  if (lane_id() == 0 && wsum) {
-    atomicAdd(&s_wsum, wsum);
-    atomicMax(&s_wmax, wmax);
-  }
+  if (lane_id() == 0 && wmax) atomicMax(&s_wmax, wmax);
   for (int b = tid; b < P; b += blockDim.x) binA[b] = (uint64_t)b;  // load 0, sorted
   __syncthreads();
-  const bool k32 = nc <= 0xFFFF && s_wmax <= 0xFFFFu;
-  uint32_t *keys32 = reinterpret_cast<uint32_t *>(keys);
-  for (int i = tid; i < N2; i += blockDim.x) {
-    uint64_t w = 0;
-    if (i < nc) {
-      w = weight ? weight[i] : (uint64_t)comp_size[i];
-      w = w > 0xFFFFFFFFull ? 0xFFFFFFFFull : w;
+  const bool k32 = !kBig && nc <= 0xFFFF && s_wmax <= 0xFFFFu;
+  if constexpr (!kBig) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (k * BLOCK >= N2) continue;
+      const int i = k * BLOCK + tid;
+      if (i >= N2) continue;
+      if (k32) keys32[i] = i < nc ? ((0xFFFFu - wt8[k]) << 16) | (uint32_t)i : ~0u;
+      else keys[i] = i < nc ? ((uint64_t)(0xFFFFFFFFu - wt8[k]) << 32) | (uint32_t)i : ~0ull;
     }
-    if (k32)
-      keys32[i] = i < nc ? ((0xFFFFu - (uint32_t)w) << 16) | (uint32_t)i : ~0u;
-    else
-      keys[i] = i < nc ? ((uint64_t)(0xFFFFFFFFu - (uint32_t)w) << 32) | (uint32_t)i : ~0ull;
   }
   __syncthreads();
-  // the keys in LPT order: with a 1024-thread workgroup, radix passes over
-  // the weight's bytes (one when every weight is below 256); else (fewer
-  // waves, whose rounds of the radix sort run one after another, wide keys,
-  // or more keys than the radix sort holds) a bitonic sort
-  constexpr bool kRadix = BLOCK >= 1024;
+  // the keys in LPT order: in LDS with a 1024-thread workgroup, radix passes
+  // over the weight's bytes (one when every weight is below 256), with fewer
+  // waves, whose rounds run one after another, one such pass for more than
+  // two keys a thread; else in LDS a bitonic sort; in global memory radix
+  // passes
+  auto radix = [&](int passes) {
+    return nc <= kRadixRounds * BLOCK && (BLOCK >= 1024 || (passes == 1 && nc > 2 * BLOCK));
+  };
   const uint32_t *srt = keys32;
-  if (kRadix && k32 && nc <= kRadixRounds * BLOCK)
+  if constexpr (kBig)
+    keys = radix_sort_hi32<BLOCK>(keys, keys + nc, nc, value_bytes(s_wmax), s_cnt,
+                                  reinterpret_cast<uint32_t *>(sh_scan));
+  else if (k32 && radix(s_wmax < 256u ? 1 : 2))
     srt = radix_sort_hi16<BLOCK>(keys32, keys32 + N2, nc, s_wmax < 256u ? 1 : 2, s_cnt,
                                  reinterpret_cast<uint32_t *>(sh_scan));
   else if (k32)
@@ -530,14 +697,19 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   // window is merged back into the sorted bin list.
   const int W = P < kWave ? P : kWave;
   const bool single_window = P <= kWave;
-  // Narrow keys: with kb bits for the bin index (2^kb >= P) and a total
-  // weight below 2^(32 - kb) - 1, a bin's key (load << kb) | bin fits 32 bits
-  // below the padding value 0xFFFFFFFF, and a step needs about 12 vector
-  // instructions instead of 17.  Same order, same choices.  The bin lists
-  // hold narrow keys zero-extended, so the window merge is unchanged.
+  // Narrow keys: a bin's key (load << kb) | bin with kb bits for the bin index
+  // (2^kb >= P), less the least load of the window or batch, in 32 bits below
+  // the padding value 0xFFFFFFFF: a step then needs about 12 vector
+  // instructions instead of 17.  Same order, same choices.  The loads differ
+  // by at most the largest weight wmax (a bin's last item found it the least
+  // loaded), the least load rises by at most (64 / W + 1) wmax over a window's
+  // or batch's 64 items, and a raised key adds one weight, which bounds the
+  // differences.  The bin lists hold whole 64-bit keys.
   int kb = 0;
   while ((1 << kb) < P) ++kb;
-  const bool narrow = kb <= 16 && s_wsum + 1 < (1ull << (32 - kb));
+  const bool narrow =
+      kb <= 16 && (unsigned long long)s_wmax * ((kWave + W - 1) / W + 4) + 1 < (1ull << (32 - kb));
+  const int bb = narrow ? kb : kBinBits;
   int i0 = 0;
   if (!single_window && nc > P) {
     // The first round in one pass.  Every weight is at least 1, so item t
@@ -563,8 +735,7 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
         else lo = mid + 1;
       }
       const int pos = (P - lo) + (t - g0);
-      binA[pos] = narrow ? (uint64_t)(((uint32_t)wt << kb) | (uint32_t)t)
-                         : ((uint64_t)wt << kBinBits) | (uint64_t)t;
+      binA[pos] = ((uint64_t)wt << bb) | (uint64_t)t;
       bin_of[k32 ? (srt[t] & 0xFFFFu) : (uint32_t)keys[t]] = t;
     }
     i0 = P;
@@ -578,200 +749,308 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   // barrier per window; the raised keys alternate between two buffers, so a
   // window's keys are written while the other waves still merge the last
   // ones, and the list alternates between binA and binB.
-  uint32_t key32 = 0xFFFFFFFFu;  // wave 0: the window's keys (narrow or wide)
-  uint64_t key64 = ~0ull;
-  if (tid < kWave) {
-    if (narrow) key32 = tid < W ? (uint32_t)binA[tid] : 0xFFFFFFFFu;
-    else key64 = tid < W ? binA[tid] : ~0ull;
+  // Above 64 bins, the items of the least weight (from s_last on, where there
+  // are at least 4 P of them, as one-read components are) go in whole rounds
+  // of the list as far as its order allows, by all threads.
+  int s_last = nc;
+  // items at .. at + items - 1 to bins 0 .. m - 1 of a list, over and over
+  auto store_rounds = [&](int at, int items, int m, auto bin) {
+    int r = m > 0 ? tid % m : 0;
+    const int step = m > 0 ? BLOCK % m : 0;
+#pragma unroll 8
+    for (int k = tid; k < items; k += BLOCK) {
+      bin_of[k32 ? (srt[at + k] & 0xFFFFu) : (uint32_t)keys[at + k]] = bin(r);
+      r += step;
+      r -= r >= m ? m : 0;
+    }
+  };
+  if (kBig && !single_window && nc - i0 >= 8 * P) {
+    const uint32_t wl = lpt_item_weight(srt, keys, k32, nc - 1);
+    int lo = i0, hi = nc - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (lpt_item_weight(srt, keys, k32, mid) > wl) lo = mid + 1;
+      else hi = mid;
+    }
+    if (nc - lo >= 4 * P && wl > 0) s_last = __builtin_amdgcn_readfirstlane(lo);
   }
   int cur = 0;
   while (i0 < nc) {
-    const int T = single_window ? nc - i0 : (nc - i0 < W ? nc - i0 : W);
-    if (tid < kWave && narrow) {
-      const int l = tid;
-      const uint32_t bmask = (1u << kb) - 1u;
-      uint32_t key = key32;
-      for (int base = 0; base < T; base += kWave) {
-        const int cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
-        uint64_t item = 0;
-        if (l < cnt) {
-          const int at = i0 + base + l;
-          item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at] >> 16)) << 32) | (srt[at] & 0xFFFFu)
-                     : keys[at];
+    if (kBig && i0 >= s_last) {
+      const uint64_t wk = (uint64_t)lpt_item_weight(srt, keys, k32, i0) << bb;
+      while (i0 < nc) {
+        // the m bins below the least loaded one's raised key take an item
+        // each, J times over: as long as they all stay below bin m's key
+        const int m = lower_bound_u64(binA, P, binA[0] + wk);
+        int64_t J = (nc - i0) / m;
+        if (m < P) {
+          const uint64_t jm = (binA[m] - 1 - binA[m - 1]) / wk + 1;
+          J = (uint64_t)J < jm ? J : (int64_t)jm;
         }
-        int32_t mine = 0;  // bin of item l
-        const uint32_t iw = (uint32_t)(item >> 32);
-        for (int t = 0; t < cnt;) {
-          const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)iw, t);
-          const uint32_t q = 0xFFFFFFFFu - wt;
-          const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)key, 0);
-          const uint32_t nk = k0 + (q << kb);
-          const uint64_t below = __ballot(key < nk);  // lane 0 and the lanes below nk
-          // items t, t+1, ... of the same weight (within this batch)
-          const uint64_t same = __ballot(l < cnt && iw == wt) >> t;
-          const int run = ~same ? (int)__builtin_ctzll(~same) : kWave;
-          const int m = __popcll(below);
-          const int c = run < m ? run : m;
-          // A prefix round: items t, t+1, ... go to lanes 0, 1, ... for as
-          // long as each lane's key is below every key the earlier items of
-          // the round raised (lane j is then the least loaded bin when item
-          // t + j comes), whatever the weights.  Only lanes below nk can
-          // qualify, so it is tried when m allows a long enough round and an
-          // equal run does not already take all m.
-          int cp = 0;
-          uint32_t r = 0xFFFFFFFFu;
-          if (m >= kLptPrefixMin && c < m) {
-            const bool has = l < cnt - t && l < W;
-            const uint32_t ql = 0xFFFFFFFFu - (uint32_t)__shfl((int)iw, (l + t) & (kWave - 1));
-            r = has ? key + (ql << kb) : 0xFFFFFFFFu;  // lane l's key after item t + l
-            const uint32_t lower = wave_excl_min_u32(r);
-            const uint64_t ok = __ballot(has && key < lower);
-            cp = ~ok ? (int)__builtin_ctzll(~ok) : kWave;
+        const int items = __builtin_amdgcn_readfirstlane((int)(J * m));
+        if (items < kLptBulkMin) break;
+        store_rounds(i0, items, m, [&](int r) { return (int32_t)(binA[r] & ((1ull << bb) - 1)); });
+        // the raised bins and the others, two sorted runs, merged by rank
+        for (int b = tid; b < P; b += blockDim.x) {
+          const uint64_t x = binA[b] + (b < m ? (uint64_t)J * wk : 0ull);
+          const int r = b < m ? lower_bound_u64(binA + m, P - m, x)
+                              : lower_bound_u64(binA, m, x - (uint64_t)J * wk) - m;
+          binB[b + r] = x;
+        }
+        __syncthreads();
+        uint64_t *t = binA;
+        binA = binB;
+        binB = t;
+        i0 += items;
+      }
+      if (i0 >= nc) break;
+    }
+    // the items up to lim in windows (all of them in one window up to 64 bins)
+    const int lim = i0 < s_last ? s_last : (nc - i0 < P ? nc : i0 + P);
+    uint32_t key32 = 0xFFFFFFFFu;  // wave 0: the window's keys (narrow or wide)
+    uint64_t key64 = ~0ull;
+    uint64_t load0 = 0;  // what narrow keys are relative to
+    if (tid < kWave) {
+      load0 = binA[0] >> bb << bb;
+      if (narrow) key32 = tid < W ? (uint32_t)(binA[tid] - load0) : 0xFFFFFFFFu;
+      else key64 = tid < W ? binA[tid] : ~0ull;
+    }
+    while (i0 < lim) {
+      const int T = single_window ? nc - i0 : (lim - i0 < W ? lim - i0 : W);
+      if (kBulk && tid == 0) s_op_items = 0;
+      if (tid < kWave && narrow) {
+        const int l = tid;
+        const uint32_t bmask = (1u << kb) - 1u;
+        uint32_t key = key32;
+        for (int base = 0; base < T; base += kWave) {
+          const int cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
+          // keys relative to the least load again
+          const uint32_t sub = (uint32_t)__builtin_amdgcn_readlane((int)key, 0) & ~bmask;
+          key -= l < W ? sub : 0u;
+          load0 += sub;
+          uint64_t item = 0;
+          if (l < cnt) {
+            const int at = i0 + base + l;
+            item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at] >> 16)) << 32) | (srt[at] & 0xFFFFu)
+                       : keys[at];
           }
-          if (cp >= kLptPrefixMin) {
-            const uint32_t src = (uint32_t)__shfl((int)key, (l - t) & (kWave - 1));
-            if (l >= t && l < t + cp) mine = (int32_t)(src & bmask);
-            // raised keys in lanes 0..cp-1, the rest unchanged: sort the wave
-            key = wave_sort_u32(l < cp ? r : key, l);
-            t += cp;
-          } else if (c >= kLptRoundMin) {
-            // a round: c equal items go to lanes 0..c-1 in order (each of
-            // those bins is below lane 0's raised key, so the steps would pick
-            // them one after another); the raised keys of lanes 0..c-1 and
-            // the keys of lanes c.. are two sorted runs, merged by rank
-            const uint32_t src = (uint32_t)__shfl((int)key, (l - t) & (kWave - 1));
-            if (l >= t && l < t + c) mine = (int32_t)(src & bmask);
-            const uint32_t x = l < c ? key + (q << kb) : key;
-            // rank in the other run: lanes 0..c-1 search lanes c..63, the
-            // others lanes 0..c-1 (every lane runs every step)
-            int lo = l < c ? c : 0, hi = l < c ? kWave : c;
-            for (int it = 0; it < 7; ++it) {
-              const int mid = (lo + hi) >> 1;
-              const uint32_t v = (uint32_t)__shfl((int)x, mid & (kWave - 1));
-              if (lo < hi) {
-                if (v < x) lo = mid + 1;
-                else hi = mid;
+          int32_t mine = 0;  // bin of item l
+          const uint32_t iw = (uint32_t)(item >> 32);
+          // Whole rounds of equal items: the m lanes below lane 0's raised key
+          // take an item each in order, J times over, for as long as all of
+          // them stay below lane m's key (to the run's end when they are all
+          // bins).  The workgroup stores these items' bins.
+          // (Not in the single-graph LDS form: its 8,192 components at most
+          // gain less from it than other graphs lose, 1.5 us of 25.)
+          const int at = i0 + base;
+          const uint32_t q = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, 0);
+          if (kBulk && single_window && at + kLptBulkMin <= nc && q > 0 &&
+              q == 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, kWave - 1)) {
+            const uint32_t qe = (uint32_t)__builtin_amdgcn_readfirstlane(
+                (int)lpt_item_weight(srt, keys, k32, at + kLptBulkMin - 1));
+            if (q == qe) {
+              const uint32_t wk = q << kb;
+              const int m =
+                  __popcll(__ballot(key < (uint32_t)__builtin_amdgcn_readlane((int)key, 0) + wk));
+              uint32_t J = (uint32_t)((lpt_run_end(srt, keys, k32, at, nc, q) - at) / m);
+              if (m < W) {
+                const uint32_t jm = ((uint32_t)__builtin_amdgcn_readlane((int)key, m) - 1u -
+                                     (uint32_t)__builtin_amdgcn_readlane((int)key, m - 1)) / wk + 1u;
+                J = J < jm ? J : jm;
+              }
+              const int items = (int)(J * (uint32_t)m);
+              if (items >= kLptBulkMin) {
+                if (l < m) s_opbin[l] = (int32_t)(key & bmask);
+                if (l == 0) {
+                  s_op_at = at;
+                  s_op_items = items;
+                  s_op_bins = m;
+                }
+                if (m == W) load0 += (uint64_t)J * wk;  // every key: the order stays
+                else key = lpt_merge_lanes(l < m ? key + J * wk : key, l, m);
+                break;
               }
             }
-            const int pos = l < c ? l + (lo - c) : (l - c) + lo;
-            key = (uint32_t)__builtin_amdgcn_ds_permute(pos * 4, (int)x);
-            t += c;
-          } else {
-            mine = l == t ? (int32_t)(k0 & bmask) : mine;
-            const int p = __popcll(below) - 1;  // lanes 1.. below nk
-            const uint32_t nxt = wave_next_u32(key);
-            key = l < p ? nxt : (l == p ? nk : key);
-            t += 1;
           }
-        }
-        if (l < cnt) bin_of[(uint32_t)item] = mine;
-      }
-      if (l < W) win[cur][l] = key;
-      key32 = key;
-    } else if (tid < kWave) {
-      const int l = tid;
-      uint64_t key = key64;
-      for (int base = 0; base < T; base += kWave) {
-        const int cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
-        uint64_t item = 0;
-        if (l < cnt) {
-          const int at = i0 + base + l;
-          item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at] >> 16)) << 32) | (srt[at] & 0xFFFFu)
-                     : keys[at];
-        }
-        int32_t mine = 0;  // bin of item l, kept in lane l until the batch ends
-        for (int t = 0; t < cnt; ++t) {
-          // t is uniform: broadcasts are lane reads into scalar registers
-          const uint64_t q =
-              0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(item >> 32), t);
-          const uint64_t k0 =
-              ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), 0) << 32) |
-              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, 0);
-          mine = l == t ? (int32_t)(k0 & ((1u << kBinBits) - 1)) : mine;
-          const uint64_t nk = k0 + (q << kBinBits);
-          const int p = __popcll(__ballot(key < nk)) - 1;  // lanes 1.. below nk
-          // the key of lane l + 1 (a wave-wide DPP shift; lane 63 keeps its own)
-          const uint64_t nxt = wave_next_u64(key);
-          key = l < p ? nxt : (l == p ? nk : key);
-        }
-        if (l < cnt) bin_of[(uint32_t)item] = mine;
-      }
-      if (l < W) win[cur][l] = key;
-      key64 = key;
-    }
-    // the window's raised keys are out, and the previous window's merge (by
-    // the other waves, during these steps) is done
-    __syncthreads();
-    if (single_window) {
-      if (tid < W) binA[tid] = win[cur][tid];
-    } else {
-      if (tid < kWave) {
-        if (i0 + T < nc) {
-          // the next window: the W (= 64) least of the raised keys and
-          // binA[W..2W), as min(raised key l, binA[2W-1-l]) (a bitonic run
-          // holding exactly those) sorted by the bitonic merge's stages
-          const int l = tid, j = W + (kWave - 1) - l;
-          if (narrow) {
-            const uint32_t b = j < P ? (uint32_t)binA[j] : 0xFFFFFFFFu;
-            uint32_t c = key32 < b ? key32 : b;
-            c = bitonic_lane_step<32>(c, l, kWave);
-            c = bitonic_lane_step<16>(c, l, kWave);
-            c = bitonic_lane_step<8>(c, l, kWave);
-            c = bitonic_lane_step<4>(c, l, kWave);
-            c = bitonic_lane_step<2>(c, l, kWave);
-            key32 = bitonic_lane_step<1>(c, l, kWave);
-          } else {
-            const uint64_t b = j < P ? binA[j] : ~0ull;
-            uint64_t c = key64 < b ? key64 : b;
-            c = bitonic_lane_step<32>(c, l, kWave);
-            c = bitonic_lane_step<16>(c, l, kWave);
-            c = bitonic_lane_step<8>(c, l, kWave);
-            c = bitonic_lane_step<4>(c, l, kWave);
-            c = bitonic_lane_step<2>(c, l, kWave);
-            key64 = bitonic_lane_step<1>(c, l, kWave);
-          }
-        }
-      } else {
-        // the other waves: the raised keys (sorted) merged with binA[W..P)
-        // (sorted) into binB.  Merge thread t < W places raised key t (its
-        // rank in binA[W..P) by binary search); the others place the list's
-        // keys, two at once (each one's rank among the W = 64 raised keys by
-        // six fixed steps, the two searches interleaved)
-        const uint64_t *wk = win[cur];
-        const int t = tid - kWave, mt = (int)blockDim.x - kWave - W;  // list threads
-        if (t < W) {
-          const uint64_t x = wk[t];
-          binB[t + lower_bound_u64(binA + W, P - W, x)] = x;
-        } else {
-          for (int j0 = t - W; j0 < P - W; j0 += 2 * mt) {
-            const int j1 = j0 + mt;
-            const bool two = j1 < P - W;
-            const uint64_t x0 = binA[W + j0], x1 = two ? binA[W + j1] : 0ull;
-            int r0 = 0, r1 = 0;
-#pragma unroll
-            for (int step = kWave / 2; step > 0; step >>= 1) {
-              r0 += wk[r0 + step - 1] < x0 ? step : 0;
-              r1 += wk[r1 + step - 1] < x1 ? step : 0;
+          for (int t = 0; t < cnt;) {
+            const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)iw, t);
+            const uint32_t q = 0xFFFFFFFFu - wt;
+            const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)key, 0);
+            const uint32_t nk = k0 + (q << kb);
+            const uint64_t below = __ballot(key < nk);  // lane 0 and the lanes below nk
+            // items t, t+1, ... of the same weight (within this batch)
+            const uint64_t same = __ballot(l < cnt && iw == wt) >> t;
+            const int run = ~same ? (int)__builtin_ctzll(~same) : kWave;
+            const int m = __popcll(below);
+            const int c = run < m ? run : m;
+            // A prefix round: items t, t+1, ... go to lanes 0, 1, ... for as
+            // long as each lane's key is below every key the earlier items of
+            // the round raised (lane j is then the least loaded bin when item
+            // t + j comes), whatever the weights.  Only lanes below nk can
+            // qualify, so it is tried when m allows a long enough round and an
+            // equal run does not already take all m.
+            int cp = 0;
+            uint32_t r = 0xFFFFFFFFu;
+            if (m >= kLptPrefixMin && c < m) {
+              const bool has = l < cnt - t && l < W;
+              const uint32_t ql = 0xFFFFFFFFu - (uint32_t)__shfl((int)iw, (l + t) & (kWave - 1));
+              r = has ? key + (ql << kb) : 0xFFFFFFFFu;  // lane l's key after item t + l
+              const uint32_t lower = wave_excl_min_u32(r);
+              const uint64_t ok = __ballot(has && key < lower);
+              cp = ~ok ? (int)__builtin_ctzll(~ok) : kWave;
             }
-            r0 += wk[r0] < x0 ? 1 : 0;
-            r1 += wk[r1] < x1 ? 1 : 0;
-            binB[j0 + r0] = x0;
-            if (two) binB[j1 + r1] = x1;
+            if (cp >= kLptPrefixMin) {
+              const uint32_t src = (uint32_t)__shfl((int)key, (l - t) & (kWave - 1));
+              if (l >= t && l < t + cp) mine = (int32_t)(src & bmask);
+              // raised keys in lanes 0..cp-1, the rest unchanged: sort the wave
+              key = wave_sort_u32(l < cp ? r : key, l);
+              t += cp;
+            } else if (c >= kLptRoundMin) {
+              // a round: c equal items go to lanes 0..c-1 in order (each of
+              // those bins is below lane 0's raised key, so the steps would pick
+              // them one after another); the raised keys of lanes 0..c-1 and
+              // the keys of lanes c.. are two sorted runs, merged by rank
+              const uint32_t src = (uint32_t)__shfl((int)key, (l - t) & (kWave - 1));
+              if (l >= t && l < t + c) mine = (int32_t)(src & bmask);
+              const uint32_t x = l < c ? key + (q << kb) : key;
+              key = lpt_merge_lanes(x, l, c);
+              t += c;
+            } else {
+              mine = l == t ? (int32_t)(k0 & bmask) : mine;
+              const int p = __popcll(below) - 1;  // lanes 1.. below nk
+              const uint32_t nxt = wave_next_u32(key);
+              key = l < p ? nxt : (l == p ? nk : key);
+              t += 1;
+            }
+          }
+          if (l < cnt) bin_of[(uint32_t)item] = mine;
+        }
+        if (l < W) win[cur][l] = load0 + key;
+        key32 = key;
+      } else if (tid < kWave) {
+        const int l = tid;
+        uint64_t key = key64;
+        for (int base = 0; base < T; base += kWave) {
+          const int cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
+          uint64_t item = 0;
+          if (l < cnt) {
+            const int at = i0 + base + l;
+            item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at] >> 16)) << 32) | (srt[at] & 0xFFFFu)
+                       : keys[at];
+          }
+          int32_t mine = 0;  // bin of item l, kept in lane l until the batch ends
+          for (int t = 0; t < cnt; ++t) {
+            // t is uniform: broadcasts are lane reads into scalar registers
+            const uint64_t q =
+                0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(item >> 32), t);
+            const uint64_t k0 =
+                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), 0) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, 0);
+            mine = l == t ? (int32_t)(k0 & ((1u << kBinBits) - 1)) : mine;
+            const uint64_t nk = k0 + (q << kBinBits);
+            const int p = __popcll(__ballot(key < nk)) - 1;  // lanes 1.. below nk
+            // the key of lane l + 1 (a wave-wide DPP shift; lane 63 keeps its own)
+            const uint64_t nxt = wave_next_u64(key);
+            key = l < p ? nxt : (l == p ? nk : key);
+          }
+          if (l < cnt) bin_of[(uint32_t)item] = mine;
+        }
+        if (l < W) win[cur][l] = key;
+        key64 = key;
+      }
+      // the window's raised keys are out, and the previous window's merge (by
+      // the other waves, during these steps) is done
+      __syncthreads();
+      if (single_window) {
+        if (tid < W) binA[tid] = win[cur][tid];
+        int items = 0, at = nc;
+        if constexpr (kBulk) {
+          items = __builtin_amdgcn_readfirstlane(s_op_items);
+          if (items) at = __builtin_amdgcn_readfirstlane(s_op_at);
+          store_rounds(at, items, s_op_bins, [&](int r) { return s_opbin[r]; });
+          __syncthreads();
+        }
+        i0 = at + items;
+      } else {
+        if (tid < kWave) {
+          if (i0 + T < lim) {
+            // the next window: the W (= 64) least of the raised keys and
+            // binA[W..2W), as min(raised key l, binA[2W-1-l]) (a bitonic run
+            // holding exactly those) sorted by the bitonic merge's stages
+            const int l = tid, j = W + (kWave - 1) - l;
+            if (narrow) {
+              const uint32_t b = j < P ? (uint32_t)(binA[j] - load0) : 0xFFFFFFFFu;
+              uint32_t c = key32 < b ? key32 : b;
+              c = bitonic_lane_step<32>(c, l, kWave);
+              c = bitonic_lane_step<16>(c, l, kWave);
+              c = bitonic_lane_step<8>(c, l, kWave);
+              c = bitonic_lane_step<4>(c, l, kWave);
+              c = bitonic_lane_step<2>(c, l, kWave);
+              key32 = bitonic_lane_step<1>(c, l, kWave);
+            } else {
+              const uint64_t b = j < P ? binA[j] : ~0ull;
+              uint64_t c = key64 < b ? key64 : b;
+              c = bitonic_lane_step<32>(c, l, kWave);
+              c = bitonic_lane_step<16>(c, l, kWave);
+              c = bitonic_lane_step<8>(c, l, kWave);
+              c = bitonic_lane_step<4>(c, l, kWave);
+              c = bitonic_lane_step<2>(c, l, kWave);
+              key64 = bitonic_lane_step<1>(c, l, kWave);
+            }
+          }
+        } else {
+          // the other waves: the raised keys (sorted) merged with binA[W..P)
+          // (sorted) into binB.  Merge thread t < W places raised key t (its
+          // rank in binA[W..P) by binary search); the others place the list's
+          // keys, two at once (each one's rank among the W = 64 raised keys by
+          // six fixed steps, the two searches interleaved)
+          const uint64_t *wk = win[cur];
+          const int t = tid - kWave, mt = (int)blockDim.x - kWave - W;  // list threads
+          if (t < W) {
+            const uint64_t x = wk[t];
+            binB[t + lower_bound_u64(binA + W, P - W, x)] = x;
+          } else {
+            for (int j0 = t - W; j0 < P - W; j0 += 2 * mt) {
+              const int j1 = j0 + mt;
+              const bool two = j1 < P - W;
+              const uint64_t x0 = binA[W + j0], x1 = two ? binA[W + j1] : 0ull;
+              int r0 = 0, r1 = 0;
+  #pragma unroll
+              for (int step = kWave / 2; step > 0; step >>= 1) {
+                r0 += wk[r0 + step - 1] < x0 ? step : 0;
+                r1 += wk[r1 + step - 1] < x1 ? step : 0;
+              }
+              r0 += wk[r0] < x0 ? 1 : 0;
+              r1 += wk[r1] < x1 ? 1 : 0;
+              binB[j0 + r0] = x0;
+              if (two) binB[j1 + r1] = x1;
+            }
           }
         }
+        uint64_t *t = binA;
+        binA = binB;
+        binB = t;
+        cur ^= 1;
+        i0 += T;
       }
-      uint64_t *t = binA;
-      binA = binB;
-      binB = t;
-      cur ^= 1;
     }
-    i0 += T;
+    __syncthreads();  // the last merge is done: binA holds the whole bin list
   }
-  __syncthreads();  // the last merge is done: binA holds the final bin list
   // 3. (bin, label) order, read offsets and the reads of each bin; keys
   // (bin << 16) | i in 32 bits when bin and index fit 16 bits
-  const bool b32 = nc <= 0xFFFF && P <= 0x10000;
-  for (int i = tid; i < N2; i += blockDim.x) {
+  auto store_loads = [&] {
+    for (int b = tid; b < P; b += blockDim.x) {
+      const uint64_t k = binA[b];
+      bin_load[k & ((1ull << bb) - 1)] = k >> bb;
+    }
+  };
+  if (!comp_rank) {
+    store_loads();
+    return 0;
+  }
+  const bool b32 = !kBig && nc <= 0xFFFF && P <= 0x10000;
+  if (kBig) keys = reinterpret_cast<uint64_t *>(keys32);  // the start of the key area
+  for (int i = tid; i < (kBig ? nc : N2); i += blockDim.x) {
     if (b32)
       keys32[i] = i < nc ? ((uint32_t)bin_of[i] << 16) | (uint32_t)i : ~0u;
     else
@@ -779,65 +1058,88 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   }
   // the reads of each bin are summed in binB (free once the loads are out;
   // in LDS when the bins are), then written once per bin
-  for (int b = tid; b < P; b += blockDim.x) binB[b] = 0;
-  __syncthreads();
-  for (int i = tid; i < nc; i += blockDim.x)
-    atomicAdd((unsigned long long *)binB + bin_of[i], (unsigned long long)comp_size[i]);
+  if (bin_reads) {
+    for (int b = tid; b < P; b += blockDim.x) binB[b] = 0;
+    __syncthreads();
+    for (int i = tid; i < nc; i += blockDim.x)
+      atomicAdd((unsigned long long *)binB + bin_of[i], (unsigned long long)comp_size[i]);
+  }
   __syncthreads();
   // (bin, label) order: radix passes over the bin's bytes (one up to 256
   // bins) as above, else a bitonic sort
   const uint32_t *srt2 = keys32;
-  if (kRadix && b32 && nc <= kRadixRounds * BLOCK)
+  if constexpr (kBig)
+    keys = radix_sort_hi32<BLOCK>(keys, keys + nc, nc, value_bytes((uint32_t)(P - 1)), s_cnt,
+                                  reinterpret_cast<uint32_t *>(sh_scan));
+  else if (b32 && radix(P <= 256 ? 1 : 2))
     srt2 = radix_sort_hi16<BLOCK>(keys32, keys32 + N2, nc, P <= 256 ? 1 : 2, s_cnt,
                                   reinterpret_cast<uint32_t *>(sh_scan));
   else if (b32)
     bitonic_sort(keys32, N2);
   else
     bitonic_sort(keys, N2);
+  // a thread takes up to eight consecutive components of the order per round
   int carry = 0, ecarry = 0;
-  for (int base = 0; base < nc; base += BLOCK) {
-    const int i = base + tid;
-    const uint32_t c = i < nc ? (b32 ? srt2[i] & 0xFFFFu : (uint32_t)keys[i]) : 0u;
-    const int32_t sz = i < nc ? comp_size[c] : 0;
+  for (int base = 0; base < nc; base += kPer * BLOCK) {
+    const int E = nc - base < kPer * BLOCK ? (nc - base + BLOCK - 1) / BLOCK : kPer;
+    uint32_t c[kPer];
+    int32_t sz[kPer], e2[kPer], sum = 0, esum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int i = base + tid * E + k;
+      c[k] = ~0u;
+      if (k >= E) continue;
+      c[k] = i < nc ? (b32 ? srt2[i] & 0xFFFFu : (uint32_t)keys[i]) : ~0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      sz[k] = e2[k] = 0;
+      if (k >= E) continue;
+      const bool v = c[k] != ~0u;
+      sz[k] = v ? comp_size[c[k]] : 0;
+      if (comp_estart && v) {
+        const uint8_t kd = comp_kind[c[k]];
+        e2[k] = kd == CG_KIND_PATH ? 2 * (sz[k] - 1) : (kd == CG_KIND_CYCLE ? 2 * sz[k] : 0);
+      }
+      sum += sz[k];
+      esum += e2[k];
+    }
+    // reads and local entries in one scan: (reads << 32) | entries, each
+    // field's total below 2^32 (entries <= 2 * reads, reads < 2^31)
+    int32_t st, est = 0;
     if (comp_estart) {
-      // reads and local entries in one scan: (reads << 32) | entries, each
-      // field's total below 2^32 (entries <= 2 * reads, reads < 2^31)
-      int64_t e2 = 0;
-      if (i < nc) {
-        const uint8_t kd = comp_kind[c];
-        e2 = kd == CG_KIND_PATH ? 2 * (sz - 1) : (kd == CG_KIND_CYCLE ? 2 * sz : 0);
-      }
       int64_t tot;
-      const int64_t ex = block_excl_scan<int64_t, BLOCK>(((int64_t)sz << 32) | e2, sh_scan64, &tot);
-      if (i < nc) {
-        comp_start[c] = carry + (int32_t)(ex >> 32);
-        comp_estart[c] = ecarry + (int32_t)(uint32_t)ex;
-        comp_rank[c] = i;
-      }
+      const int64_t ex = block_excl_scan<int64_t, BLOCK>(((int64_t)sum << 32) | (uint32_t)esum,
+                                                         sh_scan64, &tot);
+      st = carry + (int32_t)(ex >> 32);
+      est = ecarry + (int32_t)(uint32_t)ex;
       carry += (int32_t)(tot >> 32);
       ecarry += (int32_t)(uint32_t)tot;
     } else {
       int32_t tot;
-      const int32_t ex = block_excl_scan<int32_t, BLOCK>(sz, sh_scan, &tot);
-      if (i < nc) {
-        comp_start[c] = carry + ex;
-        comp_rank[c] = i;
-      }
+      st = carry + block_excl_scan<int32_t, BLOCK>(sum, sh_scan, &tot);
       carry += tot;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (k >= E || c[k] == ~0u) continue;
+      comp_start[c[k]] = st;
+      comp_rank[c[k]] = base + tid * E + k;
+      st += sz[k];
+      if (comp_estart) {
+        comp_estart[c[k]] = est;
+        est += e2[k];
+      }
     }
   }
   // the per-bin and per-component results, stored after the last barrier
   // (a barrier waits for the stores issued before it); binA still holds the
   // final bin list and binB the reads of each bin
-  {
-    const int bb = narrow ? kb : kBinBits;
-    for (int b = tid; b < P; b += blockDim.x) {
-      const uint64_t k = binA[b];
-      bin_load[k & ((1ull << bb) - 1)] = k >> bb;
-      bin_reads[b] = binB[b];
-    }
-  }
-  for (int i = tid; i < nc; i += blockDim.x) comp_bin[i] = bin_of[i];
+  store_loads();
+  if (bin_reads)
+    for (int b = tid; b < P; b += blockDim.x) bin_reads[b] = binB[b];
+  if (comp_bin != bin_of)
+    for (int i = tid; i < nc; i += blockDim.x) comp_bin[i] = bin_of[i];
   return ecarry;
 }
 

@@ -1075,6 +1075,7 @@ __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
   __shared__ uint64_t s_keys[kBatchSortCap];
   __shared__ int32_t s_bin[kBatchSortCap];
   __shared__ uint64_t s_binA[kBatchBinCap], s_binB[kBatchBinCap];
+  __shared__ uint32_t s_cnt[kBatchLptBlock / kWave * 256];
   __shared__ int64_t sh[kBatchLptBlock / kWave + 1];
   const int j = blockIdx.x;
   const BJob J = job_at(B.jobs, j);
@@ -1091,13 +1092,20 @@ __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
   }
   if (!ext) {
     if (nc <= kBatchSortCap && P <= kBatchBinCap)
-      m_e = lpt_body<kBatchLptBlock>(nc, P, J.parts.comp_size, wts, s_keys, s_bin, s_binA, s_binB, J.parts.comp_bin,
-                     J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load, J.s.bin_reads,
-                     &B.fixed->status, J.parts.comp_kind, J.s.estart);
+      m_e = lpt_body<kBatchLptBlock, false>(
+          nc, P, J.parts.comp_size, wts, s_keys, s_bin, s_cnt, s_binA, s_binB, J.parts.comp_bin,
+          J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load, J.s.bin_reads,
+          &B.fixed->status, J.parts.comp_kind, J.s.estart);
+    else if (P <= kBatchBinCap)
+      m_e = lpt_body<kBatchLptBlock, true>(
+          nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, s_cnt, s_binA, s_binB, J.parts.comp_bin,
+          J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load, J.s.bin_reads,
+          &B.fixed->status, J.parts.comp_kind, J.s.estart);
     else
-      m_e = lpt_body<kBatchLptBlock>(nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, J.s.bins, J.s.bins + P,
-                     J.parts.comp_bin, J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load,
-                     J.s.bin_reads, &B.fixed->status, J.parts.comp_kind, J.s.estart);
+      m_e = lpt_body<kBatchLptBlock, true>(
+          nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, s_cnt, J.s.bins, J.s.bins + P,
+          J.parts.comp_bin, J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load,
+          J.s.bin_reads, &B.fixed->status, J.parts.comp_kind, J.s.estart);
     __syncthreads();
     // bin boundaries: prefix of the reads of each bin
     for (int base = 0; base < P; base += kBatchLptBlock) {
