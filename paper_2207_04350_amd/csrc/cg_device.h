@@ -601,7 +601,6 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   __shared__ int32_t sh_scan[BLOCK / kWave + 1];
   __shared__ int64_t sh_scan64[BLOCK / kWave + 1];
   __shared__ unsigned int s_wmax;
-  constexpr bool kBulk = kBig || BLOCK < 1024;
   const int tid = threadIdx.x;
   const int N2 = next_pow2(nc > 0 ? nc : 1);
   if (tid == 0) s_wmax = 0;
@@ -817,7 +816,7 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     }
     while (i0 < lim) {
       const int T = single_window ? nc - i0 : (lim - i0 < W ? lim - i0 : W);
-      if (kBulk && tid == 0) s_op_items = 0;
+      if (kBig && tid == 0) s_op_items = 0;
       if (tid < kWave && narrow) {
         const int l = tid;
         const uint32_t bmask = (1u << kb) - 1u;
@@ -840,11 +839,11 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
           // take an item each in order, J times over, for as long as all of
           // them stay below lane m's key (to the run's end when they are all
           // bins).  The workgroup stores these items' bins.
-          // (Not in the single-graph LDS form: its 8,192 components at most
-          // gain less from it than other graphs lose, 1.5 us of 25.)
+          // (Not in the LDS forms: the few components they hold gain less from
+          // it than other graphs lose, 1.5 us of 25.)
           const int at = i0 + base;
           const uint32_t q = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, 0);
-          if (kBulk && single_window && at + kLptBulkMin <= nc && q > 0 &&
+          if (kBig && single_window && at + kLptBulkMin <= nc && q > 0 &&
               q == 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, kWave - 1)) {
             const uint32_t qe = (uint32_t)__builtin_amdgcn_readfirstlane(
                 (int)lpt_item_weight(srt, keys, k32, at + kLptBulkMin - 1));
@@ -964,7 +963,7 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
       if (single_window) {
         if (tid < W) binA[tid] = win[cur][tid];
         int items = 0, at = nc;
-        if constexpr (kBulk) {
+        if constexpr (kBig) {
           items = __builtin_amdgcn_readfirstlane(s_op_items);
           if (items) at = __builtin_amdgcn_readfirstlane(s_op_at);
           store_rounds(at, items, s_op_bins, [&](int r) { return s_opbin[r]; });

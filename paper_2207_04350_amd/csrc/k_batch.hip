@@ -1059,7 +1059,11 @@ __global__ __launch_bounds__(T) void kb_weight(BatchDev B) {
 // the batched form's LPT runs one job per workgroup of 256 threads, so that
 // all jobs' workgroups are resident at once
 constexpr int kBatchLptBlock = 256;
-// pieces per copy chunk (one wave each).  Chunks are handed to waves as
+// pieces per copy chunk (one wave each) at most.  A batch of few pieces takes
+// smaller chunks, down to kMinChunkPieces, so that it has about four for each
+// of the chip's 4,096 copy waves (256 compute units, 4 per SIMD): 8 graphs of
+// 0.2-2 Mbp took 56 us in chunks of 32, 9 us so, as a chunk's pieces follow
+// one another.  Chunks are handed to waves as
 // slots free up, so the copy ends with a tail of the last chunks: 64 pieces
 // (about 75 us of one wave's work on 3 kbp pieces) left it long, 16 paid the
 // per-chunk setup too often.  The jobs holding the last sixteenth of the
@@ -1067,8 +1071,13 @@ constexpr int kBatchLptBlock = 256;
 // chunks of kTailChunkPieces, so the waves that start last finish sooner.
 constexpr int kChunkPieces = 32;
 constexpr int kTailChunkPieces = 8;
+constexpr int kMinChunkPieces = 2;
+constexpr int kChunkTarget = 16384;
 constexpr int kWqBuckets = 4096;  // read counts from kWqBuckets - 1 up share the top bucket
-constexpr int kBatchSortCap = 2048;
+// components per job that the LPT sorts in LDS; more are sorted by radix passes
+// in global memory and equal ones placed in whole rounds (8 graphs of 0.2-2
+// Mbp, two with every read wanted: kb_lpt 44 us with 2,048 in LDS, 27 us so)
+constexpr int kBatchSortCap = 1024;
 constexpr int kBatchBinCap = 256;
 
 __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
@@ -1096,14 +1105,10 @@ __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
           nc, P, J.parts.comp_size, wts, s_keys, s_bin, s_cnt, s_binA, s_binB, J.parts.comp_bin,
           J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load, J.s.bin_reads,
           &B.fixed->status, J.parts.comp_kind, J.s.estart);
-    else if (P <= kBatchBinCap)
-      m_e = lpt_body<kBatchLptBlock, true>(
-          nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, s_cnt, s_binA, s_binB, J.parts.comp_bin,
-          J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load, J.s.bin_reads,
-          &B.fixed->status, J.parts.comp_kind, J.s.estart);
     else
       m_e = lpt_body<kBatchLptBlock, true>(
-          nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, s_cnt, J.s.bins, J.s.bins + P,
+          nc, P, J.parts.comp_size, wts, J.s.keys, J.s.aux, s_cnt,
+          P <= kBatchBinCap ? s_binA : J.s.bins, P <= kBatchBinCap ? s_binB : J.s.bins + P,
           J.parts.comp_bin, J.parts.comp_rank, J.parts.comp_start, J.parts.bin_load,
           J.s.bin_reads, &B.fixed->status, J.parts.comp_kind, J.s.estart);
     __syncthreads();
@@ -1154,13 +1159,16 @@ __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
   // batch's takes the tail chunk size
   const int64_t np = (int64_t)(uint32_t)tcp;
   const int64_t tail_at = np - (np >> 4);
+  int cpmax = (int)((np + kChunkTarget - 1) / kChunkTarget);
+  cpmax = cpmax < kMinChunkPieces ? kMinChunkPieces : (cpmax > kChunkPieces ? kChunkPieces : cpmax);
+  const int cptail = cpmax < kTailChunkPieces ? cpmax : kTailChunkPieces;
   {
     int64_t pc = (int64_t)(uint32_t)ecp;
     for (int i = i0; i < i1; ++i) {
       const uint64_t w = __hip_atomic_load((uint64_t *)(B.job_cnt + i), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
       const int64_t xp = (int32_t)(uint32_t)(w >> 32);
-      const int cp = pc + xp > tail_at ? kTailChunkPieces : kChunkPieces;
+      const int cp = pc + xp > tail_at ? cptail : cpmax;
       xh += (xp + cp - 1) / cp;
       pc += xp;
     }
@@ -1170,7 +1178,7 @@ __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
     const uint64_t w = __hip_atomic_load((uint64_t *)(B.job_cnt + i), __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
     const int64_t xc = (int32_t)(uint32_t)w, xp = (int32_t)(uint32_t)(w >> 32);
-    const int cp = (int64_t)(uint32_t)ecp + xp > tail_at ? kTailChunkPieces : kChunkPieces;
+    const int cp = (int64_t)(uint32_t)ecp + xp > tail_at ? cptail : cpmax;
     B.comp_base[i] = (int32_t)(ecp >> 32);
     B.piece_base[i] = (int32_t)(uint32_t)ecp;
     B.chunk_base[i] = (int32_t)eh;
@@ -1770,50 +1778,76 @@ __global__ void __launch_bounds__(kCountsBlock) kb_counts(const BJob *jobs, int 
   if (t == 0) out[4 * (int64_t)n_jobs] = carry;
 }
 
-// one 4-byte word of the packed results per thread (grid-stride); the job by
-// a binary search over the packed offsets, then the segment within it
+// One word of job J's packed results at byte o of them
+__device__ __forceinline__ uint32_t pack_word(const BJob *J, int64_t nc, int64_t ne, int64_t tw,
+                                              int64_t o) {
+  if (o < 16 * nc) {
+    const uint32_t *src = (const uint32_t *)(o < 8 * nc ? (const void *)J->out.len
+                                                        : (const void *)J->out.base_off);
+    return src[(o < 8 * nc ? o : o - 8 * nc) / 4];
+  }
+  if (o < 40 * nc) {
+    const int64_t r = o - 16 * nc, a = r / (4 * nc), i = (r - a * 4 * nc) / 4;
+    const uint32_t *src = a == 0 ? (const uint32_t *)J->out.label
+                        : a == 1 ? (const uint32_t *)J->out.bin
+                        : a == 2 ? (const uint32_t *)J->out.start
+                        : a == 3 ? (const uint32_t *)J->out.n_reads
+                        : a == 4 ? J->out.cflags
+                                 : (const uint32_t *)J->out.layout_off;
+    return src[i];
+  }
+  if ((o -= 40 * nc) < 4 * ne) return (uint32_t)J->out.layout_vid[o / 4];
+  if ((o -= 4 * ne) < 4 * tw) return J->out.bases[o / 4];
+  o -= 4 * tw;
+  uint32_t v = 0;
+  for (int k = 0; k < 4; ++k)
+    if (o + k < ne) v |= (uint32_t)J->out.layout_rev[o + k] << (8 * k);
+  return v;
+}
+
+// 16 bytes of the packed results per thread (grid-stride): records start at
+// 16-byte offsets, so they are one job's.  The job is looked up when the
+// thread leaves the last one's bytes; most of a record is its bases, whose
+// words are loaded together (at 4-byte alignment: they follow 40 nc + 4 ne
+// bytes).  16 graphs of 1-100 Mbp, 92 MB: 70 us with a word per thread, each
+// looking its job up.
 __global__ void __launch_bounds__(kPackBlock) kb_pack(const BJob *jobs, int n_jobs,
                                                       const int64_t *counts, uint32_t *dst,
                                                       int64_t dst_words) {
   const int64_t total_words = counts[4 * (int64_t)n_jobs] / 4;
   const int64_t lim = total_words < dst_words ? total_words : dst_words;
-  for (int64_t wd = (int64_t)blockIdx.x * kPackBlock + threadIdx.x; wd < lim;
-       wd += (int64_t)gridDim.x * kPackBlock) {
+  int64_t at = 0, end = 0, nc = 0, ne = 0, tw = 0, b0 = 0, b1 = 0;
+  const BJob *J = nullptr;
+  const uint32_t *bases = nullptr;
+  for (int64_t wd = 4 * ((int64_t)blockIdx.x * kPackBlock + threadIdx.x); wd < lim;
+       wd += 4 * (int64_t)gridDim.x * kPackBlock) {
     const int64_t byte = wd * 4;
-    int lo = 0, hi = n_jobs - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (counts[4 * (int64_t)mid + 3] <= byte) lo = mid;
-      else hi = mid - 1;
+    if (byte >= end) {
+      int lo = 0, hi = n_jobs - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (counts[4 * (int64_t)mid + 3] <= byte) lo = mid;
+        else hi = mid - 1;
+      }
+      nc = counts[4 * (int64_t)lo];
+      ne = counts[4 * (int64_t)lo + 1];
+      tw = counts[4 * (int64_t)lo + 2];
+      at = counts[4 * (int64_t)lo + 3];
+      end = at + pack_bytes(nc, ne, tw);
+      J = jobs + lo;
+      bases = J->out.bases;
+      b0 = 40 * nc + 4 * ne;
+      b1 = b0 + 4 * tw;
     }
-    const int64_t nc = counts[4 * (int64_t)lo], ne = counts[4 * (int64_t)lo + 1];
-    const int64_t tw = counts[4 * (int64_t)lo + 2];
-    int64_t o = byte - counts[4 * (int64_t)lo + 3];
-    const BJob *J = jobs + lo;
-    uint32_t v = 0;
-    if (o < 16 * nc) {
-      const uint32_t *src = (const uint32_t *)(o < 8 * nc ? (const void *)J->out.len
-                                                          : (const void *)J->out.base_off);
-      v = src[(o < 8 * nc ? o : o - 8 * nc) / 4];
-    } else if (o < 40 * nc) {
-      const int64_t r = o - 16 * nc, a = r / (4 * nc), i = (r - a * 4 * nc) / 4;
-      const uint32_t *src = a == 0 ? (const uint32_t *)J->out.label
-                          : a == 1 ? (const uint32_t *)J->out.bin
-                          : a == 2 ? (const uint32_t *)J->out.start
-                          : a == 3 ? (const uint32_t *)J->out.n_reads
-                          : a == 4 ? J->out.cflags
-                                   : (const uint32_t *)J->out.layout_off;
-      v = src[i];
-    } else if ((o -= 40 * nc) < 4 * ne) {
-      v = (uint32_t)J->out.layout_vid[o / 4];
-    } else if ((o -= 4 * ne) < 4 * tw) {
-      v = J->out.bases[o / 4];
+    const int64_t o = byte - at;
+    if (o >= b0 && o + 16 <= b1 && wd + 4 <= lim) {
+      const uint32_t *src = bases + (o - b0) / 4;
+      uint4 x;
+      __builtin_memcpy(&x, src, 16);
+      *(uint4 *)(dst + wd) = x;
     } else {
-      o -= 4 * tw;
-      for (int k = 0; k < 4; ++k)
-        if (o + k < ne) v |= (uint32_t)J->out.layout_rev[o + k] << (8 * k);
+      for (int k = 0; k < 4 && wd + k < lim; ++k) dst[wd + k] = pack_word(J, nc, ne, tw, o + 4 * k);
     }
-    dst[wd] = v;
   }
 }
 
@@ -1960,6 +1994,11 @@ static int plan_sizes(int32_t n_jobs, const cg_job *jobs, int vertex_tile, Plan 
     P->sum_chunks += (jobs[i].g.n + kChunkPieces - 1) / kChunkPieces;
     P->any_bases |= jobs[i].weight == CG_WEIGHT_BASES;
   }
+  // a batch of fewer pieces takes smaller chunks, up to kChunkTarget of them
+  // (and one partial chunk per job)
+  const int64_t small_chunks =
+      (sum_n / kMinChunkPieces < kChunkTarget ? sum_n / kMinChunkPieces : kChunkTarget) + n_jobs;
+  if (P->sum_chunks < small_chunks) P->sum_chunks = small_chunks;
   // the tail chunks: the jobs in the last sixteenth of the pieces hold at
   // most a sixteenth of all reads plus one job's, in chunks of
   // kTailChunkPieces (one partial chunk per job)
@@ -2308,7 +2347,7 @@ int cg_batch_pack(cg_batch *b, const int64_t *d_counts, void *d_dst, uint64_t ds
                           "hipDeviceGetAttribute");
   if (rc) return rc;
   const int64_t words = (int64_t)(dst_bytes / 4);
-  int64_t grid = (words + kPackBlock - 1) / kPackBlock;
+  int64_t grid = (words + 4 * kPackBlock - 1) / (4 * kPackBlock);
   if (grid > 8 * (int64_t)cus) grid = 8 * (int64_t)cus;
   CG_LAUNCH(b->ctx, kb_pack, dim3((unsigned)grid), dim3(kPackBlock), (hipStream_t)stream,
             b->dev.jobs, b->n_jobs, d_counts, (uint32_t *)d_dst, words);

@@ -112,12 +112,11 @@ __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t
   if (nc <= kSortCapLds && P <= kBinCapLds && !later)
     lpt_body<kLptBlock, false>(nc, P, comp_size, weight, s_keys, s_bin, s_cnt, s_binA, s_binB,
                                comp_bin, comp_rank, comp_start, bin_load, nullptr, status);
-  else if (P <= kBinCapLds)
-    lpt_body<kLptBlock, true>(nc, P, comp_size, weight, g_keys, bin_of, big_cnt, s_binA, s_binB,
-                              comp_bin, rank, comp_start, bin_load, nullptr, status);
   else
-    lpt_body<kLptBlock, true>(nc, P, comp_size, weight, g_keys, bin_of, big_cnt, g_bins, g_bins + P,
-                              comp_bin, rank, comp_start, bin_load, nullptr, status);
+    lpt_body<kLptBlock, true>(nc, P, comp_size, weight, g_keys, bin_of, big_cnt,
+                              P <= kBinCapLds ? s_binA : g_bins,
+                              P <= kBinCapLds ? s_binB : g_bins + P, comp_bin, rank, comp_start,
+                              bin_load, nullptr, status);
 }
 
 // ---------------------------------------------------------------------------
