@@ -59,11 +59,10 @@ def algo_bytes(kernel, s):
         "k_part_count": N + 4 * N,
         "k_part_compact": N + 4 * N + 4 * N + 9 * nc,
         "k_part_lpt": 4 * nc + 16 * nc,
-        "k_ind_zero": 4 * nc,
         "k_ind_fill": 4 * N + 4 * N + 8 * n_e,
         "k_ind_local": 8 * n_e + 4 * n_e,
         "k_ind_rows": 4 * n_e + n_e + 4 * (n_e + 1) + 8 * m_e + 4 * n_e,
-        "k_ind_rows_wide": 4 * n_e + n_e + 4 * (n_e + 1) + 8 * m_e + 4 * n_e,
+        "k_ind_comp": 16 * n_e + n_e + 4 * (n_e + 1) + 8 * m_e + 4 * n_e,
         # perm, local rows, entries (columns + ids, strands + overlaps), read
         # lengths and store offsets; layout (id, strand) and pieces (length,
         # store anchor, offset) written
@@ -418,7 +417,7 @@ def main():
             # the batched form: degrees, bitmaps and lists over the whole chip
             # (kb_mask_tiles), then kept entries, labels and the component
             # table per graph (kb_mask_cc, counted here as components)
-            "mask": pick(lambda k: k in ("k_mask", "kb_mask_tiles")),
+            "mask": pick(lambda k: k.startswith("k_mask") or k == "kb_mask_tiles"),
             "components": pick(lambda k: k.startswith("k_cc") or k == "kb_mask_cc"),
             "partition": pick(lambda k: k.startswith("k_part") or k.startswith("kb_weight")
                               or k in ("kb_lpt", "kb_tables", "kb_wq_place")),
@@ -452,7 +451,7 @@ def main():
         ms = ph["mask"] + ph["components"]
         return {"ms": ms, "edges_per_s": st["m"] / (ms * 1e-3),
                 "hbm_frac": maskcc_bytes / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9)}
-    kname = lambda k: k.replace("kb_", "k_").replace("<T>", "")
+    kname = lambda k: k.replace("kb_", "k_").split("<")[0]
     # a single graph: the faster of the two forms is the reported one (the
     # batched form is built for many graphs; one large graph is the plain
     # path's case)
@@ -461,7 +460,7 @@ def main():
     # figure; the warm one (back-to-back steps) is reported beside it
     step_ms = plain_cold if use_plain else b_cold
     warm_ms = plain_wall if use_plain else b_wall
-    form = ("plain: the five cg_* calls on one stream" if use_plain else
+    form = ("plain: cg_contig_generation on one stream" if use_plain else
             "batched: one HIP graph of %d launches for all graphs"
             % int(round(sum(v[0] for v in batch_kern.values()))))
     rkern = plain_kern if use_plain else batch_kern

@@ -337,6 +337,16 @@ int cg_induce(cg_ctx *ctx, const cg_graph *g, const uint8_t *flags, const int32_
 int cg_assemble(cg_ctx *ctx, const cg_graph *g, const cg_parts *parts, const cg_local *local,
                 int32_t P, const cg_contigs *out, void *stream);
 
+/* ---- the five steps together ----------------------------------------------- */
+
+/* cg_mask_branches, cg_components, cg_partition, cg_induce and cg_assemble on
+ * one graph in one call: the same outputs (arguments as in those calls), with
+ * fewer launches.  Errors (before anything is enqueued): as the five calls. */
+int cg_contig_generation(cg_ctx *ctx, const cg_graph *g, int32_t P, int32_t min_reads,
+                         int32_t weight, uint8_t *flags, int32_t *d_counts, int32_t *label,
+                         const cg_parts *parts, const cg_local *local, const cg_contigs *contigs,
+                         void *stream);
+
 /* ---- without allocation ---------------------------------------------------- */
 
 /* Capacity of the allocation-free entry point: the graph's context scratch
@@ -346,9 +356,8 @@ int cg_assemble(cg_ctx *ctx, const cg_graph *g, const cg_parts *parts, const cg_
 /* ContigGeneration on one graph without a context and without allocating:
  * for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc).  Runs
- * cg_mask_branches, cg_components, cg_partition, cg_induce and cg_assemble in
- * that order on `stream` with the same kernels, and fills the same outputs
- * (arguments as in those calls).  The scratch the steps need lives in a static
+ * cg_contig_generation's kernels on `stream` and fills the same outputs
+ * (arguments as there).  The scratch the steps need lives in a static
  * device array of the library, CG_NOALLOC_SCRATCH_BYTES plus a few KB, one
  * copy per GPU, held until the process ends; the call makes no allocation
  * of any kind.  The first call on a device looks up that device's copy.

@@ -100,6 +100,9 @@ def lib():
                                           P(ctypes.c_int32), P(ctypes.c_int64)]
         L.cg_reduce.argtypes = [_vp, P(CgGraph), ctypes.c_uint32, _vp, _vp, _vp, _vp, _vp, _vp,
                                 _vp, _vp]
+        L.cg_contig_generation.argtypes = [_vp, P(CgGraph), ctypes.c_int32, ctypes.c_int32,
+                                           ctypes.c_int32, _vp, _vp, _vp, P(CgParts), P(CgLocal),
+                                           P(CgContigs), _vp]
         L.cg_contig_generation_noalloc.argtypes = [P(CgGraph), ctypes.c_int32, ctypes.c_int32,
                                                    ctypes.c_int32, _vp, _vp, _vp, P(CgParts),
                                                    P(CgLocal), P(CgContigs), _vp, _vp]
@@ -122,7 +125,8 @@ def lib():
                      "cg_batch_destroy", "cg_ctx_profile", "cg_ctx_profile_read",
                      "cg_ctx_create", "cg_ctx_destroy", "cg_footprint", "cg_ctx_status",
                      "cg_validate", "cg_mask_branches", "cg_components", "cg_partition",
-                     "cg_induce", "cg_assemble", "cg_reduce", "cg_contig_generation_noalloc"):
+                     "cg_induce", "cg_assemble", "cg_reduce", "cg_contig_generation",
+                     "cg_contig_generation_noalloc"):
             getattr(L, name).restype = ctypes.c_int
         _LIB = L
     return _LIB
@@ -385,11 +389,10 @@ def assemble(ctx, dg, parts, local, P, contigs, stream=None):
 
 def run_path(ctx, dg, out, P, min_reads=2, stream=None, weight="reads"):
     """Enqueue all five steps of Algorithm 2 for one resident graph."""
-    mask_branches(ctx, dg, out.flags, out.counts, stream)
-    components(ctx, dg, out.flags, out.label, stream)
-    partition(ctx, dg, out.flags, out.label, P, min_reads, out.parts, stream, weight)
-    induce(ctx, dg, out.flags, out.label, out.parts, P, out.local, stream)
-    assemble(ctx, dg, out.parts, out.local, P, out.contigs, stream)
+    _check(lib().cg_contig_generation(
+        ctx.handle, ctypes.byref(dg.struct), int(P), int(min_reads), int(_weight(weight)),
+        _ptr(out.flags), _ptr(out.counts), _ptr(out.label), ctypes.byref(out.parts),
+        ctypes.byref(out.local), ctypes.byref(out.contigs), _stream(stream)))
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20

@@ -435,4 +435,22 @@ int cg_assemble(cg_ctx *ctx, const cg_graph *g, const cg_parts *parts, const cg_
   return launch_assemble(ctx, *g, s, *parts, *local, P, *out, (hipStream_t)stream);
 }
 
+int cg_contig_generation(cg_ctx *ctx, const cg_graph *g, int32_t P, int32_t min_reads,
+                         int32_t weight, uint8_t *flags, int32_t *d_counts, int32_t *label,
+                         const cg_parts *parts, const cg_local *local, const cg_contigs *contigs,
+                         void *stream) {
+  int rc = check_graph(g, true);
+  if (rc || (rc = check_P(P)) || (rc = check_parts(parts)) || (rc = check_local(local)) ||
+      (rc = check_contigs(contigs)))
+    return rc;
+  if (!d_counts || (g->n > 0 && (!flags || !label))) return set_error(CG_EINVAL, "NULL argument");
+  if (weight != CG_WEIGHT_READS && weight != CG_WEIGHT_BASES)
+    return set_error(CG_EINVAL, "weight=%d is neither CG_WEIGHT_READS nor CG_WEIGHT_BASES", weight);
+  Scratch s;
+  if ((rc = check_ctx(ctx, g, P, &s))) return rc;
+  return launch_path(ctx, *g, s,
+                     PathArgs{P, min_reads, weight, flags, d_counts, label, *parts, *local,
+                              *contigs, nullptr, false}, (hipStream_t)stream);
+}
+
 }  // extern "C"

@@ -34,21 +34,54 @@ __device__ __forceinline__ int32_t lds_lower_bound(const int32_t *a, int q, int3
 // entries: bit0 branch (deg >= 3); bit1 / bit2 entry 0 / 1 kept (neither end
 // is a branch vertex).
 // ---------------------------------------------------------------------------
+// u0, u1: the row's first two columns, where it has them and no more.
 __device__ __forceinline__ uint32_t vertex_flags(const int32_t *__restrict__ row_ptr,
                                                  const int32_t *__restrict__ col, int32_t b,
-                                                 int32_t deg) {
+                                                 int32_t deg, int32_t &u0, int32_t &u1) {
+  u0 = u1 = 0;
   if (deg >= 3) return 1u;
   uint32_t f = 0;
   if (deg > 0) {
-    const int32_t u0 = col[b];
+    u0 = col[b];
     if (row_ptr[u0 + 1] - row_ptr[u0] < 3) f |= 2;
     if (deg == 2) {
-      const int32_t u1 = col[b + 1];
+      u1 = col[b + 1];
       if (row_ptr[u1 + 1] - row_ptr[u1] < 3) f |= 4;
     }
   }
   return f;
 }
+
+// Cycles by component rank: a bitmap, the cycles of every kCycSuper ranks,
+// and whether there is any (most graphs have none, and then nothing else is
+// read).  Kept in the scratch's estart array.
+constexpr int kCycSuper = 2048;
+struct CycMarks {
+  uint32_t *bits, *super, *any;
+};
+__host__ __device__ __forceinline__ CycMarks cyc_marks(int32_t *area, int32_t n) {
+  uint32_t *b = reinterpret_cast<uint32_t *>(area);
+  const int64_t w = ((int64_t)n + 31) / 32, sp = ((int64_t)n + kCycSuper - 1) / kCycSuper;
+  return CycMarks{b, b + w, b + w + sp};
+}
+// words of the area they take
+__host__ __device__ __forceinline__ int32_t cyc_words(int32_t n) {
+  return n > 0 ? (int32_t)(((int64_t)n + 31) / 32 + ((int64_t)n + kCycSuper - 1) / kCycSuper + 1) : 0;
+}
+__device__ __forceinline__ void mark_cycle(const CycMarks &m, int32_t rank) {
+  atomicOr(m.bits + (rank >> 5), 1u << (rank & 31));
+  atomicAdd(m.super + rank / kCycSuper, 1u);
+  *m.any = 1;
+}
+
+// What the induce step takes from the components in rank order, written by
+// the partition step of the whole path: where the bins start, and the cycles.
+struct RankOut {
+  int32_t *bin_vptr;  // null: not wanted
+  int32_t *d_sizes, *loc_row_ptr;
+  const uint8_t *comp_kind;
+  CycMarks cyc;
+};
 
 // ---------------------------------------------------------------------------
 // ConnectedComponent: union-find with min-id roots
@@ -593,7 +626,8 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
                                         uint64_t *__restrict__ bin_reads,
                                         unsigned int *status,
                                         const uint8_t *__restrict__ comp_kind = nullptr,
-                                        int32_t *__restrict__ comp_estart = nullptr) {
+                                        int32_t *__restrict__ comp_estart = nullptr,
+                                        const RankOut &ro = RankOut{}) {
   static_assert(BLOCK > 2 * kWave, "the pipelined windows' merge needs threads beyond two waves");
   __shared__ uint64_t win[2][kWave];  // a window's raised keys, alternating buffers
   __shared__ int32_t s_opbin[kWave];                 // rounds taken at once: their bins in order,
@@ -1122,13 +1156,31 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       if (k >= E || c[k] == ~0u) continue;
+      const int i = base + tid * E + k;
       comp_start[c[k]] = st;
-      comp_rank[c[k]] = base + tid * E + k;
+      comp_rank[c[k]] = i;
+      if (ro.bin_vptr) {
+        // where the bins from the last component's on to this one's start
+        const int32_t b = (int32_t)(b32 ? srt2[i] >> 16 : (uint32_t)(keys[i] >> 32));
+        const int32_t pb =
+            i > 0 ? (int32_t)(b32 ? srt2[i - 1] >> 16 : (uint32_t)(keys[i - 1] >> 32)) : -1;
+        for (int32_t x = pb + 1; x <= b; ++x) ro.bin_vptr[x] = st;
+        if (ro.comp_kind[c[k]] == CG_KIND_CYCLE) mark_cycle(ro.cyc, i);
+      }
       st += sz[k];
       if (comp_estart) {
         comp_estart[c[k]] = est;
         est += e2[k];
       }
+    }
+  }
+  if (ro.bin_vptr) {
+    const int32_t last =
+        nc > 0 ? (int32_t)(b32 ? srt2[nc - 1] >> 16 : (uint32_t)(keys[nc - 1] >> 32)) : -1;
+    for (int b = last + 1 + tid; b <= P; b += blockDim.x) ro.bin_vptr[b] = carry;
+    if (tid == 0) {
+      ro.d_sizes[0] = carry;
+      if (nc == 0) ro.d_sizes[1] = ro.loc_row_ptr[0] = 0;
     }
   }
   // the per-bin and per-component results, stored after the last barrier

@@ -26,10 +26,11 @@ struct Fixed {
   unsigned long long mask_part[kMaskMaxBlocks];
   unsigned int mask_ticket;  // workgroups done, for grids that sum in the kernel
   unsigned int status;             // CG_STATUS_* bits
-  unsigned long long valid_best;   // packed first failure of cg_validate
+  unsigned long long valid_best;   // cg_validate: complement of the packed first failure (0: none)
   unsigned int scan_ticket;        // look-back scan: block ticket
   unsigned int scan_done;          // look-back scan: exited blocks
-  unsigned int pad[8];
+  unsigned int fill_cursor;        // the whole path: member slots given out (reset per call)
+  unsigned int pad[7];
 };
 
 // Items per block of the look-back scan (one item per thread).
@@ -39,8 +40,10 @@ struct Scratch {
   unsigned long long *scan_status;  // [scan_blocks]
   int32_t *tmp;        // [2n] induce: reads bucketed by component (the batched form:
                        // (id, tile-list slot) pairs)
-  int32_t *lidx;       // [n] induce: local number of each read
-  uint32_t *fill;      // [n] induce: bucket cursors
+  int32_t *lidx;       // [n] induce: local number of each read (the whole path, before: its
+                       // slot among its component's reads)
+  uint32_t *fill;      // [n] induce: bucket cursors (the whole path: first member slot of
+                       // each component)
   uint64_t *piece_off; // [n] assemble: base offset of each piece in its contig
   uint32_t *piece_len; // [n] assemble: bases of each piece
   uint64_t *piece_src; // [n] assemble: where each piece starts in the store (see piece_anchor)
@@ -345,7 +348,30 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
                   const int32_t *label, const cg_parts &parts, int32_t P, const cg_local &out,
                   hipStream_t st);
 int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st);
+                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
+                    uint32_t *d_status = nullptr);
+// The five steps in one call, with fewer launches than one step after another
+// (launch_path in k_partition.hip).  d_status, if given, gets the status word
+// at the end; reset: the context's counters and status are cleared first.
+struct PathArgs {
+  int32_t P, min_reads, weight;
+  uint8_t *flags;
+  int32_t *d_counts, *label;
+  cg_parts parts;
+  cg_local local;
+  cg_contigs out;
+  uint32_t *d_status;
+  bool reset;
+};
+int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                hipStream_t st);
+int launch_path_mask(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                     int *parts, hipStream_t st);
+int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                          int mask_parts, hipStream_t st);
+int launch_ind_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
+                    const cg_parts &parts, const int32_t *mstart, const cg_local &out,
+                    hipStream_t st);
 int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuzz,
                   uint8_t *contained, uint8_t *kept, int32_t *s_row_ptr, int32_t *s_col,
                   uint32_t *s_ovl, uint8_t *s_strand, int32_t *d_m, hipStream_t st);

@@ -38,18 +38,14 @@ static int scratch_on(int dev, char **out) {
   return CG_OK;
 }
 
-// What must start at zero: the counters the kernels count on (they reset
-// them themselves after use, but a call must not depend on how the previous
-// one ended), the status word, and the look-back status of this call's scans.
-__global__ void k_noalloc_reset(Fixed *fx, unsigned long long *scan_status, int n_status) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
-    fx->mask_ticket = 0;
-    fx->status = 0;
-    fx->scan_ticket = 0;
-    fx->scan_done = 0;
-  }
-  for (int i = t; i < n_status; i += gridDim.x * blockDim.x) scan_status[i] = 0;
+// What must start at zero (a call must not depend on how the previous one
+// ended) and the status word, for a graph without reads; other calls do both
+// in the path's first and last kernel.
+__global__ void k_noalloc_reset(Fixed *fx) {
+  fx->mask_ticket = 0;
+  fx->status = 0;
+  fx->scan_ticket = 0;
+  fx->scan_done = 0;
 }
 
 __global__ void k_noalloc_status(const Fixed *fx, uint32_t *d_status) { *d_status = fx->status; }
@@ -92,17 +88,15 @@ extern "C" int cg_contig_generation_noalloc(const cg_graph *g, int32_t P, int32_
   if (!carve(&view, g->n, g->m, P, &s))
     return set_error(CG_EUNSUPPORTED, "scratch layout does not fit");  // excluded above
   hipStream_t st = (hipStream_t)stream;
-  const int n_status = scan_blocks((int64_t)(g->n > 0 ? g->n : 1) + 1) + 1;
-  hipLaunchKernelGGL(k_noalloc_reset, dim3(1), dim3(256), 0, st, view.fixed, s.scan_status,
-                     n_status);
-  if ((rc = hip_check(hipGetLastError(), "k_noalloc_reset"))) return rc;
-  rc = launch_mask(&view, *g, flags, d_counts, st);
-  if (!rc) rc = launch_components(&view, *g, flags, label, st);
-  if (!rc) rc = launch_partition(&view, *g, s, flags, label, P, min_reads, weight, *parts, st);
-  if (!rc) rc = launch_induce(&view, *g, s, flags, label, *parts, P, *local, st);
-  if (!rc) rc = launch_assemble(&view, *g, s, *parts, *local, P, *contigs, st);
+  if (g->n == 0) {
+    hipLaunchKernelGGL(k_noalloc_reset, dim3(1), dim3(1), 0, st, view.fixed);
+    if ((rc = hip_check(hipGetLastError(), "k_noalloc_reset"))) return rc;
+  }
+  rc = launch_path(&view, *g, s,
+                   PathArgs{P, min_reads, weight, flags, d_counts, label, *parts, *local, *contigs,
+                            d_status, true}, st);
   if (rc) return rc;
-  if (d_status) {
+  if (d_status && g->n == 0) {
     hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(1), 0, st, view.fixed, d_status);
     rc = hip_check(hipGetLastError(), "k_noalloc_status");
   }

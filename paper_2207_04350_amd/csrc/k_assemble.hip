@@ -190,7 +190,10 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
                                                          const uint64_t *__restrict__ d_total_words,
                                                          uint64_t cap_words,
                                                          uint32_t *__restrict__ bases,
-                                                         int32_t chunk_target) {
+                                                         int32_t chunk_target,
+                                                         const Fixed *fx, uint32_t *d_status) {
+  // the last kernel of the path: no earlier one can still raise a bit
+  if (d_status && blockIdx.x == 0 && threadIdx.x == 0) *d_status = fx->status;
   if (*d_total_words > cap_words) return;
   const int32_t n_e = bin_vptr[P];
   const PieceArrays A = piece_arrays(lay_contig, piece_off, piece_len, piece_src, clen, cbase);
@@ -212,7 +215,8 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
 }
 
 int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st) {
+                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
+                    uint32_t *d_status) {
   const PhaseRange range("cg: LocalAssembly");
   const int32_t n = g.n;
   if (n == 0) {
@@ -245,7 +249,7 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
   CG_LAUNCH(ctx, k_asm_copy, dim3(cgrid), dim3(kCopyBlock), st, g.seq, g.seq_words,
                      local.bin_vptr, P, s.piece_off, s.piece_len, s.piece_src, s.lay_contig,
                      out.len, out.base_off, out.d_total_words, out.cap_words, out.bases,
-                     chunk_target);
+                     chunk_target, ctx->fixed, d_status);
   return hip_check(hipGetLastError(), "k_asm");
 }
 

@@ -2118,13 +2118,6 @@ __global__ void kb_clear_counters(unsigned int *c) {
   if (threadIdx.x < 8) c[threadIdx.x] = 0;
 }
 
-// the look-back status words of a job that runs through the single-graph
-// kernels start at zero (its slice of the batch memory may hold anything
-// from an earlier plan)
-__global__ void kb_clear_status(unsigned long long *p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
 static int plan_upload(cg_batch *b, const Plan &P, hipStream_t st) {
   char *mem = b->mem;
   int rc = hip_check(hipMemcpyAsync(mem + P.o_jobs, b->h_jobs.data(), sizeof(BJob) * P.n_jobs,
@@ -2142,12 +2135,6 @@ static int plan_upload(cg_batch *b, const Plan &P, hipStream_t st) {
   if (!rc) {
     hipLaunchKernelGGL(kb_clear_counters, dim3(1), dim3(64), 0, st, b->dev.counters);
     rc = hip_check(hipGetLastError(), "kb_clear_counters");
-  }
-  for (size_t e = 0; !rc && e < b->ext_jobs.size(); ++e) {
-    const int words = scan_blocks((int64_t)(b->ext_jobs[e].g.n > 0 ? b->ext_jobs[e].g.n : 1) + 1) + 1;
-    hipLaunchKernelGGL(kb_clear_status, dim3((words + 255) / 256), dim3(256), 0, st,
-                       b->ext_s[e].scan_status, words);
-    rc = hip_check(hipGetLastError(), "kb_clear_status");
   }
   return rc;
 }
@@ -2283,12 +2270,9 @@ int cg_batch_run(cg_batch *b, void *stream) {
   for (size_t e = 0; e < b->ext_jobs.size(); ++e) {
     const cg_job &J = b->ext_jobs[e];
     const Scratch &s = b->ext_s[e];
-    int rc = launch_mask(ctx, J.g, J.flags, J.d_counts, st);
-    if (!rc) rc = launch_components(ctx, J.g, J.flags, J.label, st);
-    if (!rc)
-      rc = launch_partition(ctx, J.g, s, J.flags, J.label, J.P, J.min_reads, J.weight, J.parts, st);
-    if (!rc) rc = launch_induce(ctx, J.g, s, J.flags, J.label, J.parts, J.P, J.local, st);
-    if (!rc) rc = launch_assemble(ctx, J.g, s, J.parts, J.local, J.P, J.contigs, st);
+    const int rc = launch_path(ctx, J.g, s,
+                               PathArgs{J.P, J.min_reads, J.weight, J.flags, J.d_counts, J.label,
+                                        J.parts, J.local, J.contigs, nullptr, false}, st);
     if (rc) return rc;
   }
   if (b->n_internal == 0) return hip_check(hipGetLastError(), "cg_batch_run");

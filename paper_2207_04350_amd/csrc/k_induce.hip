@@ -9,6 +9,7 @@
 //  k_ind_fill   each read with kept entries claims a slot in its component's
 //               block; bin_vptr and n_e from the components in rank order;
 //               cycles marked by rank
+//               (in the whole path the partition step does both, k_partition.hip)
 //  k_ind_comp   sorts each component's reads by id and writes perm and the
 //               local CSR rows: lanes for one-read components, a wave up to
 //               128 reads, a workgroup above
@@ -19,19 +20,6 @@
 #include "cg_device.h"
 
 namespace cg {
-
-// Cycles by component rank: a bitmap, the cycles of every kCycSuper ranks,
-// and whether there is any (most graphs have none, and then nothing else is
-// read).  Kept in the scratch's estart array.
-constexpr int kCycSuper = 2048;
-struct CycMarks {
-  uint32_t *bits, *super, *any;
-};
-__host__ __device__ __forceinline__ CycMarks cyc_marks(int32_t *area, int32_t n) {
-  uint32_t *b = reinterpret_cast<uint32_t *>(area);
-  const int64_t w = ((int64_t)n + 31) / 32, sp = ((int64_t)n + kCycSuper - 1) / kCycSuper;
-  return CycMarks{b, b + w, b + w + sp};
-}
 
 // cycles of rank below r; called by a whole wave with uniform r
 __device__ __forceinline__ int32_t cycles_before(const CycMarks &m, int32_t r) {
@@ -108,11 +96,7 @@ __global__ __launch_bounds__(kFillBlock) void k_ind_fill(
     const int32_t x = by_rank[r], prev = r > 0 ? parts.comp_bin[by_rank[r - 1]] : -1;
     const int32_t st = parts.comp_start[x];
     for (int32_t b = prev + 1; b <= parts.comp_bin[x]; ++b) bin_vptr[b] = st;
-    if (parts.comp_kind[x] == CG_KIND_CYCLE) {
-      atomicOr(cyc.bits + (r >> 5), 1u << (r & 31));
-      atomicAdd(cyc.super + r / kCycSuper, 1u);
-      *cyc.any = 1;
-    }
+    if (parts.comp_kind[x] == CG_KIND_CYCLE) mark_cycle(cyc, (int32_t)r);
   }
   if (nc > 0) {
     const int32_t x = by_rank[nc - 1];
@@ -237,8 +221,9 @@ constexpr int kIndCompWaves = kIndCompBlock / kWave;
 static_assert(kIndCompWaves * 4 * kIndWaveCap <= kIndCompCap, "the waves' LDS fits the sort's");
 __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const uint8_t *__restrict__ flags, cg_parts parts, const int32_t *__restrict__ tmp,
-    int32_t *__restrict__ lidx, CycMarks cyc, cg_local out, int n_big) {
+    const uint8_t *__restrict__ flags, cg_parts parts, const int32_t *__restrict__ mstart,
+    const int32_t *__restrict__ tmp, int32_t *__restrict__ lidx, CycMarks cyc, cg_local out,
+    int n_big) {
   __shared__ int32_t a[kIndCompCap];
   __shared__ int32_t sh_scan[kIndCompBlock / kWave + 1];
   __shared__ int s_n;
@@ -257,7 +242,7 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
         const int32_t x = s_list[i];
         const int32_t q = parts.comp_size[x], st = parts.comp_start[x], r = parts.comp_rank[x];
         const int32_t es = 2 * (st - r + cycles_before(cyc, r));
-        induce_component<kIndCompBlock, kIndCompCap>(q, st, es, tmp + st, flags, row_ptr, col,
+        induce_component<kIndCompBlock, kIndCompCap>(q, st, es, tmp + mstart[x], flags, row_ptr, col,
                                                      out.perm, lidx, out.loc_row_ptr, out.loc_col,
                                                      out.loc_eid, a, sh_scan);
         if (threadIdx.x == 0 && r == nc - 1) {
@@ -281,7 +266,7 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     const bool live = lane_id() < run && c < nc;
     const int32_t q = live ? parts.comp_size[c] : 0;
     const int32_t st = live ? parts.comp_start[c] : 0, r = live ? parts.comp_rank[c] : 0;
-    const int32_t lab = live ? parts.comp_label[c] : 0;
+    const int32_t lab = live ? parts.comp_label[c] : 0, ms = live ? mstart[c] : 0;
     const bool cycles = *cyc.any != 0;
     int32_t es = 2 * (st - r);
     if (cycles)
@@ -301,10 +286,26 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     for (uint64_t todo = __ballot(q > 1 && q <= kIndWaveCap); todo; todo &= todo - 1) {
       const int t = (int)__builtin_ctzll(todo);
       const int tq = __builtin_amdgcn_readlane(q, t), tst = __builtin_amdgcn_readlane(st, t);
-      ind_wave(tq, tst, __builtin_amdgcn_readlane(es, t), tmp + tst, flags, row_ptr, col,
-               a + wv * 4 * kIndWaveCap, out);
+      ind_wave(tq, tst, __builtin_amdgcn_readlane(es, t), tmp + __builtin_amdgcn_readlane(ms, t),
+               flags, row_ptr, col, a + wv * 4 * kIndWaveCap, out);
     }
   }
+}
+
+// mstart: first member slot of each component
+int launch_ind_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
+                    const cg_parts &parts, const int32_t *mstart, const cg_local &out,
+                    hipStream_t st) {
+  // workgroups: as many as can hold a component above kIndWaveCap reads,
+  // up to one per compute unit; waves for components of two reads, up to
+  // what is resident at once
+  const int32_t n = g.n;
+  const int n_big = n / (kIndWaveCap + 1) < 256 ? n / (kIndWaveCap + 1) : 256;
+  const int64_t nw = ((int64_t)n / 2 + kIndCompWaves) / kIndCompWaves;
+  CG_LAUNCH(ctx, k_ind_comp, dim3((unsigned)(n_big + (nw < 512 ? nw : 512))),
+            dim3(kIndCompBlock), st, g.row_ptr, g.col, flags, parts, mstart, s.tmp, s.lidx,
+            cyc_marks(s.estart, n), out, n_big);
+  return hip_check(hipGetLastError(), "k_ind_comp");
 }
 
 int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
@@ -321,14 +322,7 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
     const int64_t per = (int64_t)kFillBlock * kFillPer;
     CG_LAUNCH(ctx, k_ind_fill, dim3((unsigned)((n + per - 1) / per)), dim3(kFillBlock), st, n, P,
               flags, label, parts, s.fill, s.aux, cyc, s.tmp, out.bin_vptr, out.d_sizes);
-    // workgroups: as many as can hold a component above kIndWaveCap reads,
-    // up to one per compute unit; waves for components of two reads, up to
-    // what is resident at once
-    const int n_big = n / (kIndWaveCap + 1) < 256 ? n / (kIndWaveCap + 1) : 256;
-    const int64_t nw = ((int64_t)n / 2 + kIndCompWaves) / kIndCompWaves;
-    CG_LAUNCH(ctx, k_ind_comp, dim3((unsigned)(n_big + (nw < 512 ? nw : 512))),
-              dim3(kIndCompBlock), st, g.row_ptr, g.col, flags, parts, s.tmp, s.lidx, cyc, out,
-              n_big);
+    return launch_ind_comp(ctx, g, s, flags, parts, parts.comp_start, out, st);
   }
   return hip_check(hipGetLastError(), "k_ind");
 }

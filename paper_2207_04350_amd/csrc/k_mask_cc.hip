@@ -26,10 +26,37 @@ __device__ __forceinline__ void store_counts(unsigned long long a, int32_t *d_co
   d_counts[1] = (int32_t)(uint32_t)(a >> 32);
 }
 
+// What the first pass of the whole path sets up besides: every read's parent
+// in the component forest and its counter, the cycle marks, and the states
+// that start at zero.
+struct PathInit {
+  int32_t *label, *cnt;
+  int32_t *zero;  // [zero_words]
+  unsigned long long *scan_status;
+  int32_t zero_words, n_status;
+  int reset;
+};
+
+// A read's parent before any union: the smaller of its kept neighbours if it
+// is smaller than the read itself.  Every kept edge then joins its larger end
+// to its smaller one but for the second edge of a read with two smaller
+// neighbours (a third of a chain's reads in random order), and only these
+// are left for the unions.
+__device__ __forceinline__ int32_t first_parent(int32_t v, uint32_t f, int32_t u0, int32_t u1) {
+  int32_t p = v;
+  if ((f & 2) && u0 < p) p = u0;
+  if ((f & 4) && u1 < p) p = u1;
+  return p;
+}
+
+// a read's counter before the count: a read without kept entries is counted
+__device__ __forceinline__ int32_t first_count(uint32_t f) { return (f & 6) ? 0 : 4; }
+
+template <bool kPath>
 __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *__restrict__ row_ptr,
                                                      const int32_t *__restrict__ col,
                                                      uint8_t *__restrict__ flags, Fixed *fx,
-                                                     int32_t *__restrict__ d_counts) {
+                                                     int32_t *__restrict__ d_counts, PathInit pi) {
   // counts: ballots per wave, summed per workgroup in LDS, one plain store
   // per workgroup of a packed word (branch reads low, kept entries high:
   // neither sum reaches 2^32).  A large grid leaves the sum to k_mask_sum
@@ -39,6 +66,20 @@ __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *_
   if (threadIdx.x == 0) s_cnt = 0;
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * kMaskBlock;
+  if constexpr (kPath) {
+    const int64_t t = (int64_t)blockIdx.x * kMaskBlock + threadIdx.x;
+    for (int64_t i = t; i < pi.zero_words; i += stride) pi.zero[i] = 0;
+    for (int64_t i = t; i < pi.n_status; i += stride) pi.scan_status[i] = 0;
+    if (t == 0) {
+      fx->fill_cursor = 0;
+      if (pi.reset) {
+        fx->mask_ticket = 0;
+        fx->status = 0;
+        fx->scan_ticket = 0;
+        fx->scan_done = 0;
+      }
+    }
+  }
   // every lane of a wave runs the same iterations (the bound is rounded up
   // to whole workgroups), so the shuffle and the ballots see the whole wave
   const int64_t end = ((int64_t)n + kMaskBlock - 1) / kMaskBlock * kMaskBlock;
@@ -50,8 +91,13 @@ __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *_
     const int32_t deg = live ? nxt - b : 0;
     uint32_t f = 0;
     if (live) {
-      f = vertex_flags(row_ptr, col, b, deg);
+      int32_t u0, u1;
+      f = vertex_flags(row_ptr, col, b, deg, u0, u1);
       flags[v] = (uint8_t)f;
+      if constexpr (kPath) {
+        pi.label[v] = first_parent((int32_t)v, f, u0, u1);
+        pi.cnt[v] = first_count(f);
+      }
     }
     const uint32_t nb = (uint32_t)__popcll(__ballot(f & 1));
     const uint32_t ml = (uint32_t)(__popcll(__ballot(f & 2)) + __popcll(__ballot(f & 4)));
@@ -59,6 +105,10 @@ __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *_
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
+  if constexpr (kPath) {  // summed by a later pass of the path
+    fx->mask_part[blockIdx.x] = s_cnt;
+    return;
+  }
   if (gridDim.x == 1) {
     store_counts(s_cnt, d_counts);
     return;
@@ -89,31 +139,29 @@ __global__ __launch_bounds__(kScanBlock) void k_mask_sum(int nparts, const Fixed
   if (threadIdx.x == 0) store_counts(tot, d_counts);
 }
 
-int launch_mask(cg_ctx *ctx, const cg_graph &g, uint8_t *flags, int32_t *d_counts,
-                hipStream_t st) {
-  const PhaseRange range("cg: BranchRemoval");
-  int64_t grid = ((int64_t)g.n + kMaskBlock - 1) / kMaskBlock;
-  if (grid < 1) grid = 1;
-  if (grid > kMaskMaxBlocks) grid = kMaskMaxBlocks;
-  CG_LAUNCH(ctx, k_mask, dim3((unsigned)grid), dim3(kMaskBlock), st, g.n, g.row_ptr, g.col, flags,
-            ctx->fixed, d_counts);
-  if (grid > kMaskSumInKernel)
-    CG_LAUNCH(ctx, k_mask_sum, dim3(1), dim3(kScanBlock), st, (int)grid, ctx->fixed, d_counts);
-  return hip_check(hipGetLastError(), "k_mask");
-}
-
 // ---------------------------------------------------------------------------
 // Components: union-find with min-id roots.  A root is always the smallest
 // id of its tree (a larger root is only ever linked under a smaller one), so
 // after full compression every vertex holds the smallest id of its
-// component.  Links are made by compare-and-swap on the root, so concurrent
-// hooks never lose a union; path halving only ever stores an ancestor.
+// component.  The forest starts with every read under its smaller kept
+// neighbour; links are made by compare-and-swap on the root, so concurrent
+// hooks never lose a union; path halving only ever stores an ancestor.  A
+// hook is a chain of device-scope loads of about 1 us each, so what counts is
+// how many follow one another: with a hook per edge on a forest of single
+// reads the pass took 13.5 us on the 50 Mbp graph.
 // ---------------------------------------------------------------------------
 constexpr int kCcBlock = 256;
 
-__global__ __launch_bounds__(kCcBlock) void k_cc_init(int32_t n, int32_t *__restrict__ label) {
+__global__ __launch_bounds__(kCcBlock) void k_cc_init(int32_t n, const int32_t *__restrict__ row_ptr,
+                                                      const int32_t *__restrict__ col,
+                                                      const uint8_t *__restrict__ flags,
+                                                      int32_t *__restrict__ label) {
   const int64_t v = (int64_t)blockIdx.x * kCcBlock + threadIdx.x;
-  if (v < n) label[v] = (int32_t)v;
+  if (v >= n) return;
+  const uint32_t f = flags[v];
+  const int32_t b = (f & 6) ? row_ptr[v] : 0;
+  const int32_t u0 = (f & 2) ? col[b] : 0, u1 = (f & 4) ? col[b + 1] : 0;
+  label[v] = first_parent((int32_t)v, f, u0, u1);
 }
 
 __global__ __launch_bounds__(kCcBlock) void k_cc_hook(int32_t n, const int32_t *__restrict__ row_ptr,
@@ -121,19 +169,10 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_hook(int32_t n, const int32_t *
                                                       const uint8_t *__restrict__ flags,
                                                       int32_t *label) {
   const int64_t v = (int64_t)blockIdx.x * kCcBlock + threadIdx.x;
-  if (v >= n) return;
-  const uint32_t f = flags[v];
-  if (!(f & 6)) return;
+  if (v >= n || (flags[v] & 6) != 6) return;
   const int32_t b = row_ptr[v];
-  // each undirected kept edge is hooked once, from its smaller end
-  if (f & 2) {
-    int32_t u = col[b];
-    if (u > v) uf_union(label, (int32_t)v, u);
-  }
-  if (f & 4) {
-    int32_t u = col[b + 1];
-    if (u > v) uf_union(label, (int32_t)v, u);
-  }
+  const int32_t u0 = col[b], u1 = col[b + 1];
+  if (u0 < v && u1 < v) uf_union(label, u0, u1);
 }
 
 __global__ __launch_bounds__(kCcBlock) void k_cc_compress(int32_t n, int32_t *label) {
@@ -150,13 +189,43 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_compress(int32_t n, int32_t *la
   st_relaxed(label + v, p);
 }
 
+static int64_t mask_grid(int32_t n) {
+  const int64_t grid = ((int64_t)n + kMaskBlock - 1) / kMaskBlock;
+  return grid < 1 ? 1 : (grid > kMaskMaxBlocks ? kMaskMaxBlocks : grid);
+}
+
+int launch_path_mask(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                     int *parts, hipStream_t st) {
+  const PhaseRange range("cg: BranchRemoval + ConnectedComponent");
+  const int64_t grid = mask_grid(g.n);
+  const PathInit pi{a.label, a.parts.label_comp, s.estart, s.scan_status, cyc_words(g.n),
+                    scan_blocks((int64_t)g.n + 1) + 1, a.reset ? 1 : 0};
+  CG_LAUNCH(ctx, k_mask<true>, dim3((unsigned)grid), dim3(kMaskBlock), st, g.n, g.row_ptr, g.col,
+            a.flags, ctx->fixed, a.d_counts, pi);
+  CG_LAUNCH(ctx, k_cc_hook, dim3((unsigned)((g.n + kCcBlock - 1) / kCcBlock)), dim3(kCcBlock), st,
+            g.n, g.row_ptr, g.col, a.flags, a.label);
+  *parts = (int)grid;
+  return hip_check(hipGetLastError(), "k_mask");
+}
+
+int launch_mask(cg_ctx *ctx, const cg_graph &g, uint8_t *flags, int32_t *d_counts,
+                hipStream_t st) {
+  const PhaseRange range("cg: BranchRemoval");
+  const int64_t grid = mask_grid(g.n);
+  CG_LAUNCH(ctx, k_mask<false>, dim3((unsigned)grid), dim3(kMaskBlock), st, g.n, g.row_ptr, g.col,
+            flags, ctx->fixed, d_counts, PathInit{});
+  if (grid > kMaskSumInKernel)
+    CG_LAUNCH(ctx, k_mask_sum, dim3(1), dim3(kScanBlock), st, (int)grid, ctx->fixed, d_counts);
+  return hip_check(hipGetLastError(), "k_mask");
+}
+
 int launch_components(cg_ctx *ctx, const cg_graph &g, const uint8_t *flags, int32_t *label,
                       hipStream_t st) {
   const PhaseRange range("cg: ConnectedComponent");
   (void)ctx;
   if (g.n == 0) return CG_OK;
   int grid = (int)((g.n + kCcBlock - 1) / kCcBlock);
-  CG_LAUNCH(ctx, k_cc_init, dim3(grid), dim3(kCcBlock), st, g.n, label);
+  CG_LAUNCH(ctx, k_cc_init, dim3(grid), dim3(kCcBlock), st, g.n, g.row_ptr, g.col, flags, label);
   CG_LAUNCH(ctx, k_cc_hook, dim3(grid), dim3(kCcBlock), st, g.n, g.row_ptr, g.col, flags,
                      label);
   CG_LAUNCH(ctx, k_cc_compress, dim3(grid), dim3(kCcBlock), st, g.n, label);
@@ -165,8 +234,9 @@ int launch_components(cg_ctx *ctx, const cg_graph &g, const uint8_t *flags, int3
 
 // ---------------------------------------------------------------------------
 // Validation.  Every failure is packed as (phase, index, reason) and the
-// smallest packed value wins, which reproduces "first failure in check
-// order".  Indices are clamped so that even a malformed row_ptr never sends a
+// smallest packed value wins (kept as the largest complement, so that zero is
+// none and the last pass leaves it so), which reproduces "first failure in
+// check order".  Indices are clamped so that even a malformed row_ptr never sends a
 // load outside the caller's arrays.
 // ---------------------------------------------------------------------------
 constexpr int kValBlock = 256;
@@ -175,16 +245,14 @@ __device__ __forceinline__ unsigned long long pack_fail(unsigned phase, int64_t 
   return ((unsigned long long)phase << 60) | ((unsigned long long)idx << 4) | why;
 }
 
-__global__ void k_val_init(Fixed *fx) { fx->valid_best = ~0ull; }
-
 __global__ __launch_bounds__(kValBlock) void k_val_check(cg_graph g, Fixed *fx) {
   const int64_t v = (int64_t)blockIdx.x * kValBlock + threadIdx.x;
   if (v == 0) {
-    if (g.row_ptr[0] != 0 || g.row_ptr[g.n] != g.m) atomicMin(&fx->valid_best, pack_fail(0, 0, 1));
+    if (g.row_ptr[0] != 0 || g.row_ptr[g.n] != g.m) atomicMax(&fx->valid_best, ~pack_fail(0, 0, 1));
   }
   if (v >= g.n) return;
   const int32_t rb = g.row_ptr[v], re = g.row_ptr[v + 1];
-  if (re < rb) atomicMin(&fx->valid_best, pack_fail(1, v, 1));
+  if (re < rb) atomicMax(&fx->valid_best, ~pack_fail(1, v, 1));
   {
     unsigned why = 0;
     uint32_t L = g.read_len[v];
@@ -192,7 +260,7 @@ __global__ __launch_bounds__(kValBlock) void k_val_check(cg_graph g, Fixed *fx) 
     if (L < 1) why = 9;
     else if (off % 16 != 0) why = 10;
     else if (off + L > g.seq_words * 16) why = 11;
-    if (why) atomicMin(&fx->valid_best, pack_fail(2, v, why));
+    if (why) atomicMax(&fx->valid_best, ~pack_fail(2, v, why));
   }
   const int32_t lo = rb < 0 ? 0 : (rb > g.m ? g.m : rb);
   const int32_t hi = re < lo ? lo : (re > g.m ? g.m : re);
@@ -232,14 +300,15 @@ __global__ __launch_bounds__(kValBlock) void k_val_check(cg_graph g, Fixed *fx) 
       }
     }
     if (why) {
-      atomicMin(&fx->valid_best, pack_fail(3, j, why));
+      atomicMax(&fx->valid_best, ~pack_fail(3, j, why));
       break;
     }
   }
 }
 
 __global__ void k_val_final(Fixed *fx, int64_t *d_bad) {
-  unsigned long long b = fx->valid_best;
+  const unsigned long long b = ~fx->valid_best;
+  fx->valid_best = 0;
   if (b == ~0ull) {
     d_bad[0] = -1;
     d_bad[1] = 0;
@@ -254,7 +323,6 @@ int launch_validate(cg_ctx *ctx, const cg_graph &g, int64_t *d_bad, hipStream_t 
   const PhaseRange range("cg: validate");
   int grid = (int)((g.n + kValBlock - 1) / kValBlock);
   if (grid == 0) grid = 1;
-  CG_LAUNCH(ctx, k_val_init, dim3(1), dim3(1), st, ctx->fixed);
   CG_LAUNCH(ctx, k_val_check, dim3(grid), dim3(kValBlock), st, g, ctx->fixed);
   CG_LAUNCH(ctx, k_val_final, dim3(1), dim3(1), st, ctx->fixed, d_bad);
   return hip_check(hipGetLastError(), "k_val");

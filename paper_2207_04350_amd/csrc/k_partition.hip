@@ -2,9 +2,14 @@
 //
 //  k_part_zero / k_part_count  per-label counter (4 per read, +1 per read of
 //                              degree 1 in L): size q = c >> 2, roots of degree
-//                              one = c & 3 (2 for a path, 0 for a cycle)
-//  k_part_compact              eligible components in ascending label order
-//                              (single-pass look-back scan), label -> index map
+//                              one = c & 3 (2 for a path, 0 for a cycle); in the
+//                              whole path the count also finishes the component
+//                              labels and gives every read its member slot
+//  k_part_chunks               eligible roots per chunk of reads, for a least
+//                              size that the flags do not decide
+//  k_part_compact              eligible components in ascending label order,
+//                              label -> index map: a workgroup per chunk adds up
+//                              the chunks before its own
 //  k_part_wzero / k_part_weight bases weights (lengths of a component's reads)
 //  k_part_lpt                  one workgroup: sort by (weight desc, label asc),
 //                              exact LPT, sort by (bin, label), read offsets
@@ -17,59 +22,246 @@ namespace cg {
 
 constexpr int kPartBlock = 256;
 
-__global__ __launch_bounds__(kPartBlock) void k_part_zero(int32_t n, int32_t *__restrict__ cnt) {
+__global__ __launch_bounds__(kPartBlock) void k_part_zero(int32_t n, const uint8_t *__restrict__ flags,
+                                                          int32_t *__restrict__ cnt) {
   const int64_t v = (int64_t)blockIdx.x * kPartBlock + threadIdx.x;
-  if (v < n) cnt[v] = 0;
+  if (v < n) cnt[v] = (flags[v] & 6) ? 0 : 4;
 }
 
-__global__ __launch_bounds__(kPartBlock) void k_part_count(int32_t n, const uint8_t *__restrict__ flags,
-                                                           const int32_t *__restrict__ label,
-                                                           int32_t *cnt) {
-  const int64_t v = (int64_t)blockIdx.x * kPartBlock + threadIdx.x;
-  if (v >= n) return;
-  const uint32_t f = flags[v];
-  const uint32_t degL = ((f >> 1) & 1) + ((f >> 2) & 1);
-  atomicAdd((uint32_t *)cnt + label[v], 4u + (degL == 1 ? 1u : 0u));
+// Chunks of consecutive reads, a workgroup each, for the count and the
+// compaction: rounds of kChunkRound reads, and as many rounds as keep the
+// chunks at kChunks, so that adding up the chunks before one's own stays a
+// load per thread.
+constexpr int kChunkBlock = 1024;
+constexpr int kChunkPer = 2;
+constexpr int kChunkRound = kChunkBlock * kChunkPer;
+constexpr int kChunks = 1024;
+static int chunk_rounds(int32_t n) {
+  const int64_t rounds = ((int64_t)n + kChunkRound - 1) / kChunkRound;
+  return (int)((rounds + kChunks - 1) / kChunks);
+}
+static int chunk_count(int32_t n) {
+  const int64_t per = (int64_t)kChunkRound * chunk_rounds(n);
+  return n > 0 ? (int)(((int64_t)n + per - 1) / per) : 1;
 }
 
-// kCompactPer consecutive reads per thread, so that every block of a large
-// graph is resident at once and the look-back chain is short
-constexpr int kCompactPer = 4;
-__global__ __launch_bounds__(kScanBlock) void k_part_compact(
-    int32_t n, const uint8_t *__restrict__ flags, int32_t *label_comp, int32_t min_reads,
-    int32_t *__restrict__ comp_label, int32_t *__restrict__ comp_size,
-    uint8_t *__restrict__ comp_kind, int32_t *__restrict__ d_n_comp, ScanCtx sc, int nblocks) {
-  const int blk = lookback_ticket(sc);
-  const int64_t v0 = ((int64_t)blk * kScanBlock + threadIdx.x) * kCompactPer;
-  uint32_t c[kCompactPer];
-  bool elig[kCompactPer];
-  uint32_t cnt = 0;
+// Whether root v (a read that is its component's label) of q reads and flags f
+// makes an eligible component.  Up to two reads the flags tell: a component
+// of more than one read is one whose root has kept entries.
+__device__ __forceinline__ bool eligible(uint32_t f, uint32_t q, int32_t min_reads) {
+  if (f & 1) return false;
+  return min_reads <= 1 || (min_reads == 2 ? (f & 6) != 0 : q >= (uint32_t)min_reads);
+}
+
+// The workgroup's sum of x, in thread 0.
+__device__ __forceinline__ uint32_t chunk_sum(uint32_t x, uint32_t *sh) {
+  x = wave_sum(x);
+  if (lane_id() == 0) sh[threadIdx.x / kWave] = x;
+  __syncthreads();
+  if (threadIdx.x < kWave) x = wave_sum(threadIdx.x < kChunkBlock / kWave ? sh[threadIdx.x] : 0u);
+  return x;
+}
+
+// Reads without kept entries are counted already (first_count).  A
+// workgroup's others are counted per component in an LDS hash table first:
+// one atomic per read on the component's counter queues on its address
+// (about 4.5 ns each: 57 us for the 15,000 reads of 13 components).
+// kFind: the labels are a forest still; every read's is set to its root, and
+// slot gives its place among its component's reads.
+struct CountExtra {
+  int32_t *slot;
+  const Fixed *fx;  // branch and entry counts of the mask pass, mask_parts of them
+  int mask_parts;
+  int32_t *d_counts;
+};
+constexpr int kCountSlots = 2 * kChunkRound;  // at most half full
+template <bool kFind>
+__global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int rounds,
+                                                            const uint8_t *__restrict__ flags,
+                                                            int32_t *label, int32_t *cnt,
+                                                            int32_t min_reads,
+                                                            uint32_t *__restrict__ chunks,
+                                                            CountExtra ex) {
+  __shared__ int32_t s_key[kCountSlots];
+  __shared__ uint32_t s_cnt[kCountSlots];
+  __shared__ uint32_t sh[kChunkBlock / kWave];
+  uint32_t elig = 0;
+  for (int r = 0; r < rounds; ++r) {
+    const int64_t base = ((int64_t)blockIdx.x * rounds + r) * kChunkRound;
+    if (base >= n) break;
+    uint32_t f[kChunkPer];
+    int32_t v[kChunkPer], root[kChunkPer];
 #pragma unroll
-  for (int k = 0; k < kCompactPer; ++k) {
-    const int64_t v = v0 + k;
-    c[k] = v < n ? (uint32_t)label_comp[v] : 0u;
-    elig[k] = v < n && (c[k] >> 2) >= (uint32_t)min_reads && !(flags[v] & 1);
-    cnt += elig[k] ? 1u : 0u;
-  }
-  unsigned long long incl_end;
-  unsigned long long ex = lookback_block_scan(sc, blk, (unsigned long long)cnt, &incl_end);
+    for (int k = 0; k < kChunkPer; ++k) {
+      const int64_t x = base + k * kChunkBlock + threadIdx.x;
+      v[k] = (int32_t)x;
+      f[k] = x < n ? flags[x] : 1u;
+      root[k] = v[k];
+      if (x < n && (f[k] & 6u)) root[k] = kFind ? ld_relaxed(label + x) : label[x];
+    }
+    for (int i = threadIdx.x; i < kCountSlots; i += kChunkBlock) {
+      s_key[i] = -1;
+      s_cnt[i] = 0;
+    }
+    if constexpr (kFind) {
+      // both reads' climbs side by side
+      bool more = true;
+      int32_t first[kChunkPer];
 #pragma unroll
-  for (int k = 0; k < kCompactPer; ++k) {
-    const int64_t v = v0 + k;
-    if (v >= n) continue;
-    if (elig[k]) {
-      const uint32_t q = c[k] >> 2;
-      comp_label[ex] = (int32_t)v;
-      comp_size[ex] = (int32_t)q;
-      comp_kind[ex] = q == 1 ? CG_KIND_SINGLE : ((c[k] & 3u) ? CG_KIND_PATH : CG_KIND_CYCLE);
-      label_comp[v] = (int32_t)ex;
-      ++ex;
-    } else {
-      label_comp[v] = -1;
+      for (int k = 0; k < kChunkPer; ++k) first[k] = root[k];
+      while (more) {
+        int32_t p[kChunkPer];
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) p[k] = (f[k] & 6u) ? ld_relaxed(label + root[k]) : root[k];
+        more = false;
+#pragma unroll
+        for (int k = 0; k < kChunkPer; ++k) {
+          more = more || p[k] != root[k];
+          root[k] = p[k];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kChunkPer; ++k)
+        if (root[k] != first[k]) st_relaxed(label + v[k], root[k]);
+    }
+    int h[kChunkPer];
+    uint32_t at[kChunkPer];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kChunkPer; ++k) {
+      h[k] = -1;
+      if (root[k] == v[k] && eligible(f[k], 2, min_reads)) ++elig;
+      if (!(f[k] & 6u)) continue;
+      uint32_t i = ((uint32_t)root[k] * 2654435761u) >> 16 & (kCountSlots - 1);
+      while (true) {  // ends: the table is at most half full
+        const int32_t old = atomicCAS(s_key + i, -1, root[k]);
+        if (old == -1 || old == root[k]) break;
+        i = (i + 1) & (kCountSlots - 1);
+      }
+      h[k] = (int)i;
+      at[k] = atomicAdd(s_cnt + i, (f[k] & 6u) == 6u ? 4u : 5u);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kCountSlots; i += kChunkBlock) {
+      const int32_t x = s_key[i];
+      if (x >= 0) s_cnt[i] = atomicAdd((uint32_t *)cnt + x, s_cnt[i]) >> 2;
+    }
+    __syncthreads();
+    if constexpr (kFind) {
+#pragma unroll
+      for (int k = 0; k < kChunkPer; ++k)
+        if (h[k] >= 0) ex.slot[v[k]] = (int32_t)(s_cnt[h[k]] + (at[k] >> 2));
+      __syncthreads();
     }
   }
-  if (blk == nblocks - 1 && threadIdx.x == 0) *d_n_comp = (int32_t)incl_end;
-  lookback_finish(sc, nblocks);
+  elig = chunk_sum(elig, sh);
+  if (chunks && threadIdx.x == 0) chunks[blockIdx.x] = elig;
+  if constexpr (kFind) {
+    // the last workgroup adds up the mask pass's counts
+    static_assert(kMaskMaxBlocks <= kChunkBlock, "a part per thread");
+    if (blockIdx.x != gridDim.x - 1) return;
+    const unsigned long long p =
+        (int)threadIdx.x < ex.mask_parts ? ex.fx->mask_part[threadIdx.x] : 0ull;
+    __syncthreads();
+    const uint32_t nb = chunk_sum((uint32_t)p, sh);
+    __syncthreads();
+    const uint32_t ml = chunk_sum((uint32_t)(p >> 32), sh);
+    if (threadIdx.x == 0) {
+      ex.d_counts[0] = (int32_t)nb;
+      ex.d_counts[1] = (int32_t)ml;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int rounds,
+                                                             const uint8_t *__restrict__ flags,
+                                                             const int32_t *__restrict__ cnt,
+                                                             int32_t min_reads,
+                                                             uint32_t *__restrict__ chunks) {
+  __shared__ uint32_t sh[kChunkBlock / kWave];
+  uint32_t elig = 0;
+  const int64_t base = (int64_t)blockIdx.x * rounds * kChunkRound;
+  for (int r = 0; r < rounds * kChunkPer; ++r) {
+    const int64_t v = base + (int64_t)r * kChunkBlock + threadIdx.x;
+    if (v >= n) break;
+    const uint32_t c = (uint32_t)cnt[v];
+    if (c > 0 && eligible(flags[v], c >> 2, min_reads)) ++elig;
+  }
+  elig = chunk_sum(elig, sh);
+  if (threadIdx.x == 0) chunks[blockIdx.x] = elig;
+}
+
+// Two consecutive reads per thread and round.  (A single-pass look-back scan
+// in this place waited for its tickets, its predecessors and a release per
+// workgroup: 29 us on the 1 Gbp graph, 7 us on a graph of one workgroup.)
+// mstart, if given: the first member slot of each component, taken from the
+// cursor a round's components at a time, in any order.
+__global__ __launch_bounds__(kChunkBlock) void k_part_compact(
+    int32_t n, int rounds, const uint32_t *__restrict__ chunks, const uint8_t *__restrict__ flags,
+    int32_t *label_comp, int32_t min_reads, int32_t *__restrict__ comp_label,
+    int32_t *__restrict__ comp_size, uint8_t *__restrict__ comp_kind,
+    int32_t *__restrict__ d_n_comp, int32_t *__restrict__ mstart, unsigned int *cursor) {
+  __shared__ unsigned long long sh[kChunkBlock / kWave + 1];
+  __shared__ uint32_t s_before, s_slot;
+  __shared__ uint32_t sh32[kChunkBlock / kWave];
+  const int64_t base0 = (int64_t)blockIdx.x * rounds * kChunkRound;
+  static_assert(kChunks <= kChunkBlock, "a chunk per thread");
+  uint32_t before = threadIdx.x < blockIdx.x ? chunks[threadIdx.x] : 0u;
+  uint32_t c[kChunkPer], f[kChunkPer];
+  auto load = [&](int64_t base) {
+#pragma unroll
+    for (int k = 0; k < kChunkPer; ++k) {
+      const int64_t v = base + (int64_t)threadIdx.x * kChunkPer + k;
+      c[k] = v < n ? (uint32_t)label_comp[v] : 0u;
+      f[k] = v < n ? flags[v] : 1u;
+    }
+  };
+  load(base0);
+  before = chunk_sum(before, sh32);
+  if (threadIdx.x == 0) s_before = before;
+  __syncthreads();
+  before = s_before;
+  for (int r = 0; r < rounds; ++r) {
+    const int64_t base = base0 + (int64_t)r * kChunkRound;
+    if (base >= n) break;
+    if (r > 0) load(base);
+    // (components << 32) | their reads, each below 2^31
+    unsigned long long x = 0;
+    bool el[kChunkPer];
+#pragma unroll
+    for (int k = 0; k < kChunkPer; ++k) {
+      el[k] = c[k] > 0 && eligible(f[k], c[k] >> 2, min_reads);
+      x += el[k] ? 1ull << 32 | (c[k] >> 2) : 0ull;
+    }
+    unsigned long long tot;
+    const unsigned long long ex = block_excl_scan<unsigned long long, kChunkBlock>(x, sh, &tot);
+    if (mstart) {
+      if (threadIdx.x == 0 && (uint32_t)tot) s_slot = atomicAdd(cursor, (uint32_t)tot);
+      __syncthreads();
+    }
+    uint32_t at = before + (uint32_t)(ex >> 32);
+    uint32_t slot = mstart ? s_slot + (uint32_t)ex : 0u;
+#pragma unroll
+    for (int k = 0; k < kChunkPer; ++k) {
+      const int64_t v = base + (int64_t)threadIdx.x * kChunkPer + k;
+      if (v >= n) continue;
+      if (el[k]) {
+        const uint32_t q = c[k] >> 2;
+        comp_label[at] = (int32_t)v;
+        comp_size[at] = (int32_t)q;
+        comp_kind[at] = q == 1 ? CG_KIND_SINGLE : ((c[k] & 3u) ? CG_KIND_PATH : CG_KIND_CYCLE);
+        if (mstart) mstart[at] = (int32_t)slot;
+        label_comp[v] = (int32_t)at;
+        ++at;
+        slot += q;
+      } else {
+        label_comp[v] = -1;
+      }
+    }
+    before += (uint32_t)(tot >> 32);
+    if (mstart) __syncthreads();  // the slot is read before the next round's
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *d_n_comp = (int32_t)before;
 }
 
 // ---------------------------------------------------------------------------
@@ -91,6 +283,36 @@ __global__ __launch_bounds__(kPartBlock) void k_part_weight(int32_t n, const int
   if (c >= 0) atomicAdd((unsigned long long *)w + c, (unsigned long long)read_len[v]);
 }
 
+// Workgroup 0 of the LPT.  In the whole path the others put every read of a
+// component into its slot meanwhile (the partition leaves all but one compute
+// unit idle; as a launch of its own after it this took 12 us of the 50 Mbp
+// graph's and 33 us of the 1 Gbp graph's).
+struct FillArgs {
+  int32_t n;
+  const uint8_t *flags;
+  const int32_t *label, *label_comp, *mstart, *slot;
+  int32_t *tmp;
+};
+__device__ __forceinline__ void fill_members(const FillArgs &fa) {
+  const int64_t stride = (int64_t)(gridDim.x - 1) * kLptBlock;
+  constexpr int U = 2;
+  for (int64_t v0 = (int64_t)(blockIdx.x - 1) * kLptBlock + threadIdx.x; v0 < fa.n;
+       v0 += U * stride) {
+    int32_t lab[U], c[U], at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t v = v0 + u * stride;
+      lab[u] = v < fa.n && (fa.flags[v] & 6u) ? fa.label[v] : -1;
+      at[u] = lab[u] >= 0 ? fa.slot[v] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) c[u] = lab[u] >= 0 ? fa.label_comp[lab[u]] : -1;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c[u] >= 0) fa.tmp[fa.mstart[c[u]] + at[u]] = (int32_t)(v0 + u * stride);
+  }
+}
+
 // later: k_part_place takes the (bin, label) order
 __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t *__restrict__ d_n_comp,
                                                         const int32_t *__restrict__ comp_size,
@@ -100,23 +322,29 @@ __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t
                                                         int32_t *__restrict__ comp_start,
                                                         uint64_t *__restrict__ bin_load,
                                                         uint64_t *g_keys, int32_t *g_bin,
-                                                        uint64_t *g_bins, int later) {
+                                                        uint64_t *g_bins, int later, RankOut ro,
+                                                        FillArgs fa) {
   __shared__ uint64_t s_keys[kSortCapLds];
   __shared__ int32_t s_bin[kSortCapLds];
   __shared__ uint64_t s_binA[kBinCapLds], s_binB[kBinCapLds];
   __shared__ uint32_t s_cnt[kLptBlock / kWave * 256];
   uint32_t *big_cnt = reinterpret_cast<uint32_t *>(s_keys);  // s_keys is the LDS form's
+  if (blockIdx.x > 0) {
+    fill_members(fa);
+    return;
+  }
   const int nc = *d_n_comp;
   int32_t *rank = later ? nullptr : comp_rank;
   int32_t *bin_of = later ? comp_bin : g_bin;
   if (nc <= kSortCapLds && P <= kBinCapLds && !later)
     lpt_body<kLptBlock, false>(nc, P, comp_size, weight, s_keys, s_bin, s_cnt, s_binA, s_binB,
-                               comp_bin, comp_rank, comp_start, bin_load, nullptr, status);
+                               comp_bin, comp_rank, comp_start, bin_load, nullptr, status, nullptr, nullptr,
+                               ro);
   else
     lpt_body<kLptBlock, true>(nc, P, comp_size, weight, g_keys, bin_of, big_cnt,
                               P <= kBinCapLds ? s_binA : g_bins,
                               P <= kBinCapLds ? s_binB : g_bins + P, comp_bin, rank, comp_start,
-                              bin_load, nullptr, status);
+                              bin_load, nullptr, status, nullptr, nullptr, ro);
 }
 
 // ---------------------------------------------------------------------------
@@ -165,11 +393,16 @@ __global__ __launch_bounds__(kPlaceBlock) void k_part_place(int32_t P, int32_t c
                                                             const int32_t *__restrict__ comp_bin,
                                                             const uint64_t *__restrict__ hist,
                                                             int32_t *__restrict__ comp_rank,
-                                                            int32_t *__restrict__ comp_start) {
+                                                            int32_t *__restrict__ comp_start,
+                                                            RankOut ro) {
   __shared__ unsigned long long pos[kBinCapLds];
   __shared__ unsigned long long wpos[kPlaceWaves][kBinCapLds];
   __shared__ unsigned long long sh[kPlaceWaves + 1];
   const int64_t nc = *d_n_comp, c0 = (int64_t)blockIdx.x * chunk;
+  if (ro.bin_vptr && nc == 0 && blockIdx.x == 0) {
+    for (int b = threadIdx.x; b <= P; b += kPlaceBlock) ro.bin_vptr[b] = 0;
+    if (threadIdx.x == 0) ro.d_sizes[0] = ro.d_sizes[1] = ro.loc_row_ptr[0] = 0;
+  }
   if (c0 >= nc) return;
   const int chunks = (int)((nc + chunk - 1) / chunk);
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), l = lane_id();
@@ -198,9 +431,14 @@ __global__ __launch_bounds__(kPlaceBlock) void k_part_place(int32_t P, int32_t c
     }
     unsigned long long tot;
     const unsigned long long ex = block_excl_scan<unsigned long long, kPlaceBlock>(all, sh, &tot);
-    if (b < P) pos[b] = carry + ex + before;
+    if (b < P) {
+      pos[b] = carry + ex + before;
+      if (ro.bin_vptr && blockIdx.x == 0) ro.bin_vptr[b] = (int32_t)(uint32_t)(carry + ex);
+    }
     carry += tot;
   }
+  if (ro.bin_vptr && blockIdx.x == 0 && threadIdx.x == 0)
+    ro.bin_vptr[P] = ro.d_sizes[0] = (int32_t)(uint32_t)carry;
   __syncthreads();
   for (int b = threadIdx.x; b < P; b += kPlaceBlock) {
     unsigned long long x = pos[b];
@@ -239,6 +477,7 @@ __global__ __launch_bounds__(kPlaceBlock) void k_part_place(int32_t P, int32_t c
     if (v) {
       comp_rank[c] = rank;
       comp_start[c] = start;
+      if (ro.bin_vptr && q > 1 && ro.comp_kind[c] == CG_KIND_CYCLE) mark_cycle(ro.cyc, rank);
       // the bin's last lane leaves where the next round goes on
       if ((peers & ~below) == 1ull << l)
         my[b] = (unsigned long long)(uint32_t)(rank + 1) << 32 | (uint32_t)(start + q);
@@ -247,36 +486,30 @@ __global__ __launch_bounds__(kPlaceBlock) void k_part_place(int32_t P, int32_t c
   }
 }
 
-int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
-                     const int32_t *label, int32_t P, int32_t min_reads, int32_t weight,
-                     const cg_parts &out, hipStream_t st) {
-  const PhaseRange range("cg: GreedyPartitioning");
+// bases weights (if wanted), the LPT, and the order of many components; fa.n > 0:
+// with the members' slots filled meanwhile
+static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const int32_t *label,
+                       int32_t P, int32_t min_reads, int32_t weight, const cg_parts &out,
+                       const RankOut &ro, const FillArgs &fa, hipStream_t st) {
   const int32_t n = g.n;
-  if (min_reads < 1) min_reads = 1;
-  const int grid = n > 0 ? (int)((n + kPartBlock - 1) / kPartBlock) : 1;
-  if (n > 0) {
-    CG_LAUNCH(ctx, k_part_zero, dim3(grid), dim3(kPartBlock), st, n, out.label_comp);
-    CG_LAUNCH(ctx, k_part_count, dim3(grid), dim3(kPartBlock), st, n, flags, label,
-                       out.label_comp);
-  }
-  const int nb = scan_blocks(n > 0 ? (n + kCompactPer - 1) / kCompactPer : 1);
-  CG_LAUNCH(ctx, k_part_compact, dim3(nb), dim3(kScanBlock), st, n, flags, out.label_comp,
-                     min_reads, out.comp_label, out.comp_size, out.comp_kind, out.d_n_comp,
-                     scan_ctx(ctx, s), nb);
   const bool bases = weight == CG_WEIGHT_BASES;
   if (bases && n > 0) {
-    CG_LAUNCH(ctx, k_part_wzero, dim3(grid), dim3(kPartBlock), st, n, s.comp_w);
-    CG_LAUNCH(ctx, k_part_weight, dim3(grid), dim3(kPartBlock), st, n, label, out.label_comp,
+    const dim3 grid((unsigned)((n + kPartBlock - 1) / kPartBlock));
+    CG_LAUNCH(ctx, k_part_wzero, grid, dim3(kPartBlock), st, n, s.comp_w);
+    CG_LAUNCH(ctx, k_part_weight, grid, dim3(kPartBlock), st, n, label, out.label_comp,
                        g.read_len, s.comp_w);
   }
   // one-read components are most of a graph's, so where they are wanted of
   // more reads than the LDS sort holds, the order is left to the passes below
   // (two launches, which the few components of other graphs do not repay)
   const bool place = min_reads <= 1 && n > kSortCapLds && P <= kBinCapLds;
-  CG_LAUNCH(ctx, k_part_lpt, dim3(1), dim3(kLptBlock), st, P, out.d_n_comp, out.comp_size,
-                     bases ? (const uint64_t *)s.comp_w : nullptr, &ctx->fixed->status,
-                     out.comp_bin, out.comp_rank, out.comp_start, out.bin_load, s.keys, s.aux,
-                     s.bins, place ? 1 : 0);
+  // the fill takes a compute unit per workgroup (the LPT's LDS), four reads a
+  // thread where that leaves some
+  const int64_t fill = ((int64_t)fa.n + 4 * kLptBlock - 1) / (4 * kLptBlock);
+  CG_LAUNCH(ctx, k_part_lpt, dim3((unsigned)(1 + (fill < 255 ? fill : 255))), dim3(kLptBlock), st,
+            P, out.d_n_comp, out.comp_size, bases ? (const uint64_t *)s.comp_w : nullptr,
+            &ctx->fixed->status, out.comp_bin, out.comp_rank, out.comp_start, out.bin_load, s.keys,
+            s.aux, s.bins, place ? 1 : 0, place ? RankOut{} : ro, fa);
   if (place) {
     const int32_t per = (n + kPlaceChunks - 1) / kPlaceChunks;
     const int32_t chunk = per > kPlaceChunk ? per : kPlaceChunk;
@@ -284,9 +517,86 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
     CG_LAUNCH(ctx, k_part_hist, chunks, dim3(kPlaceBlock), st, P, chunk, out.d_n_comp,
               out.comp_size, out.comp_bin, s.keys);
     CG_LAUNCH(ctx, k_part_place, chunks, dim3(kPlaceBlock), st, P, chunk, out.d_n_comp,
-              out.comp_size, out.comp_bin, s.keys, out.comp_rank, out.comp_start);
+              out.comp_size, out.comp_bin, s.keys, out.comp_rank, out.comp_start, ro);
   }
+}
+
+// the eligible components (counts in label_comp, chunk sums unless the flags
+// decide), with member slots if mstart is given
+static void launch_compact(cg_ctx *ctx, const cg_graph &g, uint32_t *chunks, const uint8_t *flags,
+                           int32_t min_reads, const cg_parts &out, int32_t *mstart,
+                           hipStream_t st) {
+  const int32_t n = g.n;
+  const int rounds = chunk_rounds(n);
+  const dim3 grid((unsigned)chunk_count(n));
+  if (min_reads > 2 && n > 0)
+    CG_LAUNCH(ctx, k_part_chunks, grid, dim3(kChunkBlock), st, n, rounds, flags, out.label_comp,
+              min_reads, chunks);
+  CG_LAUNCH(ctx, k_part_compact, grid, dim3(kChunkBlock), st, n, rounds, chunks, flags,
+            out.label_comp, min_reads, out.comp_label, out.comp_size, out.comp_kind, out.d_n_comp,
+            mstart, &ctx->fixed->fill_cursor);
+}
+
+int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
+                     const int32_t *label, int32_t P, int32_t min_reads, int32_t weight,
+                     const cg_parts &out, hipStream_t st) {
+  const PhaseRange range("cg: GreedyPartitioning");
+  const int32_t n = g.n;
+  if (min_reads < 1) min_reads = 1;
+  uint32_t *chunks = reinterpret_cast<uint32_t *>(s.keys);  // until the LPT
+  if (n > 0) {
+    CG_LAUNCH(ctx, k_part_zero, dim3((unsigned)((n + kPartBlock - 1) / kPartBlock)),
+              dim3(kPartBlock), st, n, flags, out.label_comp);
+    CG_LAUNCH(ctx, k_part_count<false>, dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
+              chunk_rounds(n), flags, const_cast<int32_t *>(label), out.label_comp, min_reads,
+              min_reads <= 2 ? chunks : nullptr, CountExtra{});
+  }
+  launch_compact(ctx, g, chunks, flags, min_reads, out, nullptr, st);
+  launch_lpt(ctx, g, s, label, P, min_reads, weight, out, RankOut{}, FillArgs{}, st);
   return hip_check(hipGetLastError(), "k_part");
+}
+
+int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                          int mask_parts, hipStream_t st) {
+  const PhaseRange range("cg: GreedyPartitioning");
+  const int32_t n = g.n, min_reads = a.min_reads < 1 ? 1 : a.min_reads;
+  uint32_t *chunks = reinterpret_cast<uint32_t *>(s.keys);  // until the LPT
+  int32_t *mstart = reinterpret_cast<int32_t *>(s.fill);
+  CG_LAUNCH(ctx, k_part_count<true>, dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
+            chunk_rounds(n), a.flags, a.label, a.parts.label_comp, min_reads,
+            min_reads <= 2 ? chunks : nullptr,
+            (CountExtra{s.lidx, ctx->fixed, mask_parts, a.d_counts}));
+  launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts, mstart, st);
+  const RankOut ro{a.local.bin_vptr, a.local.d_sizes, a.local.loc_row_ptr, a.parts.comp_kind,
+                   cyc_marks(s.estart, n)};
+  const FillArgs fa{n, a.flags, a.label, a.parts.label_comp, mstart, s.lidx, s.tmp};
+  launch_lpt(ctx, g, s, a.label, a.P, min_reads, a.weight, a.parts, ro, fa, st);
+  return hip_check(hipGetLastError(), "k_part");
+}
+
+// The five steps together: ten launches (twelve with bases weights or every
+// read wanted) where the steps one by one take fifteen to eighteen.  The mask
+// pass sets up the component forest and the counters, the count finishes the
+// labels and gives out the member slots, and the LPT's launch fills them.
+int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                hipStream_t st) {
+  int parts = 0;
+  int rc;
+  if (g.n == 0) {
+    rc = launch_mask(ctx, g, a.flags, a.d_counts, st);
+    if (!rc) rc = launch_partition(ctx, g, s, a.flags, a.label, a.P, a.min_reads, a.weight, a.parts, st);
+    if (!rc) rc = launch_induce(ctx, g, s, a.flags, a.label, a.parts, a.P, a.local, st);
+  } else {
+    rc = launch_path_mask(ctx, g, s, a, &parts, st);
+    if (!rc) rc = launch_path_partition(ctx, g, s, a, parts, st);
+    if (!rc) {
+      const PhaseRange range("cg: InducedSubgraph");
+      rc = launch_ind_comp(ctx, g, s, a.flags, a.parts, reinterpret_cast<int32_t *>(s.fill),
+                           a.local, st);
+    }
+  }
+  if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.d_status);
+  return rc;
 }
 
 }  // namespace cg
