@@ -1856,6 +1856,172 @@ __device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int
 }
 
 // ---------------------------------------------------------------------------
+// InducedSubgraph and LocalAssembly of one component of at most CAP reads in
+// one pass, by a workgroup of BLOCK threads or one wave (BLOCK = kWave).  The
+// caller has gathered each member's id v, kept bits kb (1: entry 0, 2: entry
+// 1), A = (id, first column, second column, first entry), Bq = (length, overlap
+// or pre of entry 0, of entry 1, strands of both), Cq = post of both and ro,
+// where the read starts in the store.  The local numbers follow the ids; every
+// field goes into the walk's LDS arrays at its local number while perm and the
+// local CSR rows are written out, so the walk reads nothing back.
+// ---------------------------------------------------------------------------
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+template <int BLOCK, int CAP>
+__device__ __forceinline__ void iw_rows(const CompRec &cr, int q, int st, int32_t estart,
+                                        const int32_t (&v)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        const uint32_t (&kb)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        const i32x4 (&A)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        const i32x4 (&Bq)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        const i32x2 (&Cq)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        const uint64_t (&ro)[CAP >= BLOCK ? CAP / BLOCK : 1],
+                                        WalkArrays w, const cg_graph &g, const cg_local &local,
+                                        const cg_contigs &out, const Scratch &s,
+                                        uint64_t *sh_scan) {
+  constexpr int R = CAP >= BLOCK ? CAP / BLOCK : 1;  // members per thread
+  const int tid = BLOCK == kWave ? lane_id() : (int)threadIdx.x;
+  auto bar = [] {
+    if constexpr (BLOCK == kWave) wave_lds_sync();
+    else lds_barrier();
+  };
+  // 1. local numbers: the ids in order in a (the walk's ray array, unused
+  // until its rays), each member's rank among them
+  int32_t *a = reinterpret_cast<int32_t *>(w.ray);
+  int32_t rk[R];
+  if constexpr (BLOCK == kWave) {
+    // one wave: a rank is the number of smaller ids, counted over the lanes
+#pragma unroll
+    for (int u = 0; u < R; ++u) rk[u] = 0;
+#pragma unroll
+    for (int u2 = 0; u2 < R; ++u2) {
+      const int cnt = q - u2 * kWave < kWave ? q - u2 * kWave : kWave;
+      for (int l2 = 0; l2 < cnt; ++l2) {
+        const int32_t x = __builtin_amdgcn_readlane(v[u2], l2);
+#pragma unroll
+        for (int u = 0; u < R; ++u) rk[u] += x < v[u] ? 1 : 0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (tid + u * BLOCK < q) a[rk[u]] = v[u];
+    bar();
+  } else {
+    int N2 = 1;
+    while (N2 < q) N2 <<= 1;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int i = tid + u * BLOCK;
+      if (i < N2) a[i] = i < q ? v[u] : 0x7FFFFFFF;
+    }
+    bar();
+    // ids are non-negative and the padding is the largest int32, so their
+    // order as uint32 is the same; the stages within 64 elements run in
+    // registers (8 barriers for 512 ids instead of 45), and the barriers
+    // order LDS only, so the gathers above stay in flight
+    bitonic_sort<uint32_t, true>(reinterpret_cast<uint32_t *>(a), N2);
+#pragma unroll
+    for (int u = 0; u < R; ++u) rk[u] = tid + u * BLOCK < q ? lds_lower_bound(a, q, v[u]) : 0;
+  }
+  // 2. every member's fields at its local number: its kept entries in row
+  // order (slot 0, then slot 1), neighbours as local numbers
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    if (tid + u * BLOCK >= q) continue;
+    const int r = rk[u];
+    // slot 0: the first kept entry (entry 0, else entry 1); slot 1: entry 1
+    // when both are kept (selects, no indexed arrays)
+    const bool k0 = kb[u] & 1u, k1 = (kb[u] & 2u) != 0u;
+    const bool s0 = k0 || k1, s1 = k0 && k1;
+    const uint32_t sw = (uint32_t)Bq[u].w;
+    const int32_t e0 = k0 ? A[u].w : A[u].w + 1, n0 = k0 ? A[u].y : A[u].z;
+    const uint32_t es0 = k0 ? (sw & 0xFFu) : ((sw >> 8) & 0xFFu);
+    const uint32_t eo0 = (uint32_t)(k0 ? Bq[u].y : Bq[u].z);
+    const uint32_t ep0 = (uint32_t)(k0 ? Cq[u].x : Cq[u].y);
+    w.nb[2 * r] = s0 ? lds_lower_bound(a, q, n0) : -1;
+    w.eid[2 * r] = s0 ? e0 : -1;
+    w.es[2 * r] = (uint8_t)(s0 ? es0 : 0u);
+    w.eo[2 * r] = s0 ? eo0 : 0u;
+    w.ep[2 * r] = s0 ? ep0 : 0u;
+    w.nb[2 * r + 1] = s1 ? lds_lower_bound(a, q, A[u].z) : -1;
+    w.eid[2 * r + 1] = s1 ? A[u].w + 1 : -1;
+    w.es[2 * r + 1] = (uint8_t)(s1 ? (sw >> 8) & 0xFFu : 0u);
+    w.eo[2 * r + 1] = s1 ? (uint32_t)Bq[u].z : 0u;
+    w.ep[2 * r + 1] = s1 ? (uint32_t)Cq[u].y : 0u;
+    w.vid[r] = v[u];
+    w.rlen[r] = (uint32_t)Bq[u].x;
+    w.roff[r] = ro[u];
+  }
+  bar();
+  // 3. perm and the local CSR rows, in local order
+  CG_GLOBAL int32_t *perm = (CG_GLOBAL int32_t *)local.perm;
+  CG_GLOBAL int32_t *lrp = (CG_GLOBAL int32_t *)local.loc_row_ptr;
+  CG_GLOBAL int32_t *lcol = (CG_GLOBAL int32_t *)local.loc_col;
+  CG_GLOBAL int32_t *leid = (CG_GLOBAL int32_t *)local.loc_eid;
+  int32_t carry = 0;
+  int first = 0x7FFFFFFF;  // the thread's first read with one neighbour
+  for (int base = 0; base < q; base += BLOCK) {
+    const int i = base + tid;
+    int32_t n0 = -1, n1 = -1;
+    if (i < q) {
+      n0 = w.nb[2 * i];
+      n1 = w.nb[2 * i + 1];
+      if (n0 >= 0 && n1 < 0 && i < first) first = i;
+    }
+    const int32_t deg = (n0 >= 0 ? 1 : 0) + (n1 >= 0 ? 1 : 0);
+    int32_t tot;
+    const int32_t ex = block_excl_scan<int32_t, BLOCK, true>(deg, (int32_t *)sh_scan, &tot);
+    if (i < q) {
+      const int32_t r0 = estart + carry + ex;
+      perm[st + i] = a[i];
+      lrp[st + i] = r0;
+      if (n0 >= 0) {
+        lcol[r0] = st + n0;
+        leid[r0] = w.eid[2 * i];
+      }
+      if (n1 >= 0) {
+        lcol[r0 + 1] = st + n1;
+        leid[r0 + 1] = w.eid[2 * i + 1];
+      }
+    }
+    carry += tot;
+  }
+  walk_chain<BLOCK, CAP, kWalkLds>(cr, q, st, first, w, g, local.perm, out, s, sh_scan);
+}
+
+// cycles of rank below r; called by a whole wave with uniform r
+__device__ __forceinline__ int32_t cycles_before(const CycMarks &m, int32_t r) {
+  if (*m.any == 0) return 0;
+  const int32_t sp = r / kCycSuper, w = r >> 5;
+  int32_t k = 0;
+  for (int32_t i = lane_id(); i < sp; i += kWave) k += (int32_t)m.super[i];
+  for (int32_t i = sp * (kCycSuper / 32) + lane_id(); i < w; i += kWave) k += __popc(m.bits[i]);
+  if (lane_id() == 0) k += __popc(m.bits[w] & ((1u << (r & 31)) - 1u));
+  return wave_sum(k);
+}
+
+// One-read components: a lane each.
+__device__ __forceinline__ void walk_single(const cg_graph &g, const cg_parts &parts, int c, int st,
+                                            const cg_contigs &out, const Scratch &s) {
+  const CompRec cr = comp_rec(parts, c);
+  const int32_t v = cr.label;
+  const uint32_t L = g.read_len[v];
+  const uint64_t off = g.read_off[v];
+  out.layout_vid[st] = v;
+  out.layout_rev[st] = 0;
+  s.piece_len[st] = L;
+  s.piece_src[st] = piece_anchor(off, L, 0, false);
+  s.piece_off[st] = 0;
+  s.lay_contig[st] = cr.rank;
+  out.label[cr.rank] = v;
+  out.bin[cr.rank] = cr.bin;
+  out.start[cr.rank] = v;
+  out.n_reads[cr.rank] = 1;
+  out.len[cr.rank] = L;
+  out.cflags[cr.rank] = CG_CONTIG_SINGLE;
+  out.layout_off[cr.rank] = st;
+}
+
+// ---------------------------------------------------------------------------
 // Packed base copy
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t rev_fields32(uint32_t v) {

@@ -30,7 +30,8 @@ struct Fixed {
   unsigned int scan_ticket;        // look-back scan: block ticket
   unsigned int scan_done;          // look-back scan: exited blocks
   unsigned int fill_cursor;        // the whole path: member slots given out (reset per call)
-  unsigned int pad[7];
+  unsigned int n_listed;           // the whole path: components listed as large (likewise)
+  unsigned int pad[6];
 };
 
 // Items per block of the look-back scan (one item per thread).
@@ -53,7 +54,8 @@ struct Scratch {
   int32_t *aux;        // [n] partition fallback: bin of each component
   int32_t *walk;       // [16n] assemble: chain arrays of components too big for LDS
   int32_t *estart;     // [n] batched induce: first local CSR entry of each component
-  int32_t *memb;       // [n] batched components: first member slot of each component
+  int32_t *memb;       // [n] batched components: first member slot of each component (the
+                       // whole path: its large components)
   uint64_t *comp_w;    // [n] partition: bases weight of each component
   uint64_t *bin_reads; // [P] partition: reads of each bin
 };
@@ -348,8 +350,7 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
                   const int32_t *label, const cg_parts &parts, int32_t P, const cg_local &out,
                   hipStream_t st);
 int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                    uint32_t *d_status = nullptr);
+                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st);
 // The five steps in one call, with fewer launches than one step after another
 // (launch_path in k_partition.hip).  d_status, if given, gets the status word
 // at the end; reset: the context's counters and status are cleared first.
@@ -369,9 +370,11 @@ int launch_path_mask(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const Pat
                      int *parts, hipStream_t st);
 int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                           int mask_parts, hipStream_t st);
-int launch_ind_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
-                    const cg_parts &parts, const int32_t *mstart, const cg_local &out,
-                    hipStream_t st);
+int launch_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                const int32_t *mstart, hipStream_t st);
+int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
+                   const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
+                   uint32_t *d_status);
 int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuzz,
                   uint8_t *contained, uint8_t *kept, int32_t *s_row_ptr, int32_t *s_col,
                   uint32_t *s_ovl, uint8_t *s_strand, int32_t *d_m, hipStream_t st);

@@ -4,6 +4,9 @@
 // contributes the part of its walking orientation that precedes its overlap
 // with the next read (len - ovl bases), the last read all its bases.
 //
+// As a step of its own (the whole path walks in its component pass,
+// k_components.hip, and shares the last two):
+//
 //  k_asm_walk     every component by its size (a lane, a wave, a workgroup):
 //                 start read, walk order by pointer jumping over the chain's
 //                 arcs (Wyllie list ranking), orientation from the strand
@@ -16,28 +19,6 @@
 #include "cg_device.h"
 
 namespace cg {
-
-// One-read components: a lane each.
-__device__ __forceinline__ void walk_single(const cg_graph &g, const cg_parts &parts, int c, int st,
-                                            const cg_contigs &out, const Scratch &s) {
-  const CompRec cr = comp_rec(parts, c);
-  const int32_t v = cr.label;
-  const uint32_t L = g.read_len[v];
-  const uint64_t off = g.read_off[v];
-  out.layout_vid[st] = v;
-  out.layout_rev[st] = 0;
-  s.piece_len[st] = L;
-  s.piece_src[st] = piece_anchor(off, L, 0, false);
-  s.piece_off[st] = 0;
-  s.lay_contig[st] = cr.rank;
-  out.label[cr.rank] = v;
-  out.bin[cr.rank] = cr.bin;
-  out.start[cr.rank] = v;
-  out.n_reads[cr.rank] = 1;
-  out.len[cr.rank] = L;
-  out.cflags[cr.rank] = CG_CONTIG_SINGLE;
-  out.layout_off[cr.rank] = st;
-}
 
 // Components by size: a lane for one read, a wave up to kWalkSmallCap reads,
 // a workgroup up to kAsmWalkCap reads with everything in LDS, up to
@@ -214,24 +195,11 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
   }
 }
 
-int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                    uint32_t *d_status) {
-  const PhaseRange range("cg: LocalAssembly");
+// offsets and bases of the walked contigs
+int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
+                   const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
+                   uint32_t *d_status) {
   const int32_t n = g.n;
-  if (n == 0) {
-    CG_LAUNCH(ctx, k_asm_offsets, dim3(1), dim3(kScanBlock), st, parts.d_n_comp, out.len,
-                       out.base_off, out.cap_words, out.d_total_words, ctx->fixed,
-                       scan_ctx(ctx, s));
-    return hip_check(hipGetLastError(), "k_asm");
-  }
-  // workgroups for as many components above kWalkSmallCap reads as there can
-  // be, and waves for components of two reads, up to a few rounds of what is
-  // resident at once
-  const int n_big = n / (kWalkSmallCap + 1) < 2048 ? n / (kWalkSmallCap + 1) : 2048;
-  const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
-  CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
-            dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
   CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
             dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
             out.d_total_words, ctx->fixed, scan_ctx(ctx, s));
@@ -251,6 +219,26 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
                      out.len, out.base_off, out.d_total_words, out.cap_words, out.bases,
                      chunk_target, ctx->fixed, d_status);
   return hip_check(hipGetLastError(), "k_asm");
+}
+
+int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
+                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st) {
+  const PhaseRange range("cg: LocalAssembly");
+  const int32_t n = g.n;
+  if (n == 0) {
+    CG_LAUNCH(ctx, k_asm_offsets, dim3(1), dim3(kScanBlock), st, parts.d_n_comp, out.len,
+                       out.base_off, out.cap_words, out.d_total_words, ctx->fixed,
+                       scan_ctx(ctx, s));
+    return hip_check(hipGetLastError(), "k_asm");
+  }
+  // workgroups for as many components above kWalkSmallCap reads as there can
+  // be, and waves for components of two reads, up to a few rounds of what is
+  // resident at once
+  const int n_big = n / (kWalkSmallCap + 1) < 2048 ? n / (kWalkSmallCap + 1) : 2048;
+  const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
+  CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
+            dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
+  return launch_contigs(ctx, g, s, parts, local, P, out, st, nullptr);
 }
 
 }  // namespace cg

@@ -136,7 +136,6 @@ static_assert(sizeof(MaskTile) % 8 == 0, "tile descriptors are copied in 8-byte 
 constexpr int kMaskThreads = 256;
 constexpr int kMaskGroups = 2;  // groups of 4 consecutive reads per thread
 constexpr int kMaskTile = 4 * kMaskThreads * kMaskGroups;
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(kMaskThreads) void kb_mask_tiles(const MaskTile *__restrict__ tiles) {
   __shared__ int64_t sh[kMaskThreads / kWave + 1];
@@ -425,7 +424,6 @@ __device__ __forceinline__ McOut mc_out(const BJob &J) {
 // (a read without kept entries, or a job whose listed reads' state is in
 // scratch, which reuses the list's memory).  One 8-byte store.
 constexpr int32_t kNoSlot = (1 << 30) - 1;
-typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void mc_member(const McOut &O, int32_t at, int32_t v, int32_t rec) {
   *(CG_GLOBAL i32x2 *)(O.tmp + 2 * (int64_t)at) = i32x2{v, rec};
 }
@@ -1368,10 +1366,7 @@ __device__ __forceinline__ void induce_listed(const BatchDev &B, int4 d, int32_t
 // from its member record and the tile list, which gathered them in id
 // order (a record without a list slot takes them from the graph), then its
 // read length and its entries' strand bits and overlaps (or coordinates)
-// from the graph.  The local numbers follow
-// the ids; every field goes into the walk's LDS arrays at its local number
-// while perm and the local CSR rows are written out, so the walk reads
-// nothing back.
+// from the graph (iw_rows goes on from there).
 template <int BLOCK, int CAP>
 __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkArrays w,
                                              uint64_t *sh_scan) {
@@ -1449,109 +1444,8 @@ __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkAr
       if (coords) Cq[u].y = (int32_t)gpost[b + 1];
     }
   }
-  // 2. local numbers: the ids in order in a (the walk's ray array, unused
-  // until its rays), each member's rank among them
-  int32_t *a = reinterpret_cast<int32_t *>(w.ray);
-  int32_t rk[R];
-  if constexpr (BLOCK == kWave) {
-    // one wave: a rank is the number of smaller ids, counted over the lanes
-#pragma unroll
-    for (int u = 0; u < R; ++u) rk[u] = 0;
-#pragma unroll
-    for (int u2 = 0; u2 < R; ++u2) {
-      const int cnt = q - u2 * kWave < kWave ? q - u2 * kWave : kWave;
-      for (int l2 = 0; l2 < cnt; ++l2) {
-        const int32_t x = __builtin_amdgcn_readlane(v[u2], l2);
-#pragma unroll
-        for (int u = 0; u < R; ++u) rk[u] += x < v[u] ? 1 : 0;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < R; ++u)
-      if (tid + u * BLOCK < q) a[rk[u]] = v[u];
-    lds_barrier();
-  } else {
-    int N2 = 1;
-    while (N2 < q) N2 <<= 1;
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const int i = tid + u * BLOCK;
-      if (i < N2) a[i] = i < q ? v[u] : 0x7FFFFFFF;
-    }
-    lds_barrier();
-    // ids are non-negative and the padding is the largest int32, so their
-    // order as uint32 is the same; the stages within 64 elements run in
-    // registers (8 barriers for 512 ids instead of 45), and the barriers
-    // order LDS only, so the gathers above stay in flight
-    bitonic_sort<uint32_t, true>(reinterpret_cast<uint32_t *>(a), N2);
-#pragma unroll
-    for (int u = 0; u < R; ++u) rk[u] = tid + u * BLOCK < q ? lds_lower_bound(a, q, v[u]) : 0;
-  }
-  // 3. every member's fields at its local number: its kept entries in row
-  // order (slot 0, then slot 1), neighbours as local numbers
-#pragma unroll
-  for (int u = 0; u < R; ++u) {
-    if (tid + u * BLOCK >= q) continue;
-    const int r = rk[u];
-    // slot 0: the first kept entry (entry 0, else entry 1); slot 1: entry 1
-    // when both are kept (selects, no indexed arrays)
-    const bool k0 = kb[u] & 1u, k1 = (kb[u] & 2u) != 0u;
-    const bool s0 = k0 || k1, s1 = k0 && k1;
-    const uint32_t sw = (uint32_t)Bq[u].w;
-    const int32_t e0 = k0 ? A[u].w : A[u].w + 1, n0 = k0 ? A[u].y : A[u].z;
-    const uint32_t es0 = k0 ? (sw & 0xFFu) : ((sw >> 8) & 0xFFu);
-    const uint32_t eo0 = (uint32_t)(k0 ? Bq[u].y : Bq[u].z);
-    const uint32_t ep0 = (uint32_t)(k0 ? Cq[u].x : Cq[u].y);
-    w.nb[2 * r] = s0 ? lds_lower_bound(a, q, n0) : -1;
-    w.eid[2 * r] = s0 ? e0 : -1;
-    w.es[2 * r] = (uint8_t)(s0 ? es0 : 0u);
-    w.eo[2 * r] = s0 ? eo0 : 0u;
-    w.ep[2 * r] = s0 ? ep0 : 0u;
-    w.nb[2 * r + 1] = s1 ? lds_lower_bound(a, q, A[u].z) : -1;
-    w.eid[2 * r + 1] = s1 ? A[u].w + 1 : -1;
-    w.es[2 * r + 1] = (uint8_t)(s1 ? (sw >> 8) & 0xFFu : 0u);
-    w.eo[2 * r + 1] = s1 ? (uint32_t)Bq[u].z : 0u;
-    w.ep[2 * r + 1] = s1 ? (uint32_t)Cq[u].y : 0u;
-    w.vid[r] = v[u];
-    w.rlen[r] = (uint32_t)Bq[u].x;
-    w.roff[r] = ro[u];
-  }
-  lds_barrier();
-  // 4. perm and the local CSR rows, in local order
-  CG_GLOBAL int32_t *perm = (CG_GLOBAL int32_t *)J.local.perm;
-  CG_GLOBAL int32_t *lrp = (CG_GLOBAL int32_t *)J.local.loc_row_ptr;
-  CG_GLOBAL int32_t *lcol = (CG_GLOBAL int32_t *)J.local.loc_col;
-  CG_GLOBAL int32_t *leid = (CG_GLOBAL int32_t *)J.local.loc_eid;
-  const int32_t estart = e.estart;
-  int32_t carry = 0;
-  int first = 0x7FFFFFFF;  // the thread's first read with one neighbour
-  for (int base = 0; base < q; base += BLOCK) {
-    const int i = base + tid;
-    int32_t n0 = -1, n1 = -1;
-    if (i < q) {
-      n0 = w.nb[2 * i];
-      n1 = w.nb[2 * i + 1];
-      if (n0 >= 0 && n1 < 0 && i < first) first = i;
-    }
-    const int32_t deg = (n0 >= 0 ? 1 : 0) + (n1 >= 0 ? 1 : 0);
-    int32_t tot;
-    const int32_t ex = block_excl_scan<int32_t, BLOCK, true>(deg, (int32_t *)sh_scan, &tot);
-    if (i < q) {
-      const int32_t r0 = estart + carry + ex;
-      perm[st + i] = a[i];
-      lrp[st + i] = r0;
-      if (n0 >= 0) {
-        lcol[r0] = st + n0;
-        leid[r0] = w.eid[2 * i];
-      }
-      if (n1 >= 0) {
-        lcol[r0 + 1] = st + n1;
-        leid[r0 + 1] = w.eid[2 * i + 1];
-      }
-    }
-    carry += tot;
-  }
-  walk_chain<BLOCK, CAP, kWalkLds>(cr, q, st, first, w, J.g, J.local.perm, J.out, J.s, sh_scan);
+  iw_rows<BLOCK, CAP>(cr, q, st, e.estart, v, kb, A, Bq, Cq, ro, w, J.g, J.local, J.out, J.s,
+                      sh_scan);
 }
 
 // 6a. components of at most kWalkTinyCap reads (the queue's tail): one wave

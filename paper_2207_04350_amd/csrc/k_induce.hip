@@ -3,13 +3,14 @@
 // bins share one local numbering ordered by (bin, label, id): a component's
 // reads form the block [comp_start, comp_start + q), and its local CSR rows
 // the entries from comp_estart on, so one component's part of every output is
-// independent of the others':
+// independent of the others'.  As a step of its own (the whole path's
+// partition step fills the slots, k_partition.hip, and its component pass
+// does the rest, k_components.hip):
 //
 //  k_ind_init   bucket cursors, components by rank, the cycle marks cleared
 //  k_ind_fill   each read with kept entries claims a slot in its component's
 //               block; bin_vptr and n_e from the components in rank order;
 //               cycles marked by rank
-//               (in the whole path the partition step does both, k_partition.hip)
 //  k_ind_comp   sorts each component's reads by id and writes perm and the
 //               local CSR rows: lanes for one-read components, a wave up to
 //               128 reads, a workgroup above
@@ -20,17 +21,6 @@
 #include "cg_device.h"
 
 namespace cg {
-
-// cycles of rank below r; called by a whole wave with uniform r
-__device__ __forceinline__ int32_t cycles_before(const CycMarks &m, int32_t r) {
-  if (*m.any == 0) return 0;
-  const int32_t sp = r / kCycSuper, w = r >> 5;
-  int32_t k = 0;
-  for (int32_t i = lane_id(); i < sp; i += kWave) k += (int32_t)m.super[i];
-  for (int32_t i = sp * (kCycSuper / 32) + lane_id(); i < w; i += kWave) k += __popc(m.bits[i]);
-  if (lane_id() == 0) k += __popc(m.bits[w] & ((1u << (r & 31)) - 1u));
-  return wave_sum(k);
-}
 
 constexpr int kIndInitBlock = 256;
 __global__ __launch_bounds__(kIndInitBlock) void k_ind_init(
@@ -221,9 +211,8 @@ constexpr int kIndCompWaves = kIndCompBlock / kWave;
 static_assert(kIndCompWaves * 4 * kIndWaveCap <= kIndCompCap, "the waves' LDS fits the sort's");
 __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const uint8_t *__restrict__ flags, cg_parts parts, const int32_t *__restrict__ mstart,
-    const int32_t *__restrict__ tmp, int32_t *__restrict__ lidx, CycMarks cyc, cg_local out,
-    int n_big) {
+    const uint8_t *__restrict__ flags, cg_parts parts, const int32_t *__restrict__ tmp,
+    int32_t *__restrict__ lidx, CycMarks cyc, cg_local out, int n_big) {
   __shared__ int32_t a[kIndCompCap];
   __shared__ int32_t sh_scan[kIndCompBlock / kWave + 1];
   __shared__ int s_n;
@@ -242,7 +231,7 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
         const int32_t x = s_list[i];
         const int32_t q = parts.comp_size[x], st = parts.comp_start[x], r = parts.comp_rank[x];
         const int32_t es = 2 * (st - r + cycles_before(cyc, r));
-        induce_component<kIndCompBlock, kIndCompCap>(q, st, es, tmp + mstart[x], flags, row_ptr, col,
+        induce_component<kIndCompBlock, kIndCompCap>(q, st, es, tmp + st, flags, row_ptr, col,
                                                      out.perm, lidx, out.loc_row_ptr, out.loc_col,
                                                      out.loc_eid, a, sh_scan);
         if (threadIdx.x == 0 && r == nc - 1) {
@@ -266,7 +255,7 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     const bool live = lane_id() < run && c < nc;
     const int32_t q = live ? parts.comp_size[c] : 0;
     const int32_t st = live ? parts.comp_start[c] : 0, r = live ? parts.comp_rank[c] : 0;
-    const int32_t lab = live ? parts.comp_label[c] : 0, ms = live ? mstart[c] : 0;
+    const int32_t lab = live ? parts.comp_label[c] : 0;
     const bool cycles = *cyc.any != 0;
     int32_t es = 2 * (st - r);
     if (cycles)
@@ -286,26 +275,10 @@ __global__ __launch_bounds__(kIndCompBlock, 8) void k_ind_comp(
     for (uint64_t todo = __ballot(q > 1 && q <= kIndWaveCap); todo; todo &= todo - 1) {
       const int t = (int)__builtin_ctzll(todo);
       const int tq = __builtin_amdgcn_readlane(q, t), tst = __builtin_amdgcn_readlane(st, t);
-      ind_wave(tq, tst, __builtin_amdgcn_readlane(es, t), tmp + __builtin_amdgcn_readlane(ms, t),
-               flags, row_ptr, col, a + wv * 4 * kIndWaveCap, out);
+      ind_wave(tq, tst, __builtin_amdgcn_readlane(es, t), tmp + tst, flags, row_ptr, col,
+               a + wv * 4 * kIndWaveCap, out);
     }
   }
-}
-
-// mstart: first member slot of each component
-int launch_ind_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
-                    const cg_parts &parts, const int32_t *mstart, const cg_local &out,
-                    hipStream_t st) {
-  // workgroups: as many as can hold a component above kIndWaveCap reads,
-  // up to one per compute unit; waves for components of two reads, up to
-  // what is resident at once
-  const int32_t n = g.n;
-  const int n_big = n / (kIndWaveCap + 1) < 256 ? n / (kIndWaveCap + 1) : 256;
-  const int64_t nw = ((int64_t)n / 2 + kIndCompWaves) / kIndCompWaves;
-  CG_LAUNCH(ctx, k_ind_comp, dim3((unsigned)(n_big + (nw < 512 ? nw : 512))),
-            dim3(kIndCompBlock), st, g.row_ptr, g.col, flags, parts, mstart, s.tmp, s.lidx,
-            cyc_marks(s.estart, n), out, n_big);
-  return hip_check(hipGetLastError(), "k_ind_comp");
 }
 
 int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
@@ -322,7 +295,14 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
     const int64_t per = (int64_t)kFillBlock * kFillPer;
     CG_LAUNCH(ctx, k_ind_fill, dim3((unsigned)((n + per - 1) / per)), dim3(kFillBlock), st, n, P,
               flags, label, parts, s.fill, s.aux, cyc, s.tmp, out.bin_vptr, out.d_sizes);
-    return launch_ind_comp(ctx, g, s, flags, parts, parts.comp_start, out, st);
+    // workgroups: as many as can hold a component above kIndWaveCap reads,
+    // up to one per compute unit; waves for components of two reads, up to
+    // what is resident at once
+    const int n_big = n / (kIndWaveCap + 1) < 256 ? n / (kIndWaveCap + 1) : 256;
+    const int64_t nw = ((int64_t)n / 2 + kIndCompWaves) / kIndCompWaves;
+    CG_LAUNCH(ctx, k_ind_comp, dim3((unsigned)(n_big + (nw < 512 ? nw : 512))),
+              dim3(kIndCompBlock), st, g.row_ptr, g.col, flags, parts, s.tmp, s.lidx, cyc, out,
+              n_big);
   }
   return hip_check(hipGetLastError(), "k_ind");
 }

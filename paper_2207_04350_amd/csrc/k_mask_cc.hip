@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *_
     for (int64_t i = t; i < pi.zero_words; i += stride) pi.zero[i] = 0;
     for (int64_t i = t; i < pi.n_status; i += stride) pi.scan_status[i] = 0;
     if (t == 0) {
-      fx->fill_cursor = 0;
+      fx->fill_cursor = fx->n_listed = 0;
       if (pi.reset) {
         fx->mask_ticket = 0;
         fx->status = 0;

@@ -194,15 +194,20 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
 // Two consecutive reads per thread and round.  (A single-pass look-back scan
 // in this place waited for its tickets, its predecessors and a release per
 // workgroup: 29 us on the 1 Gbp graph, 7 us on a graph of one workgroup.)
-// mstart, if given: the first member slot of each component, taken from the
-// cursor a round's components at a time, in any order.
+// mo.start, if given: the first member slot of each component, taken from the
+// cursor a round's components at a time, in any order, and the list of the
+// components above kWalkSmallCap reads, likewise.
+struct MemberOut {
+  int32_t *start, *list;
+  Fixed *fx;
+};
 __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
     int32_t n, int rounds, const uint32_t *__restrict__ chunks, const uint8_t *__restrict__ flags,
     int32_t *label_comp, int32_t min_reads, int32_t *__restrict__ comp_label,
     int32_t *__restrict__ comp_size, uint8_t *__restrict__ comp_kind,
-    int32_t *__restrict__ d_n_comp, int32_t *__restrict__ mstart, unsigned int *cursor) {
+    int32_t *__restrict__ d_n_comp, MemberOut mo) {
   __shared__ unsigned long long sh[kChunkBlock / kWave + 1];
-  __shared__ uint32_t s_before, s_slot;
+  __shared__ uint32_t s_before, s_slot, s_large, s_list;
   __shared__ uint32_t sh32[kChunkBlock / kWave];
   const int64_t base0 = (int64_t)blockIdx.x * rounds * kChunkRound;
   static_assert(kChunks <= kChunkBlock, "a chunk per thread");
@@ -218,7 +223,10 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
   };
   load(base0);
   before = chunk_sum(before, sh32);
-  if (threadIdx.x == 0) s_before = before;
+  if (threadIdx.x == 0) {
+    s_before = before;
+    s_large = 0;
+  }
   __syncthreads();
   before = s_before;
   for (int r = 0; r < rounds; ++r) {
@@ -228,19 +236,24 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
     // (components << 32) | their reads, each below 2^31
     unsigned long long x = 0;
     bool el[kChunkPer];
+    uint32_t large[kChunkPer];
 #pragma unroll
     for (int k = 0; k < kChunkPer; ++k) {
+      large[k] = 0;
       el[k] = c[k] > 0 && eligible(f[k], c[k] >> 2, min_reads);
       x += el[k] ? 1ull << 32 | (c[k] >> 2) : 0ull;
+      if (mo.start && el[k] && c[k] >> 2 > (uint32_t)kWalkSmallCap) large[k] = 1 + atomicAdd(&s_large, 1u);
     }
     unsigned long long tot;
     const unsigned long long ex = block_excl_scan<unsigned long long, kChunkBlock>(x, sh, &tot);
-    if (mstart) {
-      if (threadIdx.x == 0 && (uint32_t)tot) s_slot = atomicAdd(cursor, (uint32_t)tot);
+    if (mo.start) {
+      // (the scan's barriers lie between the counts and these)
+      if (threadIdx.x == 0 && (uint32_t)tot) s_slot = atomicAdd(&mo.fx->fill_cursor, (uint32_t)tot);
+      if (threadIdx.x == kWave && s_large) s_list = atomicAdd(&mo.fx->n_listed, s_large);
       __syncthreads();
     }
     uint32_t at = before + (uint32_t)(ex >> 32);
-    uint32_t slot = mstart ? s_slot + (uint32_t)ex : 0u;
+    uint32_t slot = mo.start ? s_slot + (uint32_t)ex : 0u;
 #pragma unroll
     for (int k = 0; k < kChunkPer; ++k) {
       const int64_t v = base + (int64_t)threadIdx.x * kChunkPer + k;
@@ -250,7 +263,8 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
         comp_label[at] = (int32_t)v;
         comp_size[at] = (int32_t)q;
         comp_kind[at] = q == 1 ? CG_KIND_SINGLE : ((c[k] & 3u) ? CG_KIND_PATH : CG_KIND_CYCLE);
-        if (mstart) mstart[at] = (int32_t)slot;
+        if (mo.start) mo.start[at] = (int32_t)slot;
+        if (large[k]) mo.list[s_list + large[k] - 1] = (int32_t)at;
         label_comp[v] = (int32_t)at;
         ++at;
         slot += q;
@@ -259,7 +273,11 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
       }
     }
     before += (uint32_t)(tot >> 32);
-    if (mstart) __syncthreads();  // the slot is read before the next round's
+    if (mo.start && rounds > 1) {  // the places are read before the next round's
+      __syncthreads();
+      if (threadIdx.x == 0) s_large = 0;
+      __syncthreads();
+    }
   }
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *d_n_comp = (int32_t)before;
 }
@@ -522,9 +540,9 @@ static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const i
 }
 
 // the eligible components (counts in label_comp, chunk sums unless the flags
-// decide), with member slots if mstart is given
+// decide), with member slots and the large ones' list if wanted
 static void launch_compact(cg_ctx *ctx, const cg_graph &g, uint32_t *chunks, const uint8_t *flags,
-                           int32_t min_reads, const cg_parts &out, int32_t *mstart,
+                           int32_t min_reads, const cg_parts &out, const MemberOut &mo,
                            hipStream_t st) {
   const int32_t n = g.n;
   const int rounds = chunk_rounds(n);
@@ -534,7 +552,7 @@ static void launch_compact(cg_ctx *ctx, const cg_graph &g, uint32_t *chunks, con
               min_reads, chunks);
   CG_LAUNCH(ctx, k_part_compact, grid, dim3(kChunkBlock), st, n, rounds, chunks, flags,
             out.label_comp, min_reads, out.comp_label, out.comp_size, out.comp_kind, out.d_n_comp,
-            mstart, &ctx->fixed->fill_cursor);
+            mo);
 }
 
 int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_t *flags,
@@ -551,7 +569,7 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
               chunk_rounds(n), flags, const_cast<int32_t *>(label), out.label_comp, min_reads,
               min_reads <= 2 ? chunks : nullptr, CountExtra{});
   }
-  launch_compact(ctx, g, chunks, flags, min_reads, out, nullptr, st);
+  launch_compact(ctx, g, chunks, flags, min_reads, out, MemberOut{}, st);
   launch_lpt(ctx, g, s, label, P, min_reads, weight, out, RankOut{}, FillArgs{}, st);
   return hip_check(hipGetLastError(), "k_part");
 }
@@ -566,7 +584,8 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
             chunk_rounds(n), a.flags, a.label, a.parts.label_comp, min_reads,
             min_reads <= 2 ? chunks : nullptr,
             (CountExtra{s.lidx, ctx->fixed, mask_parts, a.d_counts}));
-  launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts, mstart, st);
+  launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts,
+                 MemberOut{mstart, s.memb, ctx->fixed}, st);
   const RankOut ro{a.local.bin_vptr, a.local.d_sizes, a.local.loc_row_ptr, a.parts.comp_kind,
                    cyc_marks(s.estart, n)};
   const FillArgs fa{n, a.flags, a.label, a.parts.label_comp, mstart, s.lidx, s.tmp};
@@ -574,10 +593,11 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
   return hip_check(hipGetLastError(), "k_part");
 }
 
-// The five steps together: ten launches (twelve with bases weights or every
+// The five steps together: eight launches (ten with bases weights or every
 // read wanted) where the steps one by one take fifteen to eighteen.  The mask
 // pass sets up the component forest and the counters, the count finishes the
-// labels and gives out the member slots, and the LPT's launch fills them.
+// labels and gives out the member slots, the LPT's launch fills them, and one
+// pass over the components induces and walks.
 int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                 hipStream_t st) {
   int parts = 0;
@@ -589,13 +609,11 @@ int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs
   } else {
     rc = launch_path_mask(ctx, g, s, a, &parts, st);
     if (!rc) rc = launch_path_partition(ctx, g, s, a, parts, st);
-    if (!rc) {
-      const PhaseRange range("cg: InducedSubgraph");
-      rc = launch_ind_comp(ctx, g, s, a.flags, a.parts, reinterpret_cast<int32_t *>(s.fill),
-                           a.local, st);
-    }
+    if (!rc) rc = launch_comp(ctx, g, s, a, reinterpret_cast<int32_t *>(s.fill), st);
+    if (!rc) rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.d_status);
+    return rc;
   }
-  if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.d_status);
+  if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st);
   return rc;
 }
 
