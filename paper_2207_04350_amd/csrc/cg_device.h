@@ -613,7 +613,10 @@ __device__ __forceinline__ uint32_t lpt_merge_lanes(uint32_t x, int l, int c) {
 // (nc up to 8 BLOCK).
 // s_cnt: LDS for the radix sorts, 256 words per wave.
 // comp_rank null: the (bin, label) order is left to a later pass, and bin_of
-// is comp_bin itself.
+// is comp_bin itself.  multi >= 0 (kBig, weights are read counts): the
+// compaction has written the keys of the multi components of more than one
+// read from `unsorted` on and those of the others, which come last in LPT
+// order, from keys + multi on.
 template <int BLOCK, bool kBig>
 __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict__ comp_size,
                                         const uint64_t *__restrict__ weight,
@@ -627,7 +630,8 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
                                         unsigned int *status,
                                         const uint8_t *__restrict__ comp_kind = nullptr,
                                         int32_t *__restrict__ comp_estart = nullptr,
-                                        const RankOut &ro = RankOut{}) {
+                                        const RankOut &ro = RankOut{}, int multi = -1,
+                                        uint64_t *unsorted = nullptr) {
   static_assert(BLOCK > 2 * kWave, "the pipelined windows' merge needs threads beyond two waves");
   __shared__ uint64_t win[2][kWave];  // a window's raised keys, alternating buffers
   __shared__ int32_t s_opbin[kWave];                 // rounds taken at once: their bins in order,
@@ -650,7 +654,16 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   constexpr int kPer = 8;
   uint32_t *keys32 = reinterpret_cast<uint32_t *>(keys);
   uint32_t wt8[kPer], wmax = 0;
-  for (int base = 0; base < nc; base += kPer * BLOCK) {
+  if constexpr (kBig) {
+    if (multi >= 0) {
+      if (multi < nc) wmax = 1;
+      for (int i = tid; i < multi; i += BLOCK) {
+        const uint32_t w = 0xFFFFFFFFu - (uint32_t)(unsorted[i] >> 32);
+        wmax = w > wmax ? w : wmax;
+      }
+    }
+  }
+  for (int base = 0; base < nc && (!kBig || multi < 0); base += kPer * BLOCK) {
     if (weight) {
       uint64_t w[kPer];
 #pragma unroll
@@ -711,10 +724,23 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     return nc <= kRadixRounds * BLOCK && (BLOCK >= 1024 || (passes == 1 && nc > 2 * BLOCK));
   };
   const uint32_t *srt = keys32;
-  if constexpr (kBig)
-    keys = radix_sort_hi32<BLOCK>(keys, keys + nc, nc, value_bytes(s_wmax), s_cnt,
-                                  reinterpret_cast<uint32_t *>(sh_scan));
-  else if (k32 && radix(s_wmax < 256u ? 1 : 2))
+  if constexpr (kBig) {
+    const int passes = value_bytes(s_wmax);
+    if (multi < 0) {
+      keys = radix_sort_hi32<BLOCK>(keys, keys + nc, nc, passes, s_cnt,
+                                    reinterpret_cast<uint32_t *>(sh_scan));
+    } else {
+      // from and to `unsorted` in turn, so that the last pass ends in keys
+      uint64_t *from = unsorted, *to = keys;
+      if (passes % 2 == 0) {
+        for (int i = tid; i < multi; i += BLOCK) keys[i] = unsorted[i];
+        __syncthreads();
+        from = keys;
+        to = unsorted;
+      }
+      radix_sort_hi32<BLOCK>(from, to, multi, passes, s_cnt, reinterpret_cast<uint32_t *>(sh_scan));
+    }
+  } else if (k32 && radix(s_wmax < 256u ? 1 : 2))
     srt = radix_sort_hi16<BLOCK>(keys32, keys32 + N2, nc, s_wmax < 256u ? 1 : 2, s_cnt,
                                  reinterpret_cast<uint32_t *>(sh_scan));
   else if (k32)

@@ -31,7 +31,8 @@ struct Fixed {
   unsigned int scan_done;          // look-back scan: exited blocks
   unsigned int fill_cursor;        // the whole path: member slots given out (reset per call)
   unsigned int n_listed;           // the whole path: components listed as large (likewise)
-  unsigned int pad[6];
+  unsigned int n_multi;            // partition: eligible components of more than one read
+  unsigned int pad[5];
 };
 
 // Items per block of the look-back scan (one item per thread).

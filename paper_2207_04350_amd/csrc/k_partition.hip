@@ -80,12 +80,12 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
                                                             const uint8_t *__restrict__ flags,
                                                             int32_t *label, int32_t *cnt,
                                                             int32_t min_reads,
-                                                            uint32_t *__restrict__ chunks,
+                                                            uint2 *__restrict__ chunks,
                                                             CountExtra ex) {
   __shared__ int32_t s_key[kCountSlots];
   __shared__ uint32_t s_cnt[kCountSlots];
   __shared__ uint32_t sh[kChunkBlock / kWave];
-  uint32_t elig = 0;
+  uint32_t elig = 0, multi = 0;
   for (int r = 0; r < rounds; ++r) {
     const int64_t base = ((int64_t)blockIdx.x * rounds + r) * kChunkRound;
     if (base >= n) break;
@@ -130,7 +130,10 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
 #pragma unroll
     for (int k = 0; k < kChunkPer; ++k) {
       h[k] = -1;
-      if (root[k] == v[k] && eligible(f[k], 2, min_reads)) ++elig;
+      if (root[k] == v[k] && eligible(f[k], 2, min_reads)) {
+        ++elig;
+        multi += (f[k] & 6u) ? 1u : 0u;
+      }
       if (!(f[k] & 6u)) continue;
       uint32_t i = ((uint32_t)root[k] * 2654435761u) >> 16 & (kCountSlots - 1);
       while (true) {  // ends: the table is at most half full
@@ -155,7 +158,9 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
     }
   }
   elig = chunk_sum(elig, sh);
-  if (chunks && threadIdx.x == 0) chunks[blockIdx.x] = elig;
+  __syncthreads();
+  multi = chunk_sum(multi, sh);
+  if (chunks && threadIdx.x == 0) chunks[blockIdx.x] = make_uint2(elig, multi);
   if constexpr (kFind) {
     // the last workgroup adds up the mask pass's counts
     static_assert(kMaskMaxBlocks <= kChunkBlock, "a part per thread");
@@ -177,7 +182,7 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
                                                              const uint8_t *__restrict__ flags,
                                                              const int32_t *__restrict__ cnt,
                                                              int32_t min_reads,
-                                                             uint32_t *__restrict__ chunks) {
+                                                             uint2 *__restrict__ chunks) {
   __shared__ uint32_t sh[kChunkBlock / kWave];
   uint32_t elig = 0;
   const int64_t base = (int64_t)blockIdx.x * rounds * kChunkRound;
@@ -188,7 +193,7 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
     if (c > 0 && eligible(flags[v], c >> 2, min_reads)) ++elig;
   }
   elig = chunk_sum(elig, sh);
-  if (threadIdx.x == 0) chunks[blockIdx.x] = elig;
+  if (threadIdx.x == 0) chunks[blockIdx.x] = make_uint2(elig, elig);
 }
 
 // Two consecutive reads per thread and round.  (A single-pass look-back scan
@@ -197,21 +202,25 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
 // mo.start, if given: the first member slot of each component, taken from the
 // cursor a round's components at a time, in any order, and the list of the
 // components above kWalkSmallCap reads, likewise.
+// keys, if given: the LPT's keys by read count, those of the components of more
+// than one read from keys[0] on, the others' from keys[n] on.
 struct MemberOut {
   int32_t *start, *list;
   Fixed *fx;
+  uint64_t *keys;
 };
 __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
-    int32_t n, int rounds, const uint32_t *__restrict__ chunks, const uint8_t *__restrict__ flags,
+    int32_t n, int rounds, const uint2 *__restrict__ chunks, const uint8_t *__restrict__ flags,
     int32_t *label_comp, int32_t min_reads, int32_t *__restrict__ comp_label,
     int32_t *__restrict__ comp_size, uint8_t *__restrict__ comp_kind,
     int32_t *__restrict__ d_n_comp, MemberOut mo) {
   __shared__ unsigned long long sh[kChunkBlock / kWave + 1];
-  __shared__ uint32_t s_before, s_slot, s_large, s_list;
-  __shared__ uint32_t sh32[kChunkBlock / kWave];
+  __shared__ uint32_t s_before, s_before2, s_slot, s_large, s_list;
+  __shared__ uint32_t sh32[kChunkBlock / kWave], sh32b[kChunkBlock / kWave + 1];
   const int64_t base0 = (int64_t)blockIdx.x * rounds * kChunkRound;
   static_assert(kChunks <= kChunkBlock, "a chunk per thread");
-  uint32_t before = threadIdx.x < blockIdx.x ? chunks[threadIdx.x] : 0u;
+  const uint2 ch = threadIdx.x < blockIdx.x ? chunks[threadIdx.x] : make_uint2(0, 0);
+  uint32_t before = ch.x, before2 = ch.y;
   uint32_t c[kChunkPer], f[kChunkPer];
   auto load = [&](int64_t base) {
 #pragma unroll
@@ -223,12 +232,18 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
   };
   load(base0);
   before = chunk_sum(before, sh32);
+  if (mo.keys) {
+    __syncthreads();
+    before2 = chunk_sum(before2, sh32);
+  }
   if (threadIdx.x == 0) {
     s_before = before;
+    s_before2 = before2;
     s_large = 0;
   }
   __syncthreads();
   before = s_before;
+  before2 = s_before2;
   for (int r = 0; r < rounds; ++r) {
     const int64_t base = base0 + (int64_t)r * kChunkRound;
     if (base >= n) break;
@@ -252,6 +267,14 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
       if (threadIdx.x == kWave && s_large) s_list = atomicAdd(&mo.fx->n_listed, s_large);
       __syncthreads();
     }
+    uint32_t at2 = before2;
+    if (mo.keys) {
+      uint32_t y = 0, tot2;
+#pragma unroll
+      for (int k = 0; k < kChunkPer; ++k) y += el[k] && c[k] >> 2 > 1u ? 1u : 0u;
+      at2 += block_excl_scan<uint32_t, kChunkBlock>(y, sh32b, &tot2);
+      before2 += tot2;
+    }
     uint32_t at = before + (uint32_t)(ex >> 32);
     uint32_t slot = mo.start ? s_slot + (uint32_t)ex : 0u;
 #pragma unroll
@@ -266,6 +289,11 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
         if (mo.start) mo.start[at] = (int32_t)slot;
         if (large[k]) mo.list[s_list + large[k] - 1] = (int32_t)at;
         label_comp[v] = (int32_t)at;
+        if (mo.keys) {
+          const uint64_t key = (uint64_t)(0xFFFFFFFFu - q) << 32 | at;
+          if (q > 1) mo.keys[at2++] = key;
+          else mo.keys[(int64_t)n + (at - at2)] = key;
+        }
         ++at;
         slot += q;
       } else {
@@ -279,7 +307,10 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
       __syncthreads();
     }
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *d_n_comp = (int32_t)before;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    *d_n_comp = (int32_t)before;
+    if (mo.keys) mo.fx->n_multi = before2;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -340,8 +371,9 @@ __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t
                                                         int32_t *__restrict__ comp_start,
                                                         uint64_t *__restrict__ bin_load,
                                                         uint64_t *g_keys, int32_t *g_bin,
-                                                        uint64_t *g_bins, int later, RankOut ro,
-                                                        FillArgs fa) {
+                                                        uint64_t *g_bins, int later,
+                                                        const unsigned int *n_multi, int32_t n,
+                                                        RankOut ro, FillArgs fa) {
   __shared__ uint64_t s_keys[kSortCapLds];
   __shared__ int32_t s_bin[kSortCapLds];
   __shared__ uint64_t s_binA[kBinCapLds], s_binB[kBinCapLds];
@@ -354,15 +386,18 @@ __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t
   const int nc = *d_n_comp;
   int32_t *rank = later ? nullptr : comp_rank;
   int32_t *bin_of = later ? comp_bin : g_bin;
+  // (the compaction has split the keys: the others' lie from key n on)
+  const int multi = n_multi ? (int)*n_multi : -1;
   if (nc <= kSortCapLds && P <= kBinCapLds && !later)
     lpt_body<kLptBlock, false>(nc, P, comp_size, weight, s_keys, s_bin, s_cnt, s_binA, s_binB,
                                comp_bin, comp_rank, comp_start, bin_load, nullptr, status, nullptr, nullptr,
                                ro);
   else
-    lpt_body<kLptBlock, true>(nc, P, comp_size, weight, g_keys, bin_of, big_cnt,
+    lpt_body<kLptBlock, true>(nc, P, comp_size, weight, multi < 0 ? g_keys : g_keys + (n - multi),
+                              bin_of, big_cnt,
                               P <= kBinCapLds ? s_binA : g_bins,
                               P <= kBinCapLds ? s_binB : g_bins + P, comp_bin, rank, comp_start,
-                              bin_load, nullptr, status, nullptr, nullptr, ro);
+                              bin_load, nullptr, status, nullptr, nullptr, ro, multi, g_keys);
 }
 
 // ---------------------------------------------------------------------------
@@ -504,6 +539,11 @@ __global__ __launch_bounds__(kPlaceBlock) void k_part_place(int32_t P, int32_t c
   }
 }
 
+// Whether the (bin, label) order is left to k_part_hist and k_part_place
+static bool place_later(int32_t n, int32_t P, int32_t min_reads) {
+  return min_reads <= 1 && n > kSortCapLds && P <= kBinCapLds;
+}
+
 // bases weights (if wanted), the LPT, and the order of many components; fa.n > 0:
 // with the members' slots filled meanwhile
 static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const int32_t *label,
@@ -520,14 +560,15 @@ static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const i
   // one-read components are most of a graph's, so where they are wanted of
   // more reads than the LDS sort holds, the order is left to the passes below
   // (two launches, which the few components of other graphs do not repay)
-  const bool place = min_reads <= 1 && n > kSortCapLds && P <= kBinCapLds;
+  const bool place = place_later(n, P, min_reads);
   // the fill takes a compute unit per workgroup (the LPT's LDS), four reads a
   // thread where that leaves some
   const int64_t fill = ((int64_t)fa.n + 4 * kLptBlock - 1) / (4 * kLptBlock);
   CG_LAUNCH(ctx, k_part_lpt, dim3((unsigned)(1 + (fill < 255 ? fill : 255))), dim3(kLptBlock), st,
             P, out.d_n_comp, out.comp_size, bases ? (const uint64_t *)s.comp_w : nullptr,
             &ctx->fixed->status, out.comp_bin, out.comp_rank, out.comp_start, out.bin_load, s.keys,
-            s.aux, s.bins, place ? 1 : 0, place ? RankOut{} : ro, fa);
+            s.aux, s.bins, place ? 1 : 0, place && !bases ? &ctx->fixed->n_multi : nullptr, n,
+            place ? RankOut{} : ro, fa);
   if (place) {
     const int32_t per = (n + kPlaceChunks - 1) / kPlaceChunks;
     const int32_t chunk = per > kPlaceChunk ? per : kPlaceChunk;
@@ -541,7 +582,7 @@ static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const i
 
 // the eligible components (counts in label_comp, chunk sums unless the flags
 // decide), with member slots and the large ones' list if wanted
-static void launch_compact(cg_ctx *ctx, const cg_graph &g, uint32_t *chunks, const uint8_t *flags,
+static void launch_compact(cg_ctx *ctx, const cg_graph &g, uint2 *chunks, const uint8_t *flags,
                            int32_t min_reads, const cg_parts &out, const MemberOut &mo,
                            hipStream_t st) {
   const int32_t n = g.n;
@@ -561,7 +602,11 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
   const PhaseRange range("cg: GreedyPartitioning");
   const int32_t n = g.n;
   if (min_reads < 1) min_reads = 1;
-  uint32_t *chunks = reinterpret_cast<uint32_t *>(s.keys);  // until the LPT
+  static_assert(sizeof(uint2) <= sizeof(uint64_t), "a chunk's counts fit a read's word");
+  uint2 *chunks = reinterpret_cast<uint2 *>(s.piece_off);  // until the pieces
+  // read counts sort themselves as far as they are one
+  uint64_t *keys =
+      place_later(n, P, min_reads) && weight == CG_WEIGHT_READS ? s.keys : nullptr;
   if (n > 0) {
     CG_LAUNCH(ctx, k_part_zero, dim3((unsigned)((n + kPartBlock - 1) / kPartBlock)),
               dim3(kPartBlock), st, n, flags, out.label_comp);
@@ -569,7 +614,8 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
               chunk_rounds(n), flags, const_cast<int32_t *>(label), out.label_comp, min_reads,
               min_reads <= 2 ? chunks : nullptr, CountExtra{});
   }
-  launch_compact(ctx, g, chunks, flags, min_reads, out, MemberOut{}, st);
+  launch_compact(ctx, g, chunks, flags, min_reads, out,
+                 MemberOut{nullptr, nullptr, ctx->fixed, keys}, st);
   launch_lpt(ctx, g, s, label, P, min_reads, weight, out, RankOut{}, FillArgs{}, st);
   return hip_check(hipGetLastError(), "k_part");
 }
@@ -578,14 +624,17 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
                           int mask_parts, hipStream_t st) {
   const PhaseRange range("cg: GreedyPartitioning");
   const int32_t n = g.n, min_reads = a.min_reads < 1 ? 1 : a.min_reads;
-  uint32_t *chunks = reinterpret_cast<uint32_t *>(s.keys);  // until the LPT
+  uint2 *chunks = reinterpret_cast<uint2 *>(s.piece_off);  // until the pieces
+  // read counts sort themselves as far as they are one
+  uint64_t *keys =
+      place_later(n, a.P, min_reads) && a.weight == CG_WEIGHT_READS ? s.keys : nullptr;
   int32_t *mstart = reinterpret_cast<int32_t *>(s.fill);
   CG_LAUNCH(ctx, k_part_count<true>, dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
             chunk_rounds(n), a.flags, a.label, a.parts.label_comp, min_reads,
             min_reads <= 2 ? chunks : nullptr,
             (CountExtra{s.lidx, ctx->fixed, mask_parts, a.d_counts}));
   launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts,
-                 MemberOut{mstart, s.memb, ctx->fixed}, st);
+                 MemberOut{mstart, s.memb, ctx->fixed, keys}, st);
   const RankOut ro{a.local.bin_vptr, a.local.d_sizes, a.local.loc_row_ptr, a.parts.comp_kind,
                    cyc_marks(s.estart, n)};
   const FillArgs fa{n, a.flags, a.label, a.parts.label_comp, mstart, s.lidx, s.tmp};
