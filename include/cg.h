@@ -423,7 +423,9 @@ typedef struct cg_batch cg_batch;
  * step of Algorithm 2 for all jobs with one launch per phase; each job's
  * outputs are identical to the five single-graph calls on that job.  A job
  * with more than 32768 directed entries is run by the single-graph kernels,
- * in the same launch sequence ahead of the batched launches. */
+ * beside the batched launches: on up to three streams of the batch's own
+ * (made with its first such job, destroyed with it) that start after what the
+ * caller's stream holds and that the caller's stream waits for. */
 int cg_batch_create(cg_ctx *ctx, int32_t n_jobs, const cg_job *jobs,
                     const cg_batch_params *params, cg_batch **out);
 

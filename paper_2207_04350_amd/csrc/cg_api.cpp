@@ -450,7 +450,7 @@ int cg_contig_generation(cg_ctx *ctx, const cg_graph *g, int32_t P, int32_t min_
   if ((rc = check_ctx(ctx, g, P, &s))) return rc;
   return launch_path(ctx, *g, s,
                      PathArgs{P, min_reads, weight, flags, d_counts, label, *parts, *local,
-                              *contigs, nullptr, false}, (hipStream_t)stream);
+                              *contigs, StatusOut{}, false}, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -353,8 +353,12 @@ int launch_induce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uint8_
 int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
                     const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st);
 // The five steps in one call, with fewer launches than one step after another
-// (launch_path in k_partition.hip).  d_status, if given, gets the status word
-// at the end; reset: the context's counters and status are cleared first.
+// (launch_path in k_partition.hip).  reset: the context's counters and status
+// are cleared first.
+struct StatusOut {  // where the status word goes at the end, each if given
+  uint32_t *set;    // stored
+  uint32_t *add;    // its bits raised
+};
 struct PathArgs {
   int32_t P, min_reads, weight;
   uint8_t *flags;
@@ -362,7 +366,7 @@ struct PathArgs {
   cg_parts parts;
   cg_local local;
   cg_contigs out;
-  uint32_t *d_status;
+  StatusOut status;
   bool reset;
 };
 int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
@@ -375,7 +379,7 @@ int launch_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs
                 const int32_t *mstart, hipStream_t st);
 int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                   uint32_t *d_status);
+                   const StatusOut &so);
 int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuzz,
                   uint8_t *contained, uint8_t *kept, int32_t *s_row_ptr, int32_t *s_col,
                   uint32_t *s_ovl, uint8_t *s_strand, int32_t *d_m, hipStream_t st);

@@ -94,7 +94,7 @@ extern "C" int cg_contig_generation_noalloc(const cg_graph *g, int32_t P, int32_
   }
   rc = launch_path(&view, *g, s,
                    PathArgs{P, min_reads, weight, flags, d_counts, label, *parts, *local, *contigs,
-                            d_status, true}, st);
+                            StatusOut{d_status, nullptr}, true}, st);
   if (rc) return rc;
   if (d_status && g->n == 0) {
     hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(1), 0, st, view.fixed, d_status);

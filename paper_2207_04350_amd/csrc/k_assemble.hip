@@ -172,9 +172,12 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
                                                          uint64_t cap_words,
                                                          uint32_t *__restrict__ bases,
                                                          int32_t chunk_target,
-                                                         const Fixed *fx, uint32_t *d_status) {
+                                                         const Fixed *fx, StatusOut so) {
   // the last kernel of the path: no earlier one can still raise a bit
-  if (d_status && blockIdx.x == 0 && threadIdx.x == 0) *d_status = fx->status;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (so.set) *so.set = fx->status;
+    if (so.add && fx->status) atomicOr(so.add, fx->status);
+  }
   if (*d_total_words > cap_words) return;
   const int32_t n_e = bin_vptr[P];
   const PieceArrays A = piece_arrays(lay_contig, piece_off, piece_len, piece_src, clen, cbase);
@@ -198,7 +201,7 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
 // offsets and bases of the walked contigs
 int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
                    const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                   uint32_t *d_status) {
+                   const StatusOut &so) {
   const int32_t n = g.n;
   CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
             dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
@@ -217,7 +220,7 @@ int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_pa
   CG_LAUNCH(ctx, k_asm_copy, dim3(cgrid), dim3(kCopyBlock), st, g.seq, g.seq_words,
                      local.bin_vptr, P, s.piece_off, s.piece_len, s.piece_src, s.lay_contig,
                      out.len, out.base_off, out.d_total_words, out.cap_words, out.bases,
-                     chunk_target, ctx->fixed, d_status);
+                     chunk_target, ctx->fixed, so);
   return hip_check(hipGetLastError(), "k_asm");
 }
 
@@ -238,7 +241,7 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
   const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
   CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
             dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
-  return launch_contigs(ctx, g, s, parts, local, P, out, st, nullptr);
+  return launch_contigs(ctx, g, s, parts, local, P, out, st, StatusOut{});
 }
 
 }  // namespace cg

@@ -1752,6 +1752,9 @@ __global__ void __launch_bounds__(kPackBlock) kb_pack(const BJob *jobs, int n_jo
 // ---------------------------------------------------------------------------
 using namespace cg;
 
+// the hardware runs four queues at once: the caller's stream and these
+constexpr int kSideStreams = 3;
+
 struct cg_batch {
   cg_ctx *ctx;
   int32_t n_jobs, n_vtiles;
@@ -1765,9 +1768,17 @@ struct cg_batch {
   // share late)
   int res_iw_tiny, res_iw_small, res_iw, res_walk;
   // jobs too large for one workgroup's components pass: they run through the
-  // single-graph kernels (grid-wide) ahead of the batched launches
+  // single-graph kernels (grid-wide) beside the batched launches, on streams
+  // of the batch's own between two events of the caller's stream, each with
+  // counters of its own.  One after another on one stream, three graphs of 50
+  // to 100 Mbp and a batch of thirteen took 455 us of a wave's 517: most of
+  // these kernels leave most of the chip idle.
   std::vector<cg_job> ext_jobs;
   std::vector<Scratch> ext_s;
+  std::vector<Fixed *> ext_fixed;
+  int n_side;
+  hipStream_t side[kSideStreams];
+  hipEvent_t fork, join[kSideStreams];
   cg_batch_params prm;
   BatchDev dev;
   char *mem;
@@ -1827,7 +1838,7 @@ struct Plan {
   bool any_bases = false;
   size_t o_jobs, o_tiles, o_cbase, o_pbase, o_hbase, o_jcnt, o_cjob, o_wq, o_wqh, o_wqc, o_wqm,
       o_hjob, o_counters, o_order, o_mtiles, o_mtcnt, o_ccp, total = 0;
-  std::vector<size_t> job_off;
+  std::vector<size_t> job_off, fixed_off;
 };
 
 static int check_params(cg_ctx *ctx, const cg_batch_params *params, cg_batch_params *out) {
@@ -1906,6 +1917,7 @@ static int plan_sizes(int32_t n_jobs, const cg_job *jobs, int vertex_tile, Plan 
   P->o_counters = take(sizeof(unsigned int) * 8);
   P->o_order = take(sizeof(int32_t) * n_jobs);
   P->job_off.resize(n_jobs);
+  P->fixed_off.assign(n_jobs, 0);
   P->n_internal = P->n_mt = 0;
   for (int i = 0; i < n_jobs; ++i) {
     // the components pass holds a job's reads as LDS bitmaps and its reads
@@ -1915,6 +1927,7 @@ static int plan_sizes(int32_t n_jobs, const cg_job *jobs, int vertex_tile, Plan 
     P->n_internal += ext ? 0 : 1;
     P->n_mt += ext ? 0 : (jobs[i].g.n + kMaskTile - 1) / kMaskTile;
     P->job_off[i] = take(layout(jobs[i].g.n, jobs[i].g.m, jobs[i].P).total);
+    if (ext) P->fixed_off[i] = take(sizeof(Fixed));
   }
   P->o_mtiles = take(sizeof(MaskTile) * (P->n_mt > 0 ? P->n_mt : 1));
   P->o_mtcnt = take(sizeof(int2) * (P->n_mt > 0 ? P->n_mt : 1));
@@ -1934,6 +1947,7 @@ static void plan_fill(cg_batch *b, const Plan &P, const cg_job *jobs) {
   b->h_order.resize(n_jobs);
   b->ext_jobs.clear();
   b->ext_s.clear();
+  b->ext_fixed.clear();
   int2 *d_mtcnt = (int2 *)(mem + P.o_mtcnt);
   int32_t nv = 0, n_mt = 0;
   for (int i = 0; i < n_jobs; ++i) {
@@ -1971,6 +1985,7 @@ static void plan_fill(cg_batch *b, const Plan &P, const cg_job *jobs) {
     if (h.external) {
       b->ext_jobs.push_back(J);
       b->ext_s.push_back(h.s);
+      b->ext_fixed.push_back((Fixed *)(mem + P.fixed_off[i]));
     }
   }
   for (int i = 0; i < n_jobs; ++i) b->h_order[i] = i;
@@ -2033,6 +2048,37 @@ static int plan_upload(cg_batch *b, const Plan &P, hipStream_t st) {
   return rc;
 }
 
+static void drop_side(cg_batch *b) {
+  for (int i = 0; i < b->n_side; ++i) {
+    (void)hipStreamDestroy(b->side[i]);
+    (void)hipEventDestroy(b->join[i]);
+  }
+  if (b->n_side > 0) (void)hipEventDestroy(b->fork);
+  b->n_side = 0;
+}
+
+// the batch's own streams, made at the first plan with external jobs; without
+// them (none could be made) these jobs run on the caller's stream
+static void make_side(cg_batch *b) {
+  if (b->n_side > 0 || b->ext_jobs.empty()) return;
+  int prev = 0;
+  (void)hipGetDevice(&prev);
+  (void)hipSetDevice(b->ctx->device);
+  if (hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) == hipSuccess) {
+    for (; b->n_side < kSideStreams; ++b->n_side) {
+      const int i = b->n_side;
+      if (hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking) != hipSuccess) break;
+      if (hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) != hipSuccess) {
+        (void)hipStreamDestroy(b->side[i]);
+        break;
+      }
+    }
+    if (b->n_side == 0) (void)hipEventDestroy(b->fork);
+  }
+  (void)hipGetLastError();  // (a failure above is no error of the plan's)
+  (void)hipSetDevice(prev);
+}
+
 static int batch_alloc(cg_ctx *ctx, const cg_batch_params &prm, size_t bytes, cg_batch **out) {
   cg_batch *b = new (std::nothrow) cg_batch();
   if (!b) return set_error(CG_EINVAL, "out of host memory");
@@ -2042,6 +2088,7 @@ static int batch_alloc(cg_ctx *ctx, const cg_batch_params &prm, size_t bytes, cg
   b->any_bases = false;
   b->chunk_slots = 0;
   b->mtiles = nullptr;
+  b->n_side = 0;
   b->graph = nullptr;
   b->exec = nullptr;
   b->mem = nullptr;
@@ -2080,6 +2127,48 @@ static int batch_alloc(cg_ctx *ctx, const cg_batch_params &prm, size_t bytes, cg
   return CG_OK;
 }
 
+// the launches of the jobs in the batched form
+static int run_internal(cg_batch *b, hipStream_t st) {
+  cg_ctx *ctx = b->ctx;
+  const BatchDev &B = b->dev;
+  const int T = b->prm.vertex_tile;
+  const int PB = b->prm.persist_blocks;
+  if (b->n_internal == 0) return CG_OK;
+  {
+    const PhaseRange range("cg_batch: BranchRemoval + ConnectedComponent");
+    if (B.n_mtiles > 0)
+      CG_LAUNCH(ctx, kb_mask_tiles, dim3(B.n_mtiles), dim3(kMaskThreads), st, b->mtiles);
+    CG_LAUNCH(ctx, kb_mask_cc, dim3(b->n_jobs), dim3(kMcBlock), st, B);
+  }
+  const PhaseRange range_p("cg_batch: GreedyPartitioning, InducedSubgraph, LocalAssembly");
+  if (b->any_bases) {
+    if (T == 256) CG_LAUNCH(ctx, kb_weight<256>, dim3(b->n_vtiles), dim3(256), st, B);
+    else if (T == 512) CG_LAUNCH(ctx, kb_weight<512>, dim3(b->n_vtiles), dim3(512), st, B);
+    else CG_LAUNCH(ctx, kb_weight<1024>, dim3(b->n_vtiles), dim3(1024), st, B);
+  }
+  CG_LAUNCH(ctx, kb_lpt, dim3(b->n_jobs), dim3(kBatchLptBlock), st, B);
+  CG_LAUNCH(ctx, kb_tables, dim3(256), dim3(kTablesBlock), st, B);
+  CG_LAUNCH(ctx, kb_wq_place, dim3(128), dim3(kWqBlock), st, B);
+  auto capped = [](int want, int fit) { return dim3((unsigned)(fit > 0 && fit < want ? fit : want)); };
+  // components above kIwCap reads in two passes (the induce step with the
+  // next ones, the walk after the last pass that reads the tile lists, since
+  // its arrays take their memory), the others in one
+  CG_LAUNCH(ctx, kb_induce_walk, capped(PB, b->res_iw), dim3(kWalkBlock), st, B);
+  CG_LAUNCH(ctx, kb_induce_walk_small, capped(4 * PB, b->res_iw_small), dim3(kWalkSmallBlock), st,
+            B);
+  CG_LAUNCH(ctx, kb_induce_walk_tiny, capped(8 * PB, b->res_iw_tiny), dim3(kWalkSmallBlock), st,
+            B);
+  CG_LAUNCH(ctx, kb_walk, capped(PB, b->res_walk), dim3(kWalkBlock), st, B);
+  CG_LAUNCH(ctx, kb_offsets, dim3(b->n_jobs), dim3(kScanBlock), st, B);
+  // one wave per copy chunk slot: the hardware hands chunks to waves as
+  // slots free up (a persistent grid with a fixed share per wave left a
+  // tail of unevenly loaded waves); slots past the batch's chunks exit
+  const int64_t wpb = b->prm.copy_block / kWave;
+  const int64_t cgrid = (b->chunk_slots + wpb - 1) / wpb;
+  CG_LAUNCH(ctx, kb_copy, dim3((unsigned)(cgrid > 0 ? cgrid : 1)), dim3(b->prm.copy_block), st, B);
+  return hip_check(hipGetLastError(), "cg_batch_run");
+}
+
 extern "C" {
 
 int cg_batch_bytes(int32_t n_jobs, const cg_job *jobs, const cg_batch_params *params,
@@ -2110,10 +2199,12 @@ int cg_batch_create(cg_ctx *ctx, int32_t n_jobs, const cg_job *jobs,
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(ctx->device);
+  make_side(b);
   rc = plan_upload(b, P, nullptr);
   if (!rc) rc = hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
   (void)hipSetDevice(prev);
   if (rc) {
+    drop_side(b);
     (void)hipFree(b->mem);
     delete b;
     return rc;
@@ -2150,6 +2241,7 @@ int cg_batch_plan(cg_batch *b, int32_t n_jobs, const cg_job *jobs, void *stream)
     b->graph = nullptr;
   }
   plan_fill(b, P, jobs);
+  make_side(b);
   return plan_upload(b, P, (hipStream_t)stream);
 }
 
@@ -2157,52 +2249,38 @@ int cg_batch_run(cg_batch *b, void *stream) {
   if (!b) return set_error(CG_EINVAL, "batch is NULL");
   if (b->n_jobs < 1) return set_error(CG_EINVAL, "batch has no jobs (cg_batch_plan)");
   hipStream_t st = (hipStream_t)stream;
-  cg_ctx *ctx = b->ctx;
-  const BatchDev &B = b->dev;
-  const int T = b->prm.vertex_tile;
-  const int PB = b->prm.persist_blocks;
-  for (size_t e = 0; e < b->ext_jobs.size(); ++e) {
+  // (per-kernel timing wants the kernels one after another)
+  const int n_ext = (int)b->ext_jobs.size();
+  const int wide = b->ctx->prof ? 0 : (n_ext < b->n_side ? n_ext : b->n_side);
+  int rc = CG_OK;
+  if (wide > 0) rc = hip_check(hipEventRecord(b->fork, st), "hipEventRecord");
+  if (rc) return rc;
+  rc = run_internal(b, st);
+  int forked = 0;
+  for (int i = 0; !rc && i < wide; ++i) {
+    rc = hip_check(hipStreamWaitEvent(b->side[i], b->fork, 0), "hipStreamWaitEvent");
+    if (!rc) ++forked;
+  }
+  for (int e = 0; !rc && e < n_ext; ++e) {
     const cg_job &J = b->ext_jobs[e];
-    const Scratch &s = b->ext_s[e];
-    const int rc = launch_path(ctx, J.g, s,
-                               PathArgs{J.P, J.min_reads, J.weight, J.flags, J.d_counts, J.label,
-                                        J.parts, J.local, J.contigs, nullptr, false}, st);
-    if (rc) return rc;
+    cg_ctx view = *b->ctx;
+    view.fixed = b->ext_fixed[e];
+    view.prof = nullptr;
+    cg_ctx *ctx = b->ctx->prof ? b->ctx : &view;
+    rc = launch_path(ctx, J.g, b->ext_s[e],
+                     PathArgs{J.P, J.min_reads, J.weight, J.flags, J.d_counts, J.label, J.parts,
+                              J.local, J.contigs,
+                              StatusOut{nullptr, ctx == &view ? &b->ctx->fixed->status : nullptr},
+                              ctx == &view},
+                     wide > 0 ? b->side[e % wide] : st);
   }
-  if (b->n_internal == 0) return hip_check(hipGetLastError(), "cg_batch_run");
-  {
-    const PhaseRange range("cg_batch: BranchRemoval + ConnectedComponent");
-    if (B.n_mtiles > 0)
-      CG_LAUNCH(ctx, kb_mask_tiles, dim3(B.n_mtiles), dim3(kMaskThreads), st, b->mtiles);
-    CG_LAUNCH(ctx, kb_mask_cc, dim3(b->n_jobs), dim3(kMcBlock), st, B);
+  // a forked stream joins whatever happened (a capture cannot end otherwise)
+  for (int i = 0; i < forked; ++i) {
+    int rj = hip_check(hipEventRecord(b->join[i], b->side[i]), "hipEventRecord");
+    if (!rj) rj = hip_check(hipStreamWaitEvent(st, b->join[i], 0), "hipStreamWaitEvent");
+    if (!rc) rc = rj;
   }
-  const PhaseRange range_p("cg_batch: GreedyPartitioning, InducedSubgraph, LocalAssembly");
-  if (b->any_bases) {
-    if (T == 256) CG_LAUNCH(ctx, kb_weight<256>, dim3(b->n_vtiles), dim3(256), st, B);
-    else if (T == 512) CG_LAUNCH(ctx, kb_weight<512>, dim3(b->n_vtiles), dim3(512), st, B);
-    else CG_LAUNCH(ctx, kb_weight<1024>, dim3(b->n_vtiles), dim3(1024), st, B);
-  }
-  CG_LAUNCH(ctx, kb_lpt, dim3(b->n_jobs), dim3(kBatchLptBlock), st, B);
-  CG_LAUNCH(ctx, kb_tables, dim3(256), dim3(kTablesBlock), st, B);
-  CG_LAUNCH(ctx, kb_wq_place, dim3(128), dim3(kWqBlock), st, B);
-  auto capped = [](int want, int fit) { return dim3((unsigned)(fit > 0 && fit < want ? fit : want)); };
-  // components above kIwCap reads in two passes (the induce step with the
-  // next ones, the walk after the last pass that reads the tile lists, since
-  // its arrays take their memory), the others in one
-  CG_LAUNCH(ctx, kb_induce_walk, capped(PB, b->res_iw), dim3(kWalkBlock), st, B);
-  CG_LAUNCH(ctx, kb_induce_walk_small, capped(4 * PB, b->res_iw_small), dim3(kWalkSmallBlock), st,
-            B);
-  CG_LAUNCH(ctx, kb_induce_walk_tiny, capped(8 * PB, b->res_iw_tiny), dim3(kWalkSmallBlock), st,
-            B);
-  CG_LAUNCH(ctx, kb_walk, capped(PB, b->res_walk), dim3(kWalkBlock), st, B);
-  CG_LAUNCH(ctx, kb_offsets, dim3(b->n_jobs), dim3(kScanBlock), st, B);
-  // one wave per copy chunk slot: the hardware hands chunks to waves as
-  // slots free up (a persistent grid with a fixed share per wave left a
-  // tail of unevenly loaded waves); slots past the batch's chunks exit
-  const int64_t wpb = b->prm.copy_block / kWave;
-  const int64_t cgrid = (b->chunk_slots + wpb - 1) / wpb;
-  CG_LAUNCH(ctx, kb_copy, dim3((unsigned)(cgrid > 0 ? cgrid : 1)), dim3(b->prm.copy_block), st, B);
-  return hip_check(hipGetLastError(), "cg_batch_run");
+  return rc;
 }
 
 int cg_batch_counts(cg_batch *b, int64_t *d_counts, void *stream) {
@@ -2268,6 +2346,7 @@ int cg_batch_destroy(cg_batch *b) {
   if (!b) return CG_OK;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
+  drop_side(b);
   int rc = CG_OK;
   if (b->mem) rc = hip_check(hipFree(b->mem), "hipFree(batch)");
   delete b;

@@ -659,7 +659,7 @@ int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs
     rc = launch_path_mask(ctx, g, s, a, &parts, st);
     if (!rc) rc = launch_path_partition(ctx, g, s, a, parts, st);
     if (!rc) rc = launch_comp(ctx, g, s, a, reinterpret_cast<int32_t *>(s.fill), st);
-    if (!rc) rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.d_status);
+    if (!rc) rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.status);
     return rc;
   }
   if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st);
