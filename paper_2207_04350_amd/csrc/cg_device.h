@@ -343,6 +343,34 @@ __device__ __forceinline__ void bitonic_sort(K *a, int N2) {
   }
 }
 
+// Sort a[0, n) (distinct keys, at most one per thread; 16-byte aligned, filled
+// up with the largest value to a multiple of four) by counting the smaller
+// keys of each: every thread reads every key, 16 bytes at one address for a
+// whole wave, and no step waits for another's result.  (A bitonic sort is a
+// chain of 36 stages for 190 keys.  Little code, too: what a launch runs once
+// it fetches from memory first.)
+template <typename K>
+__device__ __forceinline__ void rank_sort(K *a, int n) {
+  constexpr int V = 16 / sizeof(K);
+  struct alignas(16) Quad {
+    K k[V];
+  };
+  const int i = (int)threadIdx.x;
+  const K x = i < n ? a[i] : K(0);
+  int r = 0;
+  if (__builtin_amdgcn_readfirstlane(i) < n) {
+#pragma unroll 2
+    for (int c = 0; c < n; c += V) {
+      const Quad y = *reinterpret_cast<const Quad *>(a + c);
+#pragma unroll
+      for (int k = 0; k < V; ++k) r += y.k[k] < x ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  if (i < n) a[r] = x;
+  __syncthreads();
+}
+
 // Stable sort of a[0, n) by bits 16 and up of its 32-bit keys, whose low 16
 // bits are each key's index (the input is in index order), so the result is
 // the order of the whole keys.  LSD radix sort over `passes` 8-bit digits
@@ -568,8 +596,10 @@ __device__ __forceinline__ uint32_t lpt_item_weight(const uint32_t *srt, const u
 // Bin keys are (load << 16) | bin: ascending key order is ascending
 // (load, bin), i.e. the least loaded bin with the lowest index first.
 constexpr int kBinBits = 16;
-constexpr int kLptRoundMin = 6;   // equal items taken as one round from this many
-constexpr int kLptPrefixMin = 8;  // prefix rounds (any weights) from this many items
+constexpr int kLptRoundMin = 4;   // equal items taken as one round from this many
+constexpr int kLptPrefixMin = 5;  // prefix rounds (any weights) from this many items
+constexpr int kLptBlockBins = 256;  // rounds over the whole list from this many bins
+constexpr int kLptBlockMin = 96;    // ... where they place this many items
 constexpr int kLptBulkMin = 256;  // whole rounds of equal items taken at once from this many
 
 // One past the last item of item a's weight wt, by the whole wave: 64 probes
@@ -588,21 +618,17 @@ __device__ __forceinline__ int lpt_run_end(const uint32_t *srt, const uint64_t *
 }
 
 // The values of lanes 0..c-1 and those of lanes c..63, each sorted across its
-// lanes, merged by rank: lanes 0..c-1 search lanes c..63, the others lanes
-// 0..c-1 (every lane runs every step; equal values, which only padding lanes
-// hold, keep their order).
+// lanes, merged: the first run turned round makes both a bitonic run, which
+// the six stages of a bitonic merge sort (a rank search over the lanes took
+// seven lane shuffles one after another, about twice the time).
 __device__ __forceinline__ uint32_t lpt_merge_lanes(uint32_t x, int l, int c) {
-  int lo = l < c ? c : 0, hi = l < c ? kWave : c;
-  for (int it = 0; it < 7; ++it) {
-    const int mid = (lo + hi) >> 1;
-    const uint32_t v = (uint32_t)__shfl((int)x, mid & (kWave - 1));
-    if (lo < hi) {
-      if (v < x) lo = mid + 1;
-      else hi = mid;
-    }
-  }
-  const int pos = l < c ? l + (lo - c) : (l - c) + lo;
-  return (uint32_t)__builtin_amdgcn_ds_permute(pos * 4, (int)x);
+  x = (uint32_t)__shfl((int)x, l < c ? c - 1 - l : l);
+  x = bitonic_lane_step<32>(x, l, kWave);
+  x = bitonic_lane_step<16>(x, l, kWave);
+  x = bitonic_lane_step<8>(x, l, kWave);
+  x = bitonic_lane_step<4>(x, l, kWave);
+  x = bitonic_lane_step<2>(x, l, kWave);
+  return bitonic_lane_step<1>(x, l, kWave);
 }
 
 // With comp_kind and comp_estart given, it also writes each component's
@@ -634,13 +660,15 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
                                         uint64_t *unsorted = nullptr) {
   static_assert(BLOCK > 2 * kWave, "the pipelined windows' merge needs threads beyond two waves");
   __shared__ uint64_t win[2][kWave];  // a window's raised keys, alternating buffers
+  __shared__ uint32_t s_min[BLOCK / kWave];  // rounds over the list: each wave's least raised key
+  __shared__ int s_cp, s_unsorted;           // items placed; whether their keys need a sort
   __shared__ int32_t s_opbin[kWave];                 // rounds taken at once: their bins in order,
   __shared__ int32_t s_op_at, s_op_items, s_op_bins;  // first item, items (0: none), bins
   __shared__ int32_t sh_scan[BLOCK / kWave + 1];
   __shared__ int64_t sh_scan64[BLOCK / kWave + 1];
   __shared__ unsigned int s_wmax;
   const int tid = threadIdx.x;
-  const int N2 = next_pow2(nc > 0 ? nc : 1);
+  const int N2 = next_pow2(nc > 4 ? nc : 4);
   if (tid == 0) s_wmax = 0;
   __syncthreads();
 
@@ -715,13 +743,16 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     }
   }
   __syncthreads();
-  // the keys in LPT order: in LDS with a 1024-thread workgroup, radix passes
-  // over the weight's bytes (one when every weight is below 256), with fewer
-  // waves, whose rounds run one after another, one such pass for more than
-  // two keys a thread; else in LDS a bitonic sort; in global memory radix
-  // passes
+  // the keys in LPT order: in LDS up to 256 keys by ranks, above by radix passes over the weight's bytes (with fewer waves,
+  // whose rounds run one after another, only where one pass does), else by a
+  // bitonic sort; in global memory by radix passes
   auto radix = [&](int passes) {
-    return nc <= kRadixRounds * BLOCK && (BLOCK >= 1024 || (passes == 1 && nc > 2 * BLOCK));
+    return nc <= kRadixRounds * BLOCK &&
+           (BLOCK >= 1024 ? nc > 256 : passes == 1 && nc > 2 * BLOCK);
+  };
+  auto small_sort = [&](auto *k) {
+    if (nc <= 256) rank_sort(k, nc);
+    else bitonic_sort(k, N2);
   };
   const uint32_t *srt = keys32;
   if constexpr (kBig) {
@@ -744,9 +775,9 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     srt = radix_sort_hi16<BLOCK>(keys32, keys32 + N2, nc, s_wmax < 256u ? 1 : 2, s_cnt,
                                  reinterpret_cast<uint32_t *>(sh_scan));
   else if (k32)
-    bitonic_sort(keys32, N2);
+    small_sort(keys32);
   else
-    bitonic_sort(keys, N2);
+    small_sort(keys);
 
   // 2. LPT.  The bins are kept sorted by (load, bin).  A window holds the W
   // least loaded bins in the lanes of wave 0 (sorted across lanes): each
@@ -864,8 +895,103 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
       }
       if (i0 >= nc) break;
     }
+    // Rounds over the whole list, by all threads: items i0, i0 + 1, ... go to
+    // the list's bins 0, 1, ... for as long as each bin's key is below every
+    // key the earlier items of the round raised (as in a wave's prefix round
+    // below).  A list of hundreds of bins takes hundreds of items at once, where
+    // a window of 64 takes 64: 4,478 components on 1,024 bins took 54 windows,
+    // 66 us; the loop takes 36 us so.
+    const bool blocks =
+        BLOCK >= 1024 && narrow && P >= kLptBlockBins && P <= 2 * BLOCK;
+    if (blocks) {
+      constexpr int E = 2;  // bins per thread: 2 tid, 2 tid + 1
+      uint32_t *srt_bins = reinterpret_cast<uint32_t *>(binB);
+      const int Pn = next_pow2(P);  // below 2 P: fits binB
+      const int w = tid / kWave;
+      while (i0 < nc && i0 < (s_last < nc ? s_last : nc)) {
+        const int n_it = nc - i0 < P ? nc - i0 : P;
+        const uint64_t least = binA[0] >> bb << bb;
+        uint32_t key[E], r[E];
+        uint32_t mine = 0xFFFFFFFFu;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int j = tid * E + e;
+          key[e] = j < P ? (uint32_t)(binA[j] - least) : 0xFFFFFFFFu;
+          r[e] = j < n_it ? key[e] + (lpt_item_weight(srt, keys, k32, i0 + j) << kb) : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) mine = r[e] < mine ? r[e] : mine;
+        // the least raised key before this thread's bins
+        uint32_t lower = wave_excl_min_u32(mine);
+        const uint32_t wmin = lower < mine ? lower : mine;
+        if (tid == 0) s_cp = n_it;
+        if (lane_id() == kWave - 1) s_min[w] = wmin;
+        __syncthreads();
+        for (int k = 0; k < w; ++k) lower = s_min[k] < lower ? s_min[k] : lower;
+        int fail = n_it;
+#pragma unroll
+        for (int e = E - 1; e >= 0; --e) {
+          const int j = tid * E + e;
+          const uint32_t low = e == 0 ? lower : (r[0] < lower ? r[0] : lower);
+          if (j < n_it && key[e] >= low) fail = j;
+        }
+        const uint64_t bad = __ballot(fail < n_it);
+        if (bad && lane_id() == (int)__builtin_ctzll(bad)) atomicMin(&s_cp, fail);
+        if (tid == 0) s_unsorted = 0;
+        __syncthreads();
+        const int cp = __builtin_amdgcn_readfirstlane(s_cp);
+        if (cp < kLptBlockMin && cp < nc - i0) break;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int j = tid * E + e;
+          if (j < cp) {
+            const int i = i0 + j;
+            bin_of[k32 ? (srt[i] & 0xFFFFu) : (uint32_t)keys[i]] =
+                (int32_t)(key[e] & ((1u << kb) - 1u));
+            key[e] = r[e];
+          }
+          if (j < Pn) srt_bins[j] = key[e];
+        }
+        __syncthreads();
+        bool down = false;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int j = tid * E + e;
+          down = down || (j > 0 && j < cp && srt_bins[j - 1] > key[e]);
+        }
+        if (down) s_unsorted = 1;
+        __syncthreads();
+        if (!s_unsorted) {
+          // the raised bins and the others, two sorted runs, merged by rank
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const int j = tid * E + e;
+            if (j >= P) continue;
+            int lo = j < cp ? cp : 0, hi = j < cp ? P : cp;
+            while (lo < hi) {
+              const int mid = (lo + hi) >> 1;
+              if (srt_bins[mid] < key[e]) lo = mid + 1;
+              else hi = mid;
+            }
+            binA[j < cp ? j + lo - cp : j - cp + lo] = least + key[e];
+          }
+        } else {
+          bitonic_sort(srt_bins, Pn);
+#pragma unroll
+          for (int e = 0; e < E; ++e) {
+            const int j = tid * E + e;
+            if (j < P) binA[j] = least + srt_bins[j];
+          }
+        }
+        __syncthreads();
+        i0 += cp;
+      }
+      if (i0 >= nc) break;
+    }
+    // (every turn of this loop goes on to place at least one item here)
     // the items up to lim in windows (all of them in one window up to 64 bins)
-    const int lim = i0 < s_last ? s_last : (nc - i0 < P ? nc : i0 + P);
+    int lim = i0 < s_last ? s_last : (nc - i0 < P ? nc : i0 + P);
+    if (blocks && lim > i0 + 2 * kWave) lim = i0 + 2 * kWave;
     uint32_t key32 = 0xFFFFFFFFu;  // wave 0: the window's keys (narrow or wide)
     uint64_t key64 = ~0ull;
     uint64_t load0 = 0;  // what narrow keys are relative to
@@ -881,8 +1007,8 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
         const int l = tid;
         const uint32_t bmask = (1u << kb) - 1u;
         uint32_t key = key32;
-        for (int base = 0; base < T; base += kWave) {
-          const int cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
+        for (int base = 0, cnt; base < T; base += cnt) {
+          cnt = __builtin_amdgcn_readfirstlane(T - base < kWave ? T - base : kWave);
           // keys relative to the least load again
           const uint32_t sub = (uint32_t)__builtin_amdgcn_readlane((int)key, 0) & ~bmask;
           key -= l < W ? sub : 0u;
@@ -961,9 +1087,16 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
             if (cp >= kLptPrefixMin) {
               const uint32_t src = (uint32_t)__shfl((int)key, (l - t) & (kWave - 1));
               if (l >= t && l < t + cp) mine = (int32_t)(src & bmask);
-              // raised keys in lanes 0..cp-1, the rest unchanged: sort the wave
-              key = wave_sort_u32(l < cp ? r : key, l);
+              // raised keys in lanes 0..cp-1, the rest unchanged: merged where
+              // the raised ones are in order, else sorted
+              const uint32_t prev = wave_prev_u32(r);  // by every lane, before the test
+              const bool down = l > 0 && l < cp && prev > r;
+              key = l < cp ? r : key;
+              key = __ballot(down) ? wave_sort_u32(key, l) : lpt_merge_lanes(key, l, cp);
               t += cp;
+              // the next items at once, so that a round is not cut short by
+              // the end of the lanes' items
+              if (base + cnt < T) cnt = t;
             } else if (c >= kLptRoundMin) {
               // a round: c equal items go to lanes 0..c-1 in order (each of
               // those bins is below lane 0's raised key, so the steps would pick
@@ -974,6 +1107,7 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
               const uint32_t x = l < c ? key + (q << kb) : key;
               key = lpt_merge_lanes(x, l, c);
               t += c;
+              if (base + cnt < T) cnt = t;
             } else {
               mine = l == t ? (int32_t)(k0 & bmask) : mine;
               const int p = __popcll(below) - 1;  // lanes 1.. below nk
@@ -1134,9 +1268,9 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     srt2 = radix_sort_hi16<BLOCK>(keys32, keys32 + N2, nc, P <= 256 ? 1 : 2, s_cnt,
                                   reinterpret_cast<uint32_t *>(sh_scan));
   else if (b32)
-    bitonic_sort(keys32, N2);
+    small_sort(keys32);
   else
-    bitonic_sort(keys, N2);
+    small_sort(keys);
   // a thread takes up to eight consecutive components of the order per round
   int carry = 0, ecarry = 0;
   for (int base = 0; base < nc; base += kPer * BLOCK) {

@@ -1079,7 +1079,7 @@ constexpr int kBatchSortCap = 1024;
 constexpr int kBatchBinCap = 256;
 
 __global__ __launch_bounds__(kBatchLptBlock) void kb_lpt(BatchDev B) {
-  __shared__ uint64_t s_keys[kBatchSortCap];
+  __shared__ alignas(16) uint64_t s_keys[kBatchSortCap];
   __shared__ int32_t s_bin[kBatchSortCap];
   __shared__ uint64_t s_binA[kBatchBinCap], s_binB[kBatchBinCap];
   __shared__ uint32_t s_cnt[kBatchLptBlock / kWave * 256];

@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kLptBlock) void k_part_lpt(int32_t P, const int32_t
                                                         uint64_t *g_bins, int later,
                                                         const unsigned int *n_multi, int32_t n,
                                                         RankOut ro, FillArgs fa) {
-  __shared__ uint64_t s_keys[kSortCapLds];
+  __shared__ alignas(16) uint64_t s_keys[kSortCapLds];
   __shared__ int32_t s_bin[kSortCapLds];
   __shared__ uint64_t s_binA[kBinCapLds], s_binB[kBinCapLds];
   __shared__ uint32_t s_cnt[kLptBlock / kWave * 256];

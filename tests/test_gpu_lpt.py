@@ -110,3 +110,35 @@ def test_many_equal_components_batched(P):
         assert mismatches(cg.to_host(jobs[i][1], g.n), want) == [], names[i]
     b.close()
     ctx.close()
+
+
+def _sizes(kind, k, rng):
+    if kind == "exponential":
+        return np.maximum(2, rng.exponential(18, size=k)).astype(int)
+    if kind == "uniform":
+        return rng.integers(2, 60, size=k)
+    if kind == "powers":
+        return 2 ** rng.integers(1, 8, size=k)
+    return np.concatenate([rng.integers(2, 5, size=k - 3), [3000, 1500, 700]])  # a few large ones
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["exponential", "uniform", "powers", "few large"])
+@pytest.mark.parametrize("k", [257, 1100, 5000, 9000])
+def test_rounds_over_the_list(kind, k):
+    """Hundreds of bins: rounds over the whole list by all threads, and windows
+    where they are short, below and above what the LDS sort holds."""
+    from paper_2207_04350_amd import cg
+    rng = np.random.default_rng(k)
+    g = _graph(rng, [int(x) for x in rng.permutation(_sizes(kind, k, rng))], [], 40)
+    dg = cg.DeviceGraph(g, "cuda")
+    for P in (63, 64, 255, 256, 300, 1024, 2048):
+        for weight in ("reads", "bases"):
+            print("lpt rounds", kind, k, P, weight, flush=True)
+            ctx = cg.Context.for_graph(g.n, g.m, P)
+            out = cg.Outputs(g.n, P, g.seq_words, "cuda")
+            cg.run_path(ctx, dg, out, P, 2, weight=weight)
+            got = cg.to_host(out, g.n)
+            assert ctx.status() == 0
+            ctx.close()
+            assert mismatches(got, oracle.run(g, P=P, min_reads=2, weight=weight)) == []
