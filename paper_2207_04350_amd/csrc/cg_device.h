@@ -191,9 +191,20 @@ __device__ __forceinline__ uint32_t wave_excl_min_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x138, 0xF, 0xF, false);       // wave_shr:1
 }
 
+// The largest x of the wave, in every lane.  Every lane must be active.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
+  x = max(x, wave_dpp<0x111, 0xF>(x));
+  x = max(x, wave_dpp<0x112, 0xF>(x));
+  x = max(x, wave_dpp<0x114, 0xF>(x));
+  x = max(x, wave_dpp<0x118, 0xF>(x));
+  x = max(x, wave_dpp<0x142, 0xA>(x));
+  x = max(x, wave_dpp<0x143, 0xC>(x));
+  return wave_lane(x, kWave - 1);
+}
+
 // x of lane l ^ J: quad permutes for J = 1, 2, row shifts by 4 for J = 4, a
-// rotation of each 16-lane row by 8 for J = 8, a swizzle for J = 16 and a
-// bpermute for J = 32.  Every lane of the wave must be active.
+// rotation of each 16-lane row by 8 for J = 8, a swap of rows for J = 16 and of
+// halves for J = 32.  Every lane of the wave must be active.
 template <int J>
 __device__ __forceinline__ uint32_t wave_xor_u32(uint32_t x) {
   const int v = (int)x;
@@ -208,10 +219,14 @@ __device__ __forceinline__ uint32_t wave_xor_u32(uint32_t x) {
   } else if constexpr (J == 8) {
     return (uint32_t)__builtin_amdgcn_update_dpp(v, v, 0x128, 0xF, 0xF, false);  // row_ror:8
   } else if constexpr (J == 16) {
-    return (uint32_t)__builtin_amdgcn_ds_swizzle(v, 0x401F);  // lanes of 32: xor 16
+    // odd rows of 16 lanes of one copy with the even ones of the other
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    return (lane_id() & 16) ? (uint32_t)r[0] : (uint32_t)r[1];
   } else {
     static_assert(J == 32, "partner distance");
-    return (uint32_t)__shfl_xor(v, 32);
+    // the swap of one copy's upper with the other's lower half
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return (lane_id() & 32) ? (uint32_t)r[0] : (uint32_t)r[1];
   }
 }
 
@@ -724,10 +739,7 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
       }
     }
   }
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    const uint32_t o = (uint32_t)__shfl_xor((int)wmax, off);
-    wmax = o > wmax ? o : wmax;
-  }
+  wmax = wave_max_u32(wmax);
   if (lane_id() == 0 && wmax) atomicMax(&s_wmax, wmax);
   for (int b = tid; b < P; b += blockDim.x) binA[b] = (uint64_t)b;  // load 0, sorted
   __syncthreads();
@@ -1796,11 +1808,8 @@ __device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int
   }
   wbar();
   if constexpr (kOneWave) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-      const int o = __shfl_xor(first, off);
-      first = o < first ? o : first;
-    }
+    // (the largest complement: an index is never negative)
+    first = 0x7FFFFFFF - (int)wave_max_u32((uint32_t)(0x7FFFFFFF - first));
   } else {
     if (first != 0x7FFFFFFF) atomicMin(&s_start, first);
     wbar();
@@ -1977,7 +1986,7 @@ __device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int
       const uint32_t x = i < q ? (kLds ? (uint32_t)w.eid[i] : R_len[i]) : 0u;
       const uint32_t inc = wave_incl_scan(x);
       if (i < q) s.piece_off[st + i] = carry + (inc - x);
-      carry += __shfl(inc, kWave - 1);
+      carry += wave_lane(inc, kWave - 1);
     }
   } else {
     // (above the LDS form's sizes, a run of E pieces per thread)
@@ -2530,7 +2539,7 @@ __device__ __forceinline__ void copy_chunk(const uint32_t *seq_, uint64_t nwords
   }
   const uint32_t gincl = wave_incl_scan(ng);
   const uint32_t gstart = gincl - ng;
-  const uint32_t G = __shfl(gincl, kWave - 1);
+  const uint32_t G = wave_lane(gincl, kWave - 1);
   constexpr uint32_t kStep = kWave * kCopyUnroll;
   CopyStage S0, S1;
   if (G > 0) copy_fetch(S0, 0, G, gstart, my, nx, seq, nwords, lane);

@@ -120,22 +120,53 @@ __device__ __forceinline__ void st_relaxed(int32_t *p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// x of the lane that a DPP control names, 0 where it names none or the lane's
+// row is masked out.  Every lane of the wave must be active.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T wave_dpp(T x) {
+  if constexpr (sizeof(T) == 8) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(uint64_t)x, CTRL,
+                                                              ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+        0, (int)(uint32_t)((uint64_t)x >> 32), CTRL, ROWS, 0xF, false);
+    return (T)((uint64_t)hi << 32 | lo);
+  } else {
+    static_assert(sizeof(T) == 4, "a word or two");
+    return (T)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+  }
+}
+
+// lane l's x in every lane (l uniform)
+template <typename T>
+__device__ __forceinline__ T wave_lane(T x, int l) {
+  if constexpr (sizeof(T) == 8) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)x, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), l);
+    return (T)((uint64_t)hi << 32 | lo);
+  } else {
+    return (T)__builtin_amdgcn_readlane((int)x, l);
+  }
+}
+
+// Sums over the lanes up to and including each: row shifts within rows of 16
+// lanes, then the last lanes of the rows broadcast to the rows after them.
+// (Six lane shuffles through the LDS crossbar one after another take about
+// ten times as long, 600 cycles, and a workgroup's scan has two of these.)
+// Every lane of the wave must be active.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T x) {
-  const int l = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    T y = __shfl_up(x, d);
-    if (l >= d) x += y;
-  }
+  x += wave_dpp<0x111, 0xF>(x);  // row_shr:1
+  x += wave_dpp<0x112, 0xF>(x);  // row_shr:2
+  x += wave_dpp<0x114, 0xF>(x);  // row_shr:4
+  x += wave_dpp<0x118, 0xF>(x);  // row_shr:8
+  x += wave_dpp<0x142, 0xA>(x);  // row_bcast:15
+  x += wave_dpp<0x143, 0xC>(x);  // row_bcast:31
   return x;
 }
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
-  return x;
+  return wave_lane(wave_incl_scan(x), kWave - 1);
 }
 
 // A workgroup barrier that orders LDS accesses only: global loads and
@@ -156,7 +187,7 @@ __device__ __forceinline__ T block_excl_scan(T x, T *sh, T *total) {
   const int w = threadIdx.x / kWave, l = lane_id();
   T inc = wave_incl_scan(x);
   if constexpr (kLdsOnly && BLOCK == kWave) {
-    *total = __shfl(inc, kWave - 1);
+    *total = wave_lane(inc, kWave - 1);
     (void)sh;
     (void)w;
     (void)l;
@@ -257,9 +288,8 @@ __device__ __forceinline__ unsigned long long lookback_publish(ScanCtx sc, int b
       if (lane == 0) atomicOr(sc.error, CG_STATUS_SCAN_STALLED);
       break;
     }
-    unsigned long long v = ((upto >> lane) & 1ull) ? (s & kValMask) : 0ull;
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    excl += v;
+    const unsigned long long v = ((upto >> lane) & 1ull) ? (s & kValMask) : 0ull;
+    excl += wave_sum(v);
     if (pre) break;
     top -= kWave;
   }

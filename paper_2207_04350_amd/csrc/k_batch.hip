@@ -1649,12 +1649,7 @@ __global__ void __launch_bounds__(kCountsBlock) kb_counts(const BJob *jobs, int 
       sz = pack_bytes(nc, ne, tw);
     }
     // inclusive scan of sz over the workgroup
-    int64_t x = sz;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      const int64_t y = __shfl_up(x, d, kWave);
-      if (lane >= d) x += y;
-    }
+    const int64_t x = wave_incl_scan(sz);
     if (lane == kWave - 1) part[w] = x;
     __syncthreads();
     int64_t before = carry;

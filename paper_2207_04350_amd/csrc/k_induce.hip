@@ -195,7 +195,7 @@ __device__ __forceinline__ void ind_wave(int q, int st, int estart, const int32_
         out.loc_eid[t] = e + 1;
       }
     }
-    r0 += __shfl(inc, kWave - 1);
+    r0 += wave_lane(inc, kWave - 1);
   }
   wave_lds_sync();
 }

@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fu
           s_vlen[f[k]] = lv[k];
           s_pfx[f[k]] = pairs + inc - dv[k];
         }
-        pairs += __shfl(inc, kWave - 1);
+        pairs += wave_lane(inc, kWave - 1);
       }
       wave_lds_sync();
       // pair t belongs to the last neighbour j with s_pfx[j] <= t (one with
