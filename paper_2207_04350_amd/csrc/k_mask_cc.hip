@@ -33,6 +33,7 @@ struct PathInit {
   int32_t *label, *cnt;
   int32_t *zero;  // [zero_words]
   unsigned long long *scan_status;
+  uint64_t *root_w;  // null: not wanted
   int32_t zero_words, n_status;
   int reset;
 };
@@ -97,6 +98,7 @@ __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *_
       if constexpr (kPath) {
         pi.label[v] = first_parent((int32_t)v, f, u0, u1);
         pi.cnt[v] = first_count(f);
+        if (pi.root_w && (f & 6)) pi.root_w[v] = 0;
       }
     }
     const uint32_t nb = (uint32_t)__popcll(__ballot(f & 1));
@@ -198,7 +200,8 @@ int launch_path_mask(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const Pat
                      int *parts, hipStream_t st) {
   const PhaseRange range("cg: BranchRemoval + ConnectedComponent");
   const int64_t grid = mask_grid(g.n);
-  const PathInit pi{a.label, a.parts.label_comp, s.estart, s.scan_status, cyc_words(g.n),
+  const PathInit pi{a.label, a.parts.label_comp, s.estart, s.scan_status,
+                    a.weight == CG_WEIGHT_BASES ? s.piece_src : nullptr, cyc_words(g.n),
                     scan_blocks((int64_t)g.n + 1) + 1, a.reset ? 1 : 0};
   CG_LAUNCH(ctx, k_mask<true>, dim3((unsigned)grid), dim3(kMaskBlock), st, g.n, g.row_ptr, g.col,
             a.flags, ctx->fixed, a.d_counts, pi);

@@ -67,15 +67,19 @@ __device__ __forceinline__ uint32_t chunk_sum(uint32_t x, uint32_t *sh) {
 // one atomic per read on the component's counter queues on its address
 // (about 4.5 ns each: 57 us for the 15,000 reads of 13 components).
 // kFind: the labels are a forest still; every read's is set to its root, and
-// slot gives its place among its component's reads.
+// slot gives its place among its component's reads.  kBases: the lengths are
+// added up with the counts (two passes over all reads after the compaction,
+// with an atomic per read, took 11.6 us of the 17 Mbp graph's 88).
 struct CountExtra {
   int32_t *slot;
   const Fixed *fx;  // branch and entry counts of the mask pass, mask_parts of them
   int mask_parts;
   int32_t *d_counts;
+  const uint32_t *read_len;  // kBases: lengths, added up at each root
+  uint64_t *root_w;
 };
 constexpr int kCountSlots = 2 * kChunkRound;  // at most half full
-template <bool kFind>
+template <bool kFind, bool kBases>
 __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int rounds,
                                                             const uint8_t *__restrict__ flags,
                                                             int32_t *label, int32_t *cnt,
@@ -84,12 +88,13 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
                                                             CountExtra ex) {
   __shared__ int32_t s_key[kCountSlots];
   __shared__ uint32_t s_cnt[kCountSlots];
+  __shared__ unsigned long long s_w[kBases ? kCountSlots : 1];
   __shared__ uint32_t sh[kChunkBlock / kWave];
   uint32_t elig = 0, multi = 0;
   for (int r = 0; r < rounds; ++r) {
     const int64_t base = ((int64_t)blockIdx.x * rounds + r) * kChunkRound;
     if (base >= n) break;
-    uint32_t f[kChunkPer];
+    uint32_t f[kChunkPer], len[kChunkPer];
     int32_t v[kChunkPer], root[kChunkPer];
 #pragma unroll
     for (int k = 0; k < kChunkPer; ++k) {
@@ -97,11 +102,16 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
       v[k] = (int32_t)x;
       f[k] = x < n ? flags[x] : 1u;
       root[k] = v[k];
-      if (x < n && (f[k] & 6u)) root[k] = kFind ? ld_relaxed(label + x) : label[x];
+      len[k] = 0;
+      if (x < n && (f[k] & 6u)) {
+        root[k] = kFind ? ld_relaxed(label + x) : label[x];
+        if constexpr (kBases) len[k] = ex.read_len[x];
+      }
     }
     for (int i = threadIdx.x; i < kCountSlots; i += kChunkBlock) {
       s_key[i] = -1;
       s_cnt[i] = 0;
+      if constexpr (kBases) s_w[i] = 0;
     }
     if constexpr (kFind) {
       // both reads' climbs side by side
@@ -143,11 +153,14 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
       }
       h[k] = (int)i;
       at[k] = atomicAdd(s_cnt + i, (f[k] & 6u) == 6u ? 4u : 5u);
+      if constexpr (kBases) atomicAdd(s_w + i, (unsigned long long)len[k]);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kCountSlots; i += kChunkBlock) {
       const int32_t x = s_key[i];
-      if (x >= 0) s_cnt[i] = atomicAdd((uint32_t *)cnt + x, s_cnt[i]) >> 2;
+      if (x < 0) continue;
+      if constexpr (kBases) atomicAdd((unsigned long long *)ex.root_w + x, s_w[i]);
+      s_cnt[i] = atomicAdd((uint32_t *)cnt + x, s_cnt[i]) >> 2;
     }
     __syncthreads();
     if constexpr (kFind) {
@@ -204,10 +217,14 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
 // components above kWalkSmallCap reads, likewise.
 // keys, if given: the LPT's keys by read count, those of the components of more
 // than one read from keys[0] on, the others' from keys[n] on.
+// comp_w, if given: the bases weights, a lone read's length or its root's sum.
 struct MemberOut {
   int32_t *start, *list;
   Fixed *fx;
   uint64_t *keys;
+  uint64_t *comp_w;
+  const uint64_t *root_w;
+  const uint32_t *read_len;
 };
 __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
     int32_t n, int rounds, const uint2 *__restrict__ chunks, const uint8_t *__restrict__ flags,
@@ -287,6 +304,7 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
         comp_size[at] = (int32_t)q;
         comp_kind[at] = q == 1 ? CG_KIND_SINGLE : ((c[k] & 3u) ? CG_KIND_PATH : CG_KIND_CYCLE);
         if (mo.start) mo.start[at] = (int32_t)slot;
+        if (mo.comp_w) mo.comp_w[at] = (f[k] & 6u) ? mo.root_w[v] : (uint64_t)mo.read_len[v];
         if (large[k]) mo.list[s_list + large[k] - 1] = (int32_t)at;
         label_comp[v] = (int32_t)at;
         if (mo.keys) {
@@ -545,13 +563,13 @@ static bool place_later(int32_t n, int32_t P, int32_t min_reads) {
 }
 
 // bases weights (if wanted), the LPT, and the order of many components; fa.n > 0:
-// with the members' slots filled meanwhile
+// the weights are there, and the members' slots are filled meanwhile
 static void launch_lpt(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const int32_t *label,
                        int32_t P, int32_t min_reads, int32_t weight, const cg_parts &out,
                        const RankOut &ro, const FillArgs &fa, hipStream_t st) {
   const int32_t n = g.n;
   const bool bases = weight == CG_WEIGHT_BASES;
-  if (bases && n > 0) {
+  if (bases && n > 0 && fa.n == 0) {
     const dim3 grid((unsigned)((n + kPartBlock - 1) / kPartBlock));
     CG_LAUNCH(ctx, k_part_wzero, grid, dim3(kPartBlock), st, n, s.comp_w);
     CG_LAUNCH(ctx, k_part_weight, grid, dim3(kPartBlock), st, n, label, out.label_comp,
@@ -610,12 +628,12 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
   if (n > 0) {
     CG_LAUNCH(ctx, k_part_zero, dim3((unsigned)((n + kPartBlock - 1) / kPartBlock)),
               dim3(kPartBlock), st, n, flags, out.label_comp);
-    CG_LAUNCH(ctx, k_part_count<false>, dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
+    CG_LAUNCH(ctx, (k_part_count<false, false>), dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
               chunk_rounds(n), flags, const_cast<int32_t *>(label), out.label_comp, min_reads,
               min_reads <= 2 ? chunks : nullptr, CountExtra{});
   }
   launch_compact(ctx, g, chunks, flags, min_reads, out,
-                 MemberOut{nullptr, nullptr, ctx->fixed, keys}, st);
+                 MemberOut{nullptr, nullptr, ctx->fixed, keys, nullptr, nullptr, nullptr}, st);
   launch_lpt(ctx, g, s, label, P, min_reads, weight, out, RankOut{}, FillArgs{}, st);
   return hip_check(hipGetLastError(), "k_part");
 }
@@ -629,12 +647,20 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
   uint64_t *keys =
       place_later(n, a.P, min_reads) && a.weight == CG_WEIGHT_READS ? s.keys : nullptr;
   int32_t *mstart = reinterpret_cast<int32_t *>(s.fill);
-  CG_LAUNCH(ctx, k_part_count<true>, dim3((unsigned)chunk_count(n)), dim3(kChunkBlock), st, n,
-            chunk_rounds(n), a.flags, a.label, a.parts.label_comp, min_reads,
-            min_reads <= 2 ? chunks : nullptr,
-            (CountExtra{s.lidx, ctx->fixed, mask_parts, a.d_counts}));
+  const bool bases = a.weight == CG_WEIGHT_BASES;
+  uint64_t *root_w = s.piece_src;  // until the pieces
+  const CountExtra ex{s.lidx, ctx->fixed, mask_parts, a.d_counts, g.read_len, root_w};
+  const dim3 grid((unsigned)chunk_count(n));
+  uint2 *sums = min_reads <= 2 ? chunks : nullptr;
+  if (bases)
+    CG_LAUNCH(ctx, (k_part_count<true, true>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
+              a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
+  else
+    CG_LAUNCH(ctx, (k_part_count<true, false>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
+              a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
   launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts,
-                 MemberOut{mstart, s.memb, ctx->fixed, keys}, st);
+                 MemberOut{mstart, s.memb, ctx->fixed, keys, bases ? s.comp_w : nullptr, root_w,
+                           g.read_len}, st);
   const RankOut ro{a.local.bin_vptr, a.local.d_sizes, a.local.loc_row_ptr, a.parts.comp_kind,
                    cyc_marks(s.estart, n)};
   const FillArgs fa{n, a.flags, a.label, a.parts.label_comp, mstart, s.lidx, s.tmp};
@@ -642,8 +668,8 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
   return hip_check(hipGetLastError(), "k_part");
 }
 
-// The five steps together: eight launches (ten with bases weights or every
-// read wanted) where the steps one by one take fifteen to eighteen.  The mask
+// The five steps together: eight launches (ten where every read is wanted of
+// a large graph) where the steps one by one take fifteen to eighteen.  The mask
 // pass sets up the component forest and the counters, the count finishes the
 // labels and gives out the member slots, the LPT's launch fills them, and one
 // pass over the components induces and walks.
