@@ -29,6 +29,21 @@ __device__ __forceinline__ int32_t lds_lower_bound(const int32_t *a, int q, int3
   return lo;
 }
 
+// The same for N values at once, so that their loads overlap (q >= 1).
+template <int N>
+__device__ __forceinline__ void lds_lower_bounds(const int32_t *a, int q, const int32_t (&x)[N],
+                                                 int (&p)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) p[k] = 0;
+  for (int step = 1 << (31 - __clz(q)); step > 0; step >>= 1) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int t = p[k] + step;
+      if (t <= q && a[t - 1] < x[k]) p[k] = t;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // BranchRemoval: flags of a vertex whose row starts at b and has `deg`
 // entries: bit0 branch (deg >= 3); bit1 / bit2 entry 0 / 1 kept (neither end
@@ -2088,8 +2103,34 @@ __device__ __forceinline__ void iw_rows(const CompRec &cr, int q, int st, int32_
     // registers (8 barriers for 512 ids instead of 45), and the barriers
     // order LDS only, so the gathers above stay in flight
     bitonic_sort<uint32_t, true>(reinterpret_cast<uint32_t *>(a), N2);
+  }
+  // the neighbours' local numbers (and a workgroup's members' own), searched
+  // together
+  int nr[2 * R];
+  if constexpr (BLOCK == kWave) {
+    int32_t x[2 * R];
 #pragma unroll
-    for (int u = 0; u < R; ++u) rk[u] = tid + u * BLOCK < q ? lds_lower_bound(a, q, v[u]) : 0;
+    for (int u = 0; u < R; ++u) {
+      x[2 * u] = (kb[u] & 1u) ? A[u].y : A[u].z;
+      x[2 * u + 1] = A[u].z;
+    }
+    lds_lower_bounds<2 * R>(a, q, x, nr);
+  } else {
+    int32_t x[3 * R];
+    int p[3 * R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      x[3 * u] = (kb[u] & 1u) ? A[u].y : A[u].z;
+      x[3 * u + 1] = A[u].z;
+      x[3 * u + 2] = v[u];
+    }
+    lds_lower_bounds<3 * R>(a, q, x, p);
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      nr[2 * u] = p[3 * u];
+      nr[2 * u + 1] = p[3 * u + 1];
+      rk[u] = p[3 * u + 2];
+    }
   }
   // 2. every member's fields at its local number: its kept entries in row
   // order (slot 0, then slot 1), neighbours as local numbers
@@ -2102,16 +2143,16 @@ __device__ __forceinline__ void iw_rows(const CompRec &cr, int q, int st, int32_
     const bool k0 = kb[u] & 1u, k1 = (kb[u] & 2u) != 0u;
     const bool s0 = k0 || k1, s1 = k0 && k1;
     const uint32_t sw = (uint32_t)Bq[u].w;
-    const int32_t e0 = k0 ? A[u].w : A[u].w + 1, n0 = k0 ? A[u].y : A[u].z;
+    const int32_t e0 = k0 ? A[u].w : A[u].w + 1;
     const uint32_t es0 = k0 ? (sw & 0xFFu) : ((sw >> 8) & 0xFFu);
     const uint32_t eo0 = (uint32_t)(k0 ? Bq[u].y : Bq[u].z);
     const uint32_t ep0 = (uint32_t)(k0 ? Cq[u].x : Cq[u].y);
-    w.nb[2 * r] = s0 ? lds_lower_bound(a, q, n0) : -1;
+    w.nb[2 * r] = s0 ? nr[2 * u] : -1;
     w.eid[2 * r] = s0 ? e0 : -1;
     w.es[2 * r] = (uint8_t)(s0 ? es0 : 0u);
     w.eo[2 * r] = s0 ? eo0 : 0u;
     w.ep[2 * r] = s0 ? ep0 : 0u;
-    w.nb[2 * r + 1] = s1 ? lds_lower_bound(a, q, A[u].z) : -1;
+    w.nb[2 * r + 1] = s1 ? nr[2 * u + 1] : -1;
     w.eid[2 * r + 1] = s1 ? A[u].w + 1 : -1;
     w.es[2 * r + 1] = (uint8_t)(s1 ? (sw >> 8) & 0xFFu : 0u);
     w.eo[2 * r + 1] = s1 ? (uint32_t)Bq[u].z : 0u;
