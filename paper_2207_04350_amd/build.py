@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 SO = os.path.join(HERE, "libcg.so")
 SOURCES = ["cg_api.cpp", "cg_noalloc.cpp", "k_mask_cc.hip", "k_partition.hip", "k_induce.hip", "k_assemble.hip",
-           "k_components.hip", "k_batch.hip", "k_reduce.hip"]
+           "k_components.hip", "k_front.hip", "k_batch.hip", "k_reduce.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH,

@@ -67,6 +67,43 @@ __device__ __forceinline__ uint32_t vertex_flags(const int32_t *__restrict__ row
   return f;
 }
 
+// A read's parent before any union: the smaller of its kept neighbours if it
+// is smaller than the read itself.  Every kept edge then joins its larger end
+// to its smaller one but for the second edge of a read with two smaller
+// neighbours (a third of a chain's reads in random order), and only these
+// are left for the unions.
+__device__ __forceinline__ int32_t first_parent(int32_t v, uint32_t f, int32_t u0, int32_t u1) {
+  int32_t p = v;
+  if ((f & 2) && u0 < p) p = u0;
+  if ((f & 4) && u1 < p) p = u1;
+  return p;
+}
+
+// a read's counter before the count: a read without kept entries is counted
+__device__ __forceinline__ int32_t first_count(uint32_t f) { return (f & 6) ? 0 : 4; }
+
+// Whether root v (a read that is its component's label) of q reads and flags f
+// makes an eligible component.  Up to two reads the flags tell: a component
+// of more than one read is one whose root has kept entries.
+__device__ __forceinline__ bool eligible(uint32_t f, uint32_t q, int32_t min_reads) {
+  if (f & 1) return false;
+  return min_reads <= 1 || (min_reads == 2 ? (f & 6) != 0 : q >= (uint32_t)min_reads);
+}
+
+// What the compaction gives out besides the components.  start, if given: the
+// first member slot of each, and the list of those above kWalkSmallCap reads,
+// both in any order.
+// keys, if given: the LPT's keys by read count, those of the components of more
+// than one read from keys[0] on, the others' from keys[n] on.
+// comp_w, if given: the bases weights, a lone read's length or its root's sum.
+struct MemberOut {
+  int32_t *start, *list;
+  Fixed *fx;
+  uint64_t *keys;
+  uint64_t *comp_w;
+  const uint64_t *root_w;
+  const uint32_t *read_len;
+};
 // Cycles by component rank: a bitmap, the cycles of every kCycSuper ranks,
 // and whether there is any (most graphs have none, and then nothing else is
 // read).  Kept in the scratch's estart array.

@@ -401,10 +401,14 @@ struct PathArgs {
 };
 int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                 hipStream_t st);
+struct MemberOut;
+bool front_fits(int32_t n);
+int launch_front(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
+                 const MemberOut &mo, hipStream_t st);
 int launch_path_mask(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                      int *parts, hipStream_t st);
 int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
-                          int mask_parts, hipStream_t st);
+                          hipStream_t st);
 int launch_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                 const int32_t *mstart, hipStream_t st);
 int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,

@@ -38,21 +38,6 @@ struct PathInit {
   int reset;
 };
 
-// A read's parent before any union: the smaller of its kept neighbours if it
-// is smaller than the read itself.  Every kept edge then joins its larger end
-// to its smaller one but for the second edge of a read with two smaller
-// neighbours (a third of a chain's reads in random order), and only these
-// are left for the unions.
-__device__ __forceinline__ int32_t first_parent(int32_t v, uint32_t f, int32_t u0, int32_t u1) {
-  int32_t p = v;
-  if ((f & 2) && u0 < p) p = u0;
-  if ((f & 4) && u1 < p) p = u1;
-  return p;
-}
-
-// a read's counter before the count: a read without kept entries is counted
-__device__ __forceinline__ int32_t first_count(uint32_t f) { return (f & 6) ? 0 : 4; }
-
 template <bool kPath>
 __global__ __launch_bounds__(kMaskBlock) void k_mask(int32_t n, const int32_t *__restrict__ row_ptr,
                                                      const int32_t *__restrict__ col,

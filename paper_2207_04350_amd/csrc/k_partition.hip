@@ -45,14 +45,6 @@ static int chunk_count(int32_t n) {
   return n > 0 ? (int)(((int64_t)n + per - 1) / per) : 1;
 }
 
-// Whether root v (a read that is its component's label) of q reads and flags f
-// makes an eligible component.  Up to two reads the flags tell: a component
-// of more than one read is one whose root has kept entries.
-__device__ __forceinline__ bool eligible(uint32_t f, uint32_t q, int32_t min_reads) {
-  if (f & 1) return false;
-  return min_reads <= 1 || (min_reads == 2 ? (f & 6) != 0 : q >= (uint32_t)min_reads);
-}
-
 // The workgroup's sum of x, in thread 0.
 __device__ __forceinline__ uint32_t chunk_sum(uint32_t x, uint32_t *sh) {
   x = wave_sum(x);
@@ -212,20 +204,7 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_chunks(int32_t n, int roun
 // Two consecutive reads per thread and round.  (A single-pass look-back scan
 // in this place waited for its tickets, its predecessors and a release per
 // workgroup: 29 us on the 1 Gbp graph, 7 us on a graph of one workgroup.)
-// mo.start, if given: the first member slot of each component, taken from the
-// cursor a round's components at a time, in any order, and the list of the
-// components above kWalkSmallCap reads, likewise.
-// keys, if given: the LPT's keys by read count, those of the components of more
-// than one read from keys[0] on, the others' from keys[n] on.
-// comp_w, if given: the bases weights, a lone read's length or its root's sum.
-struct MemberOut {
-  int32_t *start, *list;
-  Fixed *fx;
-  uint64_t *keys;
-  uint64_t *comp_w;
-  const uint64_t *root_w;
-  const uint32_t *read_len;
-};
+// Member slots and list places come from cursors, a round's at a time.
 __global__ __launch_bounds__(kChunkBlock) void k_part_compact(
     int32_t n, int rounds, const uint2 *__restrict__ chunks, const uint8_t *__restrict__ flags,
     int32_t *label_comp, int32_t min_reads, int32_t *__restrict__ comp_label,
@@ -639,8 +618,7 @@ int launch_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const uin
 }
 
 int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
-                          int mask_parts, hipStream_t st) {
-  const PhaseRange range("cg: GreedyPartitioning");
+                          hipStream_t st) {
   const int32_t n = g.n, min_reads = a.min_reads < 1 ? 1 : a.min_reads;
   uint2 *chunks = reinterpret_cast<uint2 *>(s.piece_off);  // until the pieces
   // read counts sort themselves as far as they are one
@@ -649,18 +627,27 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
   int32_t *mstart = reinterpret_cast<int32_t *>(s.fill);
   const bool bases = a.weight == CG_WEIGHT_BASES;
   uint64_t *root_w = s.piece_src;  // until the pieces
-  const CountExtra ex{s.lidx, ctx->fixed, mask_parts, a.d_counts, g.read_len, root_w};
-  const dim3 grid((unsigned)chunk_count(n));
-  uint2 *sums = min_reads <= 2 ? chunks : nullptr;
-  if (bases)
-    CG_LAUNCH(ctx, (k_part_count<true, true>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
-              a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
-  else
-    CG_LAUNCH(ctx, (k_part_count<true, false>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
-              a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
-  launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts,
-                 MemberOut{mstart, s.memb, ctx->fixed, keys, bases ? s.comp_w : nullptr, root_w,
-                           g.read_len}, st);
+  const MemberOut mo{mstart, s.memb, ctx->fixed, keys, bases ? s.comp_w : nullptr, root_w,
+                     g.read_len};
+  if (front_fits(n)) {
+    const int rc = launch_front(ctx, g, s, a, mo, st);
+    if (rc) return rc;
+  } else {
+    int mask_parts = 0;
+    const int rc = launch_path_mask(ctx, g, s, a, &mask_parts, st);
+    if (rc) return rc;
+    const CountExtra ex{s.lidx, ctx->fixed, mask_parts, a.d_counts, g.read_len, root_w};
+    const dim3 grid((unsigned)chunk_count(n));
+    uint2 *sums = min_reads <= 2 ? chunks : nullptr;
+    if (bases)
+      CG_LAUNCH(ctx, (k_part_count<true, true>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
+                a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
+    else
+      CG_LAUNCH(ctx, (k_part_count<true, false>), grid, dim3(kChunkBlock), st, n, chunk_rounds(n),
+                a.flags, a.label, a.parts.label_comp, min_reads, sums, ex);
+    launch_compact(ctx, g, chunks, a.flags, min_reads, a.parts, mo, st);
+  }
+  const PhaseRange range("cg: GreedyPartitioning");
   const RankOut ro{a.local.bin_vptr, a.local.d_sizes, a.local.loc_row_ptr, a.parts.comp_kind,
                    cyc_marks(s.estart, n)};
   const FillArgs fa{n, a.flags, a.label, a.parts.label_comp, mstart, s.lidx, s.tmp};
@@ -669,21 +656,21 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
 }
 
 // The five steps together: eight launches (ten where every read is wanted of
-// a large graph) where the steps one by one take fifteen to eighteen.  The mask
-// pass sets up the component forest and the counters, the count finishes the
-// labels and gives out the member slots, the LPT's launch fills them, and one
-// pass over the components induces and walks.
+// a large graph, five for a small graph) where the steps one by one take
+// fifteen to eighteen.  The mask pass sets up the component forest and the
+// counters, the count finishes the labels and gives out the member slots (all
+// of it and the compaction one pass in LDS for a small graph, k_front.hip),
+// the LPT's launch fills them, and one pass over the components induces and
+// walks.
 int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                 hipStream_t st) {
-  int parts = 0;
   int rc;
   if (g.n == 0) {
     rc = launch_mask(ctx, g, a.flags, a.d_counts, st);
     if (!rc) rc = launch_partition(ctx, g, s, a.flags, a.label, a.P, a.min_reads, a.weight, a.parts, st);
     if (!rc) rc = launch_induce(ctx, g, s, a.flags, a.label, a.parts, a.P, a.local, st);
   } else {
-    rc = launch_path_mask(ctx, g, s, a, &parts, st);
-    if (!rc) rc = launch_path_partition(ctx, g, s, a, parts, st);
+    rc = launch_path_partition(ctx, g, s, a, st);
     if (!rc) rc = launch_comp(ctx, g, s, a, reinterpret_cast<int32_t *>(s.fill), st);
     if (!rc) rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.status);
     return rc;
