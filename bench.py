@@ -469,7 +469,6 @@ def main():
     dom_avg_us = 1e3 * dom_ms / dom_launches
     dom_map = {"kb_copy": ["k_asm_copy"], "kb_walk": ["k_asm_walk"], "kb_lpt": ["k_part_lpt"],
                "kb_induce_walk": ["k_ind_local", "k_ind_rows", "k_asm_walk"],
-               "kb_induce_walk_small": ["k_ind_local", "k_ind_rows", "k_asm_walk"],
                "kb_offsets": ["k_asm_offsets"]}
     dom_bytes = sum(algo_bytes(k, st) or 0 for k in dom_map.get(dom, [kname(dom)]))
     dom_bytes_per_launch = (dom_bytes or 0) / dom_launches

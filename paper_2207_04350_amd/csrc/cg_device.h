@@ -1570,7 +1570,6 @@ __device__ __forceinline__ void induce_component(
 constexpr int kWalkBlock = 256;
 constexpr int kWalkRaysCap = 4096;           // reads per component with rays in LDS
 // small components: one wave each, so many more are walked at once
-constexpr int kWalkSmallBlock = 64;
 constexpr int kWalkSmallCap = 128;
 
 // Where a piece starts in the store, as the copy needs it (Section 4.4: the

@@ -85,7 +85,7 @@ struct BatchDev {
   int32_t *wq_hist;                 // [kWqBuckets] components per read count (capped)
   int32_t *wq_cur;                  // [kWqBuckets] placement cursors
   int32_t *wq_meta;                 // [8] 0: components, 1: those above kWalkSmallCap
-                                    // reads, 2: above kIwCap, 3: above kWalkTinyCap
+                                    // reads, 2: above kIwCap
   int32_t *comp_job;                // [sum n] job of each batch-wide component
   int4 *chunk_desc;                 // [bound on the chunks] copy chunk: job, first piece,
                                     // pieces (0: the job's bases overflowed), job's pieces
@@ -1234,7 +1234,6 @@ __global__ __launch_bounds__(kTablesBlock) void kb_tables(BatchDev B) {
 // Components above kIwCap reads form the queue's head (two passes, arrays
 // in scratch), those of at most kWalkSmallCap its tail (one wave each).
 constexpr int kWqBlock = 256;
-constexpr int kWalkTinyCap = 32;  // reads of the components the tiny pass takes
 // Reads of the components that the one-pass workgroup form takes (its walk
 // arrays in LDS).  Each such component's time is mostly latency (dependent
 // gathers, barriers), about the same from 129 to 512 reads, so the pass
@@ -1275,7 +1274,6 @@ __global__ __launch_bounds__(kWqBlock) void kb_wq_place(BatchDev B) {
     B.wq_meta[0] = tot;
     B.wq_meta[1] = s_start[kWalkSmallCap];  // components above kWalkSmallCap reads
     B.wq_meta[2] = s_start[kIwCap];         // above kIwCap
-    B.wq_meta[3] = s_start[kWalkTinyCap];   // above kWalkTinyCap
   }
   // this workgroup's components: a contiguous range; counted per bucket in
   // LDS, one reservation per bucket in the queue, placed by LDS cursors
@@ -1318,12 +1316,12 @@ __global__ __launch_bounds__(kWqBlock) void kb_wq_place(BatchDev B) {
 }
 
 // The per-component passes take their part of the work queue [lo, hi) in a
-// snake order over the grid: round r gives workgroup w entry r*W + w, or
+// snake order over W workers: round r gives worker w entry r*W + w, or
 // r*W + W-1-w on odd rounds.  The queue is in decreasing read count, so this
 // deals the components out like LPT list scheduling, with no atomics.
 // Returns the entry of round r, or -1 past the end.
-__device__ __forceinline__ int32_t wq_entry(int32_t lo, int32_t hi, int32_t r) {
-  const int32_t W = (int32_t)gridDim.x, w = (int32_t)blockIdx.x;
+__device__ __forceinline__ int32_t wq_entry(int32_t lo, int32_t hi, int32_t r, int32_t W,
+                                            int32_t w) {
   const int64_t x = (int64_t)lo + (int64_t)r * W + ((r & 1) ? W - 1 - w : w);
   return x < hi ? (int32_t)x : -1;
 }
@@ -1371,7 +1369,7 @@ template <int BLOCK, int CAP>
 __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkArrays w,
                                              uint64_t *sh_scan) {
   constexpr int R = CAP >= BLOCK ? CAP / BLOCK : 1;  // members per thread
-  const int tid = threadIdx.x;
+  const int tid = BLOCK == kWave ? lane_id() : (int)threadIdx.x;
   const int q = e.q, st = e.st;
   const CG_GLOBAL i32x2 *mem = (const CG_GLOBAL i32x2 *)e.mem;
   const CG_GLOBAL i32x4 *la = (const CG_GLOBAL i32x4 *)J.s.walk;
@@ -1448,97 +1446,94 @@ __device__ __forceinline__ void iw_component(const BJob &J, const WqE &e, WalkAr
                       sh_scan);
 }
 
-// 6a. components of at most kWalkTinyCap reads (the queue's tail): one wave
-// each, both steps in one pass, with small LDS arrays so that many waves run
-// at once
-__global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_tiny(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kWalkTinyCap], s_eid[2 * kWalkTinyCap], s_vid[kWalkTinyCap];
-  __shared__ uint32_t s_ray[2 * kWalkTinyCap], s_rlen[kWalkTinyCap], s_eo[2 * kWalkTinyCap], s_ep[2 * kWalkTinyCap];
-  __shared__ uint64_t s_roff[kWalkTinyCap];
-  __shared__ uint8_t s_es[2 * kWalkTinyCap];
-  __shared__ uint64_t sh_scan[kWalkSmallBlock / kWave + 1];
-  const int32_t lo = ld_const(B.wq_meta, 3), hi = ld_const(B.wq_meta, 0);
-  // each round's entry is fetched while the previous round's component runs
-  int32_t x = wq_entry(lo, hi, 0);
-  WqE nx{};
-  if (x >= 0) nx = wq_get(B, x);
-  for (int32_t r = 1; x >= 0; ++r) {
-    const WqE e = nx;
-    x = wq_entry(lo, hi, r);
-    if (x >= 0) nx = wq_get(B, x);
-    const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
-    iw_component<kWalkSmallBlock, kWalkTinyCap>(J, e, w, sh_scan);
-  }
+// the walk's arrays of CAP reads in buf
+template <int CAP>
+__device__ __forceinline__ WalkArrays iw_arrays(uint32_t *buf) {
+  uint64_t *roff = reinterpret_cast<uint64_t *>(buf);
+  int32_t *nb = reinterpret_cast<int32_t *>(buf + 2 * CAP);
+  int32_t *eid = reinterpret_cast<int32_t *>(buf + 4 * CAP);
+  int32_t *vid = reinterpret_cast<int32_t *>(buf + 12 * CAP);
+  uint8_t *es = reinterpret_cast<uint8_t *>(buf + 14 * CAP);
+  return WalkArrays{nb,           eid, buf + 6 * CAP, nullptr,       vid,
+                    buf + 13 * CAP, roff, es,           buf + 8 * CAP, buf + 10 * CAP};
 }
+constexpr int kIwWaves = kWalkBlock / kWave;
+constexpr int kIwWords = kIwWaves * kWalkSmallCap * 58 / 4;  // 58 bytes of LDS per read
+static_assert(kWalkSmallCap * 58 % 16 == 0, "a wave's arrays start aligned");
+static_assert(kIwCap <= kIwWaves * kWalkSmallCap, "the workgroup's arrays fit the waves'");
 
-// 6b. components of kWalkTinyCap + 1 .. kWalkSmallCap reads: one wave each
-__global__ __launch_bounds__(kWalkSmallBlock) void kb_induce_walk_small(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kWalkSmallCap], s_eid[2 * kWalkSmallCap], s_vid[kWalkSmallCap];
-  __shared__ uint32_t s_ray[2 * kWalkSmallCap], s_rlen[kWalkSmallCap], s_eo[2 * kWalkSmallCap], s_ep[2 * kWalkSmallCap];
-  __shared__ uint64_t s_roff[kWalkSmallCap];
-  __shared__ uint8_t s_es[2 * kWalkSmallCap];
-  __shared__ uint64_t sh_scan[kWalkSmallBlock / kWave + 1];
-  const int32_t lo = ld_const(B.wq_meta, 1), hi = ld_const(B.wq_meta, 3);
-  // each round's entry is fetched while the previous round's component runs
-  int32_t x = wq_entry(lo, hi, 0);
-  WqE nx{};
-  if (x >= 0) nx = wq_get(B, x);
-  for (int32_t r = 1; x >= 0; ++r) {
-    const WqE e = nx;
-    x = wq_entry(lo, hi, r);
-    if (x >= 0) nx = wq_get(B, x);
-    const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
-    // one member per lane up to kWave reads (a uniform branch), two above
-    if (e.q <= kWave) iw_component<kWalkSmallBlock, kWave>(J, e, w, sh_scan);
-    else iw_component<kWalkSmallBlock, kWalkSmallCap>(J, e, w, sh_scan);
-  }
-}
-
-// 6c. components of kWalkSmallCap + 1 .. kIwCap reads: one workgroup each,
-// both steps in one pass; and, first (the queue's head, largest first), the
-// induced subgraph of each component above kIwCap reads, with the block
-// sort in LDS up to kIndLocalCap reads, else in scratch (its walk, whose
-// arrays reuse the tile lists' memory, waits for the next launch)
+// 6. every component's induced subgraph and walk in one launch, over the work
+// queue.  The queue's head, largest first: components above kWalkSmallCap
+// reads, one workgroup each, both steps in one pass up to kIwCap reads; of the
+// larger ones the induced subgraph, with the block sort in LDS up to
+// kIndLocalCap reads, else in scratch (their walk, whose arrays reuse the tile
+// lists' memory, waits for the next launch).  The others, one wave each.
+// Bound by the latency of dependent gathers, so what counts is that no
+// compute unit waits for another's: with one launch each for the workgroups,
+// the waves above 32 reads and those below, every launch ended in a tail of
+// a few components, and a small batch paid the three one after the other:
+// 512 graphs of 0.2-20 Mbp 106 us in three launches, 88 in one; eight graphs
+// of 0.2-2 Mbp 24 and 14.
+// As many workgroups as the head has components take one each and the waves
+// of the rest share the others; with a head longer than half the grid, all
+// workgroups first share it, then the others.
 static_assert(kIndBlock == kWalkBlock, "one workgroup shape for both components' steps");
 static_assert(kIndLocalCap <= 2 * kIwCap, "the induce step's sort buffer is the walk's ray array");
 static_assert(kIwCap % kWalkBlock == 0, "whole members per thread");
 __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
-  __shared__ int32_t s_nb[2 * kIwCap], s_eid[2 * kIwCap], s_vid[kIwCap];
-  __shared__ uint32_t s_ray[2 * kIwCap], s_rlen[kIwCap], s_eo[2 * kIwCap], s_ep[2 * kIwCap];
-  __shared__ uint64_t s_roff[kIwCap];
-  __shared__ uint8_t s_es[2 * kIwCap];
+  __shared__ alignas(16) uint32_t buf[kIwWords];
   __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
-  const int32_t hi = ld_const(B.wq_meta, 1);
-  // each round's entry is fetched while the previous round's component runs
-  int32_t x = wq_entry(0, hi, 0);
+  const int32_t G = (int32_t)gridDim.x, wg = (int32_t)blockIdx.x;
+  const int32_t head = ld_const(B.wq_meta, 1), all = ld_const(B.wq_meta, 0);
+  const int32_t n_wg = head < G / 2 ? head : G;  // workgroups on the head
+  if (wg < n_wg) {
+    // each round's entry is fetched while the previous round's component runs
+    int32_t x = wq_entry(0, head, 0, n_wg, wg);
+    WqE nx{};
+    if (x >= 0) nx = wq_get(B, x);
+    for (int32_t r = 1; x >= 0; ++r) {
+      const WqE e = nx;
+      x = wq_entry(0, head, r, n_wg, wg);
+      if (x >= 0) nx = wq_get(B, x);
+      __syncthreads();  // the previous round's LDS is free
+      const WalkArrays w = iw_arrays<kIwCap>(buf);
+      if (e.q > kIwCap) {
+        induce_listed<kIndBlock, kIndLocalCap>(B, make_int4(e.job, e.c, e.q, e.st),
+                                               (int32_t *)w.ray, (int32_t *)sh_scan);
+        continue;
+      }
+      const BJob J = job_at(B.jobs, e.job);
+      iw_component<kWalkBlock, kIwCap>(J, e, w, sh_scan);
+    }
+    if (n_wg < G) return;
+    __syncthreads();
+  }
+  const int32_t first_wg = n_wg < G ? n_wg : 0, nb = G - first_wg;
+  const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
+  const int32_t W = nb * kIwWaves, me = wv * nb + (wg - first_wg);
+  const WalkArrays w = iw_arrays<kWalkSmallCap>(buf + wv * (kIwWords / kIwWaves));
+  int32_t x = wq_entry(head, all, 0, W, me);
   WqE nx{};
   if (x >= 0) nx = wq_get(B, x);
   for (int32_t r = 1; x >= 0; ++r) {
     const WqE e = nx;
-    x = wq_entry(0, hi, r);
+    x = wq_entry(head, all, r, W, me);
     if (x >= 0) nx = wq_get(B, x);
-    if (e.q > kIwCap) {
-      __syncthreads();  // the previous round's LDS is free
-      induce_listed<kIndBlock, kIndLocalCap>(B, make_int4(e.job, e.c, e.q, e.st), (int32_t *)s_ray,
-                                             (int32_t *)sh_scan);
-      __syncthreads();
-      continue;
-    }
     const BJob J = job_at(B.jobs, e.job);
-    WalkArrays w{s_nb, s_eid, s_ray, nullptr, s_vid, s_rlen, s_roff, s_es, s_eo, s_ep};
-    iw_component<kWalkBlock, kIwCap>(J, e, w, sh_scan);
+    // one member per lane up to kWave reads (a uniform branch), two above
+    if (e.q <= kWave) iw_component<kWave, kWave>(J, e, w, sh_scan);
+    else iw_component<kWave, kWalkSmallCap>(J, e, w, sh_scan);
   }
 }
 
-// 7. their walks, with the walk's arrays in scratch (the rays in LDS up to
+// 7. the walks of the components above kIwCap reads, with the walk's arrays in
+// scratch (the rays in LDS up to
 // kWalkRaysCap reads)
 __global__ __launch_bounds__(kWalkBlock) void kb_walk(BatchDev B) {
   __shared__ uint32_t s_ray[2 * kWalkRaysCap];
   __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
   const int32_t hi = ld_const(B.wq_meta, 2);
-  for (int32_t r = 0, x; (x = wq_entry(0, hi, r)) >= 0; ++r) {
+  for (int32_t r = 0, x; (x = wq_entry(0, hi, r, (int32_t)gridDim.x, (int32_t)blockIdx.x)) >= 0; ++r) {
     const int4 d = wq_at(B, x);
     const int c = d.y, q = d.z, st = d.w;
     const BJob J = job_at(B.jobs, d.x);
@@ -1761,7 +1756,7 @@ struct cg_batch {
   // their grids stay within it, so every workgroup of the snake order runs
   // from the start (a workgroup that waits for a free slot starts its whole
   // share late)
-  int res_iw_tiny, res_iw_small, res_iw, res_walk;
+  int res_iw, res_walk;
   // jobs too large for one workgroup's components pass: they run through the
   // single-graph kernels (grid-wide) beside the batched launches, on streams
   // of the batch's own between two events of the caller's stream, each with
@@ -2089,21 +2084,15 @@ static int batch_alloc(cg_ctx *ctx, const cg_batch_params &prm, size_t bytes, cg
   b->mem = nullptr;
   b->mem_bytes = bytes > 0 ? bytes : 256;
   {
-    int dev = 0, cus = 0, k0 = 0, k1 = 0, k3 = 0, k4 = 0;
+    int dev = 0, cus = 0, k3 = 0, k4 = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&k0, kb_induce_walk_tiny, kWalkSmallBlock,
-                                                     0) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&k1, kb_induce_walk_small, kWalkSmallBlock,
-                                                     0) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&k3, kb_induce_walk, kWalkBlock, 0) !=
             hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&k4, kb_walk, kWalkBlock, 0) != hipSuccess) {
       delete b;
       return set_error(CG_EHIP, "occupancy query failed");
     }
-    b->res_iw_tiny = k0 * cus;
-    b->res_iw_small = k1 * cus;
     b->res_iw = k3 * cus;
     b->res_walk = k4 * cus;
   }
@@ -2146,13 +2135,9 @@ static int run_internal(cg_batch *b, hipStream_t st) {
   CG_LAUNCH(ctx, kb_wq_place, dim3(128), dim3(kWqBlock), st, B);
   auto capped = [](int want, int fit) { return dim3((unsigned)(fit > 0 && fit < want ? fit : want)); };
   // components above kIwCap reads in two passes (the induce step with the
-  // next ones, the walk after the last pass that reads the tile lists, since
-  // its arrays take their memory), the others in one
-  CG_LAUNCH(ctx, kb_induce_walk, capped(PB, b->res_iw), dim3(kWalkBlock), st, B);
-  CG_LAUNCH(ctx, kb_induce_walk_small, capped(4 * PB, b->res_iw_small), dim3(kWalkSmallBlock), st,
-            B);
-  CG_LAUNCH(ctx, kb_induce_walk_tiny, capped(8 * PB, b->res_iw_tiny), dim3(kWalkSmallBlock), st,
-            B);
+  // others' pass, the walk after it, since its arrays take the tile lists'
+  // memory), the others in one
+  CG_LAUNCH(ctx, kb_induce_walk, capped(2 * PB, b->res_iw), dim3(kWalkBlock), st, B);
   CG_LAUNCH(ctx, kb_walk, capped(PB, b->res_walk), dim3(kWalkBlock), st, B);
   CG_LAUNCH(ctx, kb_offsets, dim3(b->n_jobs), dim3(kScanBlock), st, B);
   // one wave per copy chunk slot: the hardware hands chunks to waves as
