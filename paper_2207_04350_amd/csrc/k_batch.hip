@@ -1238,7 +1238,7 @@ constexpr int kWqBlock = 256;
 // arrays in LDS).  Each such component's time is mostly latency (dependent
 // gathers, barriers), about the same from 129 to 512 reads, so the pass
 // wants every component on a workgroup of its own: LDS sized for 512 reads
-// (and 2 members per thread) lets four workgroups share a compute unit,
+// (and 2 members per thread) lets five workgroups share a compute unit,
 // where LDS for 1024 held two, so that a batch with more components above
 // 128 reads than two per compute unit took two rounds of them.  Larger
 // components take the two-pass form.
@@ -1527,8 +1527,7 @@ __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
 }
 
 // 7. the walks of the components above kIwCap reads, with the walk's arrays in
-// scratch (the rays in LDS up to
-// kWalkRaysCap reads)
+// scratch (the rays in LDS up to kWalkRaysCap reads)
 __global__ __launch_bounds__(kWalkBlock) void kb_walk(BatchDev B) {
   __shared__ uint32_t s_ray[2 * kWalkRaysCap];
   __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
