@@ -2293,15 +2293,18 @@ struct PieceD {
 };
 
 // The per-piece arrays are read in piece order (coalesced across a wave's
-// lanes); only the two per-contig arrays are gathered.
-struct PieceArrays {
+// lanes); only the two per-contig arrays are gathered.  CB points to the
+// contigs' first bases (global memory, or LDS).
+template <typename CB>
+struct PieceArraysT {
   const CG_GLOBAL int32_t *lay_contig;
   const CG_GLOBAL uint64_t *piece_off;
   const CG_GLOBAL uint32_t *piece_len;
   const CG_GLOBAL uint64_t *piece_src;
   const CG_GLOBAL uint64_t *clen;
-  const CG_GLOBAL uint64_t *cbase;
+  CB cbase;
 };
+typedef PieceArraysT<const CG_GLOBAL uint64_t *> PieceArrays;
 
 __device__ __forceinline__ PieceArrays piece_arrays(const int32_t *lay_contig,
                                                     const uint64_t *piece_off,
@@ -2313,7 +2316,8 @@ __device__ __forceinline__ PieceArrays piece_arrays(const int32_t *lay_contig,
                      (const CG_GLOBAL uint64_t *)clen,      (const CG_GLOBAL uint64_t *)cbase};
 }
 
-__device__ __forceinline__ PieceD load_piece(const PieceArrays &A, int32_t p) {
+template <typename CB>
+__device__ __forceinline__ PieceD load_piece(const PieceArraysT<CB> &A, int32_t p) {
   PieceD d;
   const int32_t k = A.lay_contig[p];
   const uint64_t a = A.piece_src[p];
@@ -2519,8 +2523,14 @@ __device__ __forceinline__ void copy_fetch(CopyStage &S, uint32_t gb, uint32_t G
   }
 }
 
+// a 16-byte store, dword aligned
+__device__ __forceinline__ void store_dwords4(CG_GLOBAL uint32_t *o, u32x4 x) {
+  __builtin_memcpy(o, &x, 16);
+}
+
 // Finish a step: words from the windows, the pieces' last words, stores.
-__device__ __forceinline__ void copy_emit(const CopyStage &S, const PieceArrays &A, int32_t c0,
+template <typename CB>
+__device__ __forceinline__ void copy_emit(const CopyStage &S, const PieceArraysT<CB> &A, int32_t c0,
                                           int32_t n_e, const CG_GLOBAL uint32_t *__restrict__ seq,
                                           uint64_t nwords, CG_GLOBAL uint32_t *__restrict__ bases) {
 #pragma unroll
@@ -2576,8 +2586,7 @@ __device__ __forceinline__ void copy_emit(const CopyStage &S, const PieceArrays 
     if (nw == kGroupWords) {
 #pragma unroll
       for (int v = 0; v < kGroupWords / 4; ++v) {
-        const u32x4 x4 = {out[4 * v], out[4 * v + 1], out[4 * v + 2], out[4 * v + 3]};
-        __builtin_memcpy(o + 4 * v, &x4, 16);  // 16-byte stores, dword aligned
+        store_dwords4(o + 4 * v, u32x4{out[4 * v], out[4 * v + 1], out[4 * v + 2], out[4 * v + 3]});
       }
     } else {
 #pragma unroll
@@ -2597,8 +2606,9 @@ __device__ __forceinline__ void copy_emit(const CopyStage &S, const PieceArrays 
 // Steps are software-pipelined: the loads of step s + 1 are issued before
 // step s is finished, so a wave always has loads in flight.
 // c0, cnt and n_e are wave-uniform; every lane runs every step.
+template <typename CB>
 __device__ __forceinline__ void copy_chunk(const uint32_t *seq_, uint64_t nwords, uint32_t *bases_,
-                                           const PieceArrays &A, int32_t c0, int cnt,
+                                           const PieceArraysT<CB> &A, int32_t c0, int cnt,
                                            int32_t n_e, int lane) {
   const CG_GLOBAL uint32_t *seq = (const CG_GLOBAL uint32_t *)seq_;
   CG_GLOBAL uint32_t *bases = (CG_GLOBAL uint32_t *)bases_;

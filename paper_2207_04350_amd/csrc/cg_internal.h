@@ -412,8 +412,8 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
 int launch_comp(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs &a,
                 const int32_t *mstart, hipStream_t st);
 int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                   const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                   const StatusOut &so);
+                   const cg_local &local, int32_t P, int32_t max_contigs, const cg_contigs &out,
+                   hipStream_t st, const StatusOut &so);
 int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuzz,
                   uint8_t *contained, uint8_t *kept, int32_t *s_row_ptr, int32_t *s_col,
                   uint32_t *s_ovl, uint8_t *s_strand, int32_t *d_m, hipStream_t st);

@@ -158,6 +158,28 @@ constexpr int kCopyWavesPerCU = 16;  // resident copy waves per compute unit (4 
 constexpr int kCopyRounds = 4;       // copy chunks per resident wave slot
 constexpr int kCopyMinPieces = 2;    // pieces per copy chunk at least
 
+// a wave's share of the pieces' chunks
+template <typename CB>
+__device__ __forceinline__ void copy_share(const uint32_t *seq, uint64_t seq_words, uint32_t *bases,
+                                           const PieceArraysT<CB> &A, int32_t n_e,
+                                           int32_t chunk_target) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int32_t gw = blockIdx.x * (blockDim.x / kWave) + wave;
+  const int32_t nwv = gridDim.x * (blockDim.x / kWave);
+  // pieces per chunk: about chunk_target chunks (a few per wave slot of the
+  // device, so the slots drain evenly while each chunk's setup, a chain of
+  // dependent descriptor loads, is paid for enough pieces), at least
+  // kCopyMinPieces, at most one piece per lane
+  int32_t C = (n_e + chunk_target - 1) / chunk_target;
+  C = C < kCopyMinPieces ? kCopyMinPieces : (C > kWave ? kWave : C);
+  const int32_t n_chunks = (n_e + C - 1) / C;
+  for (int32_t ch = gw; ch < n_chunks; ch += nwv) {
+    const int32_t c0 = ch * C;
+    const int cnt = n_e - c0 < C ? n_e - c0 : C;
+    copy_chunk(seq, seq_words, bases, A, c0, cnt, n_e, lane_id());
+  }
+}
+
 __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restrict__ seq,
                                                          uint64_t seq_words,
                                                          const int32_t *__restrict__ bin_vptr,
@@ -181,31 +203,67 @@ __global__ __launch_bounds__(kCopyBlock) void k_asm_copy(const uint32_t *__restr
   if (*d_total_words > cap_words) return;
   const int32_t n_e = bin_vptr[P];
   const PieceArrays A = piece_arrays(lay_contig, piece_off, piece_len, piece_src, clen, cbase);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int32_t gw = blockIdx.x * (blockDim.x / kWave) + wave;
-  const int32_t nwv = gridDim.x * (blockDim.x / kWave);
-  // pieces per chunk: about chunk_target chunks (a few per wave slot of the
-  // device, so the slots drain evenly while each chunk's setup, a chain of
-  // dependent descriptor loads, is paid for enough pieces), at least
-  // kCopyMinPieces, at most one piece per lane
-  int32_t C = (n_e + chunk_target - 1) / chunk_target;
-  C = C < kCopyMinPieces ? kCopyMinPieces : (C > kWave ? kWave : C);
-  const int32_t n_chunks = (n_e + C - 1) / C;
-  for (int32_t ch = gw; ch < n_chunks; ch += nwv) {
-    const int32_t c0 = ch * C;
-    const int cnt = n_e - c0 < C ? n_e - c0 : C;
-    copy_chunk(seq, seq_words, bases, A, c0, cnt, n_e, lane_id());
-  }
+  copy_share(seq, seq_words, bases, A, n_e, chunk_target);
 }
 
-// offsets and bases of the walked contigs
+// Offsets and copy of a small graph in one launch: every workgroup scans all
+// contigs' lengths for itself, in LDS (a few per thread), and copies from
+// there; the first one stores the offsets.  A launch of k_asm_offsets is 4 us
+// of latency, a workgroup's own scan @.  Up to kOwnContigs contigs and as many
+// reads as give no more workgroups (32 reads each) than are resident with that
+// much LDS: a second round of them would scan again.
+constexpr int kOwnContigs = 8192;
+constexpr int kOwnReads = 16384;
+__global__ __launch_bounds__(kCopyBlock) void k_asm_bases(cg_graph g, const int32_t *bin_vptr,
+                                                          int32_t P, const int32_t *d_n_comp,
+                                                          Scratch s, cg_contigs out,
+                                                          int32_t chunk_target, Fixed *fx,
+                                                          StatusOut so) {
+  __shared__ uint64_t base[kOwnContigs];
+  __shared__ unsigned long long sh[kCopyBlock / kWave + 1];
+  const int nc = *d_n_comp;
+  const int32_t n_e = bin_vptr[P];
+  for (int k = threadIdx.x; k < nc; k += kCopyBlock) base[k] = (out.len[k] + 15) / 16;
+  __syncthreads();
+  const int E = (nc + kCopyBlock - 1) / kCopyBlock;
+  const int k0 = (int)threadIdx.x * E, k1 = k0 + E < nc ? k0 + E : nc;
+  unsigned long long x = 0, total;
+  for (int k = k0; k < k1; ++k) x += base[k];
+  unsigned long long ex = block_excl_scan<unsigned long long, kCopyBlock>(x, sh, &total);
+  for (int k = k0; k < k1; ++k) {
+    const unsigned long long w = base[k];
+    base[k] = 16 * ex;
+    ex += w;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int k = threadIdx.x; k < nc; k += kCopyBlock) out.base_off[k] = base[k];
+    if (threadIdx.x == 0) {
+      *out.d_total_words = total;
+      // the last kernel of the path: no earlier one can still raise a bit
+      unsigned int bits = fx->status;
+      if (total > out.cap_words) {
+        atomicOr(&fx->status, CG_STATUS_BASES_OVERFLOW);
+        bits |= CG_STATUS_BASES_OVERFLOW;
+      }
+      if (so.set) *so.set = bits;
+      if (so.add && bits) atomicOr(so.add, bits);
+    }
+  }
+  if (total > out.cap_words) return;
+  typedef const __attribute__((address_space(3))) uint64_t *LdsBase;
+  const PieceArrays p = piece_arrays(s.lay_contig, s.piece_off, s.piece_len, s.piece_src, out.len,
+                                     nullptr);
+  const PieceArraysT<LdsBase> A{p.lay_contig, p.piece_off, p.piece_len, p.piece_src, p.clen,
+                                (LdsBase)base};
+  copy_share(g.seq, g.seq_words, out.bases, A, n_e, chunk_target);
+}
+
+// offsets and bases of the walked contigs, at most max_contigs of them
 int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_parts &parts,
-                   const cg_local &local, int32_t P, const cg_contigs &out, hipStream_t st,
-                   const StatusOut &so) {
+                   const cg_local &local, int32_t P, int32_t max_contigs, const cg_contigs &out,
+                   hipStream_t st, const StatusOut &so) {
   const int32_t n = g.n;
-  CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
-            dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
-            out.d_total_words, ctx->fixed, scan_ctx(ctx, s));
   // about eight pieces per wave, so a small graph still spreads over the chip
   const int cgrid = (n + 31) / 32 < 8192 ? (n + 31) / 32 : 8192;
   // chunks: kCopyRounds per resident wave slot (kCopyWavesPerCU per compute
@@ -217,6 +275,14 @@ int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_pa
   const int64_t tgt = (int64_t)kCopyRounds * kCopyWavesPerCU * cus;
   const int64_t gw = (int64_t)cgrid * (kCopyBlock / kWave);
   const int32_t chunk_target = (int32_t)(tgt > gw ? gw : tgt);
+  if (max_contigs <= kOwnContigs && n <= kOwnReads) {
+    CG_LAUNCH(ctx, k_asm_bases, dim3(cgrid), dim3(kCopyBlock), st, g, local.bin_vptr, P,
+              parts.d_n_comp, s, out, chunk_target, ctx->fixed, so);
+    return hip_check(hipGetLastError(), "k_asm");
+  }
+  CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
+            dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
+            out.d_total_words, ctx->fixed, scan_ctx(ctx, s));
   CG_LAUNCH(ctx, k_asm_copy, dim3(cgrid), dim3(kCopyBlock), st, g.seq, g.seq_words,
                      local.bin_vptr, P, s.piece_off, s.piece_len, s.piece_src, s.lay_contig,
                      out.len, out.base_off, out.d_total_words, out.cap_words, out.bases,
@@ -241,7 +307,7 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
   const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
   CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
             dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
-  return launch_contigs(ctx, g, s, parts, local, P, out, st, StatusOut{});
+  return launch_contigs(ctx, g, s, parts, local, P, n, out, st, StatusOut{});
 }
 
 }  // namespace cg

@@ -6,7 +6,7 @@
 // their rows, the entries) and latency is what bounds it: the rows written by
 // one pass were read back by the next, four more loads in a row (induce + walk
 // 12.9 + 10.7 us on the 50 Mbp graph, 40 + 28 us on the 1 Gbp graph, 62 + 147
-// us where 13 components hold up to 4,000 reads each; 20, 51 and 90 us now).
+// us where 13 components hold up to 4,000 reads each; 19, 49 and 84 us now).
 #include "cg_device.h"
 
 namespace cg {

@@ -672,7 +672,9 @@ int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs
   } else {
     rc = launch_path_partition(ctx, g, s, a, st);
     if (!rc) rc = launch_comp(ctx, g, s, a, reinterpret_cast<int32_t *>(s.fill), st);
-    if (!rc) rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, a.out, st, a.status);
+    const int32_t max_contigs = g.n / (a.min_reads < 1 ? 1 : a.min_reads);
+    if (!rc)
+      rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, max_contigs, a.out, st, a.status);
     return rc;
   }
   if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st);
