@@ -656,7 +656,7 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
 }
 
 // The five steps together: eight launches (ten where every read is wanted of
-// a large graph, five for a small graph) where the steps one by one take
+// a large graph, four for a small graph) where the steps one by one take
 // fifteen to eighteen.  The mask pass sets up the component forest and the
 // counters, the count finishes the labels and gives out the member slots (all
 // of it and the compaction one pass in LDS for a small graph, k_front.hip),
