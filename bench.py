@@ -417,16 +417,15 @@ def main():
             # the batched form: degrees, bitmaps and lists over the whole chip
             # (kb_mask_tiles), then kept entries, labels and the component
             # table per graph (kb_mask_cc, counted here as components)
-            "mask": pick(lambda k: k.startswith("k_mask") or k == "kb_mask_tiles"),
+            "mask": pick(lambda k: k.startswith("k_mask") or k in ("kb_mask_tiles", "k_front")),
             "components": pick(lambda k: k.startswith("k_cc") or k == "kb_mask_cc"),
             "partition": pick(lambda k: k.startswith("k_part") or k.startswith("kb_weight")
                               or k in ("kb_lpt", "kb_tables", "kb_wq_place")),
             "induce": pick(lambda k: k.startswith("k_ind")),
-            # the batched form induces and walks components of up to 1024
-            # reads in one pass (and induces the larger ones in it)
-            "induce_walk": pick(lambda k: k.startswith("kb_induce_walk")),
-            "assemble": pick(lambda k: k.startswith("k_asm") or k.startswith("kb_walk")
-                             or k in ("kb_offsets", "kb_copy")),
+            # both forms induce and walk every component in one pass
+            "induce_walk": pick(lambda k: k in ("kb_induce_walk", "k_comp")),
+            "assemble": pick(lambda k: k.startswith("k_asm")
+                             or k in ("kb_walk", "kb_offsets", "kb_copy")),
         }
 
     def medians(km):

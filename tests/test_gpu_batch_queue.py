@@ -17,6 +17,7 @@ HEADS = {
     "one": ([2, 31, 32, 33, 129], [4], 7),
     "two": ([63, 512], [511, 30], 20),
     "above one pass": ([513, 1100, 140, 2], [600, 128, 64], 3),
+    "rays in scratch": ([4096, 4097], [3000], 5),
     "many": ([130] * 40 + [2] * 50, [131, 128], 9),
     "only": ([200] * 30, [], 0),
 }
