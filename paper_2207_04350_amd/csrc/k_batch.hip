@@ -1474,9 +1474,13 @@ static_assert(kIwCap <= kIwWaves * kWalkSmallCap, "the workgroup's arrays fit th
 // a few components, and a small batch paid the three one after the other:
 // 512 graphs of 0.2-20 Mbp 106 us in three launches, 88 in one; eight graphs
 // of 0.2-2 Mbp 24 and 14.
-// As many workgroups as the head has components take one each and the waves
-// of the rest share the others; with a head longer than half the grid, all
-// workgroups first share it, then the others.
+// As many workgroups as the head has components take one each, or all share a
+// longer one.  Meanwhile each wave of the others takes kIwFirst components, the
+// largest of the rest, and what is left is shared by all waves: 83 us, and 100
+// instead of 116 on 512 graphs with 634 components in the head (no longer half
+// of the workgroups, which left after it).  With 2 or 3 first ones: 83 and 85,
+// 100 and 100.
+constexpr int kIwFirst = 1;
 static_assert(kIndBlock == kWalkBlock, "one workgroup shape for both components' steps");
 static_assert(kIndLocalCap <= 2 * kIwCap, "the induce step's sort buffer is the walk's ray array");
 static_assert(kIwCap % kWalkBlock == 0, "whole members per thread");
@@ -1485,7 +1489,7 @@ __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
   __shared__ uint64_t sh_scan[kWalkBlock / kWave + 1];
   const int32_t G = (int32_t)gridDim.x, wg = (int32_t)blockIdx.x;
   const int32_t head = ld_const(B.wq_meta, 1), all = ld_const(B.wq_meta, 0);
-  const int32_t n_wg = head < G / 2 ? head : G;  // workgroups on the head
+  const int32_t n_wg = head < G ? head : G;  // workgroups on the head
   if (wg < n_wg) {
     // each round's entry is fetched while the previous round's component runs
     int32_t x = wq_entry(0, head, 0, n_wg, wg);
@@ -1505,19 +1509,27 @@ __global__ __launch_bounds__(kWalkBlock) void kb_induce_walk(BatchDev B) {
       const BJob J = job_at(B.jobs, e.job);
       iw_component<kWalkBlock, kIwCap>(J, e, w, sh_scan);
     }
-    if (n_wg < G) return;
     __syncthreads();
   }
-  const int32_t first_wg = n_wg < G ? n_wg : 0, nb = G - first_wg;
   const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x / kWave));
-  const int32_t W = nb * kIwWaves, me = wv * nb + (wg - first_wg);
+  // the others' waves while the head is walked, then all
+  const int32_t F = (G - n_wg) * kIwWaves, first = wg < n_wg ? kIwFirst : 0;
+  const int32_t mid = head + (all - head < kIwFirst * F ? all - head : kIwFirst * F);
+  auto entry = [&](int32_t r) {
+    return r < kIwFirst ? wq_entry(head, mid, r, F, wv * (G - n_wg) + wg - n_wg)
+                        : wq_entry(mid, all, r - kIwFirst, G * kIwWaves, wv * G + wg);
+  };
   const WalkArrays w = iw_arrays<kWalkSmallCap>(buf + wv * (kIwWords / kIwWaves));
-  int32_t x = wq_entry(head, all, 0, W, me);
+  int32_t r = first;
+  int32_t x = entry(r);
+  // (a wave without an entry in a first round may have one when all share)
+  while (x < 0 && r < kIwFirst) x = entry(++r);
   WqE nx{};
   if (x >= 0) nx = wq_get(B, x);
-  for (int32_t r = 1; x >= 0; ++r) {
+  while (x >= 0) {
     const WqE e = nx;
-    x = wq_entry(head, all, r, W, me);
+    x = entry(++r);
+    while (x < 0 && r < kIwFirst) x = entry(++r);
     if (x >= 0) nx = wq_get(B, x);
     const BJob J = job_at(B.jobs, e.job);
     // one member per lane up to kWave reads (a uniform branch), two above

@@ -1,7 +1,7 @@
 """The batch's pass over its work queue where its split changes: no, one, a few
-and many components above a wave's, fewer and more of them than half the
-workgroups, those above one pass's among them, and grids of two workgroups to
-all that are resident.  Equal to the oracle, element by element."""
+and many components above a wave's, fewer and more of them than workgroups,
+those above one pass's among them, and grids of two workgroups to all that are
+resident.  Equal to the oracle, element by element."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  (before the library, so that both use torch's HIP runtime)
