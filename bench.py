@@ -638,8 +638,14 @@ def reduce_bench(args):
     algo = 4 * (n + 1) + 9 * m + 4 * n + n + m + 4 * (n + 1) + 9 * m_s
     dom = max(prof, key=lambda k: prof[k][1])
     dom_us = 1e3 * prof[dom][1] / prof[dom][0]
-    # the dominant kernel's own share: R read once, marks written
-    dom_bytes = {"k_red_trans": 4 * (n + 1) + 9 * m + 4 * n + n + m}.get(dom, algo)
+    # the dominant kernel's own share.  k_red_contained: rows, overlaps and
+    # lengths read, flags and marks written; k_red_trans: the near entries (16
+    # bytes each, of rows and to reads that are not contained), their table and
+    # the flags read, a mark each written
+    left = out.contained[:n].cpu().numpy() == 0
+    near = int(np.count_nonzero(np.repeat(left, np.diff(r.row_ptr)) & left[r.col]))
+    dom_bytes = {"k_red_contained": 4 * (n + 1) + 4 * m + 4 * n + n + m,
+                 "k_red_trans": n + 8 * int(left.sum()) + 17 * near}.get(dom, algo)
     result = {
         "metric": "overlap-graph entries/s (contained-read pruning + transitive reduction)",
         "value": m / (wall * 1e-3),
@@ -660,8 +666,8 @@ def reduce_bench(args):
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE "
                                      "x1.0, profiles/reduce_50mbp_hbm_bytes.md)",
                      "avg_launch_us": dom_us, "bytes_per_launch": dom_bytes,
-                     "note": "k_red_trans re-reads each neighbour's row once per row that "
-                             "holds it (sum of squared degrees), bound by those lookups"},
+                     "note": "k_red_trans reads each neighbour's near entries once per row that "
+                             "holds it, bound by those lookups; its bytes count them once"},
     }
     if not args.no_cpu:
         import oracle
