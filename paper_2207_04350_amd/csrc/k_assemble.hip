@@ -36,12 +36,19 @@ static_assert(kAsmWalkCap % kAsmWalkBlock == 0, "whole members per thread");
 static_assert(kAsmWalkCap == kAsmWalkWaves * kWalkSmallCap, "the waves share the workgroup's LDS");
 constexpr int kAsmWalkWords = 13 * kAsmWalkCap + kAsmWalkCap / 2;  // 54 bytes per read
 constexpr int kAsmRaysCap = kAsmWalkWords / 2;
+// The look-back words that k_asm_offsets scans with start at zero: as a step of
+// its own it follows whatever call had the context's scratch last, and a
+// smaller graph's arrays lie where a larger one's words do.
 __global__ __launch_bounds__(kAsmWalkBlock, 5) void k_asm_walk(
-    cg_graph g, cg_parts parts, cg_local local, cg_contigs out, Scratch s, int n_big) {
+    cg_graph g, cg_parts parts, cg_local local, cg_contigs out, Scratch s, int n_big,
+    int n_status) {
   __shared__ alignas(16) uint32_t buf[kAsmWalkWords];
   __shared__ uint64_t sh_scan[kAsmWalkBlock / kWave + 1];
   __shared__ int s_n;
   __shared__ int32_t s_list[kAsmWalkBlock];
+  for (int64_t i = (int64_t)blockIdx.x * kAsmWalkBlock + threadIdx.x; i < n_status;
+       i += (int64_t)gridDim.x * kAsmWalkBlock)
+    s.scan_status[i] = 0;
   const int nc = *parts.d_n_comp;
   // the arrays of cap reads from read slot r0 of kAsmWalkCap on
   auto arrays = [&](int r0) {
@@ -114,6 +121,7 @@ __global__ __launch_bounds__(kAsmWalkBlock, 5) void k_asm_walk(
 // leave at once (110,000 contigs: 15 us, 146 us in one workgroup's rounds).
 constexpr int kOffRun = 8;  // contigs per thread, in registers
 constexpr int kOffItems = kOffRun * kScanBlock;
+static int offsets_blocks(int32_t n) { return (int)(((int64_t)n + kOffItems - 1) / kOffItems); }
 __global__ __launch_bounds__(kScanBlock) void k_asm_offsets(const int32_t *__restrict__ d_n_comp,
                                                             const uint64_t *__restrict__ len,
                                                             uint64_t *__restrict__ base_off,
@@ -282,8 +290,8 @@ int launch_contigs(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_pa
               parts.d_n_comp, s, out, chunk_target, ctx->fixed, so);
     return hip_check(hipGetLastError(), "k_asm");
   }
-  CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)((n + kOffItems - 1) / kOffItems)),
-            dim3(kScanBlock), st, parts.d_n_comp, out.len, out.base_off, out.cap_words,
+  CG_LAUNCH(ctx, k_asm_offsets, dim3((unsigned)offsets_blocks(n)), dim3(kScanBlock), st,
+            parts.d_n_comp, out.len, out.base_off, out.cap_words,
             out.d_total_words, ctx->fixed, scan_ctx(ctx, s));
   CG_LAUNCH(ctx, k_asm_copy, dim3(cgrid), dim3(kCopyBlock), st, g.seq, g.seq_words,
                      local.bin_vptr, P, s.piece_off, s.piece_len, s.piece_src, s.lay_contig,
@@ -308,7 +316,7 @@ int launch_assemble(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const cg_p
   const int n_big = n / (kWalkSmallCap + 1) < 2048 ? n / (kWalkSmallCap + 1) : 2048;
   const int64_t nw = ((int64_t)n / 2 + kAsmWalkWaves) / kAsmWalkWaves;
   CG_LAUNCH(ctx, k_asm_walk, dim3((unsigned)(n_big + (nw < 2048 ? nw : 2048))),
-            dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big);
+            dim3(kAsmWalkBlock), st, g, parts, local, out, s, n_big, offsets_blocks(n));
   return launch_contigs(ctx, g, s, parts, local, P, n, out, st, StatusOut{});
 }
 
