@@ -57,7 +57,10 @@ __device__ __forceinline__ void front_union(int32_t *par, int32_t a, int32_t b) 
 }
 
 __global__ __launch_bounds__(kFrontBlock) void k_front(FrontArgs a) {
-  __shared__ int32_t s_par[kFrontReads];
+  // (the bases weights take its place: 64-bit sums of the components of more
+  // than one read, half as many as reads at most)
+  __shared__ alignas(16) int32_t s_par[kFrontReads];
+  static_assert(kFrontReads % 2 == 0, "a 64-bit word per two reads");
   __shared__ int32_t s_cnt[kFrontReads];  // the edge a union is left for, then the counters
   __shared__ uint16_t s_list[kFrontReads];  // the reads with kept entries, in any order
   __shared__ uint8_t s_flag[kFrontReads];
