@@ -1802,35 +1802,53 @@ __device__ __forceinline__ void ray_st(T *p, T v) {
 // time, their loads issued together).  Every pass of the loop moves a ray
 // that has not ended at least one ray on, so it ends within q passes
 // whatever the other waves do, and within about log2 q when they keep up.
-template <typename RAY, int BLOCK, int U>
+// kVisit 0: a thread's U rays are all it has.  Else it goes round its rays,
+// kVisit jumps a visit, so that all of them keep up: where the reads are
+// numbered along the chain the rays after a thread's first ones are those of
+// its later visits, and taking the first ones to their ends went through these
+// one by one (one component of 12,000 reads: 36 ms, 0.2 ms so; in random order
+// 0.34 and 0.32 ms).
+template <typename RAY, int BLOCK, int U, int kVisit>
 __device__ __forceinline__ void walk_rays(typename RAY::T *ray, int n_rays, int tid) {
   typedef typename RAY::T T;
-  for (int r0 = tid; r0 < n_rays; r0 += U * BLOCK) {
-    T x[U];
-    bool more = false;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = r0 + u * BLOCK;
-      x[u] = r < n_rays ? ray_ld(ray + r) : RAY::kAtEnd;
-      more = more || RAY::next(x[u]) < RAY::kAtStart;
-    }
-    // (no more passes than reads, so that no input can keep it here)
-    for (int pass = 0; more && pass < n_rays / 2; ++pass) {
-      T y[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const T nx = RAY::next(x[u]);
-        y[u] = ray_ld(ray + (nx < RAY::kAtStart ? (int)nx : 0));
-      }
-      more = false;
+  constexpr bool kAll = kVisit == 0;
+  // (no more passes than reads, so that no input can keep it here)
+  const int visit = kAll ? n_rays / 2 : kVisit;
+  uint64_t ended = 0;  // the first 64 visits whose rays have all ended
+  bool again = true;
+  for (int turn = 0; again && turn <= n_rays / 2; ++turn) {
+    again = false;
+    uint64_t bit = 1;
+    for (int r0 = tid; r0 < n_rays; r0 += U * BLOCK, bit <<= 1) {
+      if (!kAll && (ended & bit)) continue;
+      T x[U];
+      bool more = false;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (RAY::next(x[u]) >= RAY::kAtStart) continue;
-        x[u] = RAY::jump(x[u], y[u]);
-        ray_st(ray + r0 + u * BLOCK, x[u]);
+        const int r = r0 + u * BLOCK;
+        x[u] = r < n_rays ? ray_ld(ray + r) : RAY::kAtEnd;
         more = more || RAY::next(x[u]) < RAY::kAtStart;
       }
+      for (int pass = 0; more && pass < visit; ++pass) {
+        T y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const T nx = RAY::next(x[u]);
+          y[u] = ray_ld(ray + (nx < RAY::kAtStart ? (int)nx : 0));
+        }
+        more = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (RAY::next(x[u]) >= RAY::kAtStart) continue;
+          x[u] = RAY::jump(x[u], y[u]);
+          ray_st(ray + r0 + u * BLOCK, x[u]);
+          more = more || RAY::next(x[u]) < RAY::kAtStart;
+        }
+      }
+      again = again || more;
+      ended |= more ? 0ull : bit;
     }
+    if constexpr (kAll) break;
   }
 }
 
@@ -1920,7 +1938,13 @@ __device__ __forceinline__ void walk_chain(const CompRec &cr, int q, int st, int
     }
   }
   wbar();
-  walk_rays<RAY, BLOCK, kLds ? 2 * CAP / BLOCK : 4>(ray, 2 * q, tid);
+  // (jumps a visit: 4, 8, 16, 48 on rays in global memory, 20 components of
+  // 20,000 reads: 885, 900, 920, 950 us; rays in LDS, eight a thread and 16
+  // jumps: the 50 Mbp graph's long contigs 118.0 us, four a thread 119.8)
+  if constexpr (kLds) walk_rays<RAY, BLOCK, 2 * CAP / BLOCK, 0>(ray, 2 * q, tid);
+  else if constexpr (kMode == kWalkGlobal) walk_rays<RAY, BLOCK, 4, 4>(ray, 2 * q, tid);
+  else if (q <= 2 * BLOCK) walk_rays<RAY, BLOCK, 4, 0>(ray, 2 * q, tid);
+  else walk_rays<RAY, BLOCK, 8, 16>(ray, 2 * q, tid);
   wbar();
   // 4. rank, predecessor, successor, orientation and piece of every read, U
   // reads of a thread at a time: what a read needs comes in three rounds of
