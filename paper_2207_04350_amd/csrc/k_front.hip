@@ -36,11 +36,19 @@ struct FrontArgs {
 __device__ __forceinline__ int32_t front_ld(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-__device__ __forceinline__ int32_t front_find(const int32_t *par, int32_t x) {
+// The climb halves the path behind it: where reads are numbered along the
+// genome every read's parent is the one before it, and climbs that leave the
+// path as it was take as many steps as the component has reads (a sorted chain
+// of 12,000 reads: 40.5 ms).  A halving store only ever puts an ancestor in
+// the place of a parent, so it takes nothing from a union beside it.
+__device__ __forceinline__ int32_t front_find(int32_t *par, int32_t x) {
   while (true) {
     const int32_t p = front_ld(par + x);
     if (p == x) return x;
-    x = p;
+    const int32_t gp = front_ld(par + p);
+    if (gp == p) return p;
+    __hip_atomic_store(par + x, gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    x = gp;
   }
 }
 // a larger root goes under a smaller one, so every climb ends

@@ -159,7 +159,20 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_hook(int32_t n, const int32_t *
   if (v >= n || (flags[v] & 6) != 6) return;
   const int32_t b = row_ptr[v];
   const int32_t u0 = col[b], u1 = col[b + 1];
-  if (u0 < v && u1 < v) uf_union(label, u0, u1);
+  if (u0 < v && u1 < v) {
+    uf_union(label, u0, u1);
+  } else if (u0 < v && v - u0 <= kSortedNear) {
+    // reads numbered along the genome: no read of such a run has a union but a
+    // cycle's last, which would climb all of it alone (a sorted cycle of 30,000
+    // reads: 7.7 ms); so the run's reads double their strides beside it
+    int32_t p = ld_relaxed(label + v);
+    while (true) {
+      const int32_t q = ld_relaxed(label + p);
+      if (q == p) break;
+      st_relaxed(label + v, q);
+      p = q;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kCcBlock) void k_cc_compress(int32_t n, int32_t *label) {
@@ -168,10 +181,11 @@ __global__ __launch_bounds__(kCcBlock) void k_cc_compress(int32_t n, int32_t *la
   int32_t x = (int32_t)v;
   int32_t p = ld_relaxed(label + x);
   if (p == x) return;
-  while (true) {
+  for (int hop = 0;; ++hop) {
     int32_t q = ld_relaxed(label + p);
     if (q == p) break;
     p = q;
+    if (hop >= kClimbQuiet) st_relaxed(label + v, p);
   }
   st_relaxed(label + v, p);
 }

@@ -106,19 +106,22 @@ __global__ __launch_bounds__(kChunkBlock) void k_part_count(int32_t n, int round
       if constexpr (kBases) s_w[i] = 0;
     }
     if constexpr (kFind) {
-      // both reads' climbs side by side
+      // both reads' climbs side by side; a long one leaves where it has got to
       bool more = true;
       int32_t first[kChunkPer];
 #pragma unroll
       for (int k = 0; k < kChunkPer; ++k) first[k] = root[k];
-      while (more) {
+      for (int hop = 0; more; ++hop) {
         int32_t p[kChunkPer];
 #pragma unroll
         for (int k = 0; k < kChunkPer; ++k) p[k] = (f[k] & 6u) ? ld_relaxed(label + root[k]) : root[k];
         more = false;
 #pragma unroll
         for (int k = 0; k < kChunkPer; ++k) {
-          more = more || p[k] != root[k];
+          if (p[k] != root[k]) {
+            more = true;
+            if (hop >= kClimbQuiet) st_relaxed(label + v[k], p[k]);
+          }
           root[k] = p[k];
         }
       }
