@@ -294,14 +294,15 @@ __device__ __forceinline__ uint32_t wave_xor_u32(uint32_t x) {
 }
 
 // Bitonic sort of one value per lane across the wave, ascending in lane
-// order: stage (K, J) for K = 2..64, J = K/2..1.  All lanes active.
-template <int K = 2, int J = 1>
+// order: stage (K, J) for K = 2..64, J = K/2..1; of the first LANES lanes
+// where the others hold the largest value.  All lanes active.
+template <int LANES = kWave, int K = 2, int J = 1>
 __device__ __forceinline__ uint32_t wave_sort_u32(uint32_t x, int l) {
   const uint32_t p = wave_xor_u32<J>(x);
   const bool keep_min = ((l & J) == 0) == ((l & K) == 0);
   x = keep_min ? min(x, p) : max(x, p);
-  if constexpr (J > 1) return wave_sort_u32<K, J / 2>(x, l);
-  else if constexpr (K < kWave) return wave_sort_u32<2 * K, K>(x, l);
+  if constexpr (J > 1) return wave_sort_u32<LANES, K, J / 2>(x, l);
+  else if constexpr (K < LANES) return wave_sort_u32<LANES, 2 * K, K>(x, l);
   else return x;
 }
 
@@ -676,6 +677,13 @@ __device__ __forceinline__ uint32_t lpt_item_weight(const uint32_t *srt, const u
 constexpr int kBinBits = 16;
 constexpr int kLptRoundMin = 4;   // equal items taken as one round from this many
 constexpr int kLptPrefixMin = 5;  // prefix rounds (any weights) from this many items
+// Up to this many bins item by item without a round's tests, which cost as
+// much as several items and place few.  7,000 one-read components, 16 bins: 290
+// us either way, 24 bins: 288 us item by item, 215 in rounds; weights of many
+// values, 16 bins: 338 and 505 us, 24 bins: 340 and 374; one to three bins,
+// where no round comes about: 281 and 1,620.
+constexpr int kLptStepBins = 16;
+constexpr int kLptSteps = 8;  // items a turn there, a divisor of the wave's lanes
 constexpr int kLptBlockBins = 256;  // rounds over the whole list from this many bins
 constexpr int kLptBlockMin = 96;    // ... where they place this many items
 constexpr int kLptBulkMin = 256;  // whole rounds of equal items taken at once from this many
@@ -939,6 +947,44 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     }
     if (nc - lo >= 4 * P && wl > 0) s_last = __builtin_amdgcn_readfirstlane(lo);
   }
+  // (wave 0) Whole rounds of equal items from item `at` on, weight q, if there
+  // are: the m lanes below lane 0's raised key take an item each in order, J
+  // times over, for as long as all of them stay below lane m's key (to the
+  // run's end when they are all bins).  The workgroup stores these items' bins.
+  uint64_t load0 = 0;  // what narrow keys are relative to
+  auto whole_rounds = [&](int at, uint32_t q, uint32_t iw, uint32_t &key) {
+    const int l = tid;
+    const uint32_t bmask = (1u << kb) - 1u;
+    if (at + kLptBulkMin <= nc && q > 0 &&
+        q == 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, kWave - 1)) {
+      const uint32_t qe = (uint32_t)__builtin_amdgcn_readfirstlane(
+          (int)lpt_item_weight(srt, keys, k32, at + kLptBulkMin - 1));
+      if (q == qe) {
+        const uint32_t wk = q << kb;
+        const int m =
+            __popcll(__ballot(key < (uint32_t)__builtin_amdgcn_readlane((int)key, 0) + wk));
+        uint32_t J = (uint32_t)((lpt_run_end(srt, keys, k32, at, nc, q) - at) / m);
+        if (m < W) {
+          const uint32_t jm = ((uint32_t)__builtin_amdgcn_readlane((int)key, m) - 1u -
+                               (uint32_t)__builtin_amdgcn_readlane((int)key, m - 1)) / wk + 1u;
+          J = J < jm ? J : jm;
+        }
+        const int items = (int)(J * (uint32_t)m);
+        if (items >= kLptBulkMin) {
+          if (l < m) s_opbin[l] = (int32_t)(key & bmask);
+          if (l == 0) {
+            s_op_at = at;
+            s_op_items = items;
+            s_op_bins = m;
+          }
+          if (m == W) load0 += (uint64_t)J * wk;  // every key: the order stays
+          else key = lpt_merge_lanes(l < m ? key + J * wk : key, l, m);
+          return true;
+        }
+      }
+    }
+    return false;
+  };
   int cur = 0;
   while (i0 < nc) {
     if (kBig && i0 >= s_last) {
@@ -1069,7 +1115,6 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     if (blocks && lim > i0 + 2 * kWave) lim = i0 + 2 * kWave;
     uint32_t key32 = 0xFFFFFFFFu;  // wave 0: the window's keys (narrow or wide)
     uint64_t key64 = ~0ull;
-    uint64_t load0 = 0;  // what narrow keys are relative to
     if (tid < kWave) {
       load0 = binA[0] >> bb << bb;
       if (narrow) key32 = tid < W ? (uint32_t)(binA[tid] - load0) : 0xFFFFFFFFu;
@@ -1078,7 +1123,45 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
     while (i0 < lim) {
       const int T = single_window ? nc - i0 : (lim - i0 < W ? lim - i0 : W);
       if (kBig && tid == 0) s_op_items = 0;
-      if (tid < kWave && narrow) {
+      if (tid < kWave && narrow && P <= kLptStepBins) {
+        // Few bins (one window): no rounds but whole ones.  Item by item, lane
+        // 0's bin takes it, and its raised key nk goes among the others, which
+        // move down by one: lane l gets the middle one of its own key, lane
+        // l + 1's and nk.  (Lanes from W on hold the largest value; lanes past
+        // the items raise nothing, so that a step of theirs changes nothing.)
+        const int l = tid;
+        const uint32_t bmask = (1u << kb) - 1u;
+        uint32_t key = key32;
+        for (int base = 0; base < T; base += kWave) {
+          const uint32_t sub = (uint32_t)__builtin_amdgcn_readlane((int)key, 0) & ~bmask;
+          key -= l < W ? sub : 0u;
+          load0 += sub;
+          const int at = i0 + base, cnt = T - base < kWave ? T - base : kWave;
+          uint64_t item = 0;
+          if (l < cnt)
+            item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at + l] >> 16)) << 32) | (srt[at + l] & 0xFFFFu)
+                       : keys[at + l];
+          const uint32_t iw = (uint32_t)(item >> 32);
+          const uint32_t q = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, 0);
+          if (kBig && whole_rounds(at, q, iw, key)) break;
+          const uint32_t add = l < cnt ? (0xFFFFFFFFu - iw) << kb : 0u;
+          int32_t mine = 0;  // bin of item l
+          for (int t0 = 0; t0 < cnt; t0 += kLptSteps) {
+#pragma unroll
+            for (int t = t0; t < t0 + kLptSteps; ++t) {
+              const uint32_t k0 = (uint32_t)__builtin_amdgcn_readlane((int)key, 0);
+              const uint32_t nk = k0 + (uint32_t)__builtin_amdgcn_readlane((int)add, t);
+              mine = l == t ? (int32_t)(k0 & bmask) : mine;
+              const uint32_t nxt = (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)key, 0x130, 0xF,
+                                                                         0xF, false);  // wave_shl:1
+              key = min(nxt, max(nk, key));
+            }
+          }
+          if (l < cnt) bin_of[(uint32_t)item] = mine;
+        }
+        if (l < W) win[cur][l] = load0 + key;
+        key32 = key;
+      } else if (tid < kWave && narrow) {
         const int l = tid;
         const uint32_t bmask = (1u << kb) - 1u;
         uint32_t key = key32;
@@ -1096,42 +1179,11 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
           }
           int32_t mine = 0;  // bin of item l
           const uint32_t iw = (uint32_t)(item >> 32);
-          // Whole rounds of equal items: the m lanes below lane 0's raised key
-          // take an item each in order, J times over, for as long as all of
-          // them stay below lane m's key (to the run's end when they are all
-          // bins).  The workgroup stores these items' bins.
-          // (Not in the LDS forms: the few components they hold gain less from
-          // it than other graphs lose, 1.5 us of 25.)
+          // (no whole rounds in the LDS forms: at 64 bins the few components they
+          // hold gain less from it than other graphs lose, 1.5 us of 25)
           const int at = i0 + base;
           const uint32_t q = 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, 0);
-          if (kBig && single_window && at + kLptBulkMin <= nc && q > 0 &&
-              q == 0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)iw, kWave - 1)) {
-            const uint32_t qe = (uint32_t)__builtin_amdgcn_readfirstlane(
-                (int)lpt_item_weight(srt, keys, k32, at + kLptBulkMin - 1));
-            if (q == qe) {
-              const uint32_t wk = q << kb;
-              const int m =
-                  __popcll(__ballot(key < (uint32_t)__builtin_amdgcn_readlane((int)key, 0) + wk));
-              uint32_t J = (uint32_t)((lpt_run_end(srt, keys, k32, at, nc, q) - at) / m);
-              if (m < W) {
-                const uint32_t jm = ((uint32_t)__builtin_amdgcn_readlane((int)key, m) - 1u -
-                                     (uint32_t)__builtin_amdgcn_readlane((int)key, m - 1)) / wk + 1u;
-                J = J < jm ? J : jm;
-              }
-              const int items = (int)(J * (uint32_t)m);
-              if (items >= kLptBulkMin) {
-                if (l < m) s_opbin[l] = (int32_t)(key & bmask);
-                if (l == 0) {
-                  s_op_at = at;
-                  s_op_items = items;
-                  s_op_bins = m;
-                }
-                if (m == W) load0 += (uint64_t)J * wk;  // every key: the order stays
-                else key = lpt_merge_lanes(l < m ? key + J * wk : key, l, m);
-                break;
-              }
-            }
-          }
+          if (kBig && single_window && whole_rounds(at, q, iw, key)) break;
           for (int t = 0; t < cnt;) {
             const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)iw, t);
             const uint32_t q = 0xFFFFFFFFu - wt;
@@ -1167,7 +1219,12 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
               const uint32_t prev = wave_prev_u32(r);  // by every lane, before the test
               const bool down = l > 0 && l < cp && prev > r;
               key = l < cp ? r : key;
-              key = __ballot(down) ? wave_sort_u32(key, l) : lpt_merge_lanes(key, l, cp);
+              if (__ballot(down)) {
+                key = wave_sort_u32<32>(key, l);
+                if (W > 32) key = wave_sort_u32<kWave, kWave, 32>(key, l);
+              } else {
+                key = lpt_merge_lanes(key, l, cp);
+              }
               t += cp;
               // the next items at once, so that a round is not cut short by
               // the end of the lanes' items
