@@ -646,12 +646,12 @@ __device__ __forceinline__ int lower_bound_u64(const uint64_t *a, int len, uint6
   return lo;
 }
 
-// x of lane l + 1 in lane l, by a DPP wave shift (wave_shl:1); lane 63,
-// which has no source, keeps its own x
+// x of lane l + 1 in lane l, by a DPP wave shift (wave_shl:1), and the largest
+// value in lane 63, which has no source
 __device__ __forceinline__ uint64_t wave_next_u64(uint64_t x) {
   const int lo = (int)(uint32_t)x, hi = (int)(uint32_t)(x >> 32);
-  const uint32_t nlo = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xF, 0xF, false);
-  const uint32_t nhi = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xF, 0xF, false);
+  const uint32_t nlo = (uint32_t)__builtin_amdgcn_update_dpp(-1, lo, 0x130, 0xF, 0xF, false);
+  const uint32_t nhi = (uint32_t)__builtin_amdgcn_update_dpp(-1, hi, 0x130, 0xF, 0xF, false);
   return ((uint64_t)nhi << 32) | nlo;
 }
 
@@ -684,6 +684,7 @@ constexpr int kLptPrefixMin = 5;  // prefix rounds (any weights) from this many 
 // where no round comes about: 281 and 1,620.
 constexpr int kLptStepBins = 16;
 constexpr int kLptSteps = 8;  // items a turn there, a divisor of the wave's lanes
+constexpr int kLptWideSteps = 4;  // and with wide keys (2, 4, 8 a turn: 730, 691, 703 us)
 constexpr int kLptBlockBins = 256;  // rounds over the whole list from this many bins
 constexpr int kLptBlockMin = 96;    // ... where they place this many items
 constexpr int kLptBulkMin = 256;  // whole rounds of equal items taken at once from this many
@@ -752,10 +753,14 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   __shared__ int32_t s_op_at, s_op_items, s_op_bins;  // first item, items (0: none), bins
   __shared__ int32_t sh_scan[BLOCK / kWave + 1];
   __shared__ int64_t sh_scan64[BLOCK / kWave + 1];
+  __shared__ unsigned long long s_total;
   __shared__ unsigned int s_wmax;
   const int tid = threadIdx.x;
   const int N2 = next_pow2(nc > 4 ? nc : 4);
-  if (tid == 0) s_wmax = 0;
+  if (tid == 0) {
+    s_total = 0;
+    s_wmax = 0;
+  }
   __syncthreads();
 
   // 1. sort by (weight desc, label asc); components are indexed in label
@@ -880,8 +885,23 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
   // differences.  The bin lists hold whole 64-bit keys.
   int kb = 0;
   while ((1 << kb) < P) ++kb;
-  const bool narrow =
+  // Where one component outweighs the others by far that bound fails, but all
+  // weights together may still be below 2^(32 - kb), and so is then every load
+  // and every raised one (an item is added to a load that it is not part of):
+  // 7,000 components and one of 18 Mbases, 64 bins: 310 us, 856 with wide keys.
+  bool narrow =
       kb <= 16 && (unsigned long long)s_wmax * ((kWave + W - 1) / W + 4) + 1 < (1ull << (32 - kb));
+  if (!narrow && kb <= 16) {
+    unsigned long long sum = 0;
+    for (int i = tid; i < nc; i += BLOCK) {
+      const uint64_t w = weight ? weight[i] : (uint64_t)comp_size[i];
+      sum += w > 0xFFFFFFFFull ? 0xFFFFFFFFull : w;
+    }
+    sum = wave_sum(sum);
+    if (lane_id() == 0) atomicAdd(&s_total, sum);
+    __syncthreads();
+    narrow = s_total + 1 < (1ull << (32 - kb));
+  }
   const int bb = narrow ? kb : kBinBits;
   int i0 = 0;
   if (!single_window && nc > P) {
@@ -1263,20 +1283,18 @@ __device__ __forceinline__ int lpt_body(int nc, int P, const int32_t *__restrict
             item = k32 ? ((uint64_t)(0xFFFF0000u | (srt[at] >> 16)) << 32) | (srt[at] & 0xFFFFu)
                        : keys[at];
           }
+          // item by item, as with few bins and narrow keys
+          const uint64_t add =
+              l < cnt ? (uint64_t)(0xFFFFFFFFu - (uint32_t)(item >> 32)) << kBinBits : 0ull;
           int32_t mine = 0;  // bin of item l, kept in lane l until the batch ends
-          for (int t = 0; t < cnt; ++t) {
-            // t is uniform: broadcasts are lane reads into scalar registers
-            const uint64_t q =
-                0xFFFFFFFFu - (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(item >> 32), t);
-            const uint64_t k0 =
-                ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key >> 32), 0) << 32) |
-                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, 0);
-            mine = l == t ? (int32_t)(k0 & ((1u << kBinBits) - 1)) : mine;
-            const uint64_t nk = k0 + (q << kBinBits);
-            const int p = __popcll(__ballot(key < nk)) - 1;  // lanes 1.. below nk
-            // the key of lane l + 1 (a wave-wide DPP shift; lane 63 keeps its own)
-            const uint64_t nxt = wave_next_u64(key);
-            key = l < p ? nxt : (l == p ? nk : key);
+          for (int t0 = 0; t0 < cnt; t0 += kLptWideSteps) {
+#pragma unroll
+            for (int t = t0; t < t0 + kLptWideSteps; ++t) {
+              const uint64_t k0 = wave_lane(key, 0), nk = k0 + wave_lane(add, t);
+              mine = l == t ? (int32_t)(k0 & ((1u << kBinBits) - 1)) : mine;
+              const uint64_t nxt = wave_next_u64(key), x = nk > key ? nk : key;
+              key = nxt < x ? nxt : x;
+            }
           }
           if (l < cnt) bin_of[(uint32_t)item] = mine;
         }
