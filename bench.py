@@ -645,7 +645,7 @@ def reduce_bench(args):
     left = out.contained[:n].cpu().numpy() == 0
     near = int(np.count_nonzero(np.repeat(left, np.diff(r.row_ptr)) & left[r.col]))
     dom_bytes = {"k_red_contained": 4 * (n + 1) + 4 * m + 4 * n + n + m,
-                 "k_red_trans": n + 8 * int(left.sum()) + 17 * near}.get(dom, algo)
+                 "k_red_trans": n + 8 * int(left.sum()) + 17 * near}.get(dom.split("<")[0], algo)
     result = {
         "metric": "overlap-graph entries/s (contained-read pruning + transitive reduction)",
         "value": m / (wall * 1e-3),

@@ -51,7 +51,17 @@ constexpr int kRedWaves = 4;
 constexpr int kRedBlock = kRedWaves * kWave;
 constexpr int kRedCap = 256;   // row entries k_red_trans holds in registers
 constexpr int kRedPer = kRedCap / kWave;
-constexpr int kRedNear = 128;  // neighbours not contained it holds in LDS (11 KB a workgroup)
+// Neighbours not contained that k_red_trans holds in LDS: 11 or 22 KB a
+// workgroup, which is resident waves (100 Mbp at 15x, rows of 28 entries: 551 us
+// with room for 128, 777 for 256).  More than 128 they are where the rows have
+// well above 128 entries and most reads stay (reads of one length at 70x to
+// 120x: 1.2 to 6.7 ms with room for 256, 2.5 to 14 with the rows read in place),
+// so the room goes by the entries per read.  (Where they are twice kRedCap and
+// more, nearly every row is read in place, and the room serves none: 618 us
+// with 128, 635 with 256.)
+constexpr int kRedNear = 128, kRedNearWide = 256;
+constexpr int kRedWideRow = 96;  // entries per read from which it is kRedNearWide
+static_assert(kRedNearWide == kRedCap, "no row that fits the registers is read in place");
 constexpr int kRedRows = 64;     // rows per workgroup at most: a lane of a wave each
 constexpr int kRedShards = 64;   // parts of the near entries' memory at most, a cursor each
 // words between the cursors: atomics on one line queue up (about 4.5 ns each:
@@ -220,8 +230,8 @@ __global__ __launch_bounds__(kRedBlock) void k_red_near(cg_graph g, int R,
   }
 }
 
-// Row u longer than kRedCap or with more near neighbours than kRedNear, read
-// in place: one neighbour at a time, marks straight to kept.
+// Row u longer than kRedCap or with more near neighbours than LDS has room
+// for, read in place: one neighbour at a time, marks straight to kept.
 __device__ void red_trans_long(const cg_graph &g, uint32_t fuzz, const uint8_t *contained,
                                uint8_t *kept, int32_t u, int32_t a, int32_t du, int lane) {
   const int32_t *rc = g.col + a;
@@ -243,18 +253,19 @@ __device__ void red_trans_long(const cg_graph &g, uint32_t fuzz, const uint8_t *
   }
 }
 
+template <int kNear>
 __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fuzz, int R,
                                                          const uint8_t *__restrict__ contained,
                                                          uint8_t *kept, RedNear near) {
   // u's near neighbours in column order: their ids, overlaps, first entries
   // (near ones, or of the whole row: bit 2 of the strands), the pairs of those
   // before, lengths, strands and marks
-  __shared__ int32_t sh_col[kRedWaves][kRedNear];
-  __shared__ uint32_t sh_ovl[kRedWaves][kRedNear];
-  __shared__ int32_t sh_vb[kRedWaves][kRedNear];
-  __shared__ int32_t sh_pfx[kRedWaves][kRedNear];
-  __shared__ uint32_t sh_vlen[kRedWaves][kRedNear];
-  __shared__ uint8_t sh_str[kRedWaves][kRedNear], sh_mark[kRedWaves][kRedNear];
+  __shared__ int32_t sh_col[kRedWaves][kNear];
+  __shared__ uint32_t sh_ovl[kRedWaves][kNear];
+  __shared__ int32_t sh_vb[kRedWaves][kNear];
+  __shared__ int32_t sh_pfx[kRedWaves][kNear];
+  __shared__ uint32_t sh_vlen[kRedWaves][kNear];
+  __shared__ uint8_t sh_str[kRedWaves][kNear], sh_mark[kRedWaves][kNear];
   __shared__ int s_next;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
   if (threadIdx.x == 0) s_next = kRedWaves;
@@ -276,7 +287,7 @@ __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fu
     const int32_t du = __builtin_amdgcn_readlane(blk.entries, r);
     const int32_t own = __builtin_amdgcn_readlane(tab.x, r);
     int nf = own >= 0 ? __builtin_amdgcn_readlane(tab.y, r) : 0;
-    bool longer = own >= 0 ? nf > kRedNear : du > kRedCap;
+    bool longer = own >= 0 ? nf > kNear : du > kRedCap;
     if (!longer) {
       // the near neighbours, a lane each: rounds of 64 near entries, or of the
       // whole row
@@ -321,7 +332,7 @@ __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fu
           f[k] = nf + __popcll(m & ((1ull << lane) - 1ull));
           nf += __popcll(m);
         }
-        longer = nf > kRedNear;
+        longer = nf > kNear;
         if (longer) {
           nf = 0;  // read in place below: nothing of it goes to LDS
 #pragma unroll
@@ -583,7 +594,12 @@ int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuz
     CG_LAUNCH(ctx, k_red_contained, dim3((unsigned)groups), dim3(kRedBlock), st, g, contained,
               kept, near.cursors, shards);
     CG_LAUNCH(ctx, k_red_near, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, near);
-    CG_LAUNCH(ctx, k_red_trans, dim3(nb), dim3(kRedBlock), st, g, fuzz, R, contained, kept, near);
+    if (g.m >= (int64_t)kRedWideRow * n && g.m < (int64_t)2 * kRedCap * n)
+      CG_LAUNCH(ctx, k_red_trans<kRedNearWide>, dim3(nb), dim3(kRedBlock), st, g, fuzz, R,
+                contained, kept, near);
+    else
+      CG_LAUNCH(ctx, k_red_trans<kRedNear>, dim3(nb), dim3(kRedBlock), st, g, fuzz, R, contained,
+                kept, near);
     CG_LAUNCH(ctx, k_red_keep, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, counts,
               blocks);
     if (nb > kRedDirect) CG_LAUNCH(ctx, k_red_sums, dim3(1), dim3(kScanBlock), st, nb, blocks);

@@ -1,0 +1,89 @@
+"""cg_reduce on reads of about one length, of which hardly any is contained in
+another: rows of 129 to 256 neighbours that stay (and some above), fewer, and
+both in one graph.  Equal to the oracle's, element by element; and rows of 150
+neighbours do not cost a multiple of what their pairs do (read in place, one
+neighbour at a time, they took twice as long as with room in LDS)."""
+import numpy as np
+import pytest
+import torch  # before the library, so that both use torch's HIP runtime
+
+import synth
+from tests.test_gpu_reduce import cg, check  # noqa: F401  (cg is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _overlaps(G, cov, mean, sd, seed, runs=()):
+    """The overlap graph of cov times G bases of reads of mean +- sd bases;
+    runs: (start, bases, cov) of further reads there."""
+    rng = np.random.default_rng(seed)
+    parts = [(0, G, cov)] + list(runs)
+    n = [int(round(g * c / mean)) for _, g, c in parts]
+    ln = np.maximum(1200, np.rint(rng.normal(mean, sd, sum(n)))).astype(np.int64)
+    a = np.concatenate([s + rng.integers(0, g - mean // 2, k) for (s, g, _), k in zip(parts, n)])
+    a = np.minimum(a, G - ln)
+    rc = rng.integers(0, 2, len(a))
+    ids = rng.permutation(len(a))
+    order = np.lexsort((ids, -(a + ln), a))
+    A, B = a[order], (a + ln)[order]
+    us, vs, os_ = [], [], []
+    for k in range(1, len(a)):
+        ov = np.minimum(B[:-k], B[k:]) - A[k:]
+        if not (A[k:] + 1000 <= B[:-k]).any():
+            break
+        i = np.nonzero((A[k:] + 1000 <= B[:-k]) & (ov >= 1000))[0]
+        us.append(order[i])
+        vs.append(order[i + k])
+        os_.append(ov[i])
+    u, v, o = (np.concatenate(x) for x in (us, vs, os_))
+    s, d = rc[u], rc[v]
+    N = len(a)
+    rl = np.empty(N, np.uint32)
+    rl[ids] = ln
+    row_ptr, col, ovl, strand = synth.gen.csr_from_edges(N, ids[u], ids[v], o, s, d)
+    return synth.StringGraph(n=N, m=len(col), row_ptr=row_ptr, col=col, ovl=ovl, strand=strand,
+                             read_len=rl, read_off=np.zeros(N, np.uint64),
+                             seq=np.zeros(1, np.uint32))
+
+
+CASES = {
+    # reads, overlap reads of one length: about 2 cov (1 - 1000 / mean) neighbours a read
+    "rows below 128": (200_000, 55, 6000, 3, ()),
+    "rows around 128": (200_000, 75, 6000, 3, ()),
+    "rows around 256": (200_000, 150, 6000, 3, ()),
+    "spread lengths": (200_000, 120, 6000, 300, ()),
+    # mostly short rows, long ones where a repeat gathers reads
+    "a few long rows": (900_000, 9, 6000, 3, ((300_000, 12_000, 90), (600_000, 12_000, 200))),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("fuzz", [0, 4])
+def test_one_length(cg, name, fuzz):  # noqa: F811
+    r = _overlaps(*CASES[name][:4], seed=3, runs=CASES[name][4])
+    got = check(cg, r, fuzz, name=name)[0]
+    left = np.flatnonzero(got["contained"] == 0)
+    rows = np.diff(r.row_ptr)[left]
+    assert len(left) > 0.5 * r.n or name == "spread lengths"
+    if "long" in name or "128" in name:
+        assert rows.min() < 128 < rows.max()
+
+
+def test_longer_rows_cost_their_pairs(cg):  # noqa: F811
+    us, pairs = {}, {}
+    for cov in (60, 80):
+        r = _overlaps(1_000_000, cov, 12_000, 3, seed=4)
+        print("reduce time", cov, r.n, r.m, flush=True)
+        ctx, dg, out = cg.Context.for_graph(r.n, r.m, 1), cg.DeviceGraph(r), cg.Reduced(r.n, r.m)
+        t = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            cg.reduce(ctx, dg, out)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(1e3 * a.elapsed_time(b))
+        ctx.close()
+        deg = np.diff(r.row_ptr).astype(np.float64)
+        us[cov], pairs[cov] = min(t[1:]), float((deg[r.col]).sum())
+    assert us[80] / us[60] < 1.5 * pairs[80] / pairs[60], (us, pairs)
