@@ -8,7 +8,8 @@
 //  k_red_near       the entries of a row that lead to reads that are not
 //                   contained, with overlap, strands, place in the row and the
 //                   read's length, side by side (rows up to kRedCap entries,
-//                   while the scratch has room)
+//                   while the scratch has room; none at all where the rows are
+//                   short and most reads stay, see red_crowded)
 //  k_red_trans      row u's near neighbours v in LDS with, for each, where v's
 //                   near entries start and how many there are; the lanes
 //                   then take the (v, v->x) pairs of all neighbours together
@@ -24,20 +25,21 @@
 //                   the blocks before its own) and the kept entries in R's
 //                   column order
 //
-// Most reads of an overlap graph are contained (88% at 30x), and these rows
-// are done after the first pass.  A workgroup of the later passes takes a
-// block of up to 64 rows and its waves only those that are not contained, a
-// wave each, so that the resident waves all have a row to work on: with a
-// wave per row, contained or not, four rows to a workgroup, two thirds of a
-// workgroup's waves had left while its LDS stayed taken.  One pass moves a
+// Where read lengths spread, most reads are contained (88% at 30x, 12 +- 4
+// kbp), and these rows are done after the first pass.  A workgroup of the later
+// passes takes a block of up to 64 rows and its waves only those that are not
+// contained, a wave each, so that the resident waves all have a row to work on:
+// with a wave per row, contained or not, four rows to a workgroup, two thirds of
+// a workgroup's waves had left while its LDS stayed taken.  One pass moves a
 // row's dependent loads (row, neighbour, neighbour's row, overlap) one after
 // another, so resident waves are what bounds it.  At 30x a read that is not
 // contained has 70 entries, 11 of them to others like it: the near entries
 // leave 1.8 M pairs of 11.5 M (50 Mbp: k_red_near 15 and k_red_trans 26 us;
 // 97 us on whole rows, 224 us with a wave per row besides).
 //
-// kept[e] starts with whether the entry's read is contained in bit 2
-// (k_red_near), carries the mark in bit 0 (k_red_trans), the decision in
+// kept[e] starts with whether the entry's read is contained in bit 2 (k_red_near
+// for the rows with near entries and those above kRedCap, k_red_trans for those
+// that it reads in full), carries the mark in bit 0 (k_red_trans), the decision in
 // bit 1 (k_red_keep), and ends as 0 / 1 (k_red_compact).
 //
 // The overhang test: sfx(x->y) = len(y) - ovl(x->y), and
@@ -70,14 +72,31 @@ constexpr int kRedCursor = 64;
 constexpr int kRedList = 256;    // surviving entries a wave of k_red_keep collects
 constexpr int kRedDirect = 4096;  // blocks whose counts each workgroup of k_red_compact adds up itself
 constexpr int kRedGroup = 16;    // lanes per row of k_red_contained
+// A read's near entries from which filling their room does not pay, where the
+// rows are short; with longer ones the pairs saved outweigh the pass (10 Mbp at
+// 45x, 30 near entries a read: 20 us of it save 34, at 10x, 14 of them: 4 save 2)
+constexpr uint32_t kRedCrowd = 8;
+constexpr int kRedShortRow = 40;  // entries per read
+// the sample's words: rows that stay times this, plus their entries
+constexpr uint32_t kRedStay = 1u << 20;
+static_assert(2 * kWave * (kWave / kRedGroup) * kRedCap < (int)kRedStay &&
+              2 * kWave * (kWave / kRedGroup) < 1 << 12, "the sample's sums fit a word");
 
 // Rows per workgroup: kRedRows, or fewer where that leaves the chip's 256
 // compute units short of workgroups, at least one per wave.
-static int red_rows(int32_t n) {
+static int red_rows(int32_t n, int blocks) {
   int R = kRedRows;
-  while (R > kRedWaves && n / R < 1024) R >>= 1;
+  while (R > kRedWaves && n / R < blocks) R >>= 1;
   return R;
 }
+constexpr int kRedBlocks = 1024;
+// k_red_trans, whose rows take unequal time, wants more of them (8,333 reads of
+// about one length at 10x: 26 us instead of 37; 50 Mbp at 30x 38.8 and 40.5,
+// with 4,096 39.3, 17 Mbp 24.0 and 27.7), and its wide instance, with most rows
+// to work on, more still (2 Mbp at 100x: 4.04 ms with 2,048, 3.20 with 4,096);
+// not so where nearly every row is read in place (0.3 Mbp at 600x: 1.87 ms with
+// 1,024, 2.00 with 2,048).
+constexpr int kRedTransBlocks = 2048, kRedWideBlocks = 4096;
 
 // 16 lanes per row, four entries each in flight: a row has 55 entries on
 // average at 30x.  Only an entry that covers the read (ovl >= len) needs its
@@ -86,7 +105,9 @@ static int red_rows(int32_t n) {
 __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t *contained,
                                                              uint8_t *__restrict__ kept,
                                                              int32_t *__restrict__ cursors,
-                                                             int32_t shards) {
+                                                             int32_t shards,
+                                                             uint32_t *__restrict__ sample,
+                                                             int stride) {
   const int64_t t = (int64_t)blockIdx.x * kRedBlock + threadIdx.x;
   if (t < shards) cursors[t * kRedCursor] = 0;
   const int64_t row = t / kRedGroup;
@@ -117,8 +138,46 @@ __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t
     found = found || (__ballot(c) & group) != 0ull;
   }
   if (live && gl == 0) contained[v] = found ? 1 : 0;
+  // a sampled wave's rows that stay, and their entries (see red_crowded)
+  const int64_t wave = t / kWave;
+  if (__builtin_amdgcn_readfirstlane((int)(wave & ((1 << stride) - 1))) == 0) {
+    const uint32_t stay =
+        wave_sum(live && gl == 0 && !found ? kRedStay + (uint32_t)(d <= kRedCap ? d : 0) : 0u);
+    if (lane_id() == 0) sample[wave >> stride] = stay;
+  }
   if (found)
     for (int32_t i = gl; i < d; i += kRedGroup) kept[a + i] = 0;
+}
+
+// Whether most reads stay, so that the near entries would need far more room
+// than there is: then no row has any, and all are read in full.  Told from a
+// sample of the rows, the same for every wave that asks: the entries of rows
+// that stay times the share of reads that do is within some percent of the near
+// entries (reads of one length at 10x: 18.3 a read, of 12 +- 4 kbp at 8x to 30x
+// 2.5 to 1.8).  With room for four a read, filling it does not pay above
+// kRedCrowd.
+// red_sample loads it, ahead of the loads that do not depend on the answer: the
+// first pass's waves of 64 / kRedGroup rows, every 2^k-th of them, 64 to 127.
+__host__ __device__ __forceinline__ int32_t red_waves(int32_t n) {
+  return (int32_t)(((int64_t)n * kRedGroup + kWave - 1) / kWave);
+}
+__host__ __device__ __forceinline__ int red_stride(int32_t n) {  // k
+  int k = 0;
+  while (red_waves(n) >> k >= 2 * kWave) ++k;
+  return k;
+}
+struct RedSample {
+  uint32_t lane, rows;
+};
+__device__ __forceinline__ RedSample red_sample(const uint32_t *sample, int32_t n, int k) {
+  const int32_t ns = (red_waves(n) + (1 << k) - 1) >> k;
+  const int l = lane_id();
+  return RedSample{(l < ns ? sample[l] : 0u) + (l + kWave < ns ? sample[l + kWave] : 0u),
+                   (uint32_t)ns * (kWave / kRedGroup)};
+}
+__device__ __forceinline__ bool red_crowded(const RedSample &s) {
+  const uint32_t x = wave_sum(s.lane);
+  return x / kRedStay * (x % kRedStay) > kRedCrowd * s.rows * s.rows;
 }
 
 // A workgroup's block of R rows: lane r holds row r's first entry and its
@@ -168,16 +227,24 @@ struct RedNear {
   int2 *table;
   int32_t *cursors;
   int32_t shards, cap;  // parts of ent and entries in each
+  uint32_t *sample;     // rows that stay, for red_crowded, and its stride
+  int stride;
 };
 
 __global__ __launch_bounds__(kRedBlock) void k_red_near(cg_graph g, int R,
                                                         const uint8_t *__restrict__ contained,
                                                         uint8_t *__restrict__ kept, RedNear near) {
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
+  const RedSample sample = red_sample(near.sample, g.n, near.stride);
   const RedRows blk = red_block(g, R, contained);
+  uint64_t rows = blk.mask;
+  if (g.m < (int64_t)kRedShortRow * g.n && red_crowded(sample)) {
+    if (w == 0 && ((rows >> lane) & 1ull))
+      near.table[(int64_t)blockIdx.x * R + lane] = make_int2(-1, 0);
+    rows &= __ballot(blk.entries > kRedCap);
+  }
   // the part changes from block to block, so that its cursor is not waited for
   const int32_t part = (int32_t)(blockIdx.x % near.shards), base0 = part * near.cap;
-  uint64_t rows = blk.mask;
   for (int i = 0; rows; rows &= rows - 1, ++i) {
     if (i % kRedWaves != w) continue;
     const int r = (int)__builtin_ctzll(rows);
@@ -209,8 +276,6 @@ __global__ __launch_bounds__(kRedBlock) void k_red_near(cg_graph g, int R,
     for (int k = 0; k < kRedPer; ++k) keep[k] = x[k] >= 0 && !contained[x[k]];
 #pragma unroll
     for (int k = 0; k < kRedPer; ++k) {
-      const int32_t e = k * kWave + lane;
-      if (x[k] >= 0) kept[a + e] = keep[k] ? 0 : 4;
       const uint64_t m = __ballot(keep[k]);
       f[k] = nf + __popcll(m & ((1ull << lane) - 1ull));
       nf += __popcll(m);
@@ -221,6 +286,9 @@ __global__ __launch_bounds__(kRedBlock) void k_red_near(cg_graph g, int R,
     const bool room = at <= near.cap - nf;
     if (lane == 0) near.table[u] = room ? make_int2(base0 + at, nf) : make_int2(-1, 0);
     if (!room) continue;
+#pragma unroll
+    for (int k = 0; k < kRedPer; ++k)
+      if (x[k] >= 0) kept[a + k * kWave + lane] = keep[k] ? 0 : 4;
 #pragma unroll
     for (int k = 0; k < kRedPer; ++k)
       if (keep[k])
@@ -248,13 +316,15 @@ __device__ void red_trans_long(const cg_graph &g, uint32_t fuzz, const uint8_t *
       if (p == du || rc[p] != x) continue;
       if (!same_ends(suv, g.strand[b + i], g.strand[a + p])) continue;
       if (!within(base - (int64_t)g.ovl[b + i] + (int64_t)g.ovl[a + p], fuzz)) continue;
-      kept[a + p] = contained[x] ? 4 : 1;
+      if (!contained[x]) kept[a + p] = 1;
     }
   }
 }
 
+// 8 workgroups to a compute unit where LDS has room for them (at most 64
+// registers; seven of them and 100 Mbp at 15x took 169 us instead of 118).
 template <int kNear>
-__global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fuzz, int R,
+__global__ __launch_bounds__(kRedBlock, kNear <= kRedNear ? 8 : 1) void k_red_trans(cg_graph g, uint32_t fuzz, int R,
                                                          const uint8_t *__restrict__ contained,
                                                          uint8_t *kept, RedNear near) {
   // u's near neighbours in column order: their ids, overlaps, first entries
@@ -336,7 +406,11 @@ __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fu
         if (longer) {
           nf = 0;  // read in place below: nothing of it goes to LDS
 #pragma unroll
-          for (int k = 0; k < kRedPer; ++k) keep[k] = false;
+          for (int k = 0; k < kRedPer; ++k) {
+            if (k * kWave + lane < du) kept[a + k * kWave + lane] = keep[k] ? 0 : 4;
+            keep[k] = false;
+          }
+          __threadfence_block();  // these land before any mark
         }
       }
       int32_t b[kRedPer], dv[kRedPer];
@@ -424,9 +498,15 @@ __global__ __launch_bounds__(kRedBlock) void k_red_trans(cg_graph g, uint32_t fu
         }
       }
       wave_lds_sync();
+      if (own >= 0) {
 #pragma unroll
-      for (int k = 0; k < kRedPer; ++k)
-        if (keep[k] && s_mark[f[k]]) kept[a + e[k]] = 1;
+        for (int k = 0; k < kRedPer; ++k)
+          if (keep[k] && s_mark[f[k]]) kept[a + e[k]] = 1;
+      } else if (!longer) {
+#pragma unroll
+        for (int k = 0; k < kRedPer; ++k)
+          if (k * kWave + lane < du) kept[a + k * kWave + lane] = keep[k] ? s_mark[f[k]] : 4;
+      }
       wave_lds_sync();
     }
     if (longer) red_trans_long(g, fuzz, contained, kept, u, a, du, lane);
@@ -579,27 +659,33 @@ int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuz
                   uint32_t *s_ovl, uint8_t *s_strand, int32_t *d_m, hipStream_t st) {
   const PhaseRange range("cg: reduce");
   const int32_t n = g.n;
-  const int R = red_rows(n);
+  const int R = red_rows(n, kRedBlocks);
   const int nb = n > 0 ? (int)(((int64_t)n + R - 1) / R) : 1;
   uint32_t *counts = s.piece_len, *blocks = s.fill;
-  // four near entries per read (2.3 at most at 8x and more coverage), in the
-  // walk area; a part for every 256 reads (the cursors take 64 words of lidx
+  // room for four near entries per read, in the walk area (12 +- 4 kbp reads
+  // have 2.8 at 8x and fewer above, reads of about one length 15 and more, of
+  // which the first rows' then fit); a part for every 256 reads (the cursors take 64 words of lidx
   // each)
   const int64_t near_cap = 4 * (int64_t)n < 0x7FFFFFFF ? 4 * (int64_t)n : 0x7FFFFFFF;
   const int32_t shards = n / 256 < 1 ? 1 : (n / 256 < kRedShards ? n / 256 : kRedShards);
   const RedNear near{reinterpret_cast<uint4 *>(s.walk), reinterpret_cast<int2 *>(s.tmp), s.lidx,
-                     shards, (int32_t)(near_cap / shards)};
+                     shards, (int32_t)(near_cap / shards), reinterpret_cast<uint32_t *>(s.keys),
+                     red_stride(n)};
   if (n > 0) {
     const int64_t groups = ((int64_t)n * kRedGroup + kRedBlock - 1) / kRedBlock;
     CG_LAUNCH(ctx, k_red_contained, dim3((unsigned)groups), dim3(kRedBlock), st, g, contained,
-              kept, near.cursors, shards);
+              kept, near.cursors, shards, near.sample, near.stride);
     CG_LAUNCH(ctx, k_red_near, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, near);
-    if (g.m >= (int64_t)kRedWideRow * n && g.m < (int64_t)2 * kRedCap * n)
-      CG_LAUNCH(ctx, k_red_trans<kRedNearWide>, dim3(nb), dim3(kRedBlock), st, g, fuzz, R,
-                contained, kept, near);
-    else
-      CG_LAUNCH(ctx, k_red_trans<kRedNear>, dim3(nb), dim3(kRedBlock), st, g, fuzz, R, contained,
+    const bool longer = g.m >= (int64_t)2 * kRedCap * n;
+    const bool wide = g.m >= (int64_t)kRedWideRow * n && !longer;
+    const int Rt = red_rows(n, longer ? kRedBlocks : (wide ? kRedWideBlocks : kRedTransBlocks));
+    const dim3 tb((unsigned)(((int64_t)n + Rt - 1) / Rt));
+    if (wide)
+      CG_LAUNCH(ctx, k_red_trans<kRedNearWide>, tb, dim3(kRedBlock), st, g, fuzz, Rt, contained,
                 kept, near);
+    else
+      CG_LAUNCH(ctx, k_red_trans<kRedNear>, tb, dim3(kRedBlock), st, g, fuzz, Rt, contained, kept,
+                near);
     CG_LAUNCH(ctx, k_red_keep, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, counts,
               blocks);
     if (nb > kRedDirect) CG_LAUNCH(ctx, k_red_sums, dim3(1), dim3(kScanBlock), st, nb, blocks);

@@ -47,7 +47,10 @@ def _overlaps(G, cov, mean, sd, seed, runs=()):
 
 
 CASES = {
-    # reads, overlap reads of one length: about 2 cov (1 - 1000 / mean) neighbours a read
+    # reads of one length have about 2 cov (1 - 1000 / mean) neighbours; with few
+    # enough entries a read they are not gathered at all
+    "short rows": (900_000, 12, 6000, 3, ()),
+    "short rows, some contained": (900_000, 12, 6000, 300, ()),
     "rows below 128": (200_000, 55, 6000, 3, ()),
     "rows around 128": (200_000, 75, 6000, 3, ()),
     "rows around 256": (200_000, 150, 6000, 3, ()),
@@ -65,8 +68,12 @@ def test_one_length(cg, name, fuzz):  # noqa: F811
     left = np.flatnonzero(got["contained"] == 0)
     rows = np.diff(r.row_ptr)[left]
     assert len(left) > 0.5 * r.n or name == "spread lengths"
+    if "short" in name or "a few" in name:
+        assert r.m < 40 * r.n
     if "long" in name or "128" in name:
         assert rows.min() < 128 < rows.max()
+    if "long" in name or "256" in name:
+        assert rows.max() > 256
 
 
 def test_longer_rows_cost_their_pairs(cg):  # noqa: F811
