@@ -56,7 +56,7 @@ CASES = {
     "rows around 256": (200_000, 150, 6000, 3, ()),
     "spread lengths": (200_000, 120, 6000, 300, ()),
     # mostly short rows, long ones where a repeat gathers reads
-    "a few long rows": (900_000, 9, 6000, 3, ((300_000, 12_000, 90), (600_000, 12_000, 200))),
+    "a few long rows": (4_000_000, 9, 6000, 3, ((300_000, 7_000, 120), (900_000, 7_000, 240))),
 }
 
 
