@@ -71,7 +71,9 @@ constexpr int kRedShards = 64;   // parts of the near entries' memory at most, a
 constexpr int kRedCursor = 64;
 constexpr int kRedList = 256;    // surviving entries a wave of k_red_keep collects
 constexpr int kRedDirect = 4096;  // blocks whose counts each workgroup of k_red_compact adds up itself
-constexpr int kRedGroup = 16;    // lanes per row of k_red_contained
+// Lanes per row of k_red_contained: 16, or a wave where the rows are long.
+constexpr int kRedGroup = 16;
+constexpr int kRedWaveRow = 256;  // entries per read from which it is a wave
 // A read's near entries from which filling their room does not pay, where the
 // rows are short; with longer ones the pairs saved outweigh the pass (10 Mbp at
 // 45x, 30 near entries a read: 20 us of it save 34, at 10x, 14 of them: 4 save 2)
@@ -92,16 +94,19 @@ static int red_rows(int32_t n, int blocks) {
 constexpr int kRedBlocks = 1024;
 // k_red_trans, whose rows take unequal time, wants more of them (8,333 reads of
 // about one length at 10x: 26 us instead of 37; 50 Mbp at 30x 38.8 and 40.5,
-// with 4,096 39.3, 17 Mbp 24.0 and 27.7), and its wide instance, with most rows
-// to work on, more still (2 Mbp at 100x: 4.04 ms with 2,048, 3.20 with 4,096);
-// not so where nearly every row is read in place (0.3 Mbp at 600x: 1.87 ms with
-// 1,024, 2.00 with 2,048).
-constexpr int kRedTransBlocks = 2048, kRedWideBlocks = 4096;
+// with 4,096 39.3, 17 Mbp 24.0 and 27.7), and its wide instance more still where
+// most rows stay (2 Mbp at 100x: 4.00 ms with 1,024 and 2,048, 3.01 with 3,072;
+// where few do, 10 Mbp at 60x of 12 +- 4 kbp, 28 and 33 us; 10 Mbp at 60x of one
+// length 1.04 and 1.00 ms, 1.05 with 4,096); not so where nearly every row is
+// read in place (0.3 Mbp at 600x: 1.87 ms with 1,024, 2.00 with 2,048).
+constexpr int kRedTransBlocks = 2048, kRedWideBlocks = 3072;
 
-// 16 lanes per row, four entries each in flight: a row has 55 entries on
-// average at 30x.  Only an entry that covers the read (ovl >= len) needs its
+// 16 lanes per row, or 64 for long rows, four entries each in flight: a row has
+// 55 entries on average at 30x.  Only an entry that covers the read (ovl >= len) needs its
 // column and that read's length.  6.9 M entries: 21 us (28 us with a wave per
-// row and every column loaded).
+// row and every column loaded); rows of 590 and 1,200 entries: 6.9 and 16.9 us
+// with a wave each, 12.7 and 29.7 with 16 lanes, rows of 150: 11.3 and 11.9.
+template <int kGroup>
 __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t *contained,
                                                              uint8_t *__restrict__ kept,
                                                              int32_t *__restrict__ cursors,
@@ -110,25 +115,26 @@ __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t
                                                              int stride) {
   const int64_t t = (int64_t)blockIdx.x * kRedBlock + threadIdx.x;
   if (t < shards) cursors[t * kRedCursor] = 0;
-  const int64_t row = t / kRedGroup;
-  const int gl = (int)(threadIdx.x % kRedGroup);
+  const int64_t row = t / kGroup;
+  const int gl = (int)(threadIdx.x % kGroup);
   const bool live = row < g.n;
   const int32_t v = live ? (int32_t)row : 0;
   const int32_t a = live ? g.row_ptr[v] : 0, d = live ? g.row_ptr[v + 1] - a : 0;
   const uint32_t lv = live ? g.read_len[v] : 0u;
-  const uint64_t group = ((1ull << kRedGroup) - 1ull) << (lane_id() / kRedGroup * kRedGroup);
+  const uint64_t group = (kGroup < kWave ? (1ull << (kGroup % kWave)) - 1ull : ~0ull)
+                         << (lane_id() / kGroup * kGroup);
   bool found = false;
-  for (int32_t base = 0; __ballot(base < d && !found); base += 4 * kRedGroup) {
+  for (int32_t base = 0; __ballot(base < d && !found); base += 4 * kGroup) {
     uint32_t o[4];
     bool c = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int32_t i = base + k * kRedGroup + gl;
+      const int32_t i = base + k * kGroup + gl;
       o[k] = i < d && !found ? g.ovl[a + i] : 0u;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int32_t i = base + k * kRedGroup + gl;
+      const int32_t i = base + k * kGroup + gl;
       if (i < d && !found && o[k] >= lv) {
         const int32_t u = g.col[a + i];
         const uint32_t lu = g.read_len[u];
@@ -138,15 +144,16 @@ __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t
     found = found || (__ballot(c) & group) != 0ull;
   }
   if (live && gl == 0) contained[v] = found ? 1 : 0;
-  // a sampled wave's rows that stay, and their entries (see red_crowded)
+  // a sampled wave's rows that stay, and their entries (see red_crowded; of
+  // short rows only)
   const int64_t wave = t / kWave;
-  if (__builtin_amdgcn_readfirstlane((int)(wave & ((1 << stride) - 1))) == 0) {
+  if (kGroup < kWave && __builtin_amdgcn_readfirstlane((int)(wave & ((1 << stride) - 1))) == 0) {
     const uint32_t stay =
         wave_sum(live && gl == 0 && !found ? kRedStay + (uint32_t)(d <= kRedCap ? d : 0) : 0u);
     if (lane_id() == 0) sample[wave >> stride] = stay;
   }
   if (found)
-    for (int32_t i = gl; i < d; i += kRedGroup) kept[a + i] = 0;
+    for (int32_t i = gl; i < d; i += kGroup) kept[a + i] = 0;
 }
 
 // Whether most reads stay, so that the near entries would need far more room
@@ -672,9 +679,14 @@ int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuz
                      shards, (int32_t)(near_cap / shards), reinterpret_cast<uint32_t *>(s.keys),
                      red_stride(n)};
   if (n > 0) {
-    const int64_t groups = ((int64_t)n * kRedGroup + kRedBlock - 1) / kRedBlock;
-    CG_LAUNCH(ctx, k_red_contained, dim3((unsigned)groups), dim3(kRedBlock), st, g, contained,
-              kept, near.cursors, shards, near.sample, near.stride);
+    const bool waves = g.m >= (int64_t)kRedWaveRow * n;
+    const int64_t groups = ((int64_t)n * (waves ? kWave : kRedGroup) + kRedBlock - 1) / kRedBlock;
+    if (waves)
+      CG_LAUNCH(ctx, k_red_contained<kWave>, dim3((unsigned)groups), dim3(kRedBlock), st, g,
+                contained, kept, near.cursors, shards, near.sample, near.stride);
+    else
+      CG_LAUNCH(ctx, k_red_contained<kRedGroup>, dim3((unsigned)groups), dim3(kRedBlock), st, g,
+                contained, kept, near.cursors, shards, near.sample, near.stride);
     CG_LAUNCH(ctx, k_red_near, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, near);
     const bool longer = g.m >= (int64_t)2 * kRedCap * n;
     const bool wide = g.m >= (int64_t)kRedWideRow * n && !longer;

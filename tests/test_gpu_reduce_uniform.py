@@ -94,3 +94,12 @@ def test_longer_rows_cost_their_pairs(cg):  # noqa: F811
         deg = np.diff(r.row_ptr).astype(np.float64)
         us[cov], pairs[cov] = min(t[1:]), float((deg[r.col]).sum())
     assert us[80] / us[60] < 1.5 * pairs[80] / pairs[60], (us, pairs)
+
+
+@pytest.mark.parametrize("cov", [160, 200, 330])
+def test_rows_of_a_wave(cg, cov):  # noqa: F811
+    """Entries per read around those from which the containment pass gives a
+    row a whole wave, most reads contained."""
+    r = _overlaps(60_000, cov, 3000, 900, seed=cov)
+    got = check(cg, r, 2, name="cov%d" % cov)[0]
+    assert (r.m >= 256 * r.n) == (cov >= 200) and got["contained"].mean() > 0.5
