@@ -424,8 +424,9 @@ typedef struct cg_batch cg_batch;
  * outputs are identical to the five single-graph calls on that job.  A job
  * with more than 32768 directed entries is run by the single-graph kernels,
  * beside the batched launches: on up to three streams of the batch's own
- * (made with its first such job, destroyed with it) that start after what the
- * caller's stream holds and that the caller's stream waits for. */
+ * (made by cg_batch_create_empty, or with the batch's first such job, and
+ * destroyed with it) that start after what the caller's stream holds and that
+ * the caller's stream waits for. */
 int cg_batch_create(cg_ctx *ctx, int32_t n_jobs, const cg_job *jobs,
                     const cg_batch_params *params, cg_batch **out);
 

@@ -2058,10 +2058,10 @@ static void drop_side(cg_batch *b) {
   b->n_side = 0;
 }
 
-// the batch's own streams, made at the first plan with external jobs; without
-// them (none could be made) these jobs run on the caller's stream
+// the batch's own streams; without them (none could be made) the external jobs
+// run on the caller's stream
 static void make_side(cg_batch *b) {
-  if (b->n_side > 0 || b->ext_jobs.empty()) return;
+  if (b->n_side > 0) return;
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(b->ctx->device);
@@ -2190,7 +2190,7 @@ int cg_batch_create(cg_ctx *ctx, int32_t n_jobs, const cg_job *jobs,
   int prev = 0;
   (void)hipGetDevice(&prev);
   (void)hipSetDevice(ctx->device);
-  make_side(b);
+  if (!b->ext_jobs.empty()) make_side(b);
   rc = plan_upload(b, P, nullptr);
   if (!rc) rc = hip_check(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
   (void)hipSetDevice(prev);
@@ -2211,7 +2211,9 @@ int cg_batch_create_empty(cg_ctx *ctx, uint64_t bytes, const cg_batch_params *pa
   cg_batch_params prm;
   int rc = check_params(ctx, params, &prm);
   if (rc) return rc;
-  return batch_alloc(ctx, prm, (size_t)bytes, out);
+  if ((rc = batch_alloc(ctx, prm, (size_t)bytes, out))) return rc;
+  make_side(*out);  // here, not in the first wave that has a large job
+  return CG_OK;
 }
 
 int cg_batch_plan(cg_batch *b, int32_t n_jobs, const cg_job *jobs, void *stream) {
@@ -2232,7 +2234,7 @@ int cg_batch_plan(cg_batch *b, int32_t n_jobs, const cg_job *jobs, void *stream)
     b->graph = nullptr;
   }
   plan_fill(b, P, jobs);
-  make_side(b);
+  if (!b->ext_jobs.empty()) make_side(b);
   return plan_upload(b, P, (hipStream_t)stream);
 }
 
