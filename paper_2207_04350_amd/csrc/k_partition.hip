@@ -639,6 +639,8 @@ int launch_path_partition(cg_ctx *ctx, const cg_graph &g, const Scratch &s, cons
     int mask_parts = 0;
     const int rc = launch_path_mask(ctx, g, s, a, &mask_parts, st);
     if (rc) return rc;
+    // (the count finishes the labels, too)
+    const PhaseRange range("cg: GreedyPartitioning");
     const CountExtra ex{s.lidx, ctx->fixed, mask_parts, a.d_counts, g.read_len, root_w};
     const dim3 grid((unsigned)chunk_count(n));
     uint2 *sums = min_reads <= 2 ? chunks : nullptr;
@@ -676,8 +678,10 @@ int launch_path(cg_ctx *ctx, const cg_graph &g, const Scratch &s, const PathArgs
     rc = launch_path_partition(ctx, g, s, a, st);
     if (!rc) rc = launch_comp(ctx, g, s, a, reinterpret_cast<int32_t *>(s.fill), st);
     const int32_t max_contigs = g.n / (a.min_reads < 1 ? 1 : a.min_reads);
-    if (!rc)
+    if (!rc) {
+      const PhaseRange range("cg: LocalAssembly");
       rc = launch_contigs(ctx, g, s, a.parts, a.local, a.P, max_contigs, a.out, st, a.status);
+    }
     return rc;
   }
   if (!rc) rc = launch_assemble(ctx, g, s, a.parts, a.local, a.P, a.out, st);
