@@ -20,6 +20,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -55,25 +56,87 @@ def algo_bytes(kernel, s):
         # degree <= 2, flags, labels and label_comp written, the component
         # table (label, size, kind, member start) and the grouped members
         "k_mask_cc": 4 * (N + 1) + 4 * m_nb + N + 4 * N + 4 * N + 13 * nc + 4 * n_e,
+        "k_mask_sum": 0,  # the workgroups' sums alone
         "k_part_zero": 4 * N,
+        "k_part_chunks": 5 * N,
+        "k_part_wzero": 8 * N,
+        "k_part_weight": 5 * N + 4 * n_e + 8 * nc,
+        "k_ind_init": 4 * nc,
         "k_part_count": N + 4 * N,
         "k_part_compact": N + 4 * N + 4 * N + 9 * nc,
         "k_part_lpt": 4 * nc + 16 * nc,
+        # component sizes and bins read; ranks and first reads written
+        "k_part_hist": 8 * nc,
+        "k_part_place": 8 * nc + 8 * nc,
+        # a small graph's mask, components, counts and compaction in one: labels,
+        # the component index and the member slots written, and the table
+        "k_front": 4 * (N + 1) + 4 * m_nb + N + 4 * N + 4 * N + 13 * nc + 4 * n_e,
         "k_ind_fill": 4 * N + 4 * N + 8 * n_e,
-        "k_ind_local": 8 * n_e + 4 * n_e,
-        "k_ind_rows": 4 * n_e + n_e + 4 * (n_e + 1) + 8 * m_e + 4 * n_e,
         "k_ind_comp": 16 * n_e + n_e + 4 * (n_e + 1) + 8 * m_e + 4 * n_e,
         # perm, local rows, entries (columns + ids, strands + overlaps), read
         # lengths and store offsets; layout (id, strand) and pieces (length,
         # store anchor, offset) written
         "k_asm_walk": 4 * n_e + 8 * n_e + 8 * m_e + 9 * m_e + 12 * n_e + 5 * n_e + 20 * n_e,
+        # induce and walk in one: members, flags, rows, read lengths and store
+        # offsets, entries (columns, overlaps, strands) and component records
+        # read; perm, the local rows, layout and pieces, and contig records written
+        "k_comp": 25 * n_e + 9 * m_e + 25 * nc + 8 * n_e + 8 * m_e + 25 * n_e + 32 * nc,
         "k_asm_offsets": 16 * nc,
         # packed source bases read + contig words written + per-piece
         # descriptors (contig, offset, length, store anchor) and per-contig
         # records (length, base offset)
         "k_asm_copy": Cb // 4 + 4 * W + 24 * n_e + 16 * nc,
+        "k_asm_bases": Cb // 4 + 4 * W + 24 * n_e + 32 * nc,
+        # the batched form's: every read's degree and default outputs, the listed
+        # reads; the bases weights; the component tables and the work queue
+        "k_mask_tiles": 4 * (N + 1) + 9 * N + 4 * m_nb,
+        "k_weight": 8 * N + 4 * n_e + 8 * nc,
+        "k_tables": 16 * nc,
+        "k_wq_place": 12 * nc,
     }
-    return table.get(kernel)
+    return table[kernel]
+
+
+# the kernels of the steps' phases, both forms
+PHASES = {
+    # the batched form: degrees, bitmaps and lists over the whole chip
+    # (kb_mask_tiles), then kept entries, labels and the component table per
+    # graph (kb_mask_cc, counted here as components)
+    "mask": ("k_mask", "k_mask_sum", "k_front", "kb_mask_tiles"),
+    "components": ("k_cc_init", "k_cc_hook", "k_cc_compress", "kb_mask_cc"),
+    "partition": ("k_part_zero", "k_part_count", "k_part_chunks", "k_part_compact", "k_part_wzero",
+                  "k_part_weight", "k_part_lpt", "k_part_hist", "k_part_place", "kb_weight",
+                  "kb_lpt", "kb_tables", "kb_wq_place"),
+    "induce": ("k_ind_init", "k_ind_fill", "k_ind_comp"),
+    # both forms induce and walk every component in one pass
+    "induce_walk": ("kb_induce_walk", "k_comp"),
+    "assemble": ("k_asm_walk", "k_asm_offsets", "k_asm_copy", "k_asm_bases", "kb_walk",
+                 "kb_offsets", "kb_copy"),
+}
+# what a batched kernel does of the plain ones
+BATCHED_AS = {"kb_copy": ["k_asm_copy"], "kb_walk": ["k_asm_walk"], "kb_lpt": ["k_part_lpt"],
+              "kb_induce_walk": ["k_comp"], "kb_offsets": ["k_asm_offsets"]}
+
+
+def kernel_base(name):
+    """A profiled kernel's name without its template arguments."""
+    return name.split("<")[0]
+
+
+def phase_ms(kern):
+    """The time of each phase, from {kernel: (launches, ms)}; a kernel that none
+    of them lists is an error."""
+    of = {k: ph for ph, ks in PHASES.items() for k in ks}
+    out = {ph: 0.0 for ph in PHASES}
+    for name, v in kern.items():
+        out[of[kernel_base(name)]] += v[1]
+    return out
+
+
+def kernel_bytes(name, s):
+    """Algorithmic bytes of a profiled kernel, plain or batched."""
+    base = kernel_base(name)
+    return sum(algo_bytes(k, s) for k in BATCHED_AS.get(base, [base.replace("kb_", "k_")]))
 
 
 # least CPU time the oracle baselines are timed over (whole passes over the
@@ -109,7 +172,9 @@ def profiled_traffic(kernel, profile="batched_512graphs_hbm_bytes.md"):
             if line.startswith("csrc sha256:"):
                 digest = line.split(":", 1)[1].strip()
             cells = [c.strip() for c in line.split("|")]
-            if len(cells) >= 5 and cells[1].strip("`").startswith("cg::%s(" % kernel):
+            # (a template's name is printed with its result type)
+            if len(cells) >= 5 and re.match(r"(void )?cg::%s[(<]" % kernel_base(kernel),
+                                            cells[1].strip("`")):
                 mb = float(cells[4])
     if digest != csrc_digest() or mb is None:
         return None
@@ -411,32 +476,15 @@ def main():
         st["contig_bases"] += int(out.c_len[:nc].sum().item())
         st["words"] += int(out.total_words.item())
 
-    def phases(kern):
-        pick = lambda pred: sum(v[1] for k, v in kern.items() if pred(k))
-        return {
-            # the batched form: degrees, bitmaps and lists over the whole chip
-            # (kb_mask_tiles), then kept entries, labels and the component
-            # table per graph (kb_mask_cc, counted here as components)
-            "mask": pick(lambda k: k.startswith("k_mask") or k in ("kb_mask_tiles", "k_front")),
-            "components": pick(lambda k: k.startswith("k_cc") or k == "kb_mask_cc"),
-            "partition": pick(lambda k: k.startswith("k_part") or k.startswith("kb_weight")
-                              or k in ("kb_lpt", "kb_tables", "kb_wq_place")),
-            "induce": pick(lambda k: k.startswith("k_ind")),
-            # both forms induce and walk every component in one pass
-            "induce_walk": pick(lambda k: k in ("kb_induce_walk", "k_comp")),
-            "assemble": pick(lambda k: k.startswith("k_asm")
-                             or k in ("kb_walk", "kb_offsets", "kb_copy")),
-        }
-
     def medians(km):
-        return phases({k: (1, v) for k, v in km.items()})
+        return phase_ms({k: (1, v) for k, v in km.items()})
 
     for name, kern in (("plain", plain_kern), ("batched", batch_kern)):
         for k, (c, ms) in sorted(kern.items(), key=lambda kv: -kv[1][1]):
             log("  %-8s %-22s %6d launches/step %9.3f ms/step %9.2f us/launch"
                 % (name, k, c, ms, 1e3 * ms / c))
 
-    b_ph = phases(batch_kern)
+    b_ph = phase_ms(batch_kern)
     warm_ph, cold_ph = medians(warm_k), medians(cold_k)
     maskcc_ms = b_ph["mask"] + b_ph["components"]
     # fused minimum of mask + components: row_ptr, the columns of degree <= 2
@@ -450,7 +498,6 @@ def main():
         ms = ph["mask"] + ph["components"]
         return {"ms": ms, "edges_per_s": st["m"] / (ms * 1e-3),
                 "hbm_frac": maskcc_bytes / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9)}
-    kname = lambda k: k.replace("kb_", "k_").split("<")[0]
     # a single graph: the faster of the two forms is the reported one (the
     # batched form is built for many graphs; one large graph is the plain
     # path's case)
@@ -466,11 +513,8 @@ def main():
     dom = max(rkern, key=lambda k: rkern[k][1])
     dom_launches, dom_ms = rkern[dom]
     dom_avg_us = 1e3 * dom_ms / dom_launches
-    dom_map = {"kb_copy": ["k_asm_copy"], "kb_walk": ["k_asm_walk"], "kb_lpt": ["k_part_lpt"],
-               "kb_induce_walk": ["k_ind_local", "k_ind_rows", "k_asm_walk"],
-               "kb_offsets": ["k_asm_offsets"]}
-    dom_bytes = sum(algo_bytes(k, st) or 0 for k in dom_map.get(dom, [kname(dom)]))
-    dom_bytes_per_launch = (dom_bytes or 0) / dom_launches
+    dom_bytes = kernel_bytes(dom, st)
+    dom_bytes_per_launch = dom_bytes / dom_launches
     achieved = dom_bytes_per_launch / (dom_avg_us * 1e-6) / 1e9
 
     result = {
@@ -514,7 +558,7 @@ def main():
         "plain": {"ms_per_step": plain_wall, "gpu_ms_per_step": plain_gpu,
                   "cold_ms_per_step": plain_cold,
                   "contig_bases_per_s": st["contig_bases"] / (plain_wall * 1e-3),
-                  "phase_kernel_ms": phases(plain_kern)},
+                  "phase_kernel_ms": phase_ms(plain_kern)},
         "batched_vs_plain": plain_cold / b_cold,
         "edges_per_s_mask_cc": st["m"] / (maskcc_ms * 1e-3) if maskcc_ms else None,
         "mask_cc": {"ms_per_step": maskcc_ms, "algorithmic_bytes": maskcc_bytes,
@@ -534,9 +578,9 @@ def main():
                     if maskcc_traffic and maskcc_ms else None},
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": (profiled_traffic(kname(dom).replace("k_", "kb_", 1))
+                     "traffic": (profiled_traffic(dom)
                                  if args.workload == "batch" and not use_plain else
-                                 profiled_traffic(kname(dom), PLAIN_PROFILES[args.workload])
+                                 profiled_traffic(dom, PLAIN_PROFILES[args.workload])
                                  if use_plain and args.workload in PLAIN_PROFILES else None),
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0, "
                                      "profiles/%s)" % (PLAIN_PROFILES.get(args.workload)
@@ -645,7 +689,7 @@ def reduce_bench(args):
     left = out.contained[:n].cpu().numpy() == 0
     near = int(np.count_nonzero(np.repeat(left, np.diff(r.row_ptr)) & left[r.col]))
     dom_bytes = {"k_red_contained": 4 * (n + 1) + 4 * m + 4 * n + n + m,
-                 "k_red_trans": n + 8 * int(left.sum()) + 17 * near}.get(dom.split("<")[0], algo)
+                 "k_red_trans": n + 8 * int(left.sum()) + 17 * near}.get(kernel_base(dom), algo)
     result = {
         "metric": "overlap-graph entries/s (contained-read pruning + transitive reduction)",
         "value": m / (wall * 1e-3),

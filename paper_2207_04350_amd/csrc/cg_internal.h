@@ -359,9 +359,21 @@ struct PhaseRange {
   PhaseRange &operator=(const PhaseRange &) = delete;
 };
 
+// A kernel's name as the timing reports it: as it is written at its launch, less
+// the parentheses that an argument list with commas takes there.
+template <size_t N>
+struct KernelName {
+  char s[N] = {};
+  constexpr KernelName(const char (&x)[N]) {
+    const size_t a = x[0] == '(' ? 1 : 0, n = N - 1 - 2 * a;
+    for (size_t i = 0; i < n; ++i) s[i] = x[a + i];
+  }
+};
+
 #define CG_LAUNCH(ctx, kern, grid, block, st, ...)                 \
   do {                                                             \
-    const int cg_prof_slot_ = ::cg::prof_begin((ctx), (st), #kern); \
+    static constexpr ::cg::KernelName cg_kernel_(#kern);           \
+    const int cg_prof_slot_ = ::cg::prof_begin((ctx), (st), cg_kernel_.s); \
     hipLaunchKernelGGL(kern, grid, block, 0, st, __VA_ARGS__);     \
     ::cg::prof_end((ctx), (st), cg_prof_slot_);                    \
   } while (0)
