@@ -18,8 +18,8 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// the first position in the sorted a[0, q) holding a value >= x
-__device__ __forceinline__ int32_t lds_lower_bound(const int32_t *a, int q, int32_t x) {
+// the first position in the sorted a[0, q), in LDS or not, holding a value >= x
+__device__ __forceinline__ int32_t lower_bound_i32(const int32_t *a, int q, int32_t x) {
   int lo = 0, hi = q;
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
@@ -204,25 +204,6 @@ __device__ __forceinline__ int32_t tf_find(uint64_t *F, uint32_t tag, int32_t x)
     if (gp == p) return p;
     st_relaxed64(F + x, tf_entry(tag, gp));  // path halving
     x = gp;
-  }
-}
-
-__device__ __forceinline__ void tf_union(uint64_t *F, uint32_t tag, int32_t a, int32_t b) {
-  a = tf_find(F, tag, a);
-  b = tf_find(F, tag, b);
-  while (a != b) {
-    const int32_t hi = a > b ? a : b, lo = a > b ? b : a;
-    const uint64_t e = ld_relaxed64(F + hi);
-    if ((uint32_t)(e >> 32) == tag) {  // hi got a parent meanwhile: climb
-      const int32_t p = (int32_t)(uint32_t)e;
-      if (a == hi) a = p;
-      else b = p;
-      continue;
-    }
-    // link the larger root under the smaller one
-    if (atomicCAS((unsigned long long *)(F + hi), (unsigned long long)e,
-                  (unsigned long long)tf_entry(tag, lo)) == e)
-      return;
   }
 }
 
@@ -2438,12 +2419,6 @@ __device__ __forceinline__ PieceD load_piece(const PieceArraysT<CB> &A, int32_t 
   d.L = A.clen[k];
   d.cb = A.cbase[k] >> 4;
   return d;
-}
-
-__device__ __forceinline__ uint64_t readlane64(uint64_t x, int t) {
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, t);
-  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), t);
-  return ((uint64_t)hi << 32) | lo;
 }
 
 // Store word index clamped into [0, nwords - 1]; a window may start before

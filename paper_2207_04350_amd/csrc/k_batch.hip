@@ -444,28 +444,6 @@ __device__ __forceinline__ void mc_component(const McOut &O, int32_t cb, int32_t
   O.comp_w[cb] = 0;
 }
 
-// local number of listed read v: listed reads before its word, plus those
-// below it in the word
-__device__ __forceinline__ int32_t mc_rank(const uint32_t *lw, const int32_t *wp, int32_t v) {
-  const int w = v >> 5, b = v & 31;
-  return wp[w] + __popc(lw[w] & ((1u << b) - 1u));
-}
-
-// id of the listed read of local number l (l below the number of listed
-// reads; -1 otherwise)
-__device__ __forceinline__ int32_t mc_select(const uint32_t *lw, const int32_t *wp, int W,
-                                             int32_t l) {
-  int lo = 0, hi = W - 1;  // the last word whose prefix is at most l holds it
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (wp[mid] <= l) lo = mid;
-    else hi = mid - 1;
-  }
-  uint32_t bits = lw[lo];
-  for (int s = l - wp[lo]; s > 0 && bits; --s) bits &= bits - 1u;
-  return bits ? (lo << 5) + __builtin_ctz(bits) : -1;
-}
-
 // State of the listed reads as the sweep over all reads sees it: entry
 // (id | kept bits << 30), root (~component once numbered) and counter
 // (per-root count, then member cursor).

@@ -186,12 +186,12 @@ __device__ __forceinline__ void ind_wave(int q, int st, int estart, const int32_
       out.loc_row_ptr[st + i] = t;
       const int32_t e = s_b[i];
       if (x0 >= 0) {
-        out.loc_col[t] = st + lds_lower_bound(s_id, q, x0);
+        out.loc_col[t] = st + lower_bound_i32(s_id, q, x0);
         out.loc_eid[t] = e;
         ++t;
       }
       if (x1 >= 0) {
-        out.loc_col[t] = st + lds_lower_bound(s_id, q, x1);
+        out.loc_col[t] = st + lower_bound_i32(s_id, q, x1);
         out.loc_eid[t] = e + 1;
       }
     }

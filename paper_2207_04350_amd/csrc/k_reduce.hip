@@ -204,17 +204,6 @@ __device__ __forceinline__ RedRows red_block(const cg_graph &g, int R, const uin
   return x;
 }
 
-// the first position in a[0, len) holding a value >= x
-__device__ __forceinline__ int lower_bound_i32(const int32_t *a, int len, int32_t x) {
-  int lo = 0, hi = len;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (a[mid] < x) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
 // a valid walk u, v, x with u->x's end orientations (strand bits s = bit 0,
 // d = bit 1 of u->v, v->x and u->x)
 __device__ __forceinline__ bool same_ends(uint32_t suv, uint32_t svx, uint32_t sux) {
