@@ -225,9 +225,9 @@ __device__ __forceinline__ void comp_big(const CompArgs &a, int c, int q, int st
       cr, q, st, first, w, a.g, a.local.perm, a.out, a.s, sh_scan);
 }
 
-// The others above kCompCap reads (of graphs above 316,000 reads): sorted in LDS or by a bitmap in windows,
-// rows by scans, the walk's arrays in scratch (the rays in LDS up to
-// kCompRays reads).
+// The others above kCompCap reads (of graphs above 316,000 reads): sorted in
+// LDS or by a bitmap in windows, rows by scans, the walk's arrays in scratch
+// (the rays in LDS up to kCompRays reads).
 constexpr int kCompSortCap = 8192;
 constexpr int kCompRays = 4096;
 static_assert(kCompSortCap <= kCompWords && 2 * kCompRays <= kCompWords, "they fit the LDS");
