@@ -57,12 +57,17 @@ constexpr int kRedPer = kRedCap / kWave;
 // workgroup, which is resident waves (100 Mbp at 15x, rows of 28 entries: 551 us
 // with room for 128, 777 for 256).  More than 128 they are where the rows have
 // well above 128 entries and most reads stay (reads of one length at 70x to
-// 120x: 1.2 to 6.7 ms with room for 256, 2.5 to 14 with the rows read in place),
-// so the room goes by the entries per read.  (Where they are twice kRedCap and
-// more, nearly every row is read in place, and the room serves none: 618 us
+// 120x: 1.1 to 5.3 ms with room for 256, 2.5 to 14 with the rows read in place).
+// From kRedWideRow entries a read on a sample of the rows tells them (red_wide),
+// and the instance that is not wanted leaves, 2-3 us (10 Mbp at 60x of 12 +- 4
+// kbp 69 us, 72 with the wide one, 66 with the narrow one alone; 1 Mbp at 90x of
+// 12 +- 0.3 kbp, 74 near neighbours a row, 399, 530 and 379; 2 Mbp at 60x of one
+// length, 110 of them, 768, 765 and 1,058).  (Where the entries are twice kRedCap
+// and more, nearly every row is read in place, and the room serves none: 618 us
 // with 128, 635 with 256.)
 constexpr int kRedNear = 128, kRedNearWide = 256;
-constexpr int kRedWideRow = 96;  // entries per read from which it is kRedNearWide
+constexpr int kRedWideRow = 96;       // entries per read
+constexpr uint32_t kRedWideNear = 96;  // near neighbours per row from which it is kRedNearWide
 static_assert(kRedNearWide == kRedCap, "no row that fits the registers is read in place");
 constexpr int kRedRows = 64;     // rows per workgroup at most: a lane of a wave each
 constexpr int kRedShards = 64;   // parts of the near entries' memory at most, a cursor each
@@ -94,11 +99,11 @@ static int red_rows(int32_t n, int blocks) {
 constexpr int kRedBlocks = 1024;
 // k_red_trans, whose rows take unequal time, wants more of them (8,333 reads of
 // about one length at 10x: 26 us instead of 37; 50 Mbp at 30x 38.8 and 40.5,
-// with 4,096 39.3, 17 Mbp 24.0 and 27.7), and its wide instance more still where
-// most rows stay (2 Mbp at 100x: 4.00 ms with 1,024 and 2,048, 3.01 with 3,072;
-// where few do, 10 Mbp at 60x of 12 +- 4 kbp, 28 and 33 us; 10 Mbp at 60x of one
-// length 1.04 and 1.00 ms, 1.05 with 4,096); not so where nearly every row is
-// read in place (0.3 Mbp at 600x: 1.87 ms with 1,024, 2.00 with 2,048).
+// with 4,096 39.3, 17 Mbp 24.0 and 27.7; 2 Mbp at 100x of 12 +- 0.3 kbp 803 and
+// 1,158), and its wide instance more still (2 Mbp at 100x: 4.00 ms with 1,024 and
+// 2,048, 3.01 with 3,072; 10 Mbp at 60x of one length 1.04 and 1.00 ms, 1.05 with
+// 4,096); not so where nearly every row is read in place (0.3 Mbp at 600x: 1.87 ms
+// with 1,024, 2.00 with 2,048).
 constexpr int kRedTransBlocks = 2048, kRedWideBlocks = 3072;
 
 // 16 lanes per row, or 64 for long rows, four entries each in flight: a row has
@@ -144,12 +149,13 @@ __global__ __launch_bounds__(kRedBlock) void k_red_contained(cg_graph g, uint8_t
     found = found || (__ballot(c) & group) != 0ull;
   }
   if (live && gl == 0) contained[v] = found ? 1 : 0;
-  // a sampled wave's rows that stay, and their entries (see red_crowded; of
-  // short rows only)
+  // a sampled wave's rows that stay, and their entries (see red_crowded and
+  // red_wide; only the latter counts rows above kRedCap, which have no near ones)
   const int64_t wave = t / kWave;
   if (kGroup < kWave && __builtin_amdgcn_readfirstlane((int)(wave & ((1 << stride) - 1))) == 0) {
+    const int32_t over = g.m < (int64_t)kRedWideRow * g.n ? 0 : kRedCap;
     const uint32_t stay =
-        wave_sum(live && gl == 0 && !found ? kRedStay + (uint32_t)(d <= kRedCap ? d : 0) : 0u);
+        wave_sum(live && gl == 0 && !found ? kRedStay + (uint32_t)(d <= kRedCap ? d : over) : 0u);
     if (lane_id() == 0) sample[wave >> stride] = stay;
   }
   if (found)
@@ -185,6 +191,12 @@ __device__ __forceinline__ RedSample red_sample(const uint32_t *sample, int32_t 
 __device__ __forceinline__ bool red_crowded(const RedSample &s) {
   const uint32_t x = wave_sum(s.lane);
   return x / kRedStay * (x % kRedStay) > kRedCrowd * s.rows * s.rows;
+}
+// Whether rows want kRedNearWide near neighbours in LDS, by the same sample: the
+// entries of rows that stay, by all rows, are within some percent of the near
+// entries of such a row.
+__device__ __forceinline__ bool red_wide(const RedSample &s) {
+  return wave_sum(s.lane) % kRedStay >= kRedWideNear * s.rows;
 }
 
 // A workgroup's block of R rows: lane r holds row r's first entry and its
@@ -319,10 +331,12 @@ __device__ void red_trans_long(const cg_graph &g, uint32_t fuzz, const uint8_t *
 
 // 8 workgroups to a compute unit where LDS has room for them (at most 64
 // registers; seven of them and 100 Mbp at 15x took 169 us instead of 118).
-template <int kNear>
-__global__ __launch_bounds__(kRedBlock, kNear <= kRedNear ? 8 : 1) void k_red_trans(cg_graph g, uint32_t fuzz, int R,
-                                                         const uint8_t *__restrict__ contained,
-                                                         uint8_t *kept, RedNear near) {
+// With kAsk it leaves the rows to the instance of other kNear if red_wide says so.
+template <int kNear, bool kAsk>
+__global__ __launch_bounds__(kRedBlock, kNear <= kRedNear ? 8 : 1) void k_red_trans(
+    cg_graph g, uint32_t fuzz, int R, const uint8_t *__restrict__ contained, uint8_t *kept,
+    RedNear near) {
+  if (kAsk && red_wide(red_sample(near.sample, g.n, near.stride)) != (kNear > kRedNear)) return;
   // u's near neighbours in column order: their ids, overlaps, first entries
   // (near ones, or of the whole row: bit 2 of the strands), the pairs of those
   // before, lengths, strands and marks
@@ -678,15 +692,25 @@ int launch_reduce(cg_ctx *ctx, const cg_graph &g, const Scratch &s, uint32_t fuz
                 contained, kept, near.cursors, shards, near.sample, near.stride);
     CG_LAUNCH(ctx, k_red_near, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, near);
     const bool longer = g.m >= (int64_t)2 * kRedCap * n;
-    const bool wide = g.m >= (int64_t)kRedWideRow * n && !longer;
-    const int Rt = red_rows(n, longer ? kRedBlocks : (wide ? kRedWideBlocks : kRedTransBlocks));
-    const dim3 tb((unsigned)(((int64_t)n + Rt - 1) / Rt));
-    if (wide)
-      CG_LAUNCH(ctx, k_red_trans<kRedNearWide>, tb, dim3(kRedBlock), st, g, fuzz, Rt, contained,
+    const bool wide = g.m >= (int64_t)kRedWideRow * n && !longer, ask = wide && !waves;
+    const int Rw = red_rows(n, kRedWideBlocks);
+    const int Rn = red_rows(n, longer ? kRedBlocks : kRedTransBlocks);
+    // both instances from 96 entries a read on, and the sample has one of them
+    // leave; the pass with a wave a row takes none, and long rows want the wide one
+    const dim3 gw((unsigned)(((int64_t)n + Rw - 1) / Rw));
+    const dim3 gn((unsigned)(((int64_t)n + Rn - 1) / Rn));
+    if (ask) {
+      CG_LAUNCH(ctx, (k_red_trans<kRedNearWide, true>), gw, dim3(kRedBlock), st, g, fuzz, Rw,
+                contained, kept, near);
+      CG_LAUNCH(ctx, (k_red_trans<kRedNear, true>), gn, dim3(kRedBlock), st, g, fuzz, Rn, contained,
                 kept, near);
-    else
-      CG_LAUNCH(ctx, k_red_trans<kRedNear>, tb, dim3(kRedBlock), st, g, fuzz, Rt, contained, kept,
-                near);
+    } else if (wide) {
+      CG_LAUNCH(ctx, (k_red_trans<kRedNearWide, false>), gw, dim3(kRedBlock), st, g, fuzz, Rw,
+                contained, kept, near);
+    } else {
+      CG_LAUNCH(ctx, (k_red_trans<kRedNear, false>), gn, dim3(kRedBlock), st, g, fuzz, Rn,
+                contained, kept, near);
+    }
     CG_LAUNCH(ctx, k_red_keep, dim3(nb), dim3(kRedBlock), st, g, R, contained, kept, counts,
               blocks);
     if (nb > kRedDirect) CG_LAUNCH(ctx, k_red_sums, dim3(1), dim3(kScanBlock), st, nb, blocks);

@@ -103,3 +103,25 @@ def test_rows_of_a_wave(cg, cov):  # noqa: F811
     r = _overlaps(60_000, cov, 3000, 900, seed=cov)
     got = check(cg, r, 2, name="cov%d" % cov)[0]
     assert (r.m >= 256 * r.n) == (cov >= 200) and got["contained"].mean() > 0.5
+
+
+def _near(r, contained):
+    """Near neighbours of every read that stays: those that stay too."""
+    u = np.repeat(np.arange(r.n), np.diff(r.row_ptr))
+    return np.bincount(u, weights=1 - contained[r.col], minlength=r.n)[contained == 0]
+
+
+@pytest.mark.parametrize("cov, sd, runs, wide", [
+    (90, 30, (), True), (100, 60, (), True), (90, 150, (), False), (130, 120, (), False),
+    # few near neighbours but for a repeat's, above 128, which are read in place
+    (62, 40, ((60_000, 9_000, 90),), False),
+])
+def test_wide_rows_by_near_neighbours(cg, cov, sd, runs, wide):  # noqa: F811
+    """From 96 entries a read on, both sides of the 96 near neighbours a row that
+    give a row room for 256 of them."""
+    r = _overlaps(200_000, cov, 6000, sd, seed=cov + sd, runs=runs)
+    got = check(cg, r, 3, name="cov%d sd%d" % (cov, sd))[0]
+    near = _near(r, got["contained"])
+    assert 96 * r.n <= r.m < 256 * r.n
+    assert (near.mean() > 96 / 0.93 if wide else near.mean() < 96 * 0.93), near.mean()
+    assert not runs or (near > 128).any()
